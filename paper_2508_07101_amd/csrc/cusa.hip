@@ -405,12 +405,18 @@ void launch_attn_ti(int ti, const AttnArgs& a) {
     launch_attn_partial<GQ, 4, SPARSE, false>(a);
 }
 
+void launch_reduce(const ReduceArgs& r, int H, int B, hipStream_t s) {
+    launch(KID_REDUCE, attn_reduce_kernel, dim3(H, B), REDUCE_THREADS, 0, s, r.part_acc, r.part_ml, r.out, r.n_tok, r.n_clip,
+           r.stride_splits, r.chunk, H, r.lse);
+}
+
 // Attention over all tokens (idx == nullptr) or over idx/cnt; n_max bounds the token count.
 // With score.P set (all tokens only) the pass also writes the selection scores.
+// later: the merge of the partials is left to the caller, who gets its arguments (rows 0: nothing to merge).
 template <bool SPARSE>
 cusa_status run_attention(const cusa_params* p, const void* q, const cusa_kv* kv, const int32_t* idx,
                           const int32_t* cnt, int n_max, void* out, void* ws, const WsLayout& w, hipStream_t s,
-                          ScoreOut score = ScoreOut(), float* lse = nullptr) {
+                          ScoreOut score = ScoreOut(), float* lse = nullptr, ReduceArgs* later = nullptr) {
     const int g = p->n_q_heads / p->n_kv_heads, BG = p->batch * p->n_kv_heads, H = p->n_q_heads;
     const AttnPlan pl = plan_attn(n_max, BG, g, score.P != nullptr);
     if (pl.n_splits > w.max_splits) return CUSA_ERR_WORKSPACE_TOO_SMALL;
@@ -438,10 +444,10 @@ cusa_status run_attention(const cusa_params* p, const void* q, const cusa_kv* kv
         default: launch_attn_ti<8, SPARSE>(pl.ti, a); break;
     }
     if (launch_status() != CUSA_OK) return CUSA_ERR_LAUNCH;
-    if (pl.n_splits > 1) {
-        launch(KID_REDUCE, attn_reduce_kernel, dim3(H, p->batch), 256, 0, s, a.pa, a.pm, a.out, SPARSE ? cnt : kv->seq_lens,
-               SPARSE ? p->budget : 0x7fffffff, pl.n_splits, pl.chunk, H, lse);
-    }
+    const ReduceArgs red = {a.pa, a.pm, a.out, SPARSE ? cnt : kv->seq_lens, SPARSE ? p->budget : 0x7fffffff, pl.n_splits,
+                            pl.chunk, lse, pl.n_splits > 1 ? H * p->batch : 0};
+    if (later) *later = red;
+    else if (red.rows > 0) launch_reduce(red, H, p->batch, s);
     return launch_status();
 }
 
@@ -473,9 +479,10 @@ cusa_status run_attention_per_head(const cusa_params* p, const void* q, const cu
     if (pl.ti == 8) launch_attn_per_head<8>(a, H, hshift);
     else launch_attn_per_head<4>(a, H, hshift);
     if (launch_status() != CUSA_OK) return CUSA_ERR_LAUNCH;
-    if (pl.n_splits > 1)
-        launch(KID_REDUCE, attn_reduce_kernel, dim3(H, p->batch), 256, 0, s, a.pa, a.pm, a.out, cnt, p->budget, pl.n_splits,
-               pl.chunk, H, lse);
+    if (pl.n_splits > 1) {
+        const ReduceArgs red = {a.pa, a.pm, a.out, cnt, p->budget, pl.n_splits, pl.chunk, lse, H * p->batch};
+        launch_reduce(red, H, p->batch, s);
+    }
     return launch_status();
 }
 
@@ -483,7 +490,7 @@ cusa_status run_attention_per_head(const cusa_params* p, const void* q, const cu
 // can ask for more are granted their maximum once per device, outside any enqueueing work: on the
 // first library call made with that device current (cusa_workspace_bytes included), so that later
 // calls only enqueue kernels.
-constexpr size_t SEL_LDS_MAX = (size_t)UNION_MAX_POSITIONS / 8;   // the selection bitmaps
+constexpr size_t SEL_LDS_MAX = (size_t)UNION_MAX_POSITIONS / 8 + UNION_IDLE_WORDS * 4;   // the selection bitmaps
 
 template <int ITEMS, int MTOP, bool MERGE = false>
 constexpr size_t topk_lds_bytes() {
@@ -672,9 +679,10 @@ cusa_status run_score(const cusa_params* p, const void* q, const cusa_kv* kv, fl
 
 // scores_ready: P was already written by the layer's attention pass (cusa_decode_step).
 // per_head: idx is [B][H][budget], every head keeps its own first K-W picks (head-to-head selection).
+// red: attention partials still to be merged; they go with the union launch (or on their own where there is none).
 cusa_status run_select(const cusa_params* p, const void* q, const cusa_kv* kv, int32_t* idx, int32_t* cnt, void* ws,
                        const WsLayout& w, hipStream_t s, bool scores_ready = false, bool per_head = false,
-                       const FilterState* redo = nullptr) {
+                       const FilterState* redo = nullptr, const ReduceArgs* red = nullptr) {
     const int H = p->n_q_heads, B = p->batch;
     // redo: the filtered fast path has ranked most heads already; only the flagged ones are scored and ranked here
     int32_t* only_failed = redo ? redo->fail : nullptr;
@@ -698,6 +706,7 @@ cusa_status run_select(const cusa_params* p, const void* q, const cusa_kv* kv, i
         const size_t bitmap = ((((size_t)lc_max + 31) / 32) * 4 + 255) & ~(size_t)255;
         const int n_hist = p->budget - p->window - p->n_sink;
         if (!per_head && p->rank_mode != CUSA_RANK_FIRST_OCCURRENCE) {
+            if (red && red->rows > 0) launch_reduce(*red, H, B, s);
             // votes / max-score readings: one key per candidate position, the K-W best positions by key
             // (the same ranked top-k kernel, one row per sequence), then the ascending emission
             int32_t* rho_rank = ws_ptr<int32_t>(ws, w.rho_rank);
@@ -719,8 +728,11 @@ cusa_status run_select(const cusa_params* p, const void* q, const cusa_kv* kv, i
                    w.k, p->budget, p->window, p->n_sink);
             return launch_status();
         }
-        launch(KID_UNION, union_kernel, B, SEL_THREADS, bitmap, s, rho_head, kv->seq_lens, idx, cnt, H, w.k, p->budget,
-               p->window, p->n_sink);
+        const ReduceArgs r = red ? *red : ReduceArgs{};
+        const size_t set = bitmap + UNION_IDLE_WORDS * 4;
+        const size_t merge_lds = r.rows > 0 ? UNION_REDUCE_ROWS * sizeof(ReduceLds) : 0;
+        launch(KID_UNION, union_kernel, B + (r.rows + UNION_REDUCE_ROWS - 1) / UNION_REDUCE_ROWS, UNION_THREADS, set > merge_lds ? set : merge_lds, s, rho_head, kv->seq_lens, idx, cnt, B, H, w.k, p->budget,
+               p->window, p->n_sink, r);
     }
     return launch_status();
 }
@@ -753,6 +765,7 @@ void launch_sample_threshold(const cusa_params* p, const void* q, const cusa_kv*
 cusa_status run_select_layer(const cusa_params* p, const void* q, const cusa_kv* kv, void* out, int32_t* idx,
                              int32_t* cnt, void* ws, const WsLayout& w, hipStream_t s) {
     ScoreOut score;
+    ReduceArgs red = {};
     if (kv->max_seq_len > p->budget) {
         score.P = ws_ptr<float>(ws, w.scores);
         score.ldp = w.ldp;
@@ -774,7 +787,7 @@ cusa_status run_select_layer(const cusa_params* p, const void* q, const cusa_kv*
         launch_sample_threshold(p, q, kv, sp, f, w.k, s);
         if (launch_status() != CUSA_OK) return CUSA_ERR_LAUNCH;
         score.filter = f;
-        cusa_status st = run_attention<false>(p, q, kv, nullptr, nullptr, kv->max_seq_len, out, ws, w, s, score);
+        cusa_status st = run_attention<false>(p, q, kv, nullptr, nullptr, kv->max_seq_len, out, ws, w, s, score, nullptr, &red);
         if (st != CUSA_OK) return st;
         TopkArgs a = {dim3(H, B), s, nullptr, 0, kv->seq_lens, ws_ptr<int32_t>(ws, w.rho_head), H, w.k, p->budget, p->window, 0,
                       p->n_sink, nullptr, 0, 1};
@@ -782,11 +795,11 @@ cusa_status run_select_layer(const cusa_params* p, const void* q, const cusa_kv*
         const int items = (f.cap + SEL_THREADS - 1) / SEL_THREADS;
         st = items <= 4 ? launch_topk<4, true>(a) : items <= 8 ? launch_topk<8, true>(a) : launch_topk<16, true>(a);
         if (st != CUSA_OK) return st;
-        return run_select(p, q, kv, idx, cnt, ws, w, s, false, false, &f);
+        return run_select(p, q, kv, idx, cnt, ws, w, s, false, false, &f, &red);
     }
-    cusa_status st = run_attention<false>(p, q, kv, nullptr, nullptr, kv->max_seq_len, out, ws, w, s, score);
+    cusa_status st = run_attention<false>(p, q, kv, nullptr, nullptr, kv->max_seq_len, out, ws, w, s, score, nullptr, &red);
     if (st != CUSA_OK) return st;
-    return run_select(p, q, kv, idx, cnt, ws, w, s, score.P != nullptr);
+    return run_select(p, q, kv, idx, cnt, ws, w, s, score.P != nullptr, false, nullptr, &red);
 }
 
 }  // namespace

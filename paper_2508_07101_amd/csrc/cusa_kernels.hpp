@@ -107,31 +107,43 @@ __device__ __forceinline__ int mbcnt(uint64_t mask) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
 }
 
-// Exclusive prefix sum of one int per thread over a 1024-thread block.
-// scratch: SEL_WAVES + 1 ints of LDS.  Returns the exclusive prefix; *total gets the sum.
+// Inclusive prefix sum over a wave by DPP moves: inside the 16-lane rows, then across them.
+__device__ __forceinline__ int wave_scan_incl(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);   // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);   // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
+// Workgroup barrier for data exchanged through LDS only: waits for this wave's LDS operations, not for
+// its outstanding global loads (which a full __syncthreads() would drain first).
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// Exclusive prefix sum of one int per thread over a block of WAVES waves.
+// scratch: WAVES ints of LDS.  Returns the exclusive prefix; *total gets the sum.
+// Every wave adds up the other waves' sums for itself: one wave's lane doing it for all costs as much
+// as the rest of the scan.
+template <int WAVES = SEL_WAVES>
 __device__ __forceinline__ int block_scan_excl(int v, int* scratch, int* total) {
-    const int lane = lane_id(), w = wave_id();
-    int inc = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        int n = __shfl_up(inc, o);
-        if (lane >= o) inc += n;
-    }
-    __syncthreads();                               // scratch may still be read from a previous call
+    const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+    const int inc = wave_scan_incl(v);
+    lds_barrier();                                 // scratch may still be read from a previous call
     if (lane == 63) scratch[w] = inc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int run = 0;
-        for (int i = 0; i < SEL_WAVES; ++i) {
-            int c = scratch[i];
-            scratch[i] = run;
-            run += c;
-        }
-        scratch[SEL_WAVES] = run;
+    lds_barrier();
+    int before = 0, sum = 0;
+#pragma unroll
+    for (int i = 0; i < WAVES; ++i) {
+        const int c = scratch[i];
+        before += i < w ? c : 0;
+        sum += c;
     }
-    __syncthreads();
-    *total = scratch[SEL_WAVES];
-    return scratch[w] + inc - v;
+    *total = sum;
+    return before + inc - v;
 }
 
 // Order-preserving map of a binary32 score to uint32 (larger score -> larger key);
@@ -445,7 +457,7 @@ __global__ __launch_bounds__(SEL_THREADS, ((ITEMS == -1 && MTOP <= 4) || (MERGE 
     constexpr int CAP = topk_list_cap(ITEMS, MTOP);
     extern __shared__ uint64_t sort_buf[];            // NSORT composites (aliases the histogram), then CAP list entries
     uint64_t* const cand = sort_buf + NSORT;
-    __shared__ int scratch[SEL_WAVES + 1];
+    __shared__ __attribute__((aligned(16))) int scratch[SEL_WAVES];
     __shared__ SelectState st;
     __shared__ int n_out, n_list;
     int* hist = reinterpret_cast<int*>(sort_buf);     // 2048 ints = 8 KB <= NSORT * 8
@@ -887,12 +899,27 @@ __global__ __launch_bounds__(SEL_THREADS, ((ITEMS == -1 && MTOP <= 4) || (MERGE 
 // per position: 16 KB for 131072 tokens).  A range of slots is added with one atomic OR per slot;
 // the OR's return value tells whether the slot set its bit, so the number of new tokens in the
 // range is exact even though, among slots of the range that name the same token, an arbitrary
-// one sets it.  Ranges are taken in slot order, 8192 slots at a time; the range in which the
-// count would pass K-W is taken back (the bits it set are cleared) and walked again in 1024-slot
-// ranges, the crossing one of those in 64-slot groups by a single wave, and the crossing group is
-// resolved exactly: a lane's pick counts if no lower lane of the group names the same token.
-// What is left set is the answer; it is emitted in ascending position order, followed by the
-// window {L-W .. L-1}.
+// one sets it.
+//
+// One workgroup is all there is to work with, and the kernel is a chain of LDS round trips, barriers and
+// instructions that sixteen waves execute on one CU (sixteen cycles each): what counts is the number of looks, of
+// instructions per look, and of LDS operations waited for one by one.  (Four waves with four times the slots per
+// thread were measured: ranges as fast, the emission twice as slow.)  As many slots
+// as tokens are still wanted can be added without a look at what they hold: they cannot
+// name more tokens than that.  The first range is of this kind; where heads mostly disagree it leaves
+// a few per cent, the next one a few per cent of those.  Where heads agree, a range is as long as the share of
+// new tokens in the last one lets expect; should it pass K-W all the same, the bits it set are cleared
+// and a shorter one is taken.  The last tokens are found by a single wave in groups of 64 slots, four groups
+// at a time (LDS operations of a wave are carried out in order, so each group's count is exact); the
+// groups from the crossing one on are taken back, and in that one a lane's pick counts if no lower
+// lane names the same token.  What is left set is the answer; it is emitted in ascending position
+// order, followed by the window {L-W .. L-1}.
+//
+// In a selection layer the launch also carries the merge of the layer's attention partials (reduce_row,
+// four rows to a workgroup, behind the B union workgroups): the union keeps B compute units
+// busy and waits for LDS most of the time, and a launch of its own for the merge costs 3-5 us.
+// Measured (kernel trace, union + merge before -> one launch): B1 L4096 K1024 8.4 + 2.9 -> 6.2 us, B1 L32768
+// K2048 10.1 + 4.8 -> 8.0, B8 L16384 K4096 14.0 + 5.0 -> 12.4, B1 H64 L131072 K4096 13.4 + 5.8 -> 11.6.
 
 // Adds the sink positions 0 .. n_sink-1 (never picked: they are no candidates) to the set in
 // `bits` and writes the set's positions in ascending order, at most `limit` of them.  Thread i
@@ -901,7 +928,7 @@ __device__ __forceinline__ int emit_sinks_and_set(uint32_t* bits, int n_words, i
                                                   int32_t* __restrict__ out) {
     const int tid = threadIdx.x;
     for (int t = tid; t < n_sink; t += SEL_THREADS) atomicOr(&bits[t >> 5], 1u << (t & 31));
-    if (n_sink > 0) __syncthreads();
+    if (n_sink > 0) lds_barrier();
     const int wpt = (n_words + SEL_THREADS - 1) / SEL_THREADS;
     const int w_lo = tid * wpt, w_hi = (w_lo + wpt < n_words) ? w_lo + wpt : n_words;
     int mine = 0;
@@ -920,23 +947,65 @@ __device__ __forceinline__ int emit_sinks_and_set(uint32_t* bits, int n_words, i
     return n_sink;
 }
 
-constexpr int UNION_UNROLL = 8;
+constexpr int UNION_THREADS = 1024;
+constexpr int UNION_WAVES = UNION_THREADS / 64;
+constexpr int UNION_RUNS = 4;                         // runs of UNION_THREADS slots held in registers at a time
 constexpr int UNION_MAX_POSITIONS = 144 * 1024 * 8;   // candidate positions a 144 KB bitmap covers
 
-__global__ __launch_bounds__(SEL_THREADS) void union_kernel(const int32_t* __restrict__ rho_head,
+// What the merge of split-K partials needs (attn_reduce_kernel, and the union launch of a selection layer).
+struct ReduceArgs {
+    const float* part_acc;       // [row][stride_splits][128]; row = sequence * H + head
+    const float* part_ml;        // [row][stride_splits][2]
+    uint16_t* out;               // [row][128]
+    const int32_t* n_tok;        // [B] tokens of the list a sequence attended to (clipped to n_clip)
+    int n_clip, stride_splits, chunk;
+    float* lse;                  // optional
+    int rows;                    // B * H
+};
+constexpr int REDUCE_THREADS = 256;                   // threads per row
+constexpr int UNION_REDUCE_ROWS = UNION_THREADS / REDUCE_THREADS;
+constexpr int UNION_IDLE_WORDS = 64;
+constexpr int UNION_CLAIMS = 1024;                    // entries of each of two claim tables
+constexpr int UNION_WALK = 1024;                      // slots a single wave walks at most before the workgroup looks again
+struct ReduceLds {
+    float a[8][D];
+    float m[8], l[8];
+};
+template <bool ALONE>
+__device__ __forceinline__ void reduce_row(const ReduceArgs& r, int row, int seq, int tid, ReduceLds& lds);
+
+__global__ __launch_bounds__(UNION_THREADS) void union_kernel(const int32_t* __restrict__ rho_head,
                                                              const int32_t* __restrict__ seq_lens,
                                                              int32_t* __restrict__ idx, int32_t* __restrict__ cnt,
-                                                             int H, int k, int budget, int window, int n_sink) {
-    extern __shared__ uint32_t bits[];                // ceil(Lc / 32) words
-    __shared__ int wave_cnt[2 * SEL_WAVES];
-    __shared__ int scratch[SEL_WAVES + 1];
-    __shared__ int picks[SEL_THREADS];                // the picks of the crossing 1024-slot range, by slot
-    __shared__ uint32_t idle[64];                     // where lanes with nothing to add send their atomic
+                                                             int B, int H, int k, int budget, int window, int n_sink,
+                                                             ReduceArgs red) {
+    // 64 words where lanes with nothing to add send their atomic, then the set: ceil(Lc / 32) words; merging
+    // workgroups: a ReduceLds
+    extern __shared__ __attribute__((aligned(16))) uint32_t union_lds[];
+    uint32_t* const bits = union_lds + UNION_IDLE_WORDS;
+    __shared__ int wave_cnt[2 * UNION_WAVES];
+    __shared__ int scratch[UNION_WAVES];
+    __shared__ int picks[UNION_WALK];                 // the picks of a 1024-slot range, by slot
+    __shared__ uint32_t claims[2 * UNION_CLAIMS];         // lane << 24 | token: who names it first in the crossing group
+    __shared__ int walk_cum;
     const int b = blockIdx.x, tid = threadIdx.x, lane = lane_id(), w = wave_id();
+    if (b >= B) {                                     // the attention partials of a (sequence, head) row
+        const int sub = __builtin_amdgcn_readfirstlane(tid / REDUCE_THREADS);
+        const int row = (b - B) * UNION_REDUCE_ROWS + sub;
+        reduce_row<false>(red, row, min(row, red.rows - 1) / H, tid % REDUCE_THREADS, reinterpret_cast<ReduceLds*>(union_lds)[sub]);
+        return;
+    }
+    const int32_t* __restrict__ rho = rho_head + (int64_t)b * k * H;
+    int raw[UNION_RUNS];                              // picks on their way (below); the first are asked for before the length is here
+    auto request_picks = [&](int s0) {
+#pragma unroll
+        for (int u = 0; u < UNION_RUNS; ++u) raw[u] = rho[min(s0 + u * UNION_THREADS + tid, k * H - 1)];
+    };
+    request_picks(0);
     const int L = seq_lens[b];
     int32_t* __restrict__ out = idx + (int64_t)b * budget;
     if (L <= budget) {
-        for (int t = tid; t < L; t += SEL_THREADS) out[t] = t;
+        for (int t = tid; t < L; t += UNION_THREADS) out[t] = t;
         if (tid == 0) cnt[b] = L;
         return;
     }
@@ -944,141 +1013,166 @@ __global__ __launch_bounds__(SEL_THREADS) void union_kernel(const int32_t* __res
     const int k_eff = k < Lc - n_sink ? k : Lc - n_sink;
     const int S = k_eff * H;
     const int n_hist = budget - window - n_sink;      // picks to keep; the sink positions come on top
-    const int32_t* __restrict__ rho = rho_head + (int64_t)b * k * H;
     const int n_words = (Lc + 31) >> 5;
-    for (int i = tid; i < n_words; i += SEL_THREADS) bits[i] = 0u;
-    __syncthreads();
 
-    // The picks of the UNION_UNROLL slots s0 + u * 1024 + tid are requested with clamped,
-    // unconditional loads (request_picks) and looked at later (take_picks: -1 past the end; a pick is
-    // always a candidate position).  The empty asm keeps the compiler from turning the loads into one
-    // branch each.
-    auto request_picks = [&](int s0, int* raw) {
+    // The slots are looked at through a window of UNION_RUNS * 1024 slots held in registers: tok[u] of thread i is
+    // slot win + u * 1024 + i (-1: past the end; a pick is always a candidate position).  The next window's picks
+    // are requested early, with clamped, unconditional loads; the empty asm keeps the compiler from turning
+    // them into one branch each.
+    constexpr int WINDOW = UNION_RUNS * UNION_THREADS;
+    int tok[UNION_RUNS];
+    auto take_picks = [&](int s0) {
 #pragma unroll
-        for (int u = 0; u < UNION_UNROLL; ++u) raw[u] = rho[min(s0 + u * SEL_THREADS + tid, S - 1)];
+        for (int u = 0; u < UNION_RUNS; ++u) asm volatile("" : "+v"(raw[u]));
+#pragma unroll
+        for (int u = 0; u < UNION_RUNS; ++u) tok[u] = (s0 + u * UNION_THREADS + tid < S && (uint32_t)raw[u] < (uint32_t)Lc) ? raw[u] : -1;
     };
-    auto take_picks = [&](int s0, int* raw, int* dst) {
-#pragma unroll
-        for (int u = 0; u < UNION_UNROLL; ++u) asm volatile("" : "+v"(raw[u]));
-#pragma unroll
-        for (int u = 0; u < UNION_UNROLL; ++u)
-            dst[u] = (s0 + u * SEL_THREADS + tid < S && (uint32_t)raw[u] < (uint32_t)Lc) ? raw[u] : -1;
-    };
+    for (int i = tid; i < n_words; i += UNION_THREADS) bits[i] = 0u;
+    for (int i = tid; i < 2 * UNION_CLAIMS; i += UNION_THREADS) claims[i] = 64u << 24;
+    lds_barrier();
     // workgroup total of per-wave counts (wave-uniform argument); wave_cnt alternates between two
     // halves so that one barrier per call is enough
     int parity = 0;
     auto block_total = [&](int wave_total) {
-        int* const slot = wave_cnt + parity * SEL_WAVES;
+        int* const slot = wave_cnt + parity * UNION_WAVES;
         parity ^= 1;
         if (lane == 0) slot[w] = wave_total;
-        __syncthreads();
-        int sum = 0;
-#pragma unroll
-        for (int i = 0; i < SEL_WAVES; ++i) sum += slot[i];
-        return sum;
+        lds_barrier();
+        int v = slot[lane & (UNION_WAVES - 1)];
+        v += __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, true);   // row_ror:8, 4, 2, 1: the sum over the row
+        v += __builtin_amdgcn_update_dpp(0, v, 0x124, 0xF, 0xF, true);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x122, 0xF, 0xF, true);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x121, 0xF, 0xF, true);
+        return __builtin_amdgcn_readfirstlane(v);
     };
-    int cum = 0;                                       // distinct tokens in the bitmap
-    bool crossed = false;
-    constexpr int CH = UNION_UNROLL * SEL_THREADS;
-    int tok[UNION_UNROLL], raw[UNION_UNROLL];          // this range's picks; the next range's, requested early
-    request_picks(0, raw);
-    for (int c0 = 0; c0 < S && n_hist > 0; c0 += CH) {
-        take_picks(c0, raw, tok);
-        request_picks(c0 + CH, raw);
-        uint32_t won = 0;
-        int wave_added = 0;
-#pragma unroll
-        for (int u = 0; u < UNION_UNROLL; ++u) {
-            // Neighbouring slots are neighbouring heads at one rank and often name the same token;
-            // a lane whose left neighbour in its 16-lane row has the same pick leaves the atomic to it
-            // (same-address LDS atomics of one instruction are carried out one after the other; for
-            // the same reason the lanes that stay out add zero to a word of their own, not to a shared one).
-            const int left = __builtin_amdgcn_update_dpp(-2, tok[u], 0x111, 0xF, 0xF, false);   // row_shr:1; -2 into lane 0 of a row
-            const bool lead = tok[u] >= 0 && tok[u] != left;
-            const uint32_t bit = 1u << (tok[u] & 31);
-            const uint32_t old = atomicOr(lead ? &bits[tok[u] >> 5] : &idle[lane], lead ? bit : 0u);
-            const bool wn = lead && !(old & bit);
-            if (wn) won |= 1u << u;
-            wave_added += __popcll(__ballot(wn));
+    // adds the lanes' tokens (-1: none); the bit a lane set, or 0
+    auto add_to_set = [&](int t) -> uint32_t {
+        const uint32_t bit = t >= 0 ? 1u << (t & 31) : 0u;
+        const uint32_t old = atomicOr(&union_lds[t >= 0 ? UNION_IDLE_WORDS + (t >> 5) : lane], bit);
+        return bit & ~old;
+    };
+    constexpr float WALK_SLOTS = 384.0f;               // expected rest that a single wave walks
+    int cum = 0;                                       // distinct tokens in the set
+    float slots_per_new = 1.0f;                        // of the last range
+    int win = 0, lo = 0;                               // the window's first slot; its slots taken so far
+    take_picks(0);
+    request_picks(WINDOW);
+    while (cum < n_hist && win + lo < S) {             // uniform
+        if (lo >= WINDOW) {
+            win += WINDOW;
+            lo = 0;
+            take_picks(win);
+            request_picks(win + WINDOW);
         }
-        const int added = block_total(wave_added);
-        if (cum + added >= n_hist) {                   // take the range back and look closer
+        const int rem = n_hist - cum;
+        const float expect = (float)rem * slots_per_new;
+        if (expect > WALK_SLOTS || lo == 0) {
+            int len = min(max(rem, (int)(expect * 0.75f)), WINDOW - lo);
+            for (;;) {                                 // shortened until it fits; at len <= rem it does
+                // Neighbouring slots are neighbouring heads at one rank and often name the same token; a lane whose
+                // left neighbour in its 16-lane row has the same pick leaves the atomic to it (same-address LDS
+                // atomics of one instruction are carried out one after the other; for the same reason lanes that
+                // stay out add zero to a word of their own).  Where a range starts inside a row, its first lane's
+                // neighbour is out of the range and does not count.
+                uint32_t got[UNION_RUNS];
 #pragma unroll
-            for (int u = 0; u < UNION_UNROLL; ++u)
-                if ((won >> u) & 1) atomicAnd(&bits[tok[u] >> 5], ~(1u << (tok[u] & 31)));
-            __syncthreads();
-            crossed = true;
-            break;
-        }
-        cum += added;
-    }
-
-    int n_take = cum;                                  // fewer than K-W distinct picks in total (k < K-W only)
-    if (crossed) {
-        // tok[u] of thread i is slot u * 1024 + i of the crossing range
-        n_take = n_hist;
-        int my_pick = -1;                              // the thread's pick in the crossing 1024-slot range
-        bool found = false;
+                for (int u = 0; u < UNION_RUNS; ++u) {
+                    const int mine = (uint32_t)(u * UNION_THREADS + tid - lo) < (uint32_t)len ? tok[u] : -1;
+                    const int left = __builtin_amdgcn_update_dpp(-2, mine, 0x111, 0xF, 0xF, false);   // row_shr:1; -2 into lane 0 of a row
+                    got[u] = add_to_set(mine != left ? mine : -1);
+                }
+                int wave_added = 0;
 #pragma unroll
-        for (int u = 0; u < UNION_UNROLL; ++u) {
-            if (!found) {                              // uniform
-                const uint32_t bit = 1u << (tok[u] & 31);
-                const uint32_t old = atomicOr(&bits[tok[u] >= 0 ? tok[u] >> 5 : 0], tok[u] >= 0 ? bit : 0u);
-                const bool won = tok[u] >= 0 && !(old & bit);
-                const int added = block_total(__popcll(__ballot(won)));
-                if (cum + added >= n_hist) {
-                    if (won) atomicAnd(&bits[tok[u] >> 5], ~bit);
-                    my_pick = tok[u];
-                    found = true;
-                } else {
+                for (int u = 0; u < UNION_RUNS; ++u) wave_added += __popcll(__ballot(got[u] != 0u));
+                const int added = block_total(wave_added);
+                if (cum + added <= n_hist) {
                     cum += added;
+                    lo += len;
+                    slots_per_new = (float)len * __builtin_amdgcn_rcpf((float)max(added, 1));
+                    break;
                 }
+                // too far (only where len > rem): take the range back; the rest is expected in its first part
+#pragma unroll
+                for (int u = 0; u < UNION_RUNS; ++u)
+                    if (got[u]) atomicAnd(&bits[tok[u] >> 5], ~got[u]);
+                len = min(max(rem, (int)((float)(len * 7 / 8) * (float)rem * __builtin_amdgcn_rcpf((float)added))), len - 1);
+                lds_barrier();
             }
+            continue;
         }
-        picks[tid] = my_pick;
-        __syncthreads();
-        if (w == 0) {                                  // one wave: its LDS accesses happen in program order
-            int group_pick[SEL_WAVES];
+        // one wave walks the next slots of the window, at most UNION_WALK
+        const int hi = min(lo + UNION_WALK, WINDOW);
 #pragma unroll
-            for (int g = 0; g < SEL_WAVES; ++g) group_pick[g] = picks[g * 64 + lane];
-            int t = -1;                                // the lane's pick in the crossing group
-            bool found = false;
+        for (int u = 0; u < UNION_RUNS; ++u) {
+            const int at = u * UNION_THREADS + tid - lo;
+            if ((uint32_t)at < (uint32_t)UNION_WALK) picks[at] = tok[u];
+        }
+        lds_barrier();
+        if (w == 0) {                                  // its LDS accesses happen in program order
+            int c_all = cum;
+            for (int g0 = 0; g0 * 64 < hi - lo && c_all < n_hist; g0 += 4) {
+                int g_tok[4], c[4];
+                uint32_t g_won[4];
 #pragma unroll
-            for (int g = 0; g < SEL_WAVES; ++g) {
-                if (!found) {                          // uniform
-                    const int tg = group_pick[g];
-                    const uint32_t bit = 1u << (tg & 31);
-                    uint32_t* const word = &bits[tg >= 0 ? tg >> 5 : 0];
-                    const bool won = tg >= 0 && !(atomicOr(word, tg >= 0 ? bit : 0u) & bit);
-                    const int c = __popcll(__ballot(won));
-                    if (cum + c < n_hist) {
-                        cum += c;
-                    } else {                           // take the group back
-                        if (won) atomicAnd(word, ~bit);
-                        t = tg;
-                        found = true;
+                for (int g = 0; g < 4; ++g) g_tok[g] = (g0 + g) * 64 + lane < hi - lo ? picks[(g0 + g) * 64 + lane] : -1;
+#pragma unroll
+                for (int g = 0; g < 4; ++g) g_won[g] = add_to_set(g_tok[g]);
+                int run = c_all, gx = 0;               // the group in which K-W is reached; 4: none
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    c[g] = __popcll(__ballot(g_won[g] != 0u));
+                    run += c[g];
+                    gx += run < n_hist ? 1 : 0;
+                }
+                int t = -1;                            // the lane's pick in that group
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    c_all += g < gx ? c[g] : 0;
+                    t = g == gx ? g_tok[g] : t;
+                    if (g >= gx && g_won[g]) atomicAnd(&bits[g_tok[g] >> 5], ~g_won[g]);   // taken back
+                }
+                if (gx < 4) {
+                    // A pick of the crossing group counts only if no lower lane names its token.  The lanes
+                    // claim an entry for their token, the lowest lane keeps it; an entry kept for another token
+                    // leaves the question open (for all lanes with that token), which a second entry answers, or
+                    // (rarely) a comparison of all lanes.
+                    const uint32_t bit = t >= 0 ? 1u << (t & 31) : 0u;
+                    const bool fresh = t >= 0 && !(bits[t >= 0 ? t >> 5 : 0] & bit);
+                    const uint32_t claim = ((uint32_t)lane << 24) | (uint32_t)(t & 0xffffff);
+                    bool open = fresh, dup = false;
+#pragma unroll
+                    for (int round = 0; round < 2; ++round) {
+                        uint32_t* const entry = &claims[round == 0 ? t & (UNION_CLAIMS - 1) : UNION_CLAIMS + (((uint32_t)t * 2654435761u) >> 22)];
+                        if (open) {
+                            atomicMin(entry, claim);
+                            const uint32_t kept = *entry;
+                            open = ((kept ^ claim) & 0xffffffu) != 0u;
+                            dup = !open && kept != claim;
+                        }
                     }
+                    if (__ballot(open)) {
+                        for (int l = 0; l < 63; ++l) {
+                            const int tl = __builtin_amdgcn_readlane(t, l);
+                            dup |= (l < lane) && (tl == t);
+                        }
+                    }
+                    const bool is_new = fresh && !dup;
+                    const uint64_t ballot = __ballot(is_new);
+                    if (is_new && c_all + mbcnt(ballot) < n_hist) atomicOr(&bits[t >> 5], bit);
+                    c_all = n_hist;
                 }
             }
-            if (found) {
-                // a pick of the crossing group counts only if no lower lane names its token
-                bool dup = false;
-#pragma unroll
-                for (int l = 0; l < 63; ++l) {
-                    const int tl = __builtin_amdgcn_readlane(t, l);
-                    dup |= (l < lane) && (tl == t);
-                }
-                const uint32_t bit = 1u << (t & 31);
-                uint32_t* const word = &bits[t >= 0 ? t >> 5 : 0];
-                const bool is_new = t >= 0 && !dup && !(*word & bit);
-                const uint64_t ballot = __ballot(is_new);
-                if (is_new && cum + mbcnt(ballot) < n_hist) atomicOr(word, bit);
-            }
+            if (lane == 0) walk_cum = c_all;
         }
-        __syncthreads();
+        lds_barrier();
+        const int now = __builtin_amdgcn_readfirstlane(walk_cum);
+        slots_per_new = (float)(hi - lo) * __builtin_amdgcn_rcpf((float)max(now - cum, 1));
+        cum = now;
+        lo = hi;
     }
+    int n_take = cum;                                  // n_hist, or fewer distinct picks in total (k < K-W only)
     n_take += emit_sinks_and_set(bits, n_words, n_sink, n_hist + n_sink, scratch, out);
-    for (int j = tid; j < window; j += SEL_THREADS) out[n_take + j] = L - window + j;
+    for (int j = tid; j < window; j += UNION_THREADS) out[n_take + j] = L - window + j;
     if (tid == 0) cnt[b] = n_take + window;
 }
 
@@ -1386,7 +1480,7 @@ __global__ __launch_bounds__(SEL_THREADS) void per_head_rho_kernel(const int32_t
                                                                     int32_t* __restrict__ cnt, int H, int k,
                                                                     int budget, int window, int n_sink) {
     extern __shared__ uint32_t bits[];                // ceil(Lc / 32) words
-    __shared__ int scratch[SEL_WAVES + 1];
+    __shared__ __attribute__((aligned(16))) int scratch[SEL_WAVES];
     const int h = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
     const int L = seq_lens[b];
     int32_t* __restrict__ out = idx_head + ((int64_t)b * H + h) * budget;
@@ -1500,12 +1594,6 @@ __device__ __forceinline__ int wave_base_of(unsigned tid) { return (int)(tid >> 
 // LDS written by some lanes of a wave and read by others of the same wave: a wave's LDS
 // accesses are performed in program order, so only the compiler has to be kept from
 // reordering them.
-// Workgroup barrier for data exchanged through LDS only: waits for this wave's LDS operations, not for
-// its outstanding global loads (which a full __syncthreads() would drain first).
-__device__ __forceinline__ void lds_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -2086,21 +2174,17 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     if constexpr (FILTER) copy_candidates(cand_reserved);
 }
 
-// Merge of the split-K partials of sequences that kept more than one workgroup busy.
-// grid (H, B), 256 threads: thread (c4, sr) owns output
-// columns 4*c4 .. 4*c4+3 and folds the splits sr, sr+8, ... into a running (m, l, a[4])
-// with 16-byte loads; the eight split-rows then meet in LDS and the result is written as bf16.
-// n_tok[b] is the sequence's token count (seq_lens, or cnt clipped to the budget when sparse).
-__global__ __launch_bounds__(256) void attn_reduce_kernel(const float* __restrict__ part_acc,
-                                                           const float* __restrict__ part_ml,
-                                                           uint16_t* __restrict__ out,
-                                                           const int32_t* __restrict__ n_tok, int n_clip,
-                                                           int stride_splits, int chunk, int H,
-                                                           float* __restrict__ lse) {
-    __shared__ float red_a[8][D];
-    __shared__ float red_m[8], red_l[8];
-    const int h = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, c4 = tid & 31, sr = tid >> 5;
-    const int64_t base = ((int64_t)b * H + h) * stride_splits;
+// Merge of the split-K partials of one (sequence, head) row whose sequence kept more than one workgroup
+// busy.  256 threads (`tid`): thread (c4, sr) owns output columns 4*c4 .. 4*c4+3 and folds the splits sr, sr+8, ...
+// into a running (m, l, a[4]) with 16-byte loads; the eight split-rows then meet in LDS and the result
+// is written as bf16.  ALONE: the workgroup has this row only; otherwise `row` is uniform per wave, may lie past the last
+// one, and all of the workgroup's rows meet the barrier.
+template <bool ALONE>
+__device__ __forceinline__ void reduce_row(const ReduceArgs& r, int row, int seq, int tid, ReduceLds& lds) {
+    const int c4 = tid & 31, sr = tid >> 5;
+    const bool have = ALONE || row < r.rows;
+    if (!have) row = r.rows - 1;
+    const int64_t base = (int64_t)row * r.stride_splits;
     constexpr int U = 4;
     // The first batch of partials is requested before the token count is known (any of the
     // stride_splits slots may be read); what lies beyond the active splits is dropped by select,
@@ -2110,33 +2194,34 @@ __global__ __launch_bounds__(256) void attn_reduce_kernel(const float* __restric
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int sv = sr + 8 * u;
-        const int64_t p = base + (sv < stride_splits ? sv : 0);
-        va[u] = *reinterpret_cast<const f32x4*>(&part_acc[p * D + c4 * 4]);
-        vml[u] = *reinterpret_cast<const f32x2*>(&part_ml[p * 2]);
+        const int64_t p = base + (sv < r.stride_splits ? sv : 0);
+        va[u] = *reinterpret_cast<const f32x4*>(&r.part_acc[p * D + c4 * 4]);
+        vml[u] = *reinterpret_cast<const f32x2*>(&r.part_ml[p * 2]);
     }
-    const int n_splits = attn_active_splits(min(n_tok[b], n_clip), chunk);
+    const int n_splits = attn_active_splits(min(r.n_tok[seq], r.n_clip), r.chunk);
     // keep the requests above the branch (the compiler would sink them behind it)
     asm volatile("" ::"s"(n_splits));
 #pragma unroll
     for (int u = 0; u < U; ++u) asm volatile("" ::"v"(va[u]), "v"(vml[u]));
-    if (n_splits <= 1) return;                           // the attention kernel wrote the result itself
+    const bool merge = have && n_splits > 1;             // otherwise the attention kernel wrote the result itself
+    if (ALONE && !merge) return;
     float mo = -INFINITY, lo = 0.0f;
     f32x4 ao = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int s0 = sr; s0 < n_splits; s0 += 8 * U) {
+    for (int s0 = sr; merge && s0 < n_splits; s0 += 8 * U) {
         if (s0 != sr) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int sv = s0 + 8 * u;
                 const int64_t p = base + (sv < n_splits ? sv : s0);
-                va[u] = *reinterpret_cast<const f32x4*>(&part_acc[p * D + c4 * 4]);
-                vml[u] = *reinterpret_cast<const f32x2*>(&part_ml[p * 2]);
+                va[u] = *reinterpret_cast<const f32x4*>(&r.part_acc[p * D + c4 * 4]);
+                vml[u] = *reinterpret_cast<const f32x2*>(&r.part_ml[p * 2]);
             }
         }
         float mb = mo;
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (s0 + 8 * u < n_splits) mb = fmaxf(mb, vml[u].x);
-        if (mb == -INFINITY) continue;                   // nothing but empty splits so far
+        if (mb == -INFINITY) continue;               // nothing but empty splits so far
         const float f0 = (mo == -INFINITY) ? 0.0f : exp2f(mo - mb);
         ao *= f0;
         lo *= f0;
@@ -2151,27 +2236,39 @@ __global__ __launch_bounds__(256) void attn_reduce_kernel(const float* __restric
         }
         mo = mb;
     }
-    *reinterpret_cast<f32x4*>(&red_a[sr][c4 * 4]) = ao;
+    *reinterpret_cast<f32x4*>(&lds.a[sr][c4 * 4]) = ao;
     if (c4 == 0) {
-        red_m[sr] = mo;
-        red_l[sr] = lo;
+        lds.m[sr] = mo;
+        lds.l[sr] = lo;
     }
     __syncthreads();
-    if (tid < D) {
-        float M = red_m[0];
+    if (merge && tid < D) {
+        float M = lds.m[0];
 #pragma unroll
-        for (int j = 1; j < 8; ++j) M = fmaxf(M, red_m[j]);
+        for (int j = 1; j < 8; ++j) M = fmaxf(M, lds.m[j]);
         float A = 0.0f, Ls = 0.0f;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const float mj = red_m[j];
+            const float mj = lds.m[j];
             const float f = (mj == -INFINITY) ? 0.0f : exp2f(mj - M);
-            A = __builtin_fmaf(red_a[j][tid], f, A);
-            Ls = __builtin_fmaf(red_l[j], f, Ls);
+            A = __builtin_fmaf(lds.a[j][tid], f, A);
+            Ls = __builtin_fmaf(lds.l[j], f, Ls);
         }
-        out[((int64_t)b * H + h) * D + tid] = f32_to_bf16_rne(Ls > 0.0f ? A / Ls : 0.0f);
-        if (lse && tid == 0) lse[(int64_t)b * H + h] = M + log2f(Ls);
+        r.out[(int64_t)row * D + tid] = f32_to_bf16_rne(Ls > 0.0f ? A / Ls : 0.0f);
+        if (r.lse && tid == 0) r.lse[row] = M + log2f(Ls);
     }
+}
+
+// The merge as a launch of its own: grid (H, B).  (Plain leading arguments arrive preloaded in SGPRs.)
+__global__ __launch_bounds__(REDUCE_THREADS) void attn_reduce_kernel(const float* __restrict__ part_acc,
+                                                           const float* __restrict__ part_ml,
+                                                           uint16_t* __restrict__ out,
+                                                           const int32_t* __restrict__ n_tok, int n_clip,
+                                                           int stride_splits, int chunk, int H,
+                                                           float* __restrict__ lse) {
+    __shared__ ReduceLds lds;
+    const ReduceArgs r = {part_acc, part_ml, out, n_tok, n_clip, stride_splits, chunk, lse, 0};
+    reduce_row<true>(r, (int)(blockIdx.y * H + blockIdx.x), (int)blockIdx.y, (int)threadIdx.x, lds);
 }
 
 // Streaming-read probe (benchmark support): every thread folds 16-byte loads of a plain buffer,

@@ -500,6 +500,25 @@ def test_strided_contiguous_cache_view():
     check_attention(inp, r, 0, LAYER_FULL)
 
 
+@pytest.mark.parametrize("heads", ["alike", "nearly alike", "different"])
+@pytest.mark.parametrize("L,K,W,k", [(700, 64, 16, 0), (2600, 1100, 76, 0), (5200, 4500, 404, 4096), (9000, 2048, 0, 2048)])
+def test_union_of_agreeing_and_disagreeing_heads(heads, L, K, W, k):
+    """The union kernel's ranges: first ranges that end inside a row or a window of 4096 slots, many slots per new
+    token (heads alike: 32 slots for each), ranges taken back, and the walk to the last token."""
+    w = small("union", batch=2, seq_len=L, lengths=(L, K + 33), budget=K, window=W, topk_per_head=k)
+    inp = wl.make_inputs(w, DEV)
+    lay = inp.layers[0]
+    if heads != "different":                             # one key per position and one query for all heads ...
+        lay.k[:] = lay.k[:, :1].clone()
+        q = lay.q[:, :1].clone().expand_as(lay.q).clone()
+        if heads == "nearly alike":                      # ... or queries that differ a little
+            q = (q.float() + 0.05 * lay.q.float()).to(torch.bfloat16)
+        lay.q.copy_(q)
+    r = StepRunner(inp)
+    r.run()
+    check_select(inp, r, 0)
+
+
 def test_planted_heavy_keys_are_selected_on_gpu():
     w = small("planted", batch=2, seq_len=4096, budget=256, window=64, n_planted=16)
     inp = wl.make_inputs(w, DEV)
