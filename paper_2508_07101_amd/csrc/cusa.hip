@@ -214,6 +214,19 @@ int plan_topk_slices(int64_t rows, int lc_max, int k) {
     return s < 1 ? 1 : (int)s;
 }
 
+// The same for rows of scores, whose slices are filtered by a threshold of the row (slice_filter_kernel): pieces of
+// about 16384 candidates, no more workgroups than two per CU.
+int plan_filter_slices(int64_t rows, int lc_max) {
+    if (lc_max <= 32768) return 1;
+    int64_t s = ((int64_t)lc_max + 16383) / 16384;
+    if (s > 8) s = 8;
+    if (s > 512 / rows) s = 512 / rows;
+    return s < 1 ? 1 : (int)s;
+}
+int slice_length(int lc_max, int n_slices) { return ((lc_max + n_slices - 1) / n_slices + 4095) / 4096 * 4096; }
+constexpr int SLICE_CAP_MAX = 8192;
+int slice_cap(int k) { return k <= 4096 ? 4096 : SLICE_CAP_MAX; }
+
 // Sampling plan of the filtered fast path for sequences of up to lc candidate positions: the kernel
 // samples every SAMPLE_STEP-th tile of 64 tokens of a sequence, or as many tiles as it has LDS for
 // (n_slots sample slots per head); tile_step is the step of a sequence as long as the bound.
@@ -256,7 +269,7 @@ bool filtered_select(const cusa_params* p, int max_seq_len) {
 }
 
 struct WsLayout {
-    size_t scores, rho_head, part_acc, part_ml, agg, rho_rank, lse, out_tmp, topk_parts, total;
+    size_t scores, rho_head, part_acc, part_ml, agg, rho_rank, lse, out_tmp, topk_parts, slice_cnt, slice_lo, total;
     size_t f_thr, f_cnt, f_fail, f_nfailed, f_cand;           // the selection's filtered fast path
     int filter_cap;                                           // 0: not laid out
     int64_t ldp;
@@ -284,10 +297,11 @@ WsLayout make_layout(const cusa_params* p, int max_seq_len) {
         w.agg = off;       off += align256((size_t)(B * 2 * w.ldp) * 4);
         w.rho_rank = off;  off += align256((size_t)(B * (p->budget - p->window + 1)) * 4);
     }
-    {   // per-head top-k of few long rows: room for the slices' picks (none when rows are not cut)
+    {   // per-head top-k of few long rows: room for the slices' candidates (none when rows are not cut)
         const int lc_i = (int)(lc > 0x7fffffff ? 0x7fffffff : lc);
-        const int s1 = plan_topk_slices(B * H, lc_i, w.k);
-        size_t n = s1 > 1 ? (size_t)s1 * B * H * w.k : 0;
+        const int s1 = plan_filter_slices(B * H, lc_i);
+        const size_t rows = s1 > 1 ? (size_t)s1 * B * H : 0;
+        size_t n = rows * slice_cap(w.k);
         const int n_hist = p->budget - p->window - p->n_sink;
         if (p->rank_mode != CUSA_RANK_FIRST_OCCURRENCE && n_hist > 0) {   // one key row per sequence is ranked too
             const int s2 = plan_topk_slices(B, lc_i, n_hist);
@@ -295,6 +309,10 @@ WsLayout make_layout(const cusa_params* p, int max_seq_len) {
         }
         w.topk_parts = off;
         off += align256(n * 8);
+        w.slice_cnt = off;
+        off += align256(rows * 4);
+        w.slice_lo = off;
+        off += align256(rows > 0 ? (size_t)(B * H) * 4 : 0);
     }
     w.filter_cap = 0;
     w.f_thr = w.f_cnt = w.f_fail = w.f_nfailed = w.f_cand = off;
@@ -494,8 +512,13 @@ constexpr size_t SEL_LDS_MAX = (size_t)UNION_MAX_POSITIONS / 8 + UNION_IDLE_WORD
 
 template <int ITEMS, int MTOP, bool MERGE = false>
 constexpr size_t topk_lds_bytes() {
-    return ((size_t)MTOP * SEL_THREADS + topk_area_entries(ITEMS, MTOP, MERGE)) * sizeof(uint64_t);
+    // the general path: sort buffer and candidate list; the fast path: list and bins
+    constexpr size_t general = ((size_t)MTOP * SEL_THREADS + topk_list_cap(ITEMS, MTOP)) * sizeof(uint64_t);
+    constexpr size_t fast = MERGE ? (ITEMS <= 8 ? ITEMS : 0) * SEL_THREADS * sizeof(uint64_t) + RANK_BINS * sizeof(int)
+                                  : fast_list_cap(MTOP) * sizeof(uint64_t) + 2 * RANK_BINS * sizeof(int);
+    return general > fast ? general : fast;
 }
+size_t slice_lds_bytes(int cap) { return (size_t)cap * sizeof(uint64_t) + RANK_BINS * sizeof(int); }
 
 bool grant_lds(const void* fn, size_t bytes) {
     if (bytes <= 48 * 1024) return true;
@@ -542,7 +565,7 @@ bool device_ready() {
     std::lock_guard<std::mutex> lk(mu);
     if (ready[dev]) return true;
     const bool ok = grant_topk_items<4>() && grant_topk_items<8>() && grant_topk_items<16>() && grant_topk_items<32>() &&
-                    grant_topk_items<0>() && grant_topk_items<-1>() && grant_topk_items<4, true>() &&
+                    grant_topk_items<0>() && grant_lds(reinterpret_cast<const void*>(slice_filter_kernel), slice_lds_bytes(SLICE_CAP_MAX)) && grant_topk_items<-1>() && grant_topk_items<4, true>() &&
                     grant_topk_items<8, true>() && grant_topk_items<16, true>() && grant_lds(reinterpret_cast<const void*>(union_kernel), SEL_LDS_MAX) &&
                     grant_lds(reinterpret_cast<const void*>(per_head_rho_kernel), SEL_LDS_MAX) && grant_sample<1>() &&
                     grant_sample<2>() && grant_sample<4>();
@@ -571,13 +594,14 @@ struct TopkArgs {
     int slice_len, n_slices;
     const int32_t* only_rows = nullptr;   // rank only the rows whose flag is set
     FilterState filter = {};              // merge form: rank the candidates the filtered pass kept
+    SliceLists lists = {};                // streamed form: rank what the slices of a row left
 };
 
 template <int ITEMS, int MTOP, bool MERGE>
 cusa_status launch_topk_m(const TopkArgs& a) {
     const size_t shmem = topk_lds_bytes<ITEMS, MTOP, MERGE>();
     launch(MERGE ? (a.filter.thr ? KID_TOPK_FILTERED : KID_TOPK_MERGE) : a.parts ? KID_TOPK_SLICE : KID_TOPK, topk_kernel<ITEMS, MTOP, MERGE>, a.grid, SEL_THREADS, shmem, a.s, a.P, a.ldp, a.seq_lens, a.rho_head, a.H, a.k,
-           a.budget, a.window, a.raw, a.n_sink, a.parts, a.slice_len, a.n_slices, a.only_rows, a.filter);
+           a.budget, a.window, a.raw, a.n_sink, a.parts, a.slice_len, a.n_slices, a.only_rows, a.filter, a.lists);
     return launch_status();
 }
 
@@ -592,25 +616,39 @@ cusa_status launch_topk(const TopkArgs& a) {
 }
 
 // Ranked top-k of every row of P: rows (b, h) of length L_b - W, output rank-major out[b][j][h].
-// raw: the rows hold uint32 keys instead of scores.  parts: room for rows * slices * k composites.
+// raw: the rows hold uint32 keys instead of scores.  w: the workspace's areas for sliced rows.
 cusa_status run_topk(int lc_max, int B, int H, hipStream_t s, const float* P, int64_t ldp, const int32_t* seq_lens,
-                     int32_t* out, int k, int budget, int window, int raw, int n_sink, uint64_t* parts,
+                     int32_t* out, int k, int budget, int window, int raw, int n_sink, void* ws, const WsLayout& w,
                      const int32_t* only_rows = nullptr) {
     TopkArgs a = {dim3(H, B), s, P, ldp, seq_lens, out, H, k, budget, window, raw, n_sink, nullptr, 0, 1};
     a.only_rows = only_rows;
-    const int n_slices = plan_topk_slices((int64_t)B * H, lc_max, k);
+    const int64_t rows = (int64_t)B * H;
+    const int n_slices = raw ? plan_topk_slices(rows, lc_max, k) : plan_filter_slices(rows, lc_max);
     int n_cand = lc_max;                                  // candidates a workgroup walks
+    if (n_slices > 1 && !raw) {
+        SliceLists& l = a.lists;
+        l.cand = ws_ptr<uint64_t>(ws, w.topk_parts);
+        l.cnt = ws_ptr<int32_t>(ws, w.slice_cnt);
+        l.s_lo = ws_ptr<float>(ws, w.slice_lo);
+        l.cap = slice_cap(k);
+        l.n_slices = n_slices;
+        l.slice_len = slice_length(lc_max, n_slices);
+        launch(KID_TOPK_SLICE, slice_filter_kernel, dim3(H, B, n_slices), SEL_THREADS, slice_lds_bytes(l.cap), s, P, ldp, seq_lens, H, k,
+               budget, window, n_sink, only_rows, l);
+        if (launch_status() != CUSA_OK) return CUSA_ERR_LAUNCH;
+        return launch_topk<0>(a);
+    }
     if (n_slices > 1) {
-        a.parts = parts;
+        a.parts = ws_ptr<uint64_t>(ws, w.topk_parts);
         a.n_slices = n_slices;
-        a.slice_len = ((lc_max + n_slices - 1) / n_slices + 4095) / 4096 * 4096;
+        a.slice_len = slice_length(lc_max, n_slices);
         a.grid = dim3(H, B, n_slices);
         n_cand = a.slice_len;
     }
     const int items = (n_cand + SEL_THREADS - 1) / SEL_THREADS;
     cusa_status st;
-    // many more rows than CUs: the lean streamed kernel, two rows at a time per CU
-    if ((int64_t)B * H >= 512 && items > 8) st = launch_topk<-1>(a);
+    // more rows than CUs: forms that leave room for two rows at a time per CU
+    if (rows > 256 && items > 8) st = launch_topk<-1>(a);
     else if (items <= 4) st = launch_topk<4>(a);
     else if (items <= 8) st = launch_topk<8>(a);
     else if (items <= 16) st = launch_topk<16>(a);
@@ -697,7 +735,7 @@ cusa_status run_select(const cusa_params* p, const void* q, const cusa_kv* kv, i
             if (st != CUSA_OK) return st;
         }
         cusa_status st = run_topk(lc_max, B, H, s, P, w.ldp, kv->seq_lens, rho_head, w.k, p->budget, p->window, 0, p->n_sink,
-                                  ws_ptr<uint64_t>(ws, w.topk_parts), only_failed);
+                                  ws, w, only_failed);
         if (st != CUSA_OK) return st;
     }
     {
@@ -716,7 +754,7 @@ cusa_status run_select(const cusa_params* p, const void* q, const cusa_kv* kv, i
                        H, w.k, p->budget, p->window, p->rank_mode == CUSA_RANK_MAX_SCORE ? 1 : 0, p->n_sink);
                 if (launch_status() != CUSA_OK) return CUSA_ERR_LAUNCH;
                 const cusa_status st = run_topk(lc_max, B, 1, s, reinterpret_cast<const float*>(agg), 2 * w.ldp, kv->seq_lens,
-                                                rho_rank, n_hist, p->budget, p->window, 1, p->n_sink, ws_ptr<uint64_t>(ws, w.topk_parts));
+                                                rho_rank, n_hist, p->budget, p->window, 1, p->n_sink, ws, w);
                 if (st != CUSA_OK) return st;
             }
             launch(KID_RHO_PER_HEAD, per_head_rho_kernel, dim3(1, B), SEL_THREADS, bitmap, s, rho_rank, kv->seq_lens, idx, cnt, 1,

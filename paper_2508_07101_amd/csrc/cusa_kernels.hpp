@@ -124,6 +124,15 @@ __device__ __forceinline__ void lds_barrier() {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// LDS written by some lanes of a wave and read by others of the same wave: a wave's LDS
+// accesses are performed in program order, so only the compiler has to be kept from
+// reordering them.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Exclusive prefix sum of one int per thread over a block of WAVES waves.
 // scratch: WAVES ints of LDS.  Returns the exclusive prefix; *total gets the sum.
 // Every wave adds up the other waves' sums for itself: one wave's lane doing it for all costs as much
@@ -180,15 +189,25 @@ __device__ __forceinline__ float key_score(uint32_t key) {
 // the 64-bit composite (score_key << 32 | ~position): larger composite = better
 // score, or equal score and lower position -- a strict total order, so "the k best"
 // is a unique set and a unique ranking.
+//
+// Fast path: a threshold from a sample of the row (sample_row), one look at every score against it, the few
+// that pass compacted per wave in LDS, and these ranked by a counting sort over value bins
+// (rank_entries).  Ranks are written rank-major: rho_head[b][j][h].
+// General path, for rows where that does not work out (massive ties, scores that are not finite, best scores crowded in
+// one wave's share) and for raw keys:
 //   1. radix select (11/11/10-bit digits, LDS histograms) finds the score key T
 //      of the k-th best candidate and how many candidates tie with it;
 //   2. if more candidates equal T than are still needed, a second radix select
 //      over ~position finds the position bound among the ties;
-//   3. the k survivors are compacted into LDS and bitonic-sorted (descending);
-//   4. ranks are written rank-major: rho_head[b][j][h].
-// With ITEMS > 0 a thread keeps its ITEMS candidates (positions i*1024 + tid) in
-// registers, loaded once with independent loads; ITEMS <= 0 (streamed) re-reads the scores from
-// memory in every pass, 32 independent loads at a time (any length).
+//   3. the k survivors are compacted into LDS and bitonic-sorted (descending).
+// With ITEMS > 0 a thread keeps ITEMS scores in registers, loaded once with independent 16-byte loads;
+// ITEMS <= 0 (streamed) reads the row again in every pass, in batches (any length).
+//
+// What bounds it: one CU per row, its sixteen waves' instructions (each costs the CU sixteen cycles), the barriers
+// between them and, first, the row's way from memory (3 us of the 14 at 32 K candidates).  Measured before (selection
+// with digit histograms, then ranking) -> after, us: 1 x 32 rows of 3840, k 1024: 9.7 -> 8.5; 32 rows of 32256, k 1536: 20.0
+// -> 14.0; 256 rows of 15360, k 3072: 18.1 -> 15.4; 64 rows of 130048, k 3072, in slices: 50.6 -> 32.0; 576 rows of 11552,
+// k 2304: 57.7 -> 24; 1408 rows of 22798, k 3072: 166 -> 83.
 
 struct SelectState {
     uint32_t prefix;     // digits fixed so far
@@ -288,19 +307,8 @@ __device__ __forceinline__ int wave_reserve(int mine, int* counter) {
 // Entries of the LDS candidate list of topk_kernel<ITEMS, MTOP> (0: no list; short rows are
 // cheap to walk again).
 __host__ __device__ constexpr int topk_list_cap(int items, int mtop) {
-    return (items > 0 && items < 8) ? 0 : (mtop <= 2 ? 6144 : 10240);
+    return (items > 0 && items < 8) ? 0 : mtop <= 2 ? 6144 : mtop <= 4 ? 5120 : 10240;
 }
-// 8-byte entries of LDS behind the sort buffer: the candidate list or the quick ranking's segments, and
-// behind them its 2048 bin counters.
-__host__ __device__ constexpr int topk_area_entries(int items, int mtop, bool merge = false) {
-    int n = topk_list_cap(items, mtop) + 1024 > mtop * 1024 + 1024 ? topk_list_cap(items, mtop) + 1024 : mtop * 1024 + 1024;
-    // short rows (no list): room to rank all their candidates at once
-    if (items > 0 && items < 8 && items * 1024 + 1024 > n) n = items * 1024 + 1024;
-    // ranking all composites of a merge at once: items * 1024 segments entries and the bins, sort buffer included
-    if (merge && items * 1024 + 1024 - mtop * 1024 > n) n = items * 1024 + 1024 - mtop * 1024;
-    return n;
-}
-
 // Value of lane (l ^ STRIDE) for STRIDE < 64 without the LDS crossbar: DPP moves inside a 16-lane
 // row, row/half swaps beyond.
 template <int CTRL, int BANK_MASK = 0xF>
@@ -326,14 +334,93 @@ __device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
         return (threadIdx.x & 32) ? s[0] : s[1];
     }
 }
-__device__ __forceinline__ uint32_t lane_xor_any(uint32_t v, int stride) {
-    switch (stride) {
-        case 1: return lane_xor<1>(v);
-        case 2: return lane_xor<2>(v);
-        case 4: return lane_xor<4>(v);
-        case 8: return lane_xor<8>(v);
-        case 16: return lane_xor<16>(v);
-        default: return lane_xor<32>(v);
+// One step of the bitonic network over MTOP * 1024 composites, MTOP per thread, and all steps after it (see topk_kernel).
+template <int MTOP, int SIZE, int STRIDE>
+__device__ __forceinline__ void bitonic_sort(uint64_t (&v)[MTOP], uint64_t* sort_buf, int base) {
+    if constexpr (STRIDE >= 64 * MTOP) {               // partner in another wave
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < MTOP; ++j) sort_buf[base + j * 64] = v[j];
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < MTOP; ++j) {
+            const int i = base + j * 64;
+            const uint64_t o = sort_buf[i ^ STRIDE];
+            const bool keep_max = ((i & STRIDE) == 0) == ((i & SIZE) == 0);
+            v[j] = ((v[j] > o) == keep_max) ? v[j] : o;
+        }
+    } else if constexpr (STRIDE >= 64) {               // partner in this thread's registers
+        constexpr int JS = STRIDE >> 6;
+#pragma unroll
+        for (int j = 0; j < MTOP; ++j) {
+            if ((j & JS) == 0 && (j | JS) < MTOP) {
+                const bool desc = ((base + j * 64) & SIZE) == 0;
+                const uint64_t a = v[j], c = v[j | JS];
+                const bool sw = (a < c) == desc;
+                v[j] = sw ? c : a;
+                v[j | JS] = sw ? a : c;
+            }
+        }
+    } else {                                           // partner in another lane of this wave
+#pragma unroll
+        for (int j = 0; j < MTOP; ++j) {
+            const int i = base + j * 64;
+            const uint64_t o = ((uint64_t)lane_xor<STRIDE>((uint32_t)(v[j] >> 32)) << 32) | lane_xor<STRIDE>((uint32_t)v[j]);
+            const bool keep_max = ((i & STRIDE) == 0) == ((i & SIZE) == 0);
+            v[j] = ((v[j] > o) == keep_max) ? v[j] : o;
+        }
+    }
+    if constexpr (STRIDE > 1) bitonic_sort<MTOP, SIZE, STRIDE / 2>(v, sort_buf, base);
+    else if constexpr (SIZE < MTOP * 1024) bitonic_sort<MTOP, SIZE * 2, SIZE>(v, sort_buf, base);
+}
+
+// Maximum / sum over a wave by DPP moves; lane 63 holds the result (lanes without a source keep their own).
+__device__ __forceinline__ uint32_t wave_max_last(uint32_t v) {
+#define CUSA_STEP(CTRL, ROWS) { const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, ROWS, 0xF, false); v = o > v ? o : v; }
+    CUSA_STEP(0x111, 0xF) CUSA_STEP(0x112, 0xF) CUSA_STEP(0x114, 0xF) CUSA_STEP(0x118, 0xF) CUSA_STEP(0x142, 0xA) CUSA_STEP(0x143, 0xC)
+#undef CUSA_STEP
+    return v;
+}
+__device__ __forceinline__ float wave_sum_last(float v) {
+#define CUSA_STEP(CTRL, ROWS) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xF, false));
+    CUSA_STEP(0x111, 0xF) CUSA_STEP(0x112, 0xF) CUSA_STEP(0x114, 0xF) CUSA_STEP(0x118, 0xF) CUSA_STEP(0x142, 0xA) CUSA_STEP(0x143, 0xC)
+#undef CUSA_STEP
+    return v;
+}
+// Maximum over the sixteen values of a 16-lane row, in every lane.
+__device__ __forceinline__ uint32_t row_max16(uint32_t v) {
+#define CUSA_STEP(CTRL) { const uint32_t o = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true); v = o > v ? o : v; }
+    CUSA_STEP(0x128) CUSA_STEP(0x124) CUSA_STEP(0x122) CUSA_STEP(0x121)   // row_ror:8, 4, 2, 1
+#undef CUSA_STEP
+    return v;
+}
+
+// LDS words of the ranking, besides the bins and the segments.
+struct RankScratch {
+    float excess;                // cleared by the caller, like n
+    int n, crowded, wave[SEL_WAVES];
+};
+constexpr int RANK_BINS = 2048;
+enum { RANK_DONE = 0, RANK_FAILED = 1, RANK_TOO_FEW = 2 };
+
+// Ranks the m <= 64 CHUNKS composites of a segment that starts at rank 0, the workgroup together: every wave holds all
+// of them, 64 to a register, and compares its sixteenth of them with 64 at a time.
+template <int CHUNKS>
+__device__ __forceinline__ void rank_together(const uint64_t* seg, int m, int k_out, int32_t* __restrict__ out, int H) {
+    const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+    uint64_t r[CHUNKS];
+#pragma unroll
+    for (int c = 0; c < CHUNKS; ++c) r[c] = c * 64 + lane < m ? seg[c * 64 + lane] : 0;
+#pragma unroll
+    for (int c = 0; c < CHUNKS; ++c) {
+        for (int l = w; l < 64 && c * 64 + l < m; l += SEL_WAVES) {
+            const uint64_t cv = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(r[c] >> 32), l) << 32) |
+                                (uint32_t)__builtin_amdgcn_readlane((int)r[c], l);
+            int rank = 0;
+#pragma unroll
+            for (int q = 0; q < CHUNKS; ++q) rank += __popcll(__ballot(r[q] > cv));
+            if (lane == 0 && rank < k_out) out[(int64_t)rank * H] = (int32_t)~(uint32_t)cv;
+        }
     }
 }
 
@@ -344,114 +431,234 @@ __device__ __forceinline__ uint32_t lane_xor_any(uint32_t v, int stride) {
 // unless scores repeat -- a composite's rank is the number of entries that beat it.  The range is
 // [s_lo, s_lo + 6 x the mean excess over s_lo], not up to the best score: a few very large scores
 // (attention sinks, hot tokens) would otherwise stretch the bins over empty space and crowd the
-// rest; whatever lies above shares the first bin, which may hold more.  About a fifth of the
-// instructions of a sorting network.  Returns false, having written nothing, when a bin is crowded
-// (more than RMAX entries among the bins that hold wanted ranks, RMAX_FIRST in the first: many equal
-// scores) or the scores are not finite;
-// the caller then ranks another way.  seg: room for seg_cap composites (more: false); rbin: 2048 ints; scratch: as for
-// block_scan_excl.  Called by the whole workgroup.
+// rest; whatever lies above shares the first bin.  About a fifth of the instructions of a sorting network.
+// RANK_FAILED, with nothing written: a bin that holds wanted ranks has more than RMAX entries (many equal scores), the
+// scores are not finite or all alike, or there are more than seg_cap; the caller then ranks another way.
+// RANK_TOO_FEW: fewer than k_out composites.  seg: room for seg_cap composites; rbin: RANK_BINS zeros; *rs cleared; all
+// visible to the workgroup (one barrier since).  Called by the whole workgroup.
+//
+// Sixteen waves on one CU: an instruction that all of them execute costs sixteen cycles, a barrier a few
+// hundred, so sums and scans go by DPP and the barriers wait for LDS only.
 template <int NPT, typename Mine>
-__device__ __forceinline__ bool quick_rank(Mine mine, float s_lo, int k_out, uint64_t* seg, int seg_cap, int* rbin,
-                                           int* scratch, int32_t* __restrict__ out, int H) {
-    constexpr int RBINS = 2048, RMAX = 32, RMAX_FIRST = 512;
-    __shared__ float rk_excess;
-    __shared__ int rk_crowd, rk_first, rk_n;
-    const int tid = threadIdx.x;
-    __syncthreads();                                     // whatever the areas held before has been read
-    if (tid == 0) {
-        rk_excess = 0.0f;
-        rk_crowd = rk_n = 0;
+__device__ __forceinline__ int rank_entries(Mine mine, float s_lo, int k_out, uint64_t* seg, int seg_cap, int* rbin,
+                                            RankScratch* rs, int32_t* __restrict__ out, int H) {
+    constexpr int RMAX = 512;
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(wave_id());
+    {
+        float excess = 0.0f;
+        int n_mine = 0;
+#pragma unroll
+        for (int j = 0; j < NPT; ++j) {
+            if (mine(j) != 0) {
+                excess += key_score((uint32_t)(mine(j) >> 32)) - s_lo;
+                ++n_mine;
+            }
+        }
+        excess = wave_sum_last(excess);
+        n_mine = wave_scan_incl(n_mine);
+        if (lane_id() == 63) {
+            atomicAdd(&rs->excess, excess);
+            atomicAdd(&rs->n, n_mine);
+        }
     }
-    for (int i = tid; i < RBINS; i += SEL_THREADS) rbin[i] = 0;
-    float excess = 0.0f;
-    int n_mine = 0;
+    lds_barrier();
+    const int n = rs->n;
+    if (n < k_out) return RANK_TOO_FEW;                  // workgroup-uniform, like all that follows
+    const float range = 6.0f * rs->excess / (float)n;
+    if (!(range > 0.0f && range < 3.0e38f) || n > seg_cap) return RANK_FAILED;
+    const float scale = (float)(RANK_BINS - 1) / range;
+    auto bin_of = [&](uint64_t cv) {                     // bin 0 holds the best scores
+        const int up = (int)((key_score((uint32_t)(cv >> 32)) - s_lo) * scale);
+        return RANK_BINS - 1 - (up < 0 ? 0 : up > RANK_BINS - 1 ? RANK_BINS - 1 : up);
+    };
+    uint32_t slot[NPT];                                  // bin << 16 | place in the bin
 #pragma unroll
     for (int j = 0; j < NPT; ++j) {
         if (mine(j) != 0) {
-            excess += key_score((uint32_t)(mine(j) >> 32)) - s_lo;
-            ++n_mine;
+            const int bn = bin_of(mine(j));
+            slot[j] = ((uint32_t)bn << 16) | (uint32_t)atomicAdd(&rbin[bn], 1);
         }
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        excess += __shfl_xor(excess, o);
-        n_mine += __shfl_xor(n_mine, o);
-    }
-    __syncthreads();                                     // the counters and rbin are cleared
-    if (lane_id() == 0) {
-        atomicAdd(&rk_excess, excess);
-        atomicAdd(&rk_n, n_mine);
-    }
-    __syncthreads();
-    const int n = rk_n;
-    const float range = n > 0 ? 6.0f * rk_excess / (float)n : 0.0f;
-    // workgroup-uniform (not so: all scores equal, or not finite, or more composites than seg holds)
-    bool quick = range > 0.0f && range < 3.0e38f && n <= seg_cap;
-    const float scale = quick ? (float)(RBINS - 1) / range : 0.0f;
-    auto bin_of = [&](uint64_t cv) {                     // bin 0 holds the best scores
-        const int up = (int)((key_score((uint32_t)(cv >> 32)) - s_lo) * scale);
-        return RBINS - 1 - (up < 0 ? 0 : up > RBINS - 1 ? RBINS - 1 : up);
-    };
-    int slot[NPT];
-    if (quick) {
-#pragma unroll
-        for (int j = 0; j < NPT; ++j)
-            if (mine(j) != 0) slot[j] = atomicAdd(&rbin[bin_of(mine(j))], 1);
-    }
-    __syncthreads();
-    {   // counts -> first indices (thread i owns bins 2i, 2i + 1); the most crowded bin
+    lds_barrier();
+    {   // counts -> first indices (thread i owns bins 2i, 2i + 1)
         const int c0 = rbin[2 * tid], c1 = rbin[2 * tid + 1];
-        int total;
-        const int first = block_scan_excl(c0 + c1, scratch, &total);
-        // only segments that reach into the wanted ranks are walked: the others may be crowded; bin 0 is
-        // looked at on its own
-        int crowd = first + c0 < k_out ? c1 : 0;
-        if (tid != 0 && first < k_out && c0 > crowd) crowd = c0;
-        if (tid == 0) rk_first = c0;
+        const int inc = wave_scan_incl(c0 + c1);
+        if (lane_id() == 63) rs->wave[w] = inc;
+        lds_barrier();
+        int first = inc - c0 - c1;
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const int other = __shfl_xor(crowd, o);
-            crowd = other > crowd ? other : crowd;
-        }
-        if (lane_id() == 0) atomicMax(&rk_crowd, crowd);
+        for (int i = 0; i < SEL_WAVES; ++i) first += i < w ? rs->wave[i] : 0;
+        // only segments that reach into the wanted ranks are walked: the others may be crowded
+        if ((first < k_out && c0 > RMAX) || (first + c0 < k_out && c1 > RMAX)) rs->crowded = 1;
         rbin[2 * tid] = first;
         rbin[2 * tid + 1] = first + c0;
     }
-    __syncthreads();
-    quick = quick && rk_crowd <= RMAX && rk_first <= RMAX_FIRST;
-    if (!quick) return false;
+    lds_barrier();
+    if (rs->crowded) return RANK_FAILED;
 #pragma unroll
     for (int j = 0; j < NPT; ++j)
-        if (mine(j) != 0) seg[rbin[bin_of(mine(j))] + slot[j]] = mine(j);
-    __syncthreads();
+        if (mine(j) != 0) seg[rbin[slot[j] >> 16] + (int)(slot[j] & 0xffffu)] = mine(j);
+    lds_barrier();
+    // The first bin holds whatever lies above the range (hot tokens, often with equal scores): when there are many, the
+    // waves rank them together, an entry against 64 others per compare.
+    const int m0 = __builtin_amdgcn_readfirstlane(rbin[1]);
+    const bool many = m0 > 16;
+    if (many) {
+        if (m0 <= 64) rank_together<1>(seg, m0, k_out, out, H);
+        else if (m0 <= 128) rank_together<2>(seg, m0, k_out, out, H);
+        else if (m0 <= 256) rank_together<4>(seg, m0, k_out, out, H);
+        else rank_together<RMAX / 64>(seg, m0, k_out, out, H);
+    }
     // the composites ranked below k_out lie in the segments' first k_out entries or just behind them
-    for (int i = tid; i < n; i += SEL_THREADS) {
+    for (int i = (many ? m0 : 0) + tid; i < n; i += SEL_THREADS) {
         const uint64_t cv = seg[i];
-        const int bn = bin_of(cv), lo = rbin[bn], hi = bn == RBINS - 1 ? n : rbin[bn + 1];
+        const int bn = bin_of(cv), lo = rbin[bn], hi = bn == RANK_BINS - 1 ? n : rbin[bn + 1];
         if (lo >= k_out) break;                          // (segments are in rank order: nothing wanted from here on)
         int rank = lo;
-        for (int q = lo; q < hi; ++q) rank += seg[q] > cv ? 1 : 0;
+        for (int q = lo; q < hi; q += 4) {               // four at a time: the reads overlap
+            uint64_t o[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = seg[min(q + e, hi - 1)];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) rank += (q + e < hi && o[e] > cv) ? 1 : 0;
+        }
         if (rank < k_out) out[(int64_t)rank * H] = (int32_t)~(uint32_t)cv;
+    }
+    return RANK_DONE;
+}
+
+// Entries of the list of candidates that a whole row's fast path may keep (a sixteenth of them per wave).
+__host__ __device__ constexpr int fast_list_cap(int mtop) { return mtop <= 2 ? 4096 : mtop <= 4 ? 7168 : 14336; }
+constexpr int FAST_SAMPLE = 4;                          // sampled keys per thread
+constexpr float FAST_Z = 4.0f;
+
+// A threshold for the k_eff best of a row's N candidates from a sample of their keys: the sample is counted into
+// 2048 bins that divide [lowest, highest sampled score] evenly by value, and the threshold is the lower edge of the bin
+// below the one that holds the j-th largest of the sample.  Where all candidates are sampled, j = k_eff makes it a
+// bound that at least k_eff candidates reach; otherwise j = f n_s + FAST_Z sqrt(f (1 - f) n_s) + 1 with f = k_eff / N,
+// which leaves too few candidates once in 30 000 rows whose order has nothing to do with the scores.  The threshold only
+// decides how long a row takes.
+struct RowSample {
+    int above, c_hi, c_lo, n_s;  // this thread's two bins (from the top), sampled keys in higher bins, sampled keys
+    float smin, step;
+};
+struct SampleScratch {
+    uint32_t hi[SEL_WAVES], not_lo[SEL_WAVES];
+    int wave[SEL_WAVES], bin;
+};
+// sk: the thread's sampled keys (0: none).  shist: RANK_BINS zeros, written before the call (the first barrier in here
+// makes them visible).  False (workgroup-uniform): no usable sample.
+template <int S>
+__device__ __forceinline__ bool sample_row(const uint32_t (&sk)[S], int* shist, SampleScratch* ss, RowSample* rs) {
+    const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+    uint32_t hi = 0u, not_lo = 0u;
+#pragma unroll
+    for (int i = 0; i < S; ++i) {
+        const uint32_t nk = sk[i] != 0u ? ~sk[i] : 0u;
+        hi = sk[i] > hi ? sk[i] : hi;
+        not_lo = nk > not_lo ? nk : not_lo;
+    }
+    hi = wave_max_last(hi);
+    not_lo = wave_max_last(not_lo);
+    if (lane == 63) {
+        ss->hi[w] = hi;
+        ss->not_lo[w] = not_lo;
+    }
+    lds_barrier();
+    const uint32_t kmax = row_max16(ss->hi[lane & 15]), kmin = ~row_max16(ss->not_lo[lane & 15]);
+    rs->smin = key_score(__builtin_amdgcn_readfirstlane(kmin));
+    const float range = key_score(__builtin_amdgcn_readfirstlane(kmax)) - rs->smin;
+    if (!(range > 0.0f && range < 3.0e38f)) return false;   // nothing sampled, all alike, or not finite
+    rs->step = range * (1.0f / (RANK_BINS - 1));
+    const float scale = (float)(RANK_BINS - 1) / range;
+#pragma unroll
+    for (int i = 0; i < S; ++i) {
+        if (sk[i] != 0u) {
+            const int bi = (int)((key_score(sk[i]) - rs->smin) * scale);
+            atomicAdd(&shist[bi < 0 ? 0 : bi > RANK_BINS - 1 ? RANK_BINS - 1 : bi], 1);
+        }
+    }
+    lds_barrier();
+    rs->c_hi = shist[RANK_BINS - 1 - 2 * tid];
+    rs->c_lo = shist[RANK_BINS - 2 - 2 * tid];
+    const int inc = wave_scan_incl(rs->c_hi + rs->c_lo);
+    if (lane == 63) ss->wave[w] = inc;
+    lds_barrier();
+    rs->above = inc - rs->c_hi - rs->c_lo;
+    rs->n_s = 0;
+#pragma unroll
+    for (int i = 0; i < SEL_WAVES; ++i) {
+        const int c = ss->wave[i];
+        rs->above += i < w ? c : 0;
+        rs->n_s += c;
     }
     return true;
 }
+// The threshold for the j-th largest of the sample, and the score that ranking may start its bins at (no lower
+// than the sample's lowest, also where everything is kept).  One barrier.
+__device__ __forceinline__ float sample_threshold(const RowSample& rs, int j, SampleScratch* ss, float* s_lo) {
+    const int tid = threadIdx.x;
+    if (rs.above < j && j <= rs.above + rs.c_hi + rs.c_lo) ss->bin = RANK_BINS - (j <= rs.above + rs.c_hi ? 1 : 2) - 2 * tid;
+    lds_barrier();
+    const int bin = __builtin_amdgcn_readfirstlane(ss->bin);
+    const bool all = j >= rs.n_s || bin < 1;
+    *s_lo = all ? rs.smin : rs.smin + (float)(bin - 1) * rs.step;
+    return all ? -3.4e38f : *s_lo;
+}
+// What is no candidate (a position outside [lo, hi)) gets the score -infinity, which no threshold lets through.  (A
+// candidate's own -infinity is lost with it: if it is wanted, too few are kept, and the row is ranked the general way.)
+template <int N, typename Pos>
+__device__ __forceinline__ void mask_scores(f32x4 (&x)[N / 4], Pos pos, int lo, int hi) {
+#pragma unroll
+    for (int u = 0; u < N; ++u) x[u >> 2][u & 3] = pos(u) < hi && pos(u) >= lo ? x[u >> 2][u & 3] : -INFINITY;
+}
+// Appends the lanes' (score, position) to a wave's list in LDS; n counts all, also those past the capacity.
+__device__ __forceinline__ void list_push(bool in, float score, int t, uint64_t* list, int cap, int& n) {
+    const uint64_t mask = __ballot(in);
+    if (mask) {
+        const int at = n + mbcnt(mask);
+        if (in && at < cap) list[at] = ((uint64_t)__float_as_uint(score) << 32) | (uint32_t)~(uint32_t)t;
+        n += __popcll(mask);
+    }
+}
+__device__ __forceinline__ int sample_rank_wanted(int k_eff, int n, int n_s) {
+    const float f = (float)k_eff / (float)n;
+    return min((int)(f * (float)n_s + FAST_Z * sqrtf(f * (1.0f - f) * (float)n_s)) + 1, n_s);
+}
+
+// Position of the sample's 64-key segment number x (of `total`) of a row of n positions, spread evenly.
+__device__ __forceinline__ int sample_segment(int x, int total, int n) {
+    const int segs = (n + 63) >> 6;
+    return (segs <= total ? x : (int)((int64_t)x * segs / total)) * 64;
+}
+
+// Candidates of a slice of a long row that reach the row's threshold (slice_filter_kernel), for the ranking launch.
+struct SliceLists {
+    uint64_t* cand;              // [row][slice][cap]; nullptr: rows are not sliced
+    int32_t* cnt;                // [row][slice]; above cap: some did not fit
+    float* s_lo;                 // [row] score of the threshold
+    int cap, n_slices, slice_len;
+};
+constexpr int SLICE_SAMPLE = 8;                         // sampled keys per thread
 
 // ITEMS == -1 is the streamed kernel in a register-lean form (half the keys in flight, compiled for two
-// resident workgroups per CU): with many more rows than CUs two rows overlap on a CU, which gains more
-// than the shorter batches lose (c5, 2048 rows: 198 -> 147 us); with one row per CU it is twice as
-// slow as the wide form (c4: 65 -> 134 us), so few long rows keep ITEMS == 0.
+// resident workgroups per CU): with more rows than CUs two rows overlap on a CU, which gains more
+// than the shorter batches lose; with one row per CU it is slower than the wide form, so few long rows
+// keep ITEMS == 0.
 //
-// Few long rows (fewer rows than CUs, more than 32768 candidates) are cut into slices, one workgroup
-// each (blockIdx.z): a slice selects its own k best and leaves their composites, unsorted and padded
-// with zeros, in parts[row][slice][k]; the k best of a row are among the k best of its slices, so a
-// second launch (MERGE) selects and ranks among those n_slices * k composites instead of the row.
+// Few long rows (fewer rows than CUs, more than 32768 candidates) are cut into slices: rows of scores by
+// slice_filter_kernel and a ranking launch (sl); rows of raw keys by this kernel, one workgroup per slice (blockIdx.z): a
+// slice selects its own k best and leaves their composites, unsorted and padded with zeros, in
+// parts[row][slice][k]; the k best of a row are among the k best of its slices, so a second launch (MERGE) selects
+// and ranks among those n_slices * k composites instead of the row.  MERGE also ranks what a filtered pass kept.
 template <int ITEMS, int MTOP, bool MERGE = false>
-__global__ __launch_bounds__(SEL_THREADS, ((ITEMS == -1 && MTOP <= 4) || (MERGE && ITEMS <= 4 && MTOP <= 2)) ? 8 : 4) void topk_kernel(const float* __restrict__ P, int64_t ldp,
+__global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS > 0 && ITEMS <= 8))) ? 8 : 4) void topk_kernel(const float* __restrict__ P, int64_t ldp,
                                                             const int32_t* __restrict__ seq_lens,
                                                             int32_t* __restrict__ rho_head, int H, int k,
                                                             int budget, int window, int raw_keys, int n_sink,
                                                             uint64_t* __restrict__ parts, int slice_len, int n_slices,
-                                                            const int32_t* __restrict__ only_rows, FilterState flt) {
+                                                            const int32_t* __restrict__ only_rows, FilterState flt,
+                                                            SliceLists sl) {
     static_assert(!MERGE || ITEMS > 0, "the composites of a merge are held in registers");
     constexpr int NSORT = MTOP * SEL_THREADS;         // k <= NSORT
     constexpr int CAP = topk_list_cap(ITEMS, MTOP);
@@ -460,7 +667,10 @@ __global__ __launch_bounds__(SEL_THREADS, ((ITEMS == -1 && MTOP <= 4) || (MERGE 
     __shared__ __attribute__((aligned(16))) int scratch[SEL_WAVES];
     __shared__ SelectState st;
     __shared__ int n_out, n_list;
+    __shared__ RankScratch rank_st;
+    __shared__ SampleScratch sample_st;
     int* hist = reinterpret_cast<int*>(sort_buf);     // 2048 ints = 8 KB <= NSORT * 8
+    const int wv = __builtin_amdgcn_readfirstlane(wave_id());
 
     // Workgroups go to the 8 XCDs round-robin in launch order.  The heads of a sequence write the same
     // lines of the rank-major output (entry (j, h) next to (j, h+1)); with eight sequences or more, all
@@ -497,7 +707,18 @@ __global__ __launch_bounds__(SEL_THREADS, ((ITEMS == -1 && MTOP <= 4) || (MERGE 
     // raw_keys: the row already holds order-preserving uint32 keys (the aggregated ranking keys of
     // the votes / max-score readings) instead of binary32 scores
     auto key_of = [raw_keys](float v) { return raw_keys ? __float_as_uint(v) : score_key(v); };
-    uint32_t keys[ITEMS > 0 ? ITEMS : 1];
+    // Keys held in registers come in quads, 16-byte loads: quad q of wave w is its part of the 4096-key block
+    // rev(q) + w (rev: bits reversed), so that the first quads of all waves are 256-key pieces from all over the row;
+    // one key of each of the first four is the row's sample.
+    constexpr int QUADS = ITEMS > 4 ? ITEMS / 4 : 1;
+    int my_tid = threadIdx.x;
+    auto item_pos = [&](int i) {
+        constexpr int LOG2 = QUADS >= 8 ? 3 : QUADS >= 4 ? 2 : QUADS >= 2 ? 1 : 0;
+        const int q = i >> 2, rev = LOG2 == 0 ? 0 : (int)(__builtin_bitreverse32((uint32_t)q) >> (LOG2 == 0 ? 31 : 32 - LOG2));
+        return t_lo + ((rev + wv) & (QUADS - 1)) * (4 * SEL_THREADS) + my_tid * 4 + (i & 3);
+    };
+    f32x4 x[!MERGE && ITEMS > 0 ? QUADS : 1];         // scores (or raw keys)
+    uint32_t keys[ITEMS > 0 ? ITEMS : 1];             // 0: no candidate
     int pos_of[MERGE ? ITEMS : 1];                     // MERGE: the positions that come with the keys
     if constexpr (MERGE) {
         int n_cand = n_slices * k;
@@ -523,39 +744,22 @@ __global__ __launch_bounds__(SEL_THREADS, ((ITEMS == -1 && MTOP <= 4) || (MERGE 
             const uint64_t cv = src[sl < n_cand ? sl : n_cand - 1];
             mcv[i] = sl < n_cand ? cv : 0;
         }
-        // These composites are few and most of them among the k best, so they are first ranked as they are:
-        // quick_rank over all of them, of which only the ranks below k_eff are written.  A filtered pass's
-        // candidates are all at or above the head's threshold; the slices' picks (zeros where a slice had
-        // fewer than k) start at the lowest of their scores.  If that does not work out (crowded bins) they
-        // are selected and sorted like any row.
-        if constexpr (ITEMS <= 8 || MTOP <= 4) {       // (what fits the register file)
-            if (!raw_keys) {
-                float s_lo;
-                if (flt.thr) {
-                    s_lo = key_score(flt.thr[(int64_t)b * H + h]);
-                } else {
-                    __shared__ uint32_t merge_lowest;
-                    uint32_t lowest = 0xffffffffu;
-#pragma unroll
-                    for (int i = 0; i < ITEMS; ++i) {
-                        const uint32_t key = (uint32_t)(mcv[i] >> 32);
-                        if (mcv[i] != 0 && key < lowest) lowest = key;
-                    }
-                    if (threadIdx.x == 0) merge_lowest = 0xffffffffu;
-                    __syncthreads();
-#pragma unroll
-                    for (int o = 32; o > 0; o >>= 1) {
-                        const uint32_t other = __shfl_xor(lowest, o);
-                        lowest = other < lowest ? other : lowest;
-                    }
-                    if (lane_id() == 0) atomicMin(&merge_lowest, lowest);
-                    __syncthreads();
-                    s_lo = key_score(merge_lowest);
+        // A filtered pass's candidates are few and most of them among the k best, so they are first ranked as they
+        // are: all of them, of which only the ranks below k_eff are written.  If that does not work out
+        // (crowded bins) they are selected and sorted like any row.
+        if constexpr (ITEMS <= 8) {
+            if (flt.thr) {
+                int* const rbin = reinterpret_cast<int*>(sort_buf + ITEMS * SEL_THREADS);
+                rbin[2 * threadIdx.x] = rbin[2 * threadIdx.x + 1] = 0;
+                if (threadIdx.x == 0) {
+                    rank_st.excess = 0.0f;
+                    rank_st.n = rank_st.crowded = 0;
                 }
-                if (quick_rank<ITEMS>([&](int j) { return mcv[j]; }, s_lo, k_eff, sort_buf, ITEMS * SEL_THREADS,
-                                      reinterpret_cast<int*>(sort_buf + ITEMS * SEL_THREADS), scratch,
-                                      rho_head + (int64_t)b * k * H + h, H))
+                lds_barrier();
+                if (rank_entries<ITEMS>([&](int j) { return mcv[j]; }, key_score(flt.thr[(int64_t)b * H + h]), k_eff, sort_buf,
+                                        ITEMS * SEL_THREADS, rbin, &rank_st, rho_head + (int64_t)b * k * H + h, H) == RANK_DONE)
                     return;
+                __syncthreads();
             }
         }
 #pragma unroll
@@ -564,12 +768,10 @@ __global__ __launch_bounds__(SEL_THREADS, ((ITEMS == -1 && MTOP <= 4) || (MERGE 
             pos_of[i] = (int)~(uint32_t)mcv[i];
         }
     } else if constexpr (ITEMS > 0) {
+        // rows are padded to a multiple of 64 entries (ldp): a quad that starts below ldp stays inside its row
 #pragma unroll
-        for (int i = 0; i < ITEMS; ++i) {
-            const int t = t_lo + i * SEL_THREADS + threadIdx.x;
-            const uint32_t kv_ = key_of(row[t < t_hi ? t : t_hi - 1]);   // clamped: loads stay unconditional
-            keys[i] = (t < t_hi && t >= n_sink) ? kv_ : 0u;
-        }
+        for (int q = 0; q < QUADS; ++q) x[q] = *reinterpret_cast<const f32x4*>(row + min(item_pos(4 * q), (int)ldp - 4));
+        asm volatile("" : "+v"(my_tid));              // positions are made anew where they are needed, not kept in registers
     }
     // Streamed rows (ITEMS <= 0) are walked in batches of SB keys per thread covering the positions
     // [t0, t0 + SB * 1024): key u of a thread is position t0 + ((u / 4) * 1024 + thread) * 4 + u % 4, so a
@@ -595,14 +797,26 @@ __global__ __launch_bounds__(SEL_THREADS, ((ITEMS == -1 && MTOP <= 4) || (MERGE 
             kk[u] = (t < t_hi && t >= n_sink) ? kv_ : 0u;
         }
     };
-    // f(keys of the batch, first position of the batch) for every batch of a streamed row
+    // f(scores of the batch, first position of the batch) for every batch of a streamed row; the same with keys
+    auto stream_scores = [&](auto f) {
+        f32x4 next[SB / 4];
+        stream_issue(next, t_lo);
+        for (int t0 = t_lo; t0 < t_hi; t0 += SB * SEL_THREADS) {
+            f32x4 cur[SB / 4];
+#pragma unroll
+            for (int v = 0; v < SB / 4; ++v) cur[v] = next[v];
+            stream_issue(next, t0 + SB * SEL_THREADS);   // past the row's end: clamped loads, never used
+            __builtin_amdgcn_sched_barrier(0);
+            f(cur, t0);
+        }
+    };
     auto stream_batches = [&](auto f) {
-        f32x4 x[SB / 4];
-        stream_issue(x, t_lo);
+        f32x4 next[SB / 4];
+        stream_issue(next, t_lo);
         for (int t0 = t_lo; t0 < t_hi; t0 += SB * SEL_THREADS) {
             uint32_t kk[SB];
-            stream_take(x, kk, t0);
-            stream_issue(x, t0 + SB * SEL_THREADS);    // past the row's end: clamped loads, never used
+            stream_take(next, kk, t0);
+            stream_issue(next, t0 + SB * SEL_THREADS);
             __builtin_amdgcn_sched_barrier(0);
             f(kk, t0);
         }
@@ -611,7 +825,7 @@ __global__ __launch_bounds__(SEL_THREADS, ((ITEMS == -1 && MTOP <= 4) || (MERGE 
         if constexpr (ITEMS > 0) {
 #pragma unroll
             for (int i = 0; i < ITEMS; ++i) {
-                f(keys[i], MERGE ? pos_of[i] : t_lo + i * SEL_THREADS + (int)threadIdx.x);
+                f(keys[i], MERGE ? pos_of[i] : item_pos(i));
             }
         } else {
             stream_batches([&](const uint32_t (&kk)[SB], int t0) {
@@ -621,6 +835,144 @@ __global__ __launch_bounds__(SEL_THREADS, ((ITEMS == -1 && MTOP <= 4) || (MERGE 
         }
     };
 
+    // The fast path.  A threshold from a sample of the row lets the k_eff best and a few more candidates through;
+    // each wave compacts those it meets into its share of an LDS list, and they are ranked as they are
+    // (rank_entries).  One look at every key, one compare: what the selection below pays for -- histogram atomics that
+    // meet in a handful of digit bins, top candidates of every thread -- falls away.  It stands for rows that this
+    // does not work out for (crowded bins: massive ties; scores that are not finite; a list that overflows
+    // because a wave's share of the row holds too many of the best) and for raw keys.
+    if constexpr (!MERGE) {
+        if (!slice && !raw_keys) {                    // uniform
+            constexpr int FCAP = fast_list_cap(MTOP), WCAP = FCAP / SEL_WAVES, LPT = (WCAP + 63) / 64;
+            int* const shist = reinterpret_cast<int*>(sort_buf + FCAP);
+            int* const rbin = shist + RANK_BINS;
+            const int tid = threadIdx.x, lane = lane_id();
+            reinterpret_cast<u32x4*>(shist)[tid] = u32x4{0u, 0u, 0u, 0u};   // both areas
+            if (tid == 0) {
+                rank_st.excess = 0.0f;
+                rank_st.n = rank_st.crowded = 0;
+            }
+            int32_t* const my_out = rho_head + (int64_t)b * k * H + h;
+            uint64_t* const wlist = sort_buf + wv * WCAP;
+            bool tried = false;
+            if constexpr (ITEMS == 0) {               // a long row whose slices have been filtered already
+                if (sl.cand) {
+                    const int64_t r0 = ((int64_t)b * H + h) * sl.n_slices;
+                    int n = 0;
+                    bool fits = true;
+                    for (int z = 0; z < sl.n_slices; ++z) {
+                        const int c = sl.cnt[r0 + z];
+                        fits = fits && c <= sl.cap;
+                        n += min(c, sl.cap);
+                    }
+                    if (fits && n <= FCAP && n >= k_eff) {
+                        constexpr int NPT = (FCAP + SEL_THREADS - 1) / SEL_THREADS;
+                        uint64_t lv[NPT];
+#pragma unroll
+                        for (int j = 0; j < NPT; ++j) {
+                            int i = tid + j * SEL_THREADS;
+                            lv[j] = 0;
+                            if (i < n) {
+                                int z = 0;
+                                for (int c = sl.cnt[r0]; i >= c; c = sl.cnt[r0 + z]) {
+                                    i -= c;
+                                    ++z;
+                                }
+                                lv[j] = sl.cand[(r0 + z) * sl.cap + i];
+                            }
+                        }
+                        lds_barrier();                // the cleared areas
+                        if (rank_entries<NPT>([&](int j) { return lv[j]; }, sl.s_lo[(int64_t)b * H + h], k_eff, sort_buf, FCAP, rbin,
+                                              &rank_st, my_out, H) == RANK_DONE)
+                            return;
+                        tried = true;
+                    }
+                }
+            }
+            if (!tried) {
+                if constexpr (ITEMS > 0) {            // a wave's quad is 256 positions: all of them candidates, some, or none
+#pragma unroll
+                    for (int q = 0; q < QUADS; ++q) {
+                        const int first = __builtin_amdgcn_readfirstlane(item_pos(4 * q));
+                        if (first < n_sink || first + 256 > t_hi) {
+                            f32x4 (&xq)[1] = *reinterpret_cast<f32x4 (*)[1]>(&x[q]);
+                            mask_scores<4>(xq, [&](int u) { return item_pos(4 * q + u); }, n_sink, t_hi);
+                        }
+                    }
+                    asm volatile("" : "+v"(my_tid));
+                }
+                uint32_t sk[FAST_SAMPLE];
+#pragma unroll
+                for (int i = 0; i < FAST_SAMPLE; ++i) {
+                    if constexpr (ITEMS > 0) {
+                        const int it = QUADS >= 4 ? 5 * i : QUADS == 2 ? (i < 2 ? 2 * i : 2 * i + 1) : i;   // (5 i: element i of quad i)
+                        sk[i] = x[it >> 2][it & 3] == -INFINITY ? 0u : score_key(x[it >> 2][it & 3]);
+                    } else {
+                        const int t = sample_segment(i * SEL_WAVES + wv, FAST_SAMPLE * SEL_WAVES, t_hi) + lane;
+                        const uint32_t kv_ = key_of(row[t < t_hi ? t : t_hi - 1]);
+                        sk[i] = (t < t_hi && t >= n_sink) ? kv_ : 0u;
+                    }
+                }
+                constexpr bool EXACT = ITEMS > 0 && ITEMS <= FAST_SAMPLE;
+                RowSample rs;
+                bool go = sample_row(sk, shist, &sample_st, &rs);
+                for (int attempt = 0; go; ++attempt) {
+                    int j = EXACT ? k_eff : sample_rank_wanted(k_eff, t_hi - max(t_lo, n_sink), rs.n_s);
+                    if (attempt == 1) j = min(2 * j, rs.n_s);
+                    float s_lo;
+                    const float theta = sample_threshold(rs, j, &sample_st, &s_lo);
+                    int n_w = 0;                      // this wave's list: scores and positions, keys are made when it is read
+                    asm volatile("" : "+v"(my_tid));
+                    // "not below" keeps a NaN, which then makes the ranking fail
+                    if constexpr (ITEMS > 0) {
+#pragma unroll
+                        for (int i = 0; i < ITEMS; ++i) {
+                            list_push(!(x[i >> 2][i & 3] < theta), x[i >> 2][i & 3], item_pos(i), wlist, WCAP, n_w);
+                            if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // a few masks at a time
+                        }
+                    } else {
+                        stream_scores([&](f32x4 (&xs)[SB / 4], int t0) {
+                            if (t0 < n_sink || t0 + SB * SEL_THREADS > t_hi) mask_scores<SB>(xs, [&](int u) { return stream_pos(t0, u); }, n_sink, t_hi);
+#pragma unroll
+                            for (int u = 0; u < SB; ++u) {
+                                list_push(!(xs[u >> 2][u & 3] < theta), xs[u >> 2][u & 3], stream_pos(t0, u), wlist, WCAP, n_w);
+                                if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+                            }
+                        });
+                    }
+                    wave_lds_sync();
+                    uint64_t lv[LPT];
+#pragma unroll
+                    for (int i = 0; i < LPT; ++i) {
+                        const uint64_t e = i * 64 + lane < min(n_w, WCAP) ? wlist[i * 64 + lane] : 0;
+                        lv[i] = e != 0 ? ((uint64_t)score_key(__uint_as_float((uint32_t)(e >> 32))) << 32) | (uint32_t)e : 0;
+                    }
+                    if (lane == 0 && n_w > WCAP) atomicAdd(&rank_st.n, 1 << 24);   // too many: makes the ranking fail
+                    const int res = rank_entries<LPT>([&](int i) { return lv[i]; }, s_lo, k_eff, sort_buf, FCAP, rbin, &rank_st, my_out, H);
+                    if (res == RANK_DONE) return;
+                    if (res == RANK_FAILED || attempt == 1) break;
+                    lds_barrier();                    // everyone has read the count; try a lower threshold
+                    if (tid == 0) {
+                        rank_st.excess = 0.0f;
+                        rank_st.n = 0;
+                    }
+                    lds_barrier();
+                }
+            }
+            __syncthreads();                          // the areas are used anew below
+        }
+    }
+    // The general path, on keys.
+    if constexpr (!MERGE && ITEMS > 0) {
+        asm volatile("" : "+v"(my_tid));
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            const int t = item_pos(i);
+            const uint32_t kv_ = key_of(x[i >> 2][i & 3]);
+            keys[i] = (t < t_hi && t >= n_sink) ? kv_ : 0u;
+        }
+        asm volatile("" : "+v"(my_tid));
+    }
     // 0. a cheap lower bound for the k_eff-th best key.  Each thread keeps the MTOP largest of
     //    its own candidates (MTOP * 1024 >= k); the k_eff-th largest of those values cannot
     //    exceed the k_eff-th largest of all candidates, so its top digit d0 bounds the answer's
@@ -668,31 +1020,13 @@ __global__ __launch_bounds__(SEL_THREADS, ((ITEMS == -1 && MTOP <= 4) || (MERGE 
     d0 = st.prefix >> 21;
     __syncthreads();
     }
-    //    With the keys in registers, what lies at or above the bound -- typically 1.3 to 2 times k
-    //    candidates -- is ranked as it is (quick_rank: only the segments that reach into the first k_eff
-    //    ranks are walked); the selection below runs only if that does not work out.
-    if constexpr (ITEMS > 0 && ITEMS <= 16 && !MERGE) {   // (32 keys per thread leave no registers for it)
-        if (!slice && !raw_keys && d0 > 0u) {
-            const uint32_t bound = d0 << 21;
-            auto mine = [&](int i) -> uint64_t {
-                const int t = t_lo + i * SEL_THREADS + (int)threadIdx.x;
-                return keys[i] >= bound ? ((uint64_t)keys[i] << 32) | (uint32_t)~(uint32_t)t : 0;
-            };
-            constexpr int SEGS = topk_area_entries(ITEMS, MTOP) - 1024;
-            if (quick_rank<ITEMS>(mine, key_score(bound), k_eff, cand, SEGS, reinterpret_cast<int*>(cand + SEGS), scratch,
-                                  rho_head + (int64_t)b * k * H + h, H))
-                return;
-        }
-    }
     // 1-3 for candidates delivered by scan_fn: the remaining digits of the k_eff-th best score key
     // T (its top digit is already in st), the position bound among the keys equal to T when they
     // straddle the cut (rare), and the survivors' composites compacted into sort_buf in any order.
-    uint32_t sel_T = 0u;                               // the k_eff-th best score key, once finish has run
     auto finish = [&](auto scan_fn) {
         radix_select(1, k_eff, 0u, scan_fn, [](uint32_t skey, int, uint32_t* key) { *key = skey; return true; },
                      hist, scratch, &st);
         const uint32_t T = st.prefix;
-        sel_T = T;
         const int need_eq = st.need, count_eq = st.count_eq;
         __syncthreads();
         uint32_t pos_bound = 0xffffffffu;              // take every tie
@@ -784,23 +1118,6 @@ __global__ __launch_bounds__(SEL_THREADS, ((ITEMS == -1 && MTOP <= 4) || (MERGE 
     }
     if (listed) {
         const int n = n_list;
-        // Rows too long for the ranking from registers above: the list holds exactly what lies at or above
-        // the bound, so it is ranked as it is (the entries move to registers first: the segments take the
-        // list's place, but only once the attempt is known to work out).
-        if constexpr ((ITEMS > 16 || ITEMS == 0) && CAP > 0) {   // (not the lean streamed form: 64 registers)
-            if (!slice && !raw_keys && d0 > 0u) {
-                constexpr int LPT = CAP / SEL_THREADS;
-                uint64_t lv[LPT];
-#pragma unroll
-                for (int j = 0; j < LPT; ++j) {
-                    const int i = (int)threadIdx.x + j * SEL_THREADS;
-                    lv[j] = i < n ? cand[i] : 0;
-                }
-                if (quick_rank<LPT>([&](int j) { return lv[j]; }, key_score(d0 << 21), k_eff, cand, CAP,
-                                    reinterpret_cast<int*>(cand + CAP), scratch, rho_head + (int64_t)b * k * H + h, H))
-                    return;
-            }
-        }
         finish([&](auto f) {
             for (int i = threadIdx.x; i < n; i += SEL_THREADS) {
                 const uint64_t cv = cand[i];
@@ -814,22 +1131,9 @@ __global__ __launch_bounds__(SEL_THREADS, ((ITEMS == -1 && MTOP <= 4) || (MERGE 
         for (int i = threadIdx.x; i < k; i += SEL_THREADS) my_parts[i] = i < k_eff ? sort_buf[i] : 0;
         return;
     }
-    // 3a. The ranking, the quick way (quick_rank); the network below remains for rows with crowded bins
-    //     (many equal scores), non-finite scores and raw keys.
-    if (!raw_keys) {
-        uint64_t mine[MTOP];
-#pragma unroll
-        for (int j = 0; j < MTOP; ++j) {
-            const int i = (int)threadIdx.x + j * SEL_THREADS;
-            mine[j] = i < k_eff ? sort_buf[i] : 0;
-        }
-        if (quick_rank<MTOP>([&](int j) { return mine[j]; }, key_score(sel_T), k_eff, cand, NSORT,
-                             reinterpret_cast<int*>(cand + NSORT), scratch, rho_head + (int64_t)b * k * H + h, H))
-            return;
-    }
     for (int i = k_eff + threadIdx.x; i < NSORT; i += SEL_THREADS) sort_buf[i] = 0;
     __syncthreads();
-    // 3b. Bitonic network over NSORT = MTOP * 1024 composites, MTOP per thread in registers:
+    // 3a. Bitonic network over NSORT = MTOP * 1024 composites, MTOP per thread in registers:
     // element j of thread (wave, lane) is index wave*64*MTOP + j*64 + lane.  A step with
     // stride < 64 exchanges between lanes of a wave, a stride of 64 .. 32*MTOP between the
     // thread's own registers, and only larger strides go through LDS with workgroup barriers.
@@ -838,48 +1142,7 @@ __global__ __launch_bounds__(SEL_THREADS, ((ITEMS == -1 && MTOP <= 4) || (MERGE 
         uint64_t v[MTOP];
 #pragma unroll
         for (int j = 0; j < MTOP; ++j) v[j] = sort_buf[base + j * 64];
-#pragma unroll
-        for (int size = 2; size <= NSORT; size <<= 1) {
-#pragma unroll
-            for (int stride = size >> 1; stride > 0; stride >>= 1) {
-                if (stride >= 64 * MTOP) {             // partner in another wave
-                    __syncthreads();
-#pragma unroll
-                    for (int j = 0; j < MTOP; ++j) sort_buf[base + j * 64] = v[j];
-                    __syncthreads();
-#pragma unroll
-                    for (int j = 0; j < MTOP; ++j) {
-                        const int i = base + j * 64;
-                        const uint64_t o = sort_buf[i ^ stride];
-                        const bool keep_max = ((i & stride) == 0) == ((i & size) == 0);
-                        v[j] = ((v[j] > o) == keep_max) ? v[j] : o;
-                    }
-                } else if (stride >= 64) {             // partner in this thread's registers
-                    const int js = stride >> 6;
-#pragma unroll
-                    for (int j = 0; j < MTOP; ++j) {
-                        if ((j & js) == 0 && (j | js) < MTOP) {
-                            const int i = base + j * 64;
-                            const bool desc = (i & size) == 0;
-                            const uint64_t a = v[j], c = v[j | js];
-                            const bool sw = (a < c) == desc;
-                            v[j] = sw ? c : a;
-                            v[j | js] = sw ? a : c;
-                        }
-                    }
-                } else {                               // partner in another lane of this wave
-#pragma unroll
-                    for (int j = 0; j < MTOP; ++j) {
-                        const int i = base + j * 64;
-                        const uint32_t olo = lane_xor_any((uint32_t)v[j], stride);
-                        const uint32_t ohi = lane_xor_any((uint32_t)(v[j] >> 32), stride);
-                        const uint64_t o = ((uint64_t)ohi << 32) | olo;
-                        const bool keep_max = ((i & stride) == 0) == ((i & size) == 0);
-                        v[j] = ((v[j] > o) == keep_max) ? v[j] : o;
-                    }
-                }
-            }
-        }
+        bitonic_sort<MTOP, 2, 1>(v, sort_buf, base);
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < MTOP; ++j) sort_buf[base + j * 64] = v[j];
@@ -889,6 +1152,90 @@ __global__ __launch_bounds__(SEL_THREADS, ((ITEMS == -1 && MTOP <= 4) || (MERGE 
     int32_t* __restrict__ out = rho_head + (int64_t)b * k * H + h;
     for (int j = threadIdx.x; j < k_eff; j += SEL_THREADS)
         out[(int64_t)j * H] = (int32_t)~(uint32_t)sort_buf[j];
+}
+
+// Few long rows: one workgroup would walk a row on one CU while most of the chip idles, so a row is cut into slices
+// (blockIdx.z).  Every slice's workgroup takes the row's threshold from the same sample of the whole row (8192 keys:
+// cheaper than a launch that does it once), and leaves those of its candidates that reach it in the slice's list;
+// topk_kernel<0, .> ranks the lists' entries, or -- if a list overflowed, too few are in them, or their bins are crowded -- the row.
+__global__ __launch_bounds__(SEL_THREADS, 8) void slice_filter_kernel(const float* __restrict__ P, int64_t ldp,
+                                                                       const int32_t* __restrict__ seq_lens, int H, int k,
+                                                                       int budget, int window, int n_sink,
+                                                                       const int32_t* __restrict__ only_rows, SliceLists sl) {
+    extern __shared__ uint64_t slice_lds[];           // cap entries (a sixteenth per wave), then the sample's bins
+    __shared__ SampleScratch sample_st;
+    __shared__ int wave_n[SEL_WAVES];
+    const int h = blockIdx.x, b = blockIdx.y, z = blockIdx.z, tid = threadIdx.x, lane = lane_id();
+    const int wv = __builtin_amdgcn_readfirstlane(wave_id());
+    const int64_t r = (int64_t)b * H + h;
+    if (only_rows && only_rows[r] == 0) return;
+    const int L = seq_lens[b];
+    if (L <= budget) return;
+    const int Lc = L - window, n = Lc - n_sink, k_eff = min(k, n);
+    int* const shist = reinterpret_cast<int*>(slice_lds + sl.cap);
+    shist[2 * tid] = shist[2 * tid + 1] = 0;
+    const float* __restrict__ row = P + r * ldp;
+    float x[SLICE_SAMPLE];
+    int t_s[SLICE_SAMPLE];
+#pragma unroll
+    for (int i = 0; i < SLICE_SAMPLE; ++i) {
+        t_s[i] = sample_segment(i * SEL_WAVES + wv, SLICE_SAMPLE * SEL_WAVES, Lc) + lane;
+        x[i] = row[min(t_s[i], Lc - 1)];
+    }
+    const int t_lo = z * sl.slice_len, t_hi = min(Lc, t_lo + sl.slice_len);
+    // the slice's first keys are on their way while the sample is worked on; positions t0 + (v * 1024 + thread) * 4 + e,
+    // clamped inside the row (padded to a multiple of 64 entries) and masked
+    constexpr int V = 4;
+    f32x4 y[V];
+    auto request = [&](int t0) {
+#pragma unroll
+        for (int v = 0; v < V; ++v) y[v] = *reinterpret_cast<const f32x4*>(row + min(t0 + (v * SEL_THREADS + tid) * 4, (int)ldp - 4));
+    };
+    request(t_lo);
+    uint32_t sk[SLICE_SAMPLE];
+#pragma unroll
+    for (int i = 0; i < SLICE_SAMPLE; ++i) sk[i] = (t_s[i] < Lc && t_s[i] >= n_sink) ? score_key(x[i]) : 0u;
+    RowSample rs;
+    const bool ok = sample_row(sk, shist, &sample_st, &rs);
+    float s_lo = 0.0f;
+    float theta = INFINITY;
+    if (ok) theta = sample_threshold(rs, sample_rank_wanted(k_eff, n, rs.n_s), &sample_st, &s_lo);
+    if (tid == 0 && z == 0) sl.s_lo[r] = s_lo;
+    wave_lds_sync();
+    const int wcap = sl.cap / SEL_WAVES;
+    uint64_t* const wlist = slice_lds + wv * wcap;
+    int n_w = 0;
+    for (int t0 = t_lo; t0 < t_hi; t0 += V * 4 * SEL_THREADS) {
+        f32x4 c[V];
+#pragma unroll
+        for (int v = 0; v < V; ++v) c[v] = y[v];
+        request(t0 + V * 4 * SEL_THREADS);            // past the slice's end: never used
+        auto pos = [&](int u) { return t0 + ((u >> 2) * SEL_THREADS + tid) * 4 + (u & 3); };
+        if (t0 < n_sink || t0 + V * 4 * SEL_THREADS > t_hi) mask_scores<4 * V>(c, pos, n_sink, t_hi);
+#pragma unroll
+        for (int u = 0; u < 4 * V; ++u) {
+            list_push(!(c[u >> 2][u & 3] < theta), c[u >> 2][u & 3], pos(u), wlist, wcap, n_w);
+            if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    if (lane == 0) wave_n[wv] = n_w;
+    lds_barrier();
+    int first = 0, all = 0;
+    bool fits = ok;
+#pragma unroll
+    for (int i = 0; i < SEL_WAVES; ++i) {
+        const int c = wave_n[i];
+        first += i < wv ? c : 0;
+        all += c;
+        fits = fits && c <= wcap;
+    }
+    if (tid == 0) sl.cnt[r * sl.n_slices + z] = fits ? all : sl.cap + 1;
+    if (!fits) return;
+    uint64_t* const dst = sl.cand + (r * sl.n_slices + z) * sl.cap + first;
+    for (int i = lane; i < n_w; i += 64) {
+        const uint64_t e = wlist[i];
+        dst[i] = ((uint64_t)score_key(__uint_as_float((uint32_t)(e >> 32))) << 32) | (uint32_t)e;
+    }
 }
 
 // ---------------------------------------------------------------- union / rank / window
@@ -1590,15 +1937,6 @@ __device__ __forceinline__ float lane_value(float v, int lane) {
 }
 
 __device__ __forceinline__ int wave_base_of(unsigned tid) { return (int)(tid >> 6); }
-
-// LDS written by some lanes of a wave and read by others of the same wave: a wave's LDS
-// accesses are performed in program order, so only the compiler has to be kept from
-// reordering them.
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // SCORE (selection layer, all tokens): the scores of the candidate range [0, L - window) are also
 // written to P[b][head][t] (row stride ldp), so the layer's K is read once for both (Alg. 1 computes

@@ -519,6 +519,53 @@ def test_union_of_agreeing_and_disagreeing_heads(heads, L, K, W, k):
     check_select(inp, r, 0)
 
 
+@pytest.mark.parametrize("B,L,K,W,k", [(2, 700, 512, 128, 500), (2, 4200, 1024, 0, 0), (2, 9001, 2048, 512, 2048),
+                                        (2, 20011, 3072, 0, 3072), (1, 9000, 8192, 0, 0), (2, 41000, 4096, 1024, 0),
+                                        (1, 140001, 2048, 512, 0), (48, 9700, 3000, 100, 0)])
+@pytest.mark.parametrize("where", ["one run", "every 16th run of 64", "one position in four"])
+def test_topk_rows_whose_best_scores_cluster(B, L, K, W, k, where):
+    """The top-k's threshold comes from a sample of the row, and a wave's list holds its share of the best only: rows
+    whose best candidates stand together, or where a sample sees all of them or none, lists that overflow, thresholds that
+    let too few through.  All forms: keys in registers, streamed, slices; k up to 8192."""
+    w = small("cluster", n_q_heads=8, n_kv_heads=8, batch=B, seq_len=L, lengths=tuple([L] * (B - 1) + [L - 57]), budget=K, window=W,
+              topk_per_head=k)
+    inp = wl.make_inputs(w, DEV)
+    lay = inp.layers[0]
+    n_best = (k or K - W) + 100                          # a little more than k
+    pos = torch.arange(L, device=DEV)
+    if where == "one run":
+        chosen = (pos >= L // 3) & (pos < L // 3 + n_best)
+    elif where == "every 16th run of 64":
+        chosen = (pos // 64) % 16 == 3
+    else:
+        chosen = pos % 4 == 1
+    at = torch.nonzero(chosen).squeeze(1)
+    rows = lay.k[:, :, at].float()
+    q = lay.q.float()[:, :, None, :]                     # one query head per KV head
+    lay.k[:, :, at] = (0.3 * rows + 0.5 * q).to(torch.bfloat16)
+    r = StepRunner(inp)
+    r.run()
+    check_select(inp, r, 0, seqs=[0, B - 1], check_scores=False)
+
+
+def test_topk_of_scores_that_are_not_finite():
+    """Infinite scores are ranked like any other (largest first, ties to the lower position)."""
+    for L in (3000, 12000, 40000):
+        w = small("inf", n_q_heads=8, n_kv_heads=8, batch=1, seq_len=L, lengths=(L,), budget=512, window=128)
+        inp = wl.make_inputs(w, DEV)
+        lay = inp.layers[0]
+        big = torch.finfo(torch.bfloat16).max
+        lay.q[..., 0] = big
+        lay.q[..., 1:] = 0                               # scores: one product, 0 in the other columns
+        lay.k[:, :, :, 0] = 0
+        lay.k[:, :, 100:164, 0] = big                    # +inf
+        lay.k[:, :, 200:1500, 0] = torch.linspace(0.1, 0.9, 1300, device=DEV).to(torch.bfloat16)
+        lay.k[:, :, 2000:2010, 0] = -big                 # -inf
+        r = StepRunner(inp)
+        r.select(0)
+        check_select(inp, r, 0)
+
+
 def test_planted_heavy_keys_are_selected_on_gpu():
     w = small("planted", batch=2, seq_len=4096, budget=256, window=64, n_planted=16)
     inp = wl.make_inputs(w, DEV)
