@@ -164,7 +164,8 @@ cusa_status cusa_sparse_attn(const cusa_params* params, const void* q, const cus
  * runs on, held until the process ends).  Arguments as cusa_sparse_attn, minus the workspace.
  * Allocates nothing, frees nothing, synchronises nothing.
  * Errors: as cusa_sparse_attn; UNSUPPORTED when the partials of this problem (batch * n_q_heads *
- * splits * 520 bytes, splits as the launch plan cuts min(budget, max_seq_len) tokens) do not fit
+ * splits * 520 bytes; splits: pieces of 1/512 of all batch * n_kv_heads * min(budget, max_seq_len)
+ * tokens, 2048 at most, are what the launch makes at most) do not fit
  * the array.  All calls on one GPU share that GPU's array: calls whose kernels may overlap (two
  * streams, two threads) race on it and must be serialised by the caller. */
 size_t      cusa_noalloc_max_scratch_bytes(void);

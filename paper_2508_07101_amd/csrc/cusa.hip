@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 #include <utility>
@@ -157,29 +158,69 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 constexpr int MAX_SPLITS = 256;
 constexpr int TARGET_WGS = 512;     // two resident workgroups per CU
+constexpr int SINGLE_WGS = 192;     // (sequence, KV head) pairs from which one workgroup each is enough;
+constexpr int SINGLE_WGS_PAGED = 256;   // the block table's extra round trip per tile wants more of them
 constexpr int CHUNK_CAP = 2048;
-static_assert(ATTN_SCORE_CHUNK_CAP <= CHUNK_CAP && ATTN_SCORE_CHUNK_CAP_G8 <= CHUNK_CAP, "the split bound assumes it");
+constexpr int SPARSE_CAP = 4096;    // a token set has the same length for nearly all sequences: longer single pieces stay in step
+constexpr int PIECE = 1280;         // tokens per workgroup where the chip is filled a few times only
+constexpr int MERGE_BATCH = 32;     // splits that the merge of partials asks for at a time
+static_assert(ATTN_SCORE_CHUNK_CAP <= CHUNK_CAP && ATTN_SCORE_CHUNK_CAP_G8 <= CHUNK_CAP && ATTN_SCORE_CHUNK_CAP_G8 >= 1024 && PIECE >= 1024,
+              "the split bound assumes it");
 
 struct AttnPlan {
-    int ti;        // row-load instructions per wave iteration (4 or 8)
+    int ti;        // row-load instructions per wave iteration (4 or 8; scoring variant 8 or 16)
     int chunk;     // tokens per workgroup, a multiple of the workgroup tile
     int n_splits;  // grid.x = ceil(n_max / chunk)
 };
 
-// Workgroup granularity for n_max tokens per (sequence, KV head): about TARGET_WGS workgroups
-// when every sequence has n_max tokens, but never more than CHUNK_CAP tokens per workgroup, so
-// that a large ragged batch is cut into equal pieces instead of one piece per sequence.
-// Workgroups with long runs (1024 tokens or more) load 8 rows per lane and iteration, which keeps
-// more bytes in flight; short runs are faster with 4 (measured on all five workloads).
-AttnPlan plan_attn(int n_max, int BG, int g, bool wide = false) {
+// Workgroup granularity for n_max tokens per (sequence, KV head).
+// As many even pieces as keep all workgroups resident at once (TARGET_WGS / BG, rounded down: rounded up, the last piece
+// is a stump and the workgroups no longer fit the chip in one go: 80 pairs of 4096 tokens 39.1 -> 33.9 us, 96 of 5000
+// 51.9 -> 44.2).  From SINGLE_WGS pairs on a piece per pair: what it loses in balance it gains in the merge
+// that falls away (224 pairs of 1024: two pieces 26.3, one 23.0 us; 472 of 832: 42 and 36).
+// Where that leaves many slots idle (192 pairs: two pieces, 384 workgroups), a pass over all tokens takes more pieces that
+// fill a round and a half (192 pairs of 3400: two pieces 63.6, three 64.7, four 59.0 us); with sparse attention's short
+// lists it does not pay.
+// Splits beyond MERGE_BATCH cost the merge a second round trip (8 pairs of 20000: 64 splits 19.1, 32 18.4 us), so few pairs are
+// cut into MERGE_BATCH pieces while these stay short of 1536 tokens.
+// Lists too long for one piece per workgroup (CHUNK_CAP) fill the chip more than once: pieces of CHUNK_CAP tokens, or
+// of about PIECE where these make fewer than four rounds of workgroups, so that the last ones to finish -- of
+// ragged lengths above all -- hold up less (128 pairs of 601 to 16383 tokens: pieces of 2048 106.3 us, of 1280 96.7; 376 of 2597 to
+// 5195: 148.2 and 142.9; but 176 of 27576: 405.6 and 421.6).
+// The scoring variant keeps its scores in LDS, hence its own caps, and writes them in bursts, which are
+// better longer (pieces of 2048 against 1024 at 64 pairs of 16384: 121.3 and 123.7 us).  Sparse attention is never cut
+// into more pieces than noalloc_splits says.
+// Workgroups whose run is 512 tokens or longer load 8 rows per lane and iteration, which keeps more bytes in flight
+// (304 pairs of 512, paged: 23.9 -> 20.0 us); shorter runs are faster with 4.
+// Share of the resident slots that n workgroups keep busy over their rounds; a last round of at most one workgroup per CU
+// takes about 0.6 of a round.
+float round_share(int n) {
+    const int last = n % TARGET_WGS;
+    const float rounds = (float)(n / TARGET_WGS) + (last == 0 ? 0.0f : last <= TARGET_WGS / 2 ? 0.6f : 1.0f);
+    return (float)n / (TARGET_WGS * rounds);
+}
+enum AttnKind { ATTN_FULL, ATTN_SPARSE, ATTN_SCORE };
+AttnPlan plan_attn(int n_max, int BG, int g, AttnKind kind, bool paged) {
     AttnPlan pl;
-    int64_t chunk = ((int64_t)n_max * BG + TARGET_WGS - 1) / TARGET_WGS;
-    // the scoring variant keeps the scores of a workgroup's whole run in LDS
-    const int cap = !wide ? CHUNK_CAP : g >= 8 ? ATTN_SCORE_CHUNK_CAP_G8 : ATTN_SCORE_CHUNK_CAP;
-    if (chunk > cap) chunk = cap;
-    pl.ti = wide ? (chunk >= 512 ? 16 : 8) : chunk >= 1024 ? 8 : 4;
+    const bool wide = kind == ATTN_SCORE;
+    const int cap = kind == ATTN_FULL ? CHUNK_CAP : kind == ATTN_SPARSE ? SPARSE_CAP : g >= 8 ? ATTN_SCORE_CHUNK_CAP_G8 : ATTN_SCORE_CHUNK_CAP;
+    int pieces = BG >= (paged ? SINGLE_WGS_PAGED : SINGLE_WGS) ? 1 : TARGET_WGS / BG;
+    if (kind != ATTN_SPARSE && pieces > 1) {
+        for (int more = pieces + 1; more * BG <= 2 * TARGET_WGS && n_max >= more * 512; ++more)
+            if (round_share(more * BG) > round_share(pieces * BG) + 0.05f) pieces = more;
+    }
+    if (!wide && pieces > MERGE_BATCH && n_max <= MERGE_BATCH * 1536) pieces = MERGE_BATCH;
+    int64_t chunk = ((int64_t)n_max + pieces - 1) / pieces;
+    if (chunk > cap) {
+        const bool few = (int64_t)((n_max + CHUNK_CAP - 1) / CHUNK_CAP) * BG < 4 * TARGET_WGS;
+        const int piece = kind == ATTN_SCORE ? cap : kind == ATTN_FULL && few ? PIECE : CHUNK_CAP;
+        pieces = (n_max + piece - 1) / piece;
+        chunk = ((int64_t)n_max + pieces - 1) / pieces;
+    }
+    pl.ti = wide ? (chunk >= 512 ? 16 : 8) : chunk >= 512 ? 8 : 4;
     const int wg_tile = pl.ti * 4 * ATTN_WAVES;
-    chunk = (chunk + wg_tile - 1) / wg_tile * wg_tile;
+    // whole tiles; the scoring variant's are large, so short runs go to the nearest (88 pairs of 743: 128 against 256 tokens)
+    chunk = wide && chunk < 512 && chunk > wg_tile ? (chunk + wg_tile / 2) / wg_tile * wg_tile : (chunk + wg_tile - 1) / wg_tile * wg_tile;
     if ((n_max + chunk - 1) / chunk > MAX_SPLITS) {
         chunk = ((int64_t)n_max + MAX_SPLITS - 1) / MAX_SPLITS;
         chunk = (chunk + wg_tile - 1) / wg_tile * wg_tile;
@@ -190,16 +231,25 @@ AttnPlan plan_attn(int n_max, int BG, int g, bool wide = false) {
     return pl;
 }
 
-// Upper bound of plan_attn(m, BG', g).n_splits over every m <= n_max and BG' >= BG: with the chunk
-// below its cap a token list is cut into at most ceil(TARGET_WGS / BG) pieces, at the cap into
-// ceil(m / cap).  Monotone in n_max, so a workspace sized for a capacity serves every
-// shorter bound.
-int max_splits_bound(int n_max, int BG, int g) {
-    const int cap = g >= 8 ? ATTN_SCORE_CHUNK_CAP_G8 : CHUNK_CAP;   // the smallest cap any variant of this group size has
-    const int by_wgs = (TARGET_WGS + BG - 1) / BG;
-    const int by_cap = (n_max + cap - 1) / cap;
-    const int m = by_wgs > by_cap ? by_wgs : by_cap;
+// Upper bound of plan_attn(m, BG', ...).n_splits over every m <= n_max and BG' >= BG: a token list is cut into
+// TARGET_WGS / BG pieces (a scoring run rounded down to the nearest tile: at most half as many again), or up to twice as
+// many and one if they have 512 tokens, or into pieces of at least 1024 tokens.  Monotone in n_max, so a workspace sized for a capacity serves every shorter bound.
+int max_splits_bound(int n_max, int BG) {
+    const int by_wgs = BG < TARGET_WGS ? TARGET_WGS / BG : 1;
+    const int by_piece = (n_max + 511) / 512 < 2 * by_wgs + 1 ? (n_max + 511) / 512 : std::max(2 * by_wgs + 1, (n_max + 1023) / 1024);
+    const int m = by_wgs + (by_wgs + 1) / 2 > by_piece ? by_wgs + (by_wgs + 1) / 2 : by_piece;
     return m < MAX_SPLITS ? m : MAX_SPLITS;
+}
+
+// Splits that decide whether cusa_sparse_attn_noalloc takes a problem (a statement to callers: it does not
+// follow the plan, which never makes more): pieces of about 1/TARGET_WGS of all tokens, 2048 at most.
+int noalloc_splits(int n_max, int BG) {
+    int64_t chunk = ((int64_t)n_max * BG + TARGET_WGS - 1) / TARGET_WGS;
+    if (chunk > CHUNK_CAP) chunk = CHUNK_CAP;
+    const int wg_tile = (chunk >= 1024 ? 8 : 4) * 4 * ATTN_WAVES;
+    chunk = (chunk + wg_tile - 1) / wg_tile * wg_tile;
+    const int64_t n = ((int64_t)n_max + chunk - 1) / chunk;
+    return (int)(n < 1 ? 1 : n > MAX_SPLITS ? MAX_SPLITS : n);
 }
 
 // Slices a row of up to lc_max candidates is cut into: only few long rows are cut (more rows than
@@ -280,13 +330,13 @@ struct WsLayout {
 WsLayout make_layout(const cusa_params* p, int max_seq_len) {
     WsLayout w;
     const int64_t B = p->batch, H = p->n_q_heads;
-    const int BG = p->batch * p->n_kv_heads, g = p->n_q_heads / p->n_kv_heads;
+    const int BG = p->batch * p->n_kv_heads;
     int64_t lc = (int64_t)max_seq_len - p->window;
     if (lc < 1) lc = 1;
     w.ldp = (lc + 63) / 64 * 64;
     w.k = resolved_k(p);
     if (w.k < 1) w.k = 1;
-    w.max_splits = max_splits_bound(max_seq_len > p->budget ? max_seq_len : p->budget, BG, g);
+    w.max_splits = max_splits_bound(max_seq_len > p->budget ? max_seq_len : p->budget, BG);
     size_t off = 0;
     w.scores = off;    off += align256((size_t)(B * H * w.ldp) * 4);
     w.rho_head = off;  off += align256((size_t)(B * w.k * H) * 4);
@@ -436,7 +486,8 @@ cusa_status run_attention(const cusa_params* p, const void* q, const cusa_kv* kv
                           const int32_t* cnt, int n_max, void* out, void* ws, const WsLayout& w, hipStream_t s,
                           ScoreOut score = ScoreOut(), float* lse = nullptr, ReduceArgs* later = nullptr) {
     const int g = p->n_q_heads / p->n_kv_heads, BG = p->batch * p->n_kv_heads, H = p->n_q_heads;
-    const AttnPlan pl = plan_attn(n_max, BG, g, score.P != nullptr);
+    const AttnPlan pl = plan_attn(n_max, BG, g, SPARSE ? ATTN_SPARSE : score.P != nullptr ? ATTN_SCORE : ATTN_FULL,
+                                  kv->layout == CUSA_KV_PAGED);
     if (pl.n_splits > w.max_splits) return CUSA_ERR_WORKSPACE_TOO_SMALL;
     AttnArgs a;
     a.paged = kv->layout == CUSA_KV_PAGED;
@@ -475,7 +526,7 @@ cusa_status run_attention_per_head(const cusa_params* p, const void* q, const cu
                                    float* lse = nullptr) {
     const int H = p->n_q_heads, g = H / p->n_kv_heads;
     const int n_max = p->budget < kv->max_seq_len ? p->budget : kv->max_seq_len;
-    const AttnPlan pl = plan_attn(n_max, p->batch * H, 1);
+    const AttnPlan pl = plan_attn(n_max, p->batch * H, 1, ATTN_SPARSE, kv->layout == CUSA_KV_PAGED);
     if (pl.n_splits > w.max_splits) return CUSA_ERR_WORKSPACE_TOO_SMALL;
     AttnArgs a;
     a.paged = kv->layout == CUSA_KV_PAGED;
@@ -686,7 +737,7 @@ cusa_status run_score(const cusa_params* p, const void* q, const cusa_kv* kv, fl
     const int g = p->n_q_heads / p->n_kv_heads, BG = p->batch * p->n_kv_heads;
     const int lc_max = kv->max_seq_len - p->window;
     if (lc_max < 1) return CUSA_OK;
-    const AttnPlan pl = plan_attn(lc_max, BG, g, true);
+    const AttnPlan pl = plan_attn(lc_max, BG, g, ATTN_SCORE, kv->layout == CUSA_KV_PAGED);
     AttnArgs a;
     a.paged = kv->layout == CUSA_KV_PAGED;
     a.grid = dim3(pl.n_splits, p->n_kv_heads, p->batch);
@@ -904,10 +955,10 @@ cusa_status cusa_sparse_attn_noalloc(const cusa_params* params, const void* q, c
     if ((st = check_kv(params, kv)) != CUSA_OK) return st;
     if (!q || !idx || !cnt || !out || ((uintptr_t)q & 15)) return CUSA_ERR_INVALID_ARG;
     const int n_max = params->budget < kv->max_seq_len ? params->budget : kv->max_seq_len;
-    const int g = params->n_q_heads / params->n_kv_heads, BG = params->batch * params->n_kv_heads;
-    // only the two partial arrays are laid out, for exactly the splits this launch makes
+    const int BG = params->batch * params->n_kv_heads;
+    // only the two partial arrays are laid out, for the splits that callers are told of (the launch makes no more)
     WsLayout w = {};
-    w.max_splits = plan_attn(n_max, BG, g).n_splits;
+    w.max_splits = noalloc_splits(n_max, BG);
     const size_t rows = (size_t)params->batch * params->n_q_heads * w.max_splits;
     w.part_acc = 0;
     w.part_ml = align256(rows * D * 4);

@@ -566,6 +566,23 @@ def test_topk_of_scores_that_are_not_finite():
         check_select(inp, r, 0)
 
 
+@pytest.mark.parametrize("B,L,K,paged,min_len", [(24, 1100, 512, False, 0), (24, 2100, 1000, True, 900), (26, 2060, 640, False, 700),
+                                                  (33, 700, 330, True, 0), (12, 5000, 2500, False, 0), (1, 9000, 4100, False, 0),
+                                                  (16, 5000, 300, True, 601), (65, 500, 257, False, 300)])
+def test_workgroup_granularity_of_the_attention_passes(B, L, K, paged, min_len):
+    """The launch plan's regimes: one piece per (sequence, KV head), even pieces, pieces that fill a round and a half,
+    at most 32 pieces for few pairs, pieces of a long ragged batch; full, scoring and sparse passes."""
+    w = small("plan", n_layers=3, schedule=(LAYER_FULL, LAYER_SELECT, LAYER_SPARSE), batch=B, seq_len=L, min_seq_len=min_len,
+              budget=K, window=K // 4, paged=paged)
+    inp = wl.make_inputs(w, DEV)
+    r = StepRunner(inp)
+    r.run()
+    longest, shortest = int(np.argmax(inp.seq_lens_host)), int(np.argmin(inp.seq_lens_host))
+    check_select(inp, r, 1, seqs=[longest, shortest], check_scores=False)
+    for i, kind in enumerate(w.schedule):
+        check_attention(inp, r, i, kind, seqs=[longest, shortest, B - 1])
+
+
 def test_planted_heavy_keys_are_selected_on_gpu():
     w = small("planted", batch=2, seq_len=4096, budget=256, window=64, n_planted=16)
     inp = wl.make_inputs(w, DEV)
