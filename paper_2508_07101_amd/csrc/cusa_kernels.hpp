@@ -1,9 +1,9 @@
 // Device code of libcusa: gfx950 kernels for the CUSA decode hot path.
 //
-//   topk_kernel         per-head ranked top-k (Sec. 3.2): radix select on order-preserving keys;
-//                       the ranking by a counting sort over value bins (quick_rank) or, where
-//                       scores crowd, a bitonic sort held in registers (lane exchanges by DPP /
-//                       permlane swaps, LDS across waves)
+//   topk_kernel         per-head ranked top-k (Sec. 3.2): a threshold from a sample, one compare per
+//                       score, a counting sort over value bins of what passes (rank_entries); radix select
+//                       and a bitonic sort held in registers for rows where that does not work out
+//   slice_filter_kernel the same threshold on slices of few long rows
 //   union_kernel        cross-head union, first-occurrence global rank, cut at
 //                       K-W, recency window (Sec. 3.2, 3.3) -> ascending rho
 //   attn_kernel         split-K flash-decode over all tokens or over rho
@@ -207,7 +207,7 @@ __device__ __forceinline__ float key_score(uint32_t key) {
 // between them and, first, the row's way from memory (3 us of the 14 at 32 K candidates).  Measured before (selection
 // with digit histograms, then ranking) -> after, us: 1 x 32 rows of 3840, k 1024: 9.7 -> 8.5; 32 rows of 32256, k 1536: 20.0
 // -> 14.0; 256 rows of 15360, k 3072: 18.1 -> 15.4; 64 rows of 130048, k 3072, in slices: 50.6 -> 32.0; 576 rows of 11552,
-// k 2304: 57.7 -> 24; 1408 rows of 22798, k 3072: 166 -> 83.
+// k 2304: 57.7 -> 32.9; 1408 rows of 22798, k 3072: 166 -> 89.5.
 
 struct SelectState {
     uint32_t prefix;     // digits fixed so far
