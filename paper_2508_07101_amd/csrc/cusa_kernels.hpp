@@ -221,11 +221,13 @@ template <int NB>
 __device__ __forceinline__ void pick_digit(int* hist, int* scratch, SelectState* st, int shift) {
     // thread i owns bins [i*PER, i*PER+PER) counted from the top (descending digits)
     constexpr int PER = (NB + SEL_THREADS - 1) / SEL_THREADS;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));                        // addresses are made here, not kept from far above
     int local[PER];
     int sum = 0;
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-        int bin = NB - 1 - (threadIdx.x * PER + j);
+        int bin = NB - 1 - (tid * PER + j);
         local[j] = bin >= 0 ? hist[bin] : 0;
         sum += local[j];
     }
@@ -238,7 +240,7 @@ __device__ __forceinline__ void pick_digit(int* hist, int* scratch, SelectState*
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
             if (run < need && need <= run + local[j]) {
-                int bin = NB - 1 - (threadIdx.x * PER + j);
+                int bin = NB - 1 - (tid * PER + j);
                 st->prefix |= (uint32_t)bin << shift;
                 st->need = need - run;
                 st->count_eq = local[j];
@@ -293,15 +295,10 @@ __device__ __forceinline__ void radix_select(int first_pass, int need, uint32_t 
 // the thread's slots.  The counter must be zero and visible before, and is complete after the next
 // workgroup barrier.
 __device__ __forceinline__ int wave_reserve(int mine, int* counter) {
-    int inc = mine;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int nb = __shfl_up(inc, o);
-        if (lane_id() >= o) inc += nb;
-    }
+    const int inc = wave_scan_incl(mine);
     int wave_base = 0;
     if (lane_id() == 63) wave_base = atomicAdd(counter, inc);
-    return __shfl(wave_base, 63) + inc - mine;
+    return __builtin_amdgcn_readlane(wave_base, 63) + inc - mine;
 }
 
 // Entries of the LDS candidate list of topk_kernel<ITEMS, MTOP> (0: no list; short rows are
@@ -397,11 +394,10 @@ __device__ __forceinline__ uint32_t row_max16(uint32_t v) {
 
 // LDS words of the ranking, besides the bins and the segments.
 struct RankScratch {
-    float excess;                // cleared by the caller, like n
-    int n, crowded, wave[SEL_WAVES];
+    float excess;                // cleared by the caller, like crowded
+    int crowded, wave[SEL_WAVES];
 };
 constexpr int RANK_BINS = 2048;
-enum { RANK_DONE = 0, RANK_FAILED = 1, RANK_TOO_FEW = 2 };
 
 // Ranks the m <= 64 CHUNKS composites of a segment that starts at rank 0, the workgroup together: every wave holds all
 // of them, 64 to a register, and compares its sixteenth of them with 64 at a time.
@@ -424,48 +420,37 @@ __device__ __forceinline__ void rank_together(const uint64_t* seg, int m, int k_
     }
 }
 
-// Ranks the composites mine(0) .. mine(NPT - 1) of every thread (zero: none; all at or above the score s_lo)
-// and writes the picks ranked below k_out, rank-major (out[rank * H]) -- without a sorting network:
+// Ranks the n composites mine(0) .. mine(NPT - 1) of every thread (zero: none; all at or above the score s_lo)
+// and writes the picks ranked below k_out <= n, rank-major (out[rank * H]) -- without a sorting network:
 // 2048 bins divide the score range evenly by value (monotone in the key, so bins are in rank order), a
 // counting sort puts every composite into its bin's segment, and inside a segment -- a few entries,
 // unless scores repeat -- a composite's rank is the number of entries that beat it.  The range is
 // [s_lo, s_lo + 6 x the mean excess over s_lo], not up to the best score: a few very large scores
 // (attention sinks, hot tokens) would otherwise stretch the bins over empty space and crowd the
 // rest; whatever lies above shares the first bin.  About a fifth of the instructions of a sorting network.
-// RANK_FAILED, with nothing written: a bin that holds wanted ranks has more than RMAX entries (many equal scores), the
-// scores are not finite or all alike, or there are more than seg_cap; the caller then ranks another way.
-// RANK_TOO_FEW: fewer than k_out composites.  seg: room for seg_cap composites; rbin: RANK_BINS zeros; *rs cleared; all
+// False, with nothing written: a bin that holds wanted ranks has more than RMAX entries (many equal scores), or the scores
+// are not finite or all alike; the caller then ranks another way.
+// seg: room for n composites; rbin: RANK_BINS zeros; *rs cleared; all
 // visible to the workgroup (one barrier since).  Called by the whole workgroup.
 //
 // Sixteen waves on one CU: an instruction that all of them execute costs sixteen cycles, a barrier a few
 // hundred, so sums and scans go by DPP and the barriers wait for LDS only.
 template <int NPT, typename Mine>
-__device__ __forceinline__ int rank_entries(Mine mine, float s_lo, int k_out, uint64_t* seg, int seg_cap, int* rbin,
-                                            RankScratch* rs, int32_t* __restrict__ out, int H) {
+__device__ __forceinline__ bool rank_entries(Mine mine, int n, float s_lo, int k_out, uint64_t* seg, int* rbin,
+                                             RankScratch* rs, int32_t* __restrict__ out, int H) {
     constexpr int RMAX = 512;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(wave_id());
     {
         float excess = 0.0f;
-        int n_mine = 0;
 #pragma unroll
-        for (int j = 0; j < NPT; ++j) {
-            if (mine(j) != 0) {
-                excess += key_score((uint32_t)(mine(j) >> 32)) - s_lo;
-                ++n_mine;
-            }
-        }
+        for (int j = 0; j < NPT; ++j)
+            if (mine(j) != 0) excess += key_score((uint32_t)(mine(j) >> 32)) - s_lo;
         excess = wave_sum_last(excess);
-        n_mine = wave_scan_incl(n_mine);
-        if (lane_id() == 63) {
-            atomicAdd(&rs->excess, excess);
-            atomicAdd(&rs->n, n_mine);
-        }
+        if (lane_id() == 63) atomicAdd(&rs->excess, excess);
     }
     lds_barrier();
-    const int n = rs->n;
-    if (n < k_out) return RANK_TOO_FEW;                  // workgroup-uniform, like all that follows
-    const float range = 6.0f * rs->excess / (float)n;
-    if (!(range > 0.0f && range < 3.0e38f) || n > seg_cap) return RANK_FAILED;
+    const float range = 6.0f * rs->excess / (float)n;    // workgroup-uniform, like all that follows
+    if (!(range > 0.0f && range < 3.0e38f)) return false;
     const float scale = (float)(RANK_BINS - 1) / range;
     auto bin_of = [&](uint64_t cv) {                     // bin 0 holds the best scores
         const int up = (int)((key_score((uint32_t)(cv >> 32)) - s_lo) * scale);
@@ -494,7 +479,7 @@ __device__ __forceinline__ int rank_entries(Mine mine, float s_lo, int k_out, ui
         rbin[2 * tid + 1] = first + c0;
     }
     lds_barrier();
-    if (rs->crowded) return RANK_FAILED;
+    if (rs->crowded) return false;
 #pragma unroll
     for (int j = 0; j < NPT; ++j)
         if (mine(j) != 0) seg[rbin[slot[j] >> 16] + (int)(slot[j] & 0xffffu)] = mine(j);
@@ -524,7 +509,7 @@ __device__ __forceinline__ int rank_entries(Mine mine, float s_lo, int k_out, ui
         }
         if (rank < k_out) out[(int64_t)rank * H] = (int32_t)~(uint32_t)cv;
     }
-    return RANK_DONE;
+    return true;
 }
 
 // Entries of the list of candidates that a whole row's fast path may keep (a sixteenth of them per wave).
@@ -753,11 +738,11 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
                 rbin[2 * threadIdx.x] = rbin[2 * threadIdx.x + 1] = 0;
                 if (threadIdx.x == 0) {
                     rank_st.excess = 0.0f;
-                    rank_st.n = rank_st.crowded = 0;
+                    rank_st.crowded = 0;
                 }
                 lds_barrier();
-                if (rank_entries<ITEMS>([&](int j) { return mcv[j]; }, key_score(flt.thr[(int64_t)b * H + h]), k_eff, sort_buf,
-                                        ITEMS * SEL_THREADS, rbin, &rank_st, rho_head + (int64_t)b * k * H + h, H) == RANK_DONE)
+                if (rank_entries<ITEMS>([&](int j) { return mcv[j]; }, n_cand, key_score(flt.thr[(int64_t)b * H + h]), k_eff, sort_buf,
+                                        rbin, &rank_st, rho_head + (int64_t)b * k * H + h, H))
                     return;
                 __syncthreads();
             }
@@ -843,31 +828,29 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
     // because a wave's share of the row holds too many of the best) and for raw keys.
     if constexpr (!MERGE) {
         if (!slice && !raw_keys) {                    // uniform
-            constexpr int FCAP = fast_list_cap(MTOP), WCAP = FCAP / SEL_WAVES, LPT = (WCAP + 63) / 64;
+            constexpr int FCAP = fast_list_cap(MTOP), WCAP = FCAP / SEL_WAVES, NPT = FCAP / SEL_THREADS;
+            static_assert(FCAP % SEL_THREADS == 0, "a wave's share is read 64 entries at a time");
             int* const shist = reinterpret_cast<int*>(sort_buf + FCAP);
             int* const rbin = shist + RANK_BINS;
             const int tid = threadIdx.x, lane = lane_id();
             reinterpret_cast<u32x4*>(shist)[tid] = u32x4{0u, 0u, 0u, 0u};   // both areas
             if (tid == 0) {
                 rank_st.excess = 0.0f;
-                rank_st.n = rank_st.crowded = 0;
+                rank_st.crowded = 0;
+                n_list = 0;
             }
-            int32_t* const my_out = rho_head + (int64_t)b * k * H + h;
-            uint64_t* const wlist = sort_buf + wv * WCAP;
-            bool tried = false;
+            uint64_t* const wlist = sort_buf + wv * WCAP;   // this wave's list: scores and positions, keys are made when it is read
+            uint64_t lv[NPT];                         // this thread's share of the list
+            int n = 0, n_w = 0;                       // its length; this wave's part of it
+            float s_lo = 0.0f;
+            bool go = true;
             if constexpr (ITEMS == 0) {               // a long row whose slices have been filtered already
                 if (sl.cand) {
                     const int64_t r0 = ((int64_t)b * H + h) * sl.n_slices;
-                    int n = 0;
-                    bool fits = true;
-                    for (int z = 0; z < sl.n_slices; ++z) {
-                        const int c = sl.cnt[r0 + z];
-                        fits = fits && c <= sl.cap;
-                        n += min(c, sl.cap);
-                    }
-                    if (fits && n <= FCAP && n >= k_eff) {
-                        constexpr int NPT = (FCAP + SEL_THREADS - 1) / SEL_THREADS;
-                        uint64_t lv[NPT];
+                    for (int z = 0; z < sl.n_slices; ++z) n += sl.cnt[r0 + z] <= sl.cap ? sl.cnt[r0 + z] : FCAP + 1;
+                    go = n < k_eff || n > FCAP;
+                    if (!go) {
+                        s_lo = sl.s_lo[(int64_t)b * H + h];
 #pragma unroll
                         for (int j = 0; j < NPT; ++j) {
                             int i = tid + j * SEL_THREADS;
@@ -882,14 +865,10 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
                             }
                         }
                         lds_barrier();                // the cleared areas
-                        if (rank_entries<NPT>([&](int j) { return lv[j]; }, sl.s_lo[(int64_t)b * H + h], k_eff, sort_buf, FCAP, rbin,
-                                              &rank_st, my_out, H) == RANK_DONE)
-                            return;
-                        tried = true;
                     }
                 }
             }
-            if (!tried) {
+            if (go) {
                 if constexpr (ITEMS > 0) {            // a wave's quad is 256 positions: all of them candidates, some, or none
 #pragma unroll
                     for (int q = 0; q < QUADS; ++q) {
@@ -915,14 +894,14 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
                 }
                 constexpr bool EXACT = ITEMS > 0 && ITEMS <= FAST_SAMPLE;
                 RowSample rs;
-                bool go = sample_row(sk, shist, &sample_st, &rs);
+                go = sample_row(sk, shist, &sample_st, &rs);
+                n = 0;
                 for (int attempt = 0; go; ++attempt) {
                     int j = EXACT ? k_eff : sample_rank_wanted(k_eff, t_hi - max(t_lo, n_sink), rs.n_s);
                     if (attempt == 1) j = min(2 * j, rs.n_s);
-                    float s_lo;
                     const float theta = sample_threshold(rs, j, &sample_st, &s_lo);
-                    int n_w = 0;                      // this wave's list: scores and positions, keys are made when it is read
                     asm volatile("" : "+v"(my_tid));
+                    n_w = 0;
                     // "not below" keeps a NaN, which then makes the ranking fail
                     if constexpr (ITEMS > 0) {
 #pragma unroll
@@ -940,24 +919,26 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
                             }
                         });
                     }
-                    wave_lds_sync();
-                    uint64_t lv[LPT];
-#pragma unroll
-                    for (int i = 0; i < LPT; ++i) {
-                        const uint64_t e = i * 64 + lane < min(n_w, WCAP) ? wlist[i * 64 + lane] : 0;
-                        lv[i] = e != 0 ? ((uint64_t)score_key(__uint_as_float((uint32_t)(e >> 32))) << 32) | (uint32_t)e : 0;
-                    }
-                    if (lane == 0 && n_w > WCAP) atomicAdd(&rank_st.n, 1 << 24);   // too many: makes the ranking fail
-                    const int res = rank_entries<LPT>([&](int i) { return lv[i]; }, s_lo, k_eff, sort_buf, FCAP, rbin, &rank_st, my_out, H);
-                    if (res == RANK_DONE) return;
-                    if (res == RANK_FAILED || attempt == 1) break;
+                    if (lane == 0) atomicAdd(&n_list, n_w <= WCAP ? n_w : 1 << 24);   // too many in one wave: no list
+                    lds_barrier();
+                    n = __builtin_amdgcn_readfirstlane(n_list);
+                    if (n >= k_eff || attempt == 1) break;
                     lds_barrier();                    // everyone has read the count; try a lower threshold
-                    if (tid == 0) {
-                        rank_st.excess = 0.0f;
-                        rank_st.n = 0;
-                    }
+                    if (tid == 0) n_list = 0;
                     lds_barrier();
                 }
+            }
+            if (n >= k_eff && n <= FCAP) {            // uniform
+                if (go) {
+#pragma unroll
+                    for (int j = 0; j < NPT; ++j) {
+                        const uint64_t e = j * 64 + lane < n_w ? wlist[j * 64 + lane] : 0;
+                        lv[j] = e != 0 ? ((uint64_t)score_key(__uint_as_float((uint32_t)(e >> 32))) << 32) | (uint32_t)e : 0;
+                    }
+                }
+                if (rank_entries<NPT>([&](int j) { return lv[j]; }, n, s_lo, k_eff, sort_buf, rbin, &rank_st,
+                                      rho_head + (int64_t)b * k * H + h, H))
+                    return;
             }
             __syncthreads();                          // the areas are used anew below
         }
