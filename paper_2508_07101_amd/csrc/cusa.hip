@@ -266,6 +266,7 @@ int plan_topk_slices(int64_t rows, int lc_max, int k) {
 
 // The same for rows of scores, whose slices are filtered by a threshold of the row (slice_filter_kernel): pieces of
 // about 16384 candidates, no more workgroups than two per CU.
+int topk_mtop(int k) { return k <= 1024 ? 1 : k <= 2048 ? 2 : k <= 4096 ? 4 : 8; }   // composites sorted per thread of 1024
 int plan_filter_slices(int64_t rows, int lc_max) {
     if (lc_max <= 32768) return 1;
     int64_t s = ((int64_t)lc_max + 16383) / 16384;
@@ -274,8 +275,7 @@ int plan_filter_slices(int64_t rows, int lc_max) {
     return s < 1 ? 1 : (int)s;
 }
 int slice_length(int lc_max, int n_slices) { return ((lc_max + n_slices - 1) / n_slices + 4095) / 4096 * 4096; }
-constexpr int SLICE_CAP_MAX = 8192;
-int slice_cap(int k) { return k <= 4096 ? 4096 : SLICE_CAP_MAX; }
+int slice_cap(int k) { return fast_list_cap(topk_mtop(k)); }   // all that the row's ranking takes may stand in one slice
 
 // Sampling plan of the filtered fast path for sequences of up to lc candidate positions: the kernel
 // samples every SAMPLE_STEP-th tile of 64 tokens of a sequence, or as many tiles as it has LDS for
@@ -563,13 +563,13 @@ constexpr size_t SEL_LDS_MAX = (size_t)UNION_MAX_POSITIONS / 8 + UNION_IDLE_WORD
 
 template <int ITEMS, int MTOP, bool MERGE = false>
 constexpr size_t topk_lds_bytes() {
-    // the general path: sort buffer and candidate list; the fast path: list and bins
-    constexpr size_t general = ((size_t)MTOP * SEL_THREADS + topk_list_cap(ITEMS, MTOP)) * sizeof(uint64_t);
+    // the general path: sort buffer, then candidate list or ranking bins; the fast path: list and bins
+    constexpr size_t list = topk_list_cap(ITEMS, MTOP) * sizeof(uint64_t), bins = RANK_BINS * sizeof(int);
+    constexpr size_t general = (size_t)MTOP * SEL_THREADS * sizeof(uint64_t) + (list > bins ? list : bins);
     constexpr size_t fast = MERGE ? (ITEMS <= 8 ? ITEMS : 0) * SEL_THREADS * sizeof(uint64_t) + RANK_BINS * sizeof(int)
                                   : fast_list_cap(MTOP) * sizeof(uint64_t) + 2 * RANK_BINS * sizeof(int);
     return general > fast ? general : fast;
 }
-size_t slice_lds_bytes(int cap) { return (size_t)cap * sizeof(uint64_t) + RANK_BINS * sizeof(int); }
 
 bool grant_lds(const void* fn, size_t bytes) {
     if (bytes <= 48 * 1024) return true;
@@ -616,7 +616,7 @@ bool device_ready() {
     std::lock_guard<std::mutex> lk(mu);
     if (ready[dev]) return true;
     const bool ok = grant_topk_items<4>() && grant_topk_items<8>() && grant_topk_items<16>() && grant_topk_items<32>() &&
-                    grant_topk_items<0>() && grant_lds(reinterpret_cast<const void*>(slice_filter_kernel), slice_lds_bytes(SLICE_CAP_MAX)) && grant_topk_items<-1>() && grant_topk_items<4, true>() &&
+                    grant_topk_items<0>() && grant_topk_items<-1>() && grant_topk_items<4, true>() &&
                     grant_topk_items<8, true>() && grant_topk_items<16, true>() && grant_lds(reinterpret_cast<const void*>(union_kernel), SEL_LDS_MAX) &&
                     grant_lds(reinterpret_cast<const void*>(per_head_rho_kernel), SEL_LDS_MAX) && grant_sample<1>() &&
                     grant_sample<2>() && grant_sample<4>();
@@ -660,10 +660,12 @@ cusa_status launch_topk_m(const TopkArgs& a) {
 // candidates kept for the lower bound.
 template <int ITEMS, bool MERGE = false>
 cusa_status launch_topk(const TopkArgs& a) {
-    if (a.k <= 1024) return launch_topk_m<ITEMS, 1, MERGE>(a);
-    if (a.k <= 2048) return launch_topk_m<ITEMS, 2, MERGE>(a);
-    if (a.k <= 4096) return launch_topk_m<ITEMS, 4, MERGE>(a);
-    return launch_topk_m<ITEMS, 8, MERGE>(a);
+    switch (topk_mtop(a.k)) {
+        case 1: return launch_topk_m<ITEMS, 1, MERGE>(a);
+        case 2: return launch_topk_m<ITEMS, 2, MERGE>(a);
+        case 4: return launch_topk_m<ITEMS, 4, MERGE>(a);
+        default: return launch_topk_m<ITEMS, 8, MERGE>(a);
+    }
 }
 
 // Ranked top-k of every row of P: rows (b, h) of length L_b - W, output rank-major out[b][j][h].
@@ -684,7 +686,7 @@ cusa_status run_topk(int lc_max, int B, int H, hipStream_t s, const float* P, in
         l.cap = slice_cap(k);
         l.n_slices = n_slices;
         l.slice_len = slice_length(lc_max, n_slices);
-        launch(KID_TOPK_SLICE, slice_filter_kernel, dim3(H, B, n_slices), SEL_THREADS, slice_lds_bytes(l.cap), s, P, ldp, seq_lens, H, k,
+        launch(KID_TOPK_SLICE, slice_filter_kernel, dim3(H, B, n_slices), SEL_THREADS, 0, s, P, ldp, seq_lens, H, k,
                budget, window, n_sink, only_rows, l);
         if (launch_status() != CUSA_OK) return CUSA_ERR_LAUNCH;
         return launch_topk<0>(a);

@@ -191,15 +191,15 @@ __device__ __forceinline__ float key_score(uint32_t key) {
 // is a unique set and a unique ranking.
 //
 // Fast path: a threshold from a sample of the row (sample_row), one look at every score against it, the few
-// that pass compacted per wave in LDS, and these ranked by a counting sort over value bins
+// that pass compacted into one LDS list, and these ranked by a counting sort over value bins
 // (rank_entries).  Ranks are written rank-major: rho_head[b][j][h].
-// General path, for rows where that does not work out (massive ties, scores that are not finite, best scores crowded in
-// one wave's share) and for raw keys:
+// General path, for rows where that does not work out (massive ties, scores that are not finite, thresholds that were no
+// good) and for raw keys:
 //   1. radix select (11/11/10-bit digits, LDS histograms) finds the score key T
 //      of the k-th best candidate and how many candidates tie with it;
 //   2. if more candidates equal T than are still needed, a second radix select
 //      over ~position finds the position bound among the ties;
-//   3. the k survivors are compacted into LDS and bitonic-sorted (descending).
+//   3. the k survivors are compacted into LDS and ranked, or bitonic-sorted (descending).
 // With ITEMS > 0 a thread keeps ITEMS scores in registers, loaded once with independent 16-byte loads;
 // ITEMS <= 0 (streamed) reads the row again in every pass, in batches (any length).
 //
@@ -512,7 +512,7 @@ __device__ __forceinline__ bool rank_entries(Mine mine, int n, float s_lo, int k
     return true;
 }
 
-// Entries of the list of candidates that a whole row's fast path may keep (a sixteenth of them per wave).
+// Candidates of a row that the fast path may keep, whichever wave or slice they come from.
 __host__ __device__ constexpr int fast_list_cap(int mtop) { return mtop <= 2 ? 4096 : mtop <= 4 ? 7168 : 14336; }
 constexpr int FAST_SAMPLE = 4;                          // sampled keys per thread
 constexpr float FAST_Z = 4.0f;
@@ -597,14 +597,36 @@ __device__ __forceinline__ void mask_scores(f32x4 (&x)[N / 4], Pos pos, int lo, 
 #pragma unroll
     for (int u = 0; u < N; ++u) x[u >> 2][u & 3] = pos(u) < hi && pos(u) >= lo ? x[u >> 2][u & 3] : -INFINITY;
 }
-// Appends the lanes' (score, position) to a wave's list in LDS; n counts all, also those past the capacity.
-__device__ __forceinline__ void list_push(bool in, float score, int t, uint64_t* list, int cap, int& n) {
-    const uint64_t mask = __ballot(in);
-    if (mask) {
-        const int at = n + mbcnt(mask);
-        if (in && at < cap) list[at] = ((uint64_t)__float_as_uint(score) << 32) | (uint32_t)~(uint32_t)t;
-        n += __popcll(mask);
+// Hands those of a batch of N scores per thread that are not below theta (a NaN is kept, too) to put(slot, score,
+// position), with the slots of a list that the whole workgroup shares: one LDS atomic per wave and batch reserves them.
+// The counter counts all; a batch that does not fit any more is left out, and what then is in the list is of no use.  (A share of the list per wave would need no atomic, but scores
+// are correlated along the sequence: the best of them are in a few waves' parts of the row.)
+template <int N, typename Val, typename Pos, typename Put>
+__device__ __forceinline__ void list_push(Val val, Pos pos, float theta, int* counter, int cap, Put put) {
+    uint64_t mask[N];
+    int n = 0;
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        mask[u] = __ballot(!(val(u) < theta));
+        n += __popcll(mask[u]);
     }
+    if (n == 0) return;                                  // uniform
+    int at = 0;
+    if (lane_id() == 0) at = atomicAdd(counter, n);
+    at = __builtin_amdgcn_readfirstlane(at);
+    if (at + n > cap) return;                            // uniform
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        if (!(val(u) < theta)) put(at + mbcnt(mask[u]), val(u), pos(u));
+        at += __popcll(mask[u]);
+    }
+}
+// An entry of an LDS list (the score as it is; made a composite when the list is read).
+__device__ __forceinline__ uint64_t list_entry(float score, int t) {
+    return ((uint64_t)__float_as_uint(score) << 32) | (uint32_t)~(uint32_t)t;
+}
+__device__ __forceinline__ uint64_t entry_composite(uint64_t e) {
+    return ((uint64_t)score_key(__uint_as_float((uint32_t)(e >> 32))) << 32) | (uint32_t)e;
 }
 __device__ __forceinline__ int sample_rank_wanted(int k_eff, int n, int n_s) {
     const float f = (float)k_eff / (float)n;
@@ -619,7 +641,7 @@ __device__ __forceinline__ int sample_segment(int x, int total, int n) {
 
 // Candidates of a slice of a long row that reach the row's threshold (slice_filter_kernel), for the ranking launch.
 struct SliceLists {
-    uint64_t* cand;              // [row][slice][cap]; nullptr: rows are not sliced
+    uint64_t* cand;              // [row][slice][cap] composites; nullptr: rows are not sliced
     int32_t* cnt;                // [row][slice]; above cap: some did not fit
     float* s_lo;                 // [row] score of the threshold
     int cap, n_slices, slice_len;
@@ -821,15 +843,14 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
     };
 
     // The fast path.  A threshold from a sample of the row lets the k_eff best and a few more candidates through;
-    // each wave compacts those it meets into its share of an LDS list, and they are ranked as they are
+    // the waves compact those into one LDS list, and they are ranked as they are
     // (rank_entries).  One look at every key, one compare: what the selection below pays for -- histogram atomics that
     // meet in a handful of digit bins, top candidates of every thread -- falls away.  It stands for rows that this
-    // does not work out for (crowded bins: massive ties; scores that are not finite; a list that overflows
-    // because a wave's share of the row holds too many of the best) and for raw keys.
+    // does not work out for (massive ties, scores that are not finite, more candidates at the threshold than the list holds,
+    // thresholds that let too few through) and for raw keys.
     if constexpr (!MERGE) {
         if (!slice && !raw_keys) {                    // uniform
-            constexpr int FCAP = fast_list_cap(MTOP), WCAP = FCAP / SEL_WAVES, NPT = FCAP / SEL_THREADS;
-            static_assert(FCAP % SEL_THREADS == 0, "a wave's share is read 64 entries at a time");
+            constexpr int FCAP = fast_list_cap(MTOP), NPT = FCAP / SEL_THREADS;
             int* const shist = reinterpret_cast<int*>(sort_buf + FCAP);
             int* const rbin = shist + RANK_BINS;
             const int tid = threadIdx.x, lane = lane_id();
@@ -839,15 +860,14 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
                 rank_st.crowded = 0;
                 n_list = 0;
             }
-            uint64_t* const wlist = sort_buf + wv * WCAP;   // this wave's list: scores and positions, keys are made when it is read
             uint64_t lv[NPT];                         // this thread's share of the list
-            int n = 0, n_w = 0;                       // its length; this wave's part of it
+            int n = 0;
             float s_lo = 0.0f;
             bool go = true;
             if constexpr (ITEMS == 0) {               // a long row whose slices have been filtered already
                 if (sl.cand) {
                     const int64_t r0 = ((int64_t)b * H + h) * sl.n_slices;
-                    for (int z = 0; z < sl.n_slices; ++z) n += sl.cnt[r0 + z] <= sl.cap ? sl.cnt[r0 + z] : FCAP + 1;
+                    for (int z = 0; z < sl.n_slices; ++z) n += min(sl.cnt[r0 + z], FCAP + 1);
                     go = n < k_eff || n > FCAP;
                     if (!go) {
                         s_lo = sl.s_lo[(int64_t)b * H + h];
@@ -901,25 +921,22 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
                     if (attempt == 1) j = min(2 * j, rs.n_s);
                     const float theta = sample_threshold(rs, j, &sample_st, &s_lo);
                     asm volatile("" : "+v"(my_tid));
-                    n_w = 0;
-                    // "not below" keeps a NaN, which then makes the ranking fail
+                    auto put = [&](int slot, float score, int t) {
+                        sort_buf[slot] = list_entry(score, t);
+                    };
                     if constexpr (ITEMS > 0) {
+                        constexpr int PB = ITEMS < 8 ? ITEMS : 8;
 #pragma unroll
-                        for (int i = 0; i < ITEMS; ++i) {
-                            list_push(!(x[i >> 2][i & 3] < theta), x[i >> 2][i & 3], item_pos(i), wlist, WCAP, n_w);
-                            if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // a few masks at a time
+                        for (int i0 = 0; i0 < ITEMS; i0 += PB) {
+                            list_push<PB>([&](int u) { return x[(i0 + u) >> 2][u & 3]; }, [&](int u) { return item_pos(i0 + u); }, theta, &n_list, FCAP, put);
+                            __builtin_amdgcn_sched_barrier(0);   // a few masks at a time
                         }
                     } else {
                         stream_scores([&](f32x4 (&xs)[SB / 4], int t0) {
                             if (t0 < n_sink || t0 + SB * SEL_THREADS > t_hi) mask_scores<SB>(xs, [&](int u) { return stream_pos(t0, u); }, n_sink, t_hi);
-#pragma unroll
-                            for (int u = 0; u < SB; ++u) {
-                                list_push(!(xs[u >> 2][u & 3] < theta), xs[u >> 2][u & 3], stream_pos(t0, u), wlist, WCAP, n_w);
-                                if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-                            }
+                            list_push<SB>([&](int u) { return xs[u >> 2][u & 3]; }, [&](int u) { return stream_pos(t0, u); }, theta, &n_list, FCAP, put);
                         });
                     }
-                    if (lane == 0) atomicAdd(&n_list, n_w <= WCAP ? n_w : 1 << 24);   // too many in one wave: no list
                     lds_barrier();
                     n = __builtin_amdgcn_readfirstlane(n_list);
                     if (n >= k_eff || attempt == 1) break;
@@ -931,10 +948,7 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
             if (n >= k_eff && n <= FCAP) {            // uniform
                 if (go) {
 #pragma unroll
-                    for (int j = 0; j < NPT; ++j) {
-                        const uint64_t e = j * 64 + lane < n_w ? wlist[j * 64 + lane] : 0;
-                        lv[j] = e != 0 ? ((uint64_t)score_key(__uint_as_float((uint32_t)(e >> 32))) << 32) | (uint32_t)e : 0;
-                    }
+                    for (int j = 0; j < NPT; ++j) lv[j] = tid + j * SEL_THREADS < n ? entry_composite(sort_buf[tid + j * SEL_THREADS]) : 0;
                 }
                 if (rank_entries<NPT>([&](int j) { return lv[j]; }, n, s_lo, k_eff, sort_buf, rbin, &rank_st,
                                       rho_head + (int64_t)b * k * H + h, H))
@@ -1004,10 +1018,12 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
     // 1-3 for candidates delivered by scan_fn: the remaining digits of the k_eff-th best score key
     // T (its top digit is already in st), the position bound among the keys equal to T when they
     // straddle the cut (rare), and the survivors' composites compacted into sort_buf in any order.
+    uint32_t sel_T = 0u;                              // the k_eff-th best score key, once this has run
     auto finish = [&](auto scan_fn) {
         radix_select(1, k_eff, 0u, scan_fn, [](uint32_t skey, int, uint32_t* key) { *key = skey; return true; },
                      hist, scratch, &st);
         const uint32_t T = st.prefix;
+        sel_T = T;
         const int need_eq = st.need, count_eq = st.count_eq;
         __syncthreads();
         uint32_t pos_bound = 0xffffffffu;              // take every tie
@@ -1112,9 +1128,28 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
         for (int i = threadIdx.x; i < k; i += SEL_THREADS) my_parts[i] = i < k_eff ? sort_buf[i] : 0;
         return;
     }
+    // 3a. The ranking as in the fast path; the network below remains for many equal scores, scores that are not finite and raw keys.
+    if (!raw_keys && !direct) {                       // (ranking a filtered pass's candidates has been tried)
+        uint64_t mine[MTOP];
+#pragma unroll
+        for (int j = 0; j < MTOP; ++j) {
+            const int i = (int)threadIdx.x + j * SEL_THREADS;
+            mine[j] = i < k_eff ? sort_buf[i] : 0;
+        }
+        int* const rbin = reinterpret_cast<int*>(sort_buf + NSORT);
+        rbin[2 * threadIdx.x] = rbin[2 * threadIdx.x + 1] = 0;
+        if (threadIdx.x == 0) {
+            rank_st.excess = 0.0f;
+            rank_st.crowded = 0;
+        }
+        lds_barrier();
+        if (rank_entries<MTOP>([&](int j) { return mine[j]; }, k_eff, key_score(sel_T), k_eff, sort_buf, rbin, &rank_st,
+                               rho_head + (int64_t)b * k * H + h, H))
+            return;
+    }
     for (int i = k_eff + threadIdx.x; i < NSORT; i += SEL_THREADS) sort_buf[i] = 0;
     __syncthreads();
-    // 3a. Bitonic network over NSORT = MTOP * 1024 composites, MTOP per thread in registers:
+    // 3b. Bitonic network over NSORT = MTOP * 1024 composites, MTOP per thread in registers:
     // element j of thread (wave, lane) is index wave*64*MTOP + j*64 + lane.  A step with
     // stride < 64 exchanges between lanes of a wave, a stride of 64 .. 32*MTOP between the
     // thread's own registers, and only larger strides go through LDS with workgroup barriers.
@@ -1137,15 +1172,16 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
 
 // Few long rows: one workgroup would walk a row on one CU while most of the chip idles, so a row is cut into slices
 // (blockIdx.z).  Every slice's workgroup takes the row's threshold from the same sample of the whole row (8192 keys:
-// cheaper than a launch that does it once), and leaves those of its candidates that reach it in the slice's list;
-// topk_kernel<0, .> ranks the lists' entries, or -- if a list overflowed, too few are in them, or their bins are crowded -- the row.
+// cheaper than a launch that does it once), and leaves those of its candidates that reach it in the slice's list, which
+// holds as many as the row's ranking takes: where in the row they stand does not matter.
+// topk_kernel<0, .> ranks the lists' entries, or -- if these are too many, too few or not finite -- the row.
 __global__ __launch_bounds__(SEL_THREADS, 8) void slice_filter_kernel(const float* __restrict__ P, int64_t ldp,
                                                                        const int32_t* __restrict__ seq_lens, int H, int k,
                                                                        int budget, int window, int n_sink,
                                                                        const int32_t* __restrict__ only_rows, SliceLists sl) {
-    extern __shared__ uint64_t slice_lds[];           // cap entries (a sixteenth per wave), then the sample's bins
+    __shared__ __attribute__((aligned(16))) int shist[RANK_BINS];
     __shared__ SampleScratch sample_st;
-    __shared__ int wave_n[SEL_WAVES];
+    __shared__ int n_list;
     const int h = blockIdx.x, b = blockIdx.y, z = blockIdx.z, tid = threadIdx.x, lane = lane_id();
     const int wv = __builtin_amdgcn_readfirstlane(wave_id());
     const int64_t r = (int64_t)b * H + h;
@@ -1153,8 +1189,8 @@ __global__ __launch_bounds__(SEL_THREADS, 8) void slice_filter_kernel(const floa
     const int L = seq_lens[b];
     if (L <= budget) return;
     const int Lc = L - window, n = Lc - n_sink, k_eff = min(k, n);
-    int* const shist = reinterpret_cast<int*>(slice_lds + sl.cap);
     shist[2 * tid] = shist[2 * tid + 1] = 0;
+    if (tid == 0) n_list = 0;
     const float* __restrict__ row = P + r * ldp;
     float x[SLICE_SAMPLE];
     int t_s[SLICE_SAMPLE];
@@ -1182,10 +1218,10 @@ __global__ __launch_bounds__(SEL_THREADS, 8) void slice_filter_kernel(const floa
     float theta = INFINITY;
     if (ok) theta = sample_threshold(rs, sample_rank_wanted(k_eff, n, rs.n_s), &sample_st, &s_lo);
     if (tid == 0 && z == 0) sl.s_lo[r] = s_lo;
-    wave_lds_sync();
-    const int wcap = sl.cap / SEL_WAVES;
-    uint64_t* const wlist = slice_lds + wv * wcap;
-    int n_w = 0;
+    uint64_t* const list = sl.cand + (r * sl.n_slices + z) * sl.cap;
+    auto put = [&](int slot, float score, int t) {
+        list[slot] = entry_composite(list_entry(score, t));
+    };
     for (int t0 = t_lo; t0 < t_hi; t0 += V * 4 * SEL_THREADS) {
         f32x4 c[V];
 #pragma unroll
@@ -1193,30 +1229,10 @@ __global__ __launch_bounds__(SEL_THREADS, 8) void slice_filter_kernel(const floa
         request(t0 + V * 4 * SEL_THREADS);            // past the slice's end: never used
         auto pos = [&](int u) { return t0 + ((u >> 2) * SEL_THREADS + tid) * 4 + (u & 3); };
         if (t0 < n_sink || t0 + V * 4 * SEL_THREADS > t_hi) mask_scores<4 * V>(c, pos, n_sink, t_hi);
-#pragma unroll
-        for (int u = 0; u < 4 * V; ++u) {
-            list_push(!(c[u >> 2][u & 3] < theta), c[u >> 2][u & 3], pos(u), wlist, wcap, n_w);
-            if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-        }
+        list_push<4 * V>([&](int u) { return c[u >> 2][u & 3]; }, pos, theta, &n_list, sl.cap, put);
     }
-    if (lane == 0) wave_n[wv] = n_w;
     lds_barrier();
-    int first = 0, all = 0;
-    bool fits = ok;
-#pragma unroll
-    for (int i = 0; i < SEL_WAVES; ++i) {
-        const int c = wave_n[i];
-        first += i < wv ? c : 0;
-        all += c;
-        fits = fits && c <= wcap;
-    }
-    if (tid == 0) sl.cnt[r * sl.n_slices + z] = fits ? all : sl.cap + 1;
-    if (!fits) return;
-    uint64_t* const dst = sl.cand + (r * sl.n_slices + z) * sl.cap + first;
-    for (int i = lane; i < n_w; i += 64) {
-        const uint64_t e = wlist[i];
-        dst[i] = ((uint64_t)score_key(__uint_as_float((uint32_t)(e >> 32))) << 32) | (uint32_t)e;
-    }
+    if (tid == 0) sl.cnt[r * sl.n_slices + z] = ok ? n_list : sl.cap + 1;
 }
 
 // ---------------------------------------------------------------- union / rank / window

@@ -1,0 +1,60 @@
+"""The top-k's own time on scores as attention has them: correlated along the sequence, or repeating.  The kernels' durations
+come from the library's timing facility; they are compared with those of the same call on independent scores, on the
+same device a moment earlier."""
+import pytest
+import torch
+
+from paper_2508_07101_amd import binding as cb
+
+pytestmark = pytest.mark.gpu
+DEV, D, G = "cuda", 128, 8
+
+
+def _topk_us(B, H, L, K, W, k, span=0, distinct=0):
+    """Fastest of five means of ten calls.  span: each span of that many positions has an offset of its own, as wide as the
+    scores are spread; distinct: that many different keys."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(11)
+    q = torch.randn((B, H, D), generator=gen, device=DEV, dtype=torch.bfloat16)
+    keys = torch.randn((B, G, distinct or L, D), generator=gen, device=DEV, dtype=torch.bfloat16)
+    if distinct:
+        keys = keys[:, :, torch.randint(distinct, (L,), generator=gen, device=DEV)].contiguous()
+    if span:
+        groups = q.float().view(B, G, -1, D)
+        u = torch.nn.functional.normalize(groups.sum(2), dim=-1)          # moves the scores of all heads of a group alike
+        per = (groups * u.unsqueeze(2)).sum(-1).mean(2, keepdim=True)
+        off = torch.randn((B, G, (L + span - 1) // span), generator=gen, device=DEV) * D ** 0.5 / per
+        keys = (keys.float() + off.repeat_interleave(span, 2)[:, :, :L].unsqueeze(-1) * u.unsqueeze(2)).to(torch.bfloat16)
+    kv = cb.KvCache(keys, keys, torch.full((B,), L, dtype=torch.int32, device=DEV), L)
+    p = cb.make_params(B, H, G, K, W, k)
+    idx = torch.zeros((B, K), dtype=torch.int32, device=DEV)
+    cnt = torch.zeros((B,), dtype=torch.int32, device=DEV)
+    ws = cb.alloc_workspace(p, L, DEV)
+    cb.select(p, q, kv, idx, cnt, ws)
+    torch.cuda.synchronize()
+    best = float("inf")
+    cb.profile_enable(True)
+    try:
+        for _ in range(5):
+            cb.profile_reset()
+            for _ in range(10):
+                cb.select(p, q, kv, idx, cnt, ws)
+            prof = cb.profile_read()
+            best = min(best, sum(v["total_ms"] for name, v in prof.items() if name.startswith("topk")) * 100.0)
+    finally:
+        cb.profile_enable(False)
+        cb.profile_reset()
+    return best
+
+
+SIZES = [(1, 32, 32768, 2048, 512, 0), (8, 32, 16384, 4096, 1024, 0), (16, 32, 16384, 2048, 512, 0),
+         (1, 64, 131072, 4096, 1024, 0)]
+
+
+@pytest.mark.parametrize("size", SIZES)
+def test_scores_correlated_along_the_sequence_take_no_longer(size):
+    """One list for the whole row: where its best candidates stand does not matter.  (With a sixteenth of the list for
+    each wave these took 2.5 to 6 times as long as independent scores.)"""
+    plain, clustered = _topk_us(*size), _topk_us(*size, span=256)
+    print(f"[time] {size}: independent {plain:.1f} us, correlated {clustered:.1f} us", flush=True)
+    assert clustered < 1.5 * plain
