@@ -628,15 +628,17 @@ __device__ __forceinline__ uint64_t list_entry(float score, int t) {
 __device__ __forceinline__ uint64_t entry_composite(uint64_t e) {
     return ((uint64_t)score_key(__uint_as_float((uint32_t)(e >> 32))) << 32) | (uint32_t)e;
 }
-__device__ __forceinline__ int sample_rank_wanted(int k_eff, int n, int n_s) {
+__device__ __forceinline__ int sample_rank_wanted(int k_eff, int n, int n_s, float z) {
     const float f = (float)k_eff / (float)n;
-    return min((int)(f * (float)n_s + FAST_Z * sqrtf(f * (1.0f - f) * (float)n_s)) + 1, n_s);
+    return min((int)(f * (float)n_s + z * sqrtf(f * (1.0f - f) * (float)n_s)) + 1, n_s);
 }
 
-// Position of the sample's 64-key segment number x (of `total`) of a row of n positions, spread evenly.
-__device__ __forceinline__ int sample_segment(int x, int total, int n) {
-    const int segs = (n + 63) >> 6;
-    return (segs <= total ? x : (int)((int64_t)x * segs / total)) * 64;
+// First position of quad number x of a sample of TOTAL keys of a row of n positions (of a shorter row: past its end): runs of 16
+// keys (64 bytes), spread evenly.  (Scores are correlated along the sequence: fewer, longer runs say less about the row.)
+template <int TOTAL>
+__device__ __forceinline__ int sample_quad(int x, int n) {
+    const int runs = (n + 15) >> 4;
+    return (runs <= TOTAL / 16 ? x >> 2 : (int)((uint32_t)(x >> 2) * (uint32_t)runs / (TOTAL / 16))) * 16 + (x & 3) * 4;
 }
 
 // Candidates of a slice of a long row that reach the row's threshold (slice_filter_kernel), for the ranking launch.
@@ -647,6 +649,7 @@ struct SliceLists {
     int cap, n_slices, slice_len;
 };
 constexpr int SLICE_SAMPLE = 8;                         // sampled keys per thread
+constexpr float SLICE_Z = 6.0f;                         // instead of FAST_Z: a second walk is that of a whole row by one workgroup
 
 // ITEMS == -1 is the streamed kernel in a register-lean form (half the keys in flight, compiled for two
 // resident workgroups per CU): with more rows than CUs two rows overlap on a CU, which gains more
@@ -716,7 +719,7 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
     auto key_of = [raw_keys](float v) { return raw_keys ? __float_as_uint(v) : score_key(v); };
     // Keys held in registers come in quads, 16-byte loads: quad q of wave w is its part of the 4096-key block
     // rev(q) + w (rev: bits reversed), so that the first quads of all waves are 256-key pieces from all over the row;
-    // one key of each of the first four is the row's sample.
+    // a key of each of four (where there are eight, of the first or the last four) is the row's sample.
     constexpr int QUADS = ITEMS > 4 ? ITEMS / 4 : 1;
     int my_tid = threadIdx.x;
     auto item_pos = [&](int i) {
@@ -901,24 +904,29 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
                     asm volatile("" : "+v"(my_tid));
                 }
                 uint32_t sk[FAST_SAMPLE];
+                if constexpr (ITEMS > 0) {
 #pragma unroll
-                for (int i = 0; i < FAST_SAMPLE; ++i) {
-                    if constexpr (ITEMS > 0) {
+                    for (int i = 0; i < FAST_SAMPLE; ++i) {
                         const int it = QUADS >= 4 ? 5 * i : QUADS == 2 ? (i < 2 ? 2 * i : 2 * i + 1) : i;   // (5 i: element i of quad i)
-                        sk[i] = x[it >> 2][it & 3] == -INFINITY ? 0u : score_key(x[it >> 2][it & 3]);
-                    } else {
-                        const int t = sample_segment(i * SEL_WAVES + wv, FAST_SAMPLE * SEL_WAVES, t_hi) + lane;
-                        const uint32_t kv_ = key_of(row[t < t_hi ? t : t_hi - 1]);
-                        sk[i] = (t < t_hi && t >= n_sink) ? kv_ : 0u;
+                        // of eight quads, every other lane samples the last four: no part of the row is left out
+                        const float s = QUADS == 8 && (lane & 1) ? x[(it >> 2) + (QUADS == 8 ? 4 : 0)][it & 3] : x[it >> 2][it & 3];
+                        sk[i] = s == -INFINITY ? 0u : score_key(s);
                     }
+                } else {
+                    static_assert(FAST_SAMPLE == 4, "one 16-byte load");
+                    const int t = sample_quad<FAST_SAMPLE * SEL_THREADS>(tid, t_hi);
+                    const f32x4 y = *reinterpret_cast<const f32x4*>(row + min(t, (int)ldp - 4));
+#pragma unroll
+                    for (int i = 0; i < FAST_SAMPLE; ++i) sk[i] = t + i < t_hi && t + i >= n_sink ? score_key(y[i]) : 0u;
                 }
                 constexpr bool EXACT = ITEMS > 0 && ITEMS <= FAST_SAMPLE;
                 RowSample rs;
                 go = sample_row(sk, shist, &sample_st, &rs);
-                n = 0;
-                for (int attempt = 0; go; ++attempt) {
-                    int j = EXACT ? k_eff : sample_rank_wanted(k_eff, t_hi - max(t_lo, n_sink), rs.n_s);
-                    if (attempt == 1) j = min(2 * j, rs.n_s);
+                // (slices that failed have told how many reach a threshold like the first)
+                for (int attempt = ITEMS == 0 && sl.cand ? 1 : 0; go; ++attempt) {
+                    int j = EXACT ? k_eff : sample_rank_wanted(k_eff, t_hi - max(t_lo, n_sink), rs.n_s, FAST_Z);
+                    if (attempt == 1)                 // n were too few (too many): as many more (fewer) as should do, twice as many at most
+                        j = min(min(2 * j, (int)(1.25f * (float)j * (float)k_eff * __builtin_amdgcn_rcpf((float)max(n, 1))) + 8), rs.n_s);
                     const float theta = sample_threshold(rs, j, &sample_st, &s_lo);
                     asm volatile("" : "+v"(my_tid));
                     auto put = [&](int slot, float score, int t) {
@@ -1182,8 +1190,7 @@ __global__ __launch_bounds__(SEL_THREADS, 8) void slice_filter_kernel(const floa
     __shared__ __attribute__((aligned(16))) int shist[RANK_BINS];
     __shared__ SampleScratch sample_st;
     __shared__ int n_list;
-    const int h = blockIdx.x, b = blockIdx.y, z = blockIdx.z, tid = threadIdx.x, lane = lane_id();
-    const int wv = __builtin_amdgcn_readfirstlane(wave_id());
+    const int h = blockIdx.x, b = blockIdx.y, z = blockIdx.z, tid = threadIdx.x;
     const int64_t r = (int64_t)b * H + h;
     if (only_rows && only_rows[r] == 0) return;
     const int L = seq_lens[b];
@@ -1192,12 +1199,12 @@ __global__ __launch_bounds__(SEL_THREADS, 8) void slice_filter_kernel(const floa
     shist[2 * tid] = shist[2 * tid + 1] = 0;
     if (tid == 0) n_list = 0;
     const float* __restrict__ row = P + r * ldp;
-    float x[SLICE_SAMPLE];
-    int t_s[SLICE_SAMPLE];
+    f32x4 x[SLICE_SAMPLE / 4];
+    int t_s[SLICE_SAMPLE / 4];
 #pragma unroll
-    for (int i = 0; i < SLICE_SAMPLE; ++i) {
-        t_s[i] = sample_segment(i * SEL_WAVES + wv, SLICE_SAMPLE * SEL_WAVES, Lc) + lane;
-        x[i] = row[min(t_s[i], Lc - 1)];
+    for (int i = 0; i < SLICE_SAMPLE / 4; ++i) {
+        t_s[i] = sample_quad<SLICE_SAMPLE * SEL_THREADS>(i * SEL_THREADS + tid, Lc);
+        x[i] = *reinterpret_cast<const f32x4*>(row + min(t_s[i], (int)ldp - 4));
     }
     const int t_lo = z * sl.slice_len, t_hi = min(Lc, t_lo + sl.slice_len);
     // the slice's first keys are on their way while the sample is worked on; positions t0 + (v * 1024 + thread) * 4 + e,
@@ -1211,12 +1218,15 @@ __global__ __launch_bounds__(SEL_THREADS, 8) void slice_filter_kernel(const floa
     request(t_lo);
     uint32_t sk[SLICE_SAMPLE];
 #pragma unroll
-    for (int i = 0; i < SLICE_SAMPLE; ++i) sk[i] = (t_s[i] < Lc && t_s[i] >= n_sink) ? score_key(x[i]) : 0u;
+    for (int i = 0; i < SLICE_SAMPLE; ++i) {
+        const int t = t_s[i / 4] + i % 4;
+        sk[i] = t < Lc && t >= n_sink ? score_key(x[i / 4][i % 4]) : 0u;
+    }
     RowSample rs;
     const bool ok = sample_row(sk, shist, &sample_st, &rs);
     float s_lo = 0.0f;
     float theta = INFINITY;
-    if (ok) theta = sample_threshold(rs, sample_rank_wanted(k_eff, n, rs.n_s), &sample_st, &s_lo);
+    if (ok) theta = sample_threshold(rs, sample_rank_wanted(k_eff, n, rs.n_s, SLICE_Z), &sample_st, &s_lo);
     if (tid == 0 && z == 0) sl.s_lo[r] = s_lo;
     uint64_t* const list = sl.cand + (r * sl.n_slices + z) * sl.cap;
     auto put = [&](int slot, float score, int t) {

@@ -58,3 +58,13 @@ def test_scores_correlated_along_the_sequence_take_no_longer(size):
     plain, clustered = _topk_us(*size), _topk_us(*size, span=256)
     print(f"[time] {size}: independent {plain:.1f} us, correlated {clustered:.1f} us", flush=True)
     assert clustered < 1.5 * plain
+
+
+@pytest.mark.parametrize("size,span", [((1, 32, 30512, 2560, 512, 0), 256), ((1, 32, 30512, 2560, 512, 0), 64),
+                                       ((1, 64, 131072, 2048, 512, 0), 64), ((1, 32, 60512, 2560, 512, 0), 64)])
+def test_the_sample_speaks_for_rows_correlated_along_the_sequence(size, span):
+    """The threshold's sample is spread over the row in short runs and a second threshold goes by what the first let through.
+    (Half the row in 256-key pieces, or 64-key runs, and twice as many the second time: 1.6 to 4 times as long.)"""
+    plain, clustered = _topk_us(*size), _topk_us(*size, span=span)
+    print(f"[time] {size} spans of {span}: independent {plain:.1f} us, correlated {clustered:.1f} us", flush=True)
+    assert clustered < 1.4 * plain
