@@ -192,9 +192,9 @@ __device__ __forceinline__ float key_score(uint32_t key) {
 //
 // Fast path: a threshold from a sample of the row (sample_row), one look at every score against it, the few
 // that pass compacted into one LDS list, and these ranked by a counting sort over value bins
-// (rank_entries).  Ranks are written rank-major: rho_head[b][j][h].
-// General path, for rows where that does not work out (massive ties, scores that are not finite, thresholds that were no
-// good) and for raw keys:
+// (rank_entries) -- or, where many of them are equal, sorted.  Ranks are written rank-major: rho_head[b][j][h].
+// General path, for rows where that does not work out (scores that are not finite, more passing than the list holds: massive
+// ties, thresholds that were no good) and for raw keys:
 //   1. radix select (11/11/10-bit digits, LDS histograms) finds the score key T
 //      of the k-th best candidate and how many candidates tie with it;
 //   2. if more candidates equal T than are still needed, a second radix select
@@ -394,10 +394,11 @@ __device__ __forceinline__ uint32_t row_max16(uint32_t v) {
 
 // LDS words of the ranking, besides the bins and the segments.
 struct RankScratch {
-    float excess;                // cleared by the caller, like crowded
-    int crowded, wave[SEL_WAVES];
+    float excess;                // cleared by the caller, like walk
+    int walk, wave[SEL_WAVES];
 };
 constexpr int RANK_BINS = 2048;
+enum { RANK_DONE = 0, RANK_FAILED = 1, RANK_CROWDED = 2 };
 
 // Ranks the m <= 64 CHUNKS composites of a segment that starts at rank 0, the workgroup together: every wave holds all
 // of them, 64 to a register, and compares its sixteenth of them with 64 at a time.
@@ -428,17 +429,19 @@ __device__ __forceinline__ void rank_together(const uint64_t* seg, int m, int k_
 // [s_lo, s_lo + 6 x the mean excess over s_lo], not up to the best score: a few very large scores
 // (attention sinks, hot tokens) would otherwise stretch the bins over empty space and crowd the
 // rest; whatever lies above shares the first bin.  About a fifth of the instructions of a sorting network.
-// False, with nothing written: a bin that holds wanted ranks has more than RMAX entries (many equal scores), or the scores
-// are not finite or all alike; the caller then ranks another way.
+// Otherwise nothing is written and the caller ranks another way: RANK_FAILED, the scores are not finite; RANK_CROWDED, they
+// are, but all alike, or repeat so often that walking their segments (the sum of the squares of their lengths; WALK_MAX) would
+// take longer than the network, which adds 17 us: 32 rows of 32256, k 1536, whose scores come 32 at a time 16.1 us, 126 at a
+// time 24.8, 252 at a time 44.8, all different 13.3.
 // seg: room for n composites; rbin: RANK_BINS zeros; *rs cleared; all
 // visible to the workgroup (one barrier since).  Called by the whole workgroup.
 //
 // Sixteen waves on one CU: an instruction that all of them execute costs sixteen cycles, a barrier a few
 // hundred, so sums and scans go by DPP and the barriers wait for LDS only.
 template <int NPT, typename Mine>
-__device__ __forceinline__ bool rank_entries(Mine mine, int n, float s_lo, int k_out, uint64_t* seg, int* rbin,
-                                             RankScratch* rs, int32_t* __restrict__ out, int H) {
-    constexpr int RMAX = 512;
+__device__ __forceinline__ int rank_entries(Mine mine, int n, float s_lo, int k_out, uint64_t* seg, int* rbin,
+                                            RankScratch* rs, int32_t* __restrict__ out, int H) {
+    constexpr int RMAX = 32, RMAX_FIRST = 512, WALK_MAX = 1 << 18;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(wave_id());
     {
         float excess = 0.0f;
@@ -450,7 +453,8 @@ __device__ __forceinline__ bool rank_entries(Mine mine, int n, float s_lo, int k
     }
     lds_barrier();
     const float range = 6.0f * rs->excess / (float)n;    // workgroup-uniform, like all that follows
-    if (!(range > 0.0f && range < 3.0e38f)) return false;
+    if (!(fabsf(range) < 3.0e38f)) return RANK_FAILED;
+    if (!(range > 0.0f)) return RANK_CROWDED;
     const float scale = (float)(RANK_BINS - 1) / range;
     auto bin_of = [&](uint64_t cv) {                     // bin 0 holds the best scores
         const int up = (int)((key_score((uint32_t)(cv >> 32)) - s_lo) * scale);
@@ -474,12 +478,15 @@ __device__ __forceinline__ bool rank_entries(Mine mine, int n, float s_lo, int k
 #pragma unroll
         for (int i = 0; i < SEL_WAVES; ++i) first += i < w ? rs->wave[i] : 0;
         // only segments that reach into the wanted ranks are walked: the others may be crowded
-        if ((first < k_out && c0 > RMAX) || (first + c0 < k_out && c1 > RMAX)) rs->crowded = 1;
+        int walk = first + c0 < k_out && c1 > RMAX ? c1 * c1 : 0;
+        if (tid == 0) walk += c0 > RMAX_FIRST ? WALK_MAX + 1 : 0;
+        else if (first < k_out && c0 > RMAX) walk += c0 * c0;
+        if (walk != 0) atomicAdd(&rs->walk, walk);
         rbin[2 * tid] = first;
         rbin[2 * tid + 1] = first + c0;
     }
     lds_barrier();
-    if (rs->crowded) return false;
+    if (rs->walk > WALK_MAX) return RANK_CROWDED;
 #pragma unroll
     for (int j = 0; j < NPT; ++j)
         if (mine(j) != 0) seg[rbin[slot[j] >> 16] + (int)(slot[j] & 0xffffu)] = mine(j);
@@ -492,7 +499,7 @@ __device__ __forceinline__ bool rank_entries(Mine mine, int n, float s_lo, int k
         if (m0 <= 64) rank_together<1>(seg, m0, k_out, out, H);
         else if (m0 <= 128) rank_together<2>(seg, m0, k_out, out, H);
         else if (m0 <= 256) rank_together<4>(seg, m0, k_out, out, H);
-        else rank_together<RMAX / 64>(seg, m0, k_out, out, H);
+        else rank_together<RMAX_FIRST / 64>(seg, m0, k_out, out, H);
     }
     // the composites ranked below k_out lie in the segments' first k_out entries or just behind them
     for (int i = (many ? m0 : 0) + tid; i < n; i += SEL_THREADS) {
@@ -509,7 +516,7 @@ __device__ __forceinline__ bool rank_entries(Mine mine, int n, float s_lo, int k
         }
         if (rank < k_out) out[(int64_t)rank * H] = (int32_t)~(uint32_t)cv;
     }
-    return true;
+    return RANK_DONE;
 }
 
 // Candidates of a row that the fast path may keep, whichever wave or slice they come from.
@@ -727,7 +734,7 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
         const int q = i >> 2, rev = LOG2 == 0 ? 0 : (int)(__builtin_bitreverse32((uint32_t)q) >> (LOG2 == 0 ? 31 : 32 - LOG2));
         return t_lo + ((rev + wv) & (QUADS - 1)) * (4 * SEL_THREADS) + my_tid * 4 + (i & 3);
     };
-    f32x4 x[!MERGE && ITEMS > 0 ? QUADS : 1];         // scores (or raw keys)
+    f32x4 x[!MERGE && ITEMS > 0 ? QUADS : 1];         // scores
     uint32_t keys[ITEMS > 0 ? ITEMS : 1];             // 0: no candidate
     int pos_of[MERGE ? ITEMS : 1];                     // MERGE: the positions that come with the keys
     if constexpr (MERGE) {
@@ -763,11 +770,11 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
                 rbin[2 * threadIdx.x] = rbin[2 * threadIdx.x + 1] = 0;
                 if (threadIdx.x == 0) {
                     rank_st.excess = 0.0f;
-                    rank_st.crowded = 0;
+                    rank_st.walk = 0;
                 }
                 lds_barrier();
                 if (rank_entries<ITEMS>([&](int j) { return mcv[j]; }, n_cand, key_score(flt.thr[(int64_t)b * H + h]), k_eff, sort_buf,
-                                        rbin, &rank_st, rho_head + (int64_t)b * k * H + h, H))
+                                        rbin, &rank_st, rho_head + (int64_t)b * k * H + h, H) == RANK_DONE)
                     return;
                 __syncthreads();
             }
@@ -777,11 +784,15 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
             keys[i] = (uint32_t)(mcv[i] >> 32);
             pos_of[i] = (int)~(uint32_t)mcv[i];
         }
-    } else if constexpr (ITEMS > 0) {
-        // rows are padded to a multiple of 64 entries (ldp): a quad that starts below ldp stays inside its row
+    }
+    // rows are padded to a multiple of 64 entries (ldp): a quad that starts below ldp stays inside its row
+    auto load_row = [&]() {
 #pragma unroll
         for (int q = 0; q < QUADS; ++q) x[q] = *reinterpret_cast<const f32x4*>(row + min(item_pos(4 * q), (int)ldp - 4));
         asm volatile("" : "+v"(my_tid));              // positions are made anew where they are needed, not kept in registers
+    };
+    if constexpr (!MERGE && ITEMS > 0) {
+        if (!slice && !raw_keys) load_row();          // uniform
     }
     // Streamed rows (ITEMS <= 0) are walked in batches of SB keys per thread covering the positions
     // [t0, t0 + SB * 1024): key u of a thread is position t0 + ((u / 4) * 1024 + thread) * 4 + u % 4, so a
@@ -845,12 +856,49 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
         }
     };
 
+    // 1-3 for candidates delivered by scan_fn: the digits of the k_eff-th best score key
+    // T (first_pass 1: its top digit is already in st), the position bound among the keys equal to T when they
+    // straddle the cut (rare), and the survivors' composites compacted into sort_buf in any order.
+    uint32_t sel_T = 0u;                              // the k_eff-th best score key, once this has run
+    auto finish = [&](int first_pass, auto scan_fn) {
+        radix_select(first_pass, k_eff, 0u, scan_fn, [](uint32_t skey, int, uint32_t* key) { *key = skey; return true; },
+                     hist, scratch, &st);
+        const uint32_t T = st.prefix;
+        sel_T = T;
+        const int need_eq = st.need, count_eq = st.count_eq;
+        __syncthreads();
+        uint32_t pos_bound = 0xffffffffu;              // take every tie
+        if (count_eq > need_eq) {
+            radix_select(0, need_eq, 0u, scan_fn,
+                         [T](uint32_t skey, int t, uint32_t* key) { *key = ~(uint32_t)t; return skey == T; },
+                         hist, scratch, &st);
+            pos_bound = ~st.prefix;                    // need_eq-th smallest tying position
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) n_out = 0;
+        __syncthreads();                               // also: histogram no longer needed
+        // one reservation per wave: count this thread's survivors, scan the counts over the wave
+        int mine = 0;
+        scan_fn([&](uint32_t key, int t) {
+            mine += (key > T || (key == T && (uint32_t)t <= pos_bound)) ? 1 : 0;
+        });
+        int slot = wave_reserve(mine, &n_out);
+        scan_fn([&](uint32_t key, int t) {
+            if (key > T || (key == T && (uint32_t)t <= pos_bound)) {
+                if (slot < NSORT) sort_buf[slot] = ((uint64_t)key << 32) | (uint32_t)~(uint32_t)t;
+                ++slot;
+            }
+        });
+        __syncthreads();
+    };
+
+    int n_sort = 0;                                   // composites in sort_buf that only have to be sorted (0: not that far)
     // The fast path.  A threshold from a sample of the row lets the k_eff best and a few more candidates through;
     // the waves compact those into one LDS list, and they are ranked as they are
     // (rank_entries).  One look at every key, one compare: what the selection below pays for -- histogram atomics that
-    // meet in a handful of digit bins, top candidates of every thread -- falls away.  It stands for rows that this
-    // does not work out for (massive ties, scores that are not finite, more candidates at the threshold than the list holds,
-    // thresholds that let too few through) and for raw keys.
+    // meet in a handful of digit bins, top candidates of every thread -- falls away.  Where many scores of the list are equal it
+    // is sorted instead; the selection stands for rows that have no such list (scores that are not finite, more
+    // candidates at the threshold than it holds, thresholds that let too few through) and for raw keys.
     if constexpr (!MERGE) {
         if (!slice && !raw_keys) {                    // uniform
             constexpr int FCAP = fast_list_cap(MTOP), NPT = FCAP / SEL_THREADS;
@@ -860,7 +908,7 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
             reinterpret_cast<u32x4*>(shist)[tid] = u32x4{0u, 0u, 0u, 0u};   // both areas
             if (tid == 0) {
                 rank_st.excess = 0.0f;
-                rank_st.crowded = 0;
+                rank_st.walk = 0;
                 n_list = 0;
             }
             uint64_t lv[NPT];                         // this thread's share of the list
@@ -892,7 +940,7 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
                 }
             }
             if (go) {
-                if constexpr (ITEMS > 0) {            // a wave's quad is 256 positions: all of them candidates, some, or none
+                auto mask_row = [&]() {               // a wave's quad is 256 positions: all of them candidates, some, or none
 #pragma unroll
                     for (int q = 0; q < QUADS; ++q) {
                         const int first = __builtin_amdgcn_readfirstlane(item_pos(4 * q));
@@ -902,7 +950,8 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
                         }
                     }
                     asm volatile("" : "+v"(my_tid));
-                }
+                };
+                if constexpr (ITEMS > 0) mask_row();
                 uint32_t sk[FAST_SAMPLE];
                 if constexpr (ITEMS > 0) {
 #pragma unroll
@@ -950,6 +999,10 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
                     if (n >= k_eff || attempt == 1) break;
                     lds_barrier();                    // everyone has read the count; try a lower threshold
                     if (tid == 0) n_list = 0;
+                    if constexpr (ITEMS > 0) {        // (not kept in registers for this)
+                        load_row();
+                        mask_row();
+                    }
                     lds_barrier();
                 }
             }
@@ -958,16 +1011,32 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
 #pragma unroll
                     for (int j = 0; j < NPT; ++j) lv[j] = tid + j * SEL_THREADS < n ? entry_composite(sort_buf[tid + j * SEL_THREADS]) : 0;
                 }
-                if (rank_entries<NPT>([&](int j) { return lv[j]; }, n, s_lo, k_eff, sort_buf, rbin, &rank_st,
-                                      rho_head + (int64_t)b * k * H + h, H))
-                    return;
+                const int res = rank_entries<NPT>([&](int j) { return lv[j]; }, n, s_lo, k_eff, sort_buf, rbin, &rank_st,
+                                                  rho_head + (int64_t)b * k * H + h, H);
+                if (res == RANK_DONE) return;
+                lds_barrier();                        // the areas are used anew
+                if (res == RANK_CROWDED) {            // all finite, so the k_eff best are among them
+                    if (n <= NSORT) {
+#pragma unroll
+                        for (int j = 0; j < MTOP; ++j) sort_buf[tid + j * SEL_THREADS] = lv[j];
+                        n_sort = NSORT;
+                    } else {
+                        finish(0, [&](auto f) {
+#pragma unroll
+                            for (int j = 0; j < NPT; ++j)
+                                if (lv[j] != 0) f((uint32_t)(lv[j] >> 32), (int)~(uint32_t)lv[j]);
+                        });
+                        n_sort = k_eff;
+                    }
+                }
             }
             __syncthreads();                          // the areas are used anew below
         }
     }
+    if (n_sort == 0) {                                // uniform
     // The general path, on keys.
-    if constexpr (!MERGE && ITEMS > 0) {
-        asm volatile("" : "+v"(my_tid));
+    if constexpr (!MERGE && ITEMS > 0) {              // (fetched anew: kept beside what the fast path needs, the scores do not fit the registers)
+        load_row();
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) {
             const int t = item_pos(i);
@@ -1023,42 +1092,6 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
     d0 = st.prefix >> 21;
     __syncthreads();
     }
-    // 1-3 for candidates delivered by scan_fn: the remaining digits of the k_eff-th best score key
-    // T (its top digit is already in st), the position bound among the keys equal to T when they
-    // straddle the cut (rare), and the survivors' composites compacted into sort_buf in any order.
-    uint32_t sel_T = 0u;                              // the k_eff-th best score key, once this has run
-    auto finish = [&](auto scan_fn) {
-        radix_select(1, k_eff, 0u, scan_fn, [](uint32_t skey, int, uint32_t* key) { *key = skey; return true; },
-                     hist, scratch, &st);
-        const uint32_t T = st.prefix;
-        sel_T = T;
-        const int need_eq = st.need, count_eq = st.count_eq;
-        __syncthreads();
-        uint32_t pos_bound = 0xffffffffu;              // take every tie
-        if (count_eq > need_eq) {
-            radix_select(0, need_eq, 0u, scan_fn,
-                         [T](uint32_t skey, int t, uint32_t* key) { *key = ~(uint32_t)t; return skey == T; },
-                         hist, scratch, &st);
-            pos_bound = ~st.prefix;                    // need_eq-th smallest tying position
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) n_out = 0;
-        __syncthreads();                               // also: histogram no longer needed
-        // one reservation per wave: count this thread's survivors, scan the counts over the wave
-        int mine = 0;
-        scan_fn([&](uint32_t key, int t) {
-            mine += (key > T || (key == T && (uint32_t)t <= pos_bound)) ? 1 : 0;
-        });
-        int slot = wave_reserve(mine, &n_out);
-        scan_fn([&](uint32_t key, int t) {
-            if (key > T || (key == T && (uint32_t)t <= pos_bound)) {
-                if (slot < NSORT) sort_buf[slot] = ((uint64_t)key << 32) | (uint32_t)~(uint32_t)t;
-                ++slot;
-            }
-        });
-        __syncthreads();
-    };
-
     // The top digit of T comes from one histogram pass over all candidates whose top digit is at
     // least d0.  Those are the only ones that can still matter; when they fit they are copied to
     // an LDS list and everything after this pass walks the list (a few entries per thread)
@@ -1123,19 +1156,20 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
     }
     if (listed) {
         const int n = n_list;
-        finish([&](auto f) {
+        finish(1, [&](auto f) {
             for (int i = threadIdx.x; i < n; i += SEL_THREADS) {
                 const uint64_t cv = cand[i];
                 f((uint32_t)(cv >> 32), (int)~(uint32_t)cv);
             }
         });
     } else {
-        finish(scan);
+        finish(1, scan);
     }
     if (slice) {                                      // the slice's k best, in any order; the merge ranks
         for (int i = threadIdx.x; i < k; i += SEL_THREADS) my_parts[i] = i < k_eff ? sort_buf[i] : 0;
         return;
     }
+    n_sort = k_eff;
     // 3a. The ranking as in the fast path; the network below remains for many equal scores, scores that are not finite and raw keys.
     if (!raw_keys && !direct) {                       // (ranking a filtered pass's candidates has been tried)
         uint64_t mine[MTOP];
@@ -1148,14 +1182,15 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
         rbin[2 * threadIdx.x] = rbin[2 * threadIdx.x + 1] = 0;
         if (threadIdx.x == 0) {
             rank_st.excess = 0.0f;
-            rank_st.crowded = 0;
+            rank_st.walk = 0;
         }
         lds_barrier();
         if (rank_entries<MTOP>([&](int j) { return mine[j]; }, k_eff, key_score(sel_T), k_eff, sort_buf, rbin, &rank_st,
-                               rho_head + (int64_t)b * k * H + h, H))
+                               rho_head + (int64_t)b * k * H + h, H) == RANK_DONE)
             return;
     }
-    for (int i = k_eff + threadIdx.x; i < NSORT; i += SEL_THREADS) sort_buf[i] = 0;
+    }                                                 // n_sort == 0
+    for (int i = n_sort + threadIdx.x; i < NSORT; i += SEL_THREADS) sort_buf[i] = 0;
     __syncthreads();
     // 3b. Bitonic network over NSORT = MTOP * 1024 composites, MTOP per thread in registers:
     // element j of thread (wave, lane) is index wave*64*MTOP + j*64 + lane.  A step with

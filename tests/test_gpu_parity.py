@@ -548,6 +548,24 @@ def test_topk_rows_whose_best_scores_cluster(B, L, K, W, k, where):
     check_select(inp, r, 0, seqs=[0, B - 1], check_scores=False)
 
 
+@pytest.mark.parametrize("B,L,K,W,k", [(2, 4000, 1300, 276, 1024), (2, 7000, 1000, 100, 0), (2, 9000, 2560, 512, 0),
+                                        (2, 20011, 4096, 0, 0), (1, 12000, 8192, 192, 0), (1, 70001, 2048, 512, 0), (36, 9700, 1500, 100, 0)])
+@pytest.mark.parametrize("distinct", [9, 50, 200, 900])
+def test_topk_of_rows_whose_scores_repeat(B, L, K, W, k, distinct):
+    """Few different keys: lists that are sorted as they are (up to a power of two above k), lists that are selected from
+    first, first bins with more than 512 equal scores, lists that overflow, segments that are still walked."""
+    w = small("repeat", n_q_heads=8, n_kv_heads=8, batch=B, seq_len=L, lengths=tuple([L] * (B - 1) + [L - 57]), budget=K, window=W,
+              topk_per_head=k)
+    inp = wl.make_inputs(w, DEV)
+    lay = inp.layers[0]
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(distinct)
+    lay.k.copy_(lay.k[:, :, torch.randint(distinct, (L,), generator=gen, device=DEV)].clone())
+    r = StepRunner(inp)
+    r.select(0)
+    check_select(inp, r, 0, seqs=[0, B - 1], check_scores=False)
+
+
 def test_topk_of_scores_that_are_not_finite():
     """Infinite scores are ranked like any other (largest first, ties to the lower position)."""
     for L in (3000, 12000, 40000):
