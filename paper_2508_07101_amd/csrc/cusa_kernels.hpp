@@ -20,6 +20,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "attn_plan.hpp"
+
 namespace cusa {
 
 constexpr int D = 128;        // head_dim
@@ -1935,12 +1937,7 @@ __device__ __forceinline__ float row_sum16(float v) {
     return v;
 }
 
-constexpr int ATTN_THREADS = 256;
-constexpr int ATTN_WAVES = 4;
-// Longest run of tokens a workgroup of the scoring variant may own: its scores wait in LDS (32 KB)
-// until the run is done.
-constexpr int ATTN_SCORE_CHUNK_CAP = 2048;
-constexpr int ATTN_SCORE_CHUNK_CAP_G8 = 1024;
+constexpr int ATTN_THREADS = 64 * ATTN_WAVES;
 
 // Workgroup `split` of a (sequence, KV head) owns tokens [split*chunk, split*chunk + chunk) of
 // the token list; a list of n tokens keeps ceil(n / chunk) workgroups busy (at least one) and

@@ -1,0 +1,58 @@
+"""The launch plan of the attention passes (csrc/attn_plan.hpp), compiled for the host and looked at without a GPU."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2508_07101_amd import build as lib_build
+
+CXX = shutil.which("g++") or shutil.which("c++")
+pytestmark = pytest.mark.skipif(CXX is None, reason="no host compiler")
+
+
+def run_checks(tmp_path, body):
+    """Compiles `body` (uses plan(n, pairs, g, kind, paged); FAIL(...) prints a line) and returns what it printed."""
+    src = tmp_path / "check.cpp"
+    src.write_text(r'''
+#include <cstdio>
+#include "attn_plan.hpp"
+using namespace cusa;
+static int fails = 0;
+#define FAIL(...) do { if (++fails <= 20) { std::printf(__VA_ARGS__); std::printf("\n"); } } while (0)
+static AttnPlan plan(int n, int pairs, int g, AttnKind kind, bool paged) { return plan_attn(n, pairs, g, kind, paged); }
+static const AttnKind KINDS[] = {ATTN_FULL, ATTN_SPARSE, ATTN_SCORE};
+static int cap_of(int g) { return g >= 8 ? ATTN_SCORE_CHUNK_CAP_G8 : ATTN_SCORE_CHUNK_CAP; }
+static int step(int n) { return n < 3000 ? 1 + n / 100 : 1 + n / 37; }     // lengths to look at, odd ones among them
+int main() {
+''' + body + '\n    return 0;\n}\n')
+    exe = tmp_path / "check"
+    subprocess.check_call([CXX, "-std=c++17", "-O1", "-Wall", "-Werror", "-I", lib_build.CSRC, "-o", str(exe), str(src)])
+    return subprocess.run([str(exe)], capture_output=True, text=True, check=True).stdout
+
+
+def test_splits_cover_the_list_and_stay_within_what_the_workspace_and_callers_are_told(tmp_path):
+    """Every plan covers its list with whole tiles; its splits fit a workspace laid out for any longer bound and any
+    smaller number of pairs (the per-head kernels count heads), and the static scratch's promise."""
+    out = run_checks(tmp_path, r'''
+    for (int pairs = 1; pairs <= 1100; pairs += pairs < 80 ? 1 : 7)
+        for (int n = 1; n <= 140000; n += step(n))
+            for (int g : {1, 8})
+                for (AttnKind kind : KINDS)
+                    for (bool paged : {false, true}) {
+                        const AttnPlan p = plan(n, pairs, g, kind, paged);
+                        const int tile = p.ti * 4 * ATTN_WAVES;
+                        if (p.chunk % tile || (int64_t)p.chunk * p.n_splits < n || (p.n_splits > 1 && (int64_t)p.chunk * (p.n_splits - 1) >= n))
+                            FAIL("%d pairs of %d: %d pieces of %d", pairs, n, p.n_splits, p.chunk);
+                        if (kind == ATTN_SCORE && p.chunk > cap_of(g) && p.n_splits * 2 <= MAX_SPLITS) FAIL("scores of %d tokens at a time", p.chunk);
+                        for (int fewer : {pairs, (pairs + 1) / 2, (pairs + 7) / 8})
+                            if (p.n_splits > max_splits_bound(n, fewer)) FAIL("%d pairs of %d: %d splits, bound %d", pairs, n, p.n_splits, max_splits_bound(n, fewer));
+                        if (kind == ATTN_SPARSE && p.n_splits > noalloc_splits(n, pairs)) FAIL("%d pairs of %d: %d splits, told %d", pairs, n, p.n_splits, noalloc_splits(n, pairs));
+                    }
+    for (int pairs = 1; pairs <= 1100; ++pairs)
+        for (int n = 1, last = 0; n <= 1300000; n += step(n)) {
+            if (max_splits_bound(n, pairs) < last) FAIL("the bound shrinks at %d pairs of %d", pairs, n);
+            last = max_splits_bound(n, pairs);
+        }
+''')
+    assert out == "", out
