@@ -13,7 +13,8 @@ constexpr int ATTN_SCORE_CHUNK_CAP = 2048;
 constexpr int ATTN_SCORE_CHUNK_CAP_G8 = 1024;
 
 constexpr int MAX_SPLITS = 256;
-constexpr int TARGET_WGS = 512;     // two resident workgroups per CU
+constexpr int CUS = 256;
+constexpr int TARGET_WGS = 2 * CUS; // two resident workgroups per CU
 constexpr int SINGLE_WGS = 192;     // (sequence, KV head) pairs from which one workgroup each is enough;
 constexpr int SINGLE_WGS_PAGED = 256;   // the block table's extra round trip per tile wants more of them
 constexpr int CHUNK_CAP = 2048;
@@ -28,6 +29,17 @@ struct AttnPlan {
     int chunk;     // tokens per workgroup, a multiple of the workgroup tile
     int n_splits;  // grid.x = ceil(n_max / chunk)
 };
+
+// Share of the resident slots that n workgroups keep busy over their rounds; a last round of at most one workgroup per CU
+// takes about 0.6 of a round.
+inline float round_share(int n) {
+    const int last = n % TARGET_WGS;
+    const float rounds = (float)(n / TARGET_WGS) + (last == 0 ? 0.0f : last <= TARGET_WGS / 2 ? 0.6f : 1.0f);
+    return (float)n / (TARGET_WGS * rounds);
+}
+
+enum AttnKind { ATTN_FULL, ATTN_SPARSE, ATTN_SCORE };
+inline int noalloc_splits(int n_max, int BG);
 
 // Workgroup granularity for n_max tokens per (sequence, KV head).
 // As many even pieces as keep all workgroups resident at once (TARGET_WGS / BG, rounded down: rounded up, the last piece
@@ -44,18 +56,14 @@ struct AttnPlan {
 // ragged lengths above all -- hold up less (128 pairs of 601 to 16383 tokens: pieces of 2048 106.3 us, of 1280 96.7; 376 of 2597 to
 // 5195: 148.2 and 142.9; but 176 of 27576: 405.6 and 421.6).
 // The scoring variant keeps its scores in LDS, hence its own caps, and writes them in bursts, which are
-// better longer (pieces of 2048 against 1024 at 64 pairs of 16384: 121.3 and 123.7 us).  Sparse attention is never cut
-// into more pieces than noalloc_splits says.
+// better longer (pieces of 2048 against 1024 at 64 pairs of 16384: 121.3 and 123.7 us).
+// Sparse attention takes one piece of up to SPARSE_CAP tokens (128 sequences of 8 KV heads, lists of 2560: 201 us, cut at 2048 249), but two where
+// a few pairs are left over after every CU has had one, two, ... of the others and those long pieces would run alone (264 pairs of 4096: 118 us,
+// in two pieces 105; 520: 198 and 184; 520 paged: 215 and 192; 384, half a round left over: 128 and 126; from three rounds
+// on it no longer pays: 776 of 2560 172 and 172, of 4096 271 and 268).  It is never cut into more pieces than
+// noalloc_splits says.
 // Workgroups whose run is 512 tokens or longer load 8 rows per lane and iteration, which keeps more bytes in flight
 // (304 pairs of 512, paged: 23.9 -> 20.0 us); shorter runs are faster with 4.
-// Share of the resident slots that n workgroups keep busy over their rounds; a last round of at most one workgroup per CU
-// takes about 0.6 of a round.
-inline float round_share(int n) {
-    const int last = n % TARGET_WGS;
-    const float rounds = (float)(n / TARGET_WGS) + (last == 0 ? 0.0f : last <= TARGET_WGS / 2 ? 0.6f : 1.0f);
-    return (float)n / (TARGET_WGS * rounds);
-}
-enum AttnKind { ATTN_FULL, ATTN_SPARSE, ATTN_SCORE };
 inline AttnPlan plan_attn(int n_max, int BG, int g, AttnKind kind, bool paged) {
     AttnPlan pl;
     const bool wide = kind == ATTN_SCORE;
@@ -65,6 +73,8 @@ inline AttnPlan plan_attn(int n_max, int BG, int g, AttnKind kind, bool paged) {
         for (int more = pieces + 1; more * BG <= 2 * TARGET_WGS && n_max >= more * 512; ++more)
             if (round_share(more * BG) > round_share(pieces * BG) + 0.05f) pieces = more;
     }
+    if (kind == ATTN_SPARSE && pieces == 1 && BG > CUS && BG < 3 * CUS && BG % CUS > 0 && BG % CUS < CUS / 2 && n_max >= CHUNK_CAP)
+        pieces = std::min(2, noalloc_splits(n_max, BG));
     if (!wide && pieces > MERGE_BATCH && n_max <= MERGE_BATCH * 1536) pieces = MERGE_BATCH;
     int64_t chunk = ((int64_t)n_max + pieces - 1) / pieces;
     if (chunk > cap) {

@@ -21,9 +21,9 @@ using namespace cusa;
 static int fails = 0;
 #define FAIL(...) do { if (++fails <= 20) { std::printf(__VA_ARGS__); std::printf("\n"); } } while (0)
 static AttnPlan plan(int n, int pairs, int g, AttnKind kind, bool paged) { return plan_attn(n, pairs, g, kind, paged); }
-static const AttnKind KINDS[] = {ATTN_FULL, ATTN_SPARSE, ATTN_SCORE};
-static int cap_of(int g) { return g >= 8 ? ATTN_SCORE_CHUNK_CAP_G8 : ATTN_SCORE_CHUNK_CAP; }
-static int step(int n) { return n < 3000 ? 1 + n / 100 : 1 + n / 37; }     // lengths to look at, odd ones among them
+[[maybe_unused]] static const AttnKind KINDS[] = {ATTN_FULL, ATTN_SPARSE, ATTN_SCORE};
+[[maybe_unused]] static int cap_of(int g) { return g >= 8 ? ATTN_SCORE_CHUNK_CAP_G8 : ATTN_SCORE_CHUNK_CAP; }
+[[maybe_unused]] static int step(int n) { return n < 3000 ? 1 + n / 100 : 1 + n / 37; }     // lengths to look at, odd ones among them
 int main() {
 ''' + body + '\n    return 0;\n}\n')
     exe = tmp_path / "check"
@@ -54,5 +54,20 @@ def test_splits_cover_the_list_and_stay_within_what_the_workspace_and_callers_ar
             if (max_splits_bound(n, pairs) < last) FAIL("the bound shrinks at %d pairs of %d", pairs, n);
             last = max_splits_bound(n, pairs);
         }
+''')
+    assert out == "", out
+
+
+def test_sparse_lists_are_cut_where_a_few_pairs_are_left_over(tmp_path):
+    """Long single pieces of a few pairs would run alone after all the others (264 pairs of 4096: 118 us against 105)."""
+    out = run_checks(tmp_path, r'''
+    for (int pairs = 1; pairs <= 1100; ++pairs)
+        for (int n = 2048; n <= 4096; n += 61)
+            for (bool paged : {false, true}) {
+                const AttnPlan p = plan(n, pairs, 4, ATTN_SPARSE, paged);
+                const bool left_over = (pairs > 256 && pairs < 384) || (pairs > 512 && pairs < 640);
+                if (left_over && p.n_splits != std::min(2, noalloc_splits(n, pairs))) FAIL("%d pairs of %d: %d pieces", pairs, n, p.n_splits);
+                if (pairs >= 384 && pairs <= 512 && p.n_splits != 1) FAIL("%d pairs of %d: %d pieces", pairs, n, p.n_splits);
+            }
 ''')
     assert out == "", out
