@@ -19,7 +19,7 @@ constexpr int SINGLE_WGS = 192;     // (sequence, KV head) pairs from which one 
 constexpr int SINGLE_WGS_PAGED = 256;   // the block table's extra round trip per tile wants more of them
 constexpr int CHUNK_CAP = 2048;
 constexpr int SPARSE_CAP = 4096;    // a token set has the same length for nearly all sequences: longer single pieces stay in step
-constexpr int PIECE = 1280;         // tokens per workgroup where the chip is filled a few times only
+constexpr int PIECE = 1024;         // tokens per workgroup of a ragged batch that fills the chip once or twice
 constexpr int MERGE_BATCH = 32;     // splits that the merge of partials asks for at a time
 static_assert(ATTN_SCORE_CHUNK_CAP <= CHUNK_CAP && ATTN_SCORE_CHUNK_CAP_G8 <= CHUNK_CAP && ATTN_SCORE_CHUNK_CAP_G8 >= 1024 && PIECE >= 1024,
               "the split bound assumes it");
@@ -46,15 +46,18 @@ inline int noalloc_splits(int n_max, int BG);
 // is a stump and the workgroups no longer fit the chip in one go: 80 pairs of 4096 tokens 39.1 -> 33.9 us, 96 of 5000
 // 51.9 -> 44.2).  From SINGLE_WGS pairs on a piece per pair: what it loses in balance it gains in the merge
 // that falls away (224 pairs of 1024: two pieces 26.3, one 23.0 us; 472 of 832: 42 and 36).
-// Where that leaves many slots idle (192 pairs: two pieces, 384 workgroups), a pass over all tokens takes more pieces that
-// fill a round and a half (192 pairs of 3400: two pieces 63.6, three 64.7, four 59.0 us); with sparse attention's short
-// lists it does not pay.
-// Splits beyond MERGE_BATCH cost the merge a second round trip (8 pairs of 20000: 64 splits 19.1, 32 18.4 us), so few pairs are
-// cut into MERGE_BATCH pieces while these stay short of 1536 tokens.
-// Lists too long for one piece per workgroup (CHUNK_CAP) fill the chip more than once: pieces of CHUNK_CAP tokens, or
-// of about PIECE where these make fewer than four rounds of workgroups, so that the last ones to finish -- of
-// ragged lengths above all -- hold up less (128 pairs of 601 to 16383 tokens: pieces of 2048 106.3 us, of 1280 96.7; 376 of 2597 to
-// 5195: 148.2 and 142.9; but 176 of 27576: 405.6 and 421.6).
+// Where fewer pairs leave many slots idle (136 pairs: three pieces, 408 workgroups), a pass over all tokens takes more pieces that
+// fill a round and a half or two (144 pairs of 5000, paged: three pieces 0.93 of the time that pieces of 1 / 512 of all tokens take,
+// five 0.88; 192 paged pairs of 3400: two 0.99, three 1.02, four 0.93); with sparse attention's short lists it does not pay.
+// Splits beyond MERGE_BATCH cost the merge a second round trip, so few pairs are cut into MERGE_BATCH pieces while these stay
+// short of 1536 tokens (8 pairs, 64 splits and 32, us: of 16384 15.2 and 13.8, 20000 17.1 and 15.9, 32768 25.1 and 24.0, 49152 34.8 and 33.8).
+// Lists too long for one piece per workgroup (CHUNK_CAP) take even pieces of about 1 / 512 of all tokens, CHUNK_CAP at most.  A paged cache's sequences
+// are of all lengths as a rule, and many workgroups have nothing to do: where pieces of CHUNK_CAP would fill the chip once or
+// twice if all were of the full length, pieces of about PIECE hold up less at the end.  Mean over 4 draws of lengths and 12
+// sizes, against pieces of CHUNK_CAP: lengths L / 16, L / 4 or L / 2 to L 0.95 of the time (1280 tokens: 0.955, 1536: 0.98), all of length L
+// 1.01; between two and four rounds 0.99 and 1.02, where a draw differs by more than that.  (128 pairs of 601 to 16383 tokens:
+// 106.3 and 96.3 us.)  A contiguous cache holds sequences of one length as a rule: 224 pairs of 6000 tokens, pieces of 2048 107.3 us, of
+// 1280 114.6; 40 of 32768: 105.5 and 114.8.
 // The scoring variant keeps its scores in LDS, hence its own caps, and writes them in bursts, which are
 // better longer (pieces of 2048 against 1024 at 64 pairs of 16384: 121.3 and 123.7 us).
 // Sparse attention takes one piece of up to SPARSE_CAP tokens (128 sequences of 8 KV heads, lists of 2560: 201 us, cut at 2048 249), but two where
@@ -78,8 +81,10 @@ inline AttnPlan plan_attn(int n_max, int BG, int g, AttnKind kind, bool paged) {
     if (!wide && pieces > MERGE_BATCH && n_max <= MERGE_BATCH * 1536) pieces = MERGE_BATCH;
     int64_t chunk = ((int64_t)n_max + pieces - 1) / pieces;
     if (chunk > cap) {
-        const bool few = (int64_t)((n_max + CHUNK_CAP - 1) / CHUNK_CAP) * BG < 4 * TARGET_WGS;
-        const int piece = kind == ATTN_SCORE ? cap : kind == ATTN_FULL && few ? PIECE : CHUNK_CAP;
+        const int64_t wgs = (int64_t)((n_max + CHUNK_CAP - 1) / CHUNK_CAP) * BG;
+        const bool ragged = kind == ATTN_FULL && paged && wgs > TARGET_WGS && wgs <= 2 * TARGET_WGS;
+        const int even = std::min(CHUNK_CAP, (int)((((int64_t)n_max * BG + TARGET_WGS - 1) / TARGET_WGS + 127) / 128 * 128));
+        const int piece = kind == ATTN_SCORE ? cap : kind == ATTN_SPARSE ? CHUNK_CAP : ragged ? PIECE : even;
         pieces = (n_max + piece - 1) / piece;
         chunk = ((int64_t)n_max + pieces - 1) / pieces;
     }

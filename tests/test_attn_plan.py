@@ -71,3 +71,25 @@ def test_sparse_lists_are_cut_where_a_few_pairs_are_left_over(tmp_path):
             }
 ''')
     assert out == "", out
+
+
+def test_long_lists_take_long_pieces_unless_the_batch_is_paged_and_fills_the_chip_once_or_twice(tmp_path):
+    """Small pieces help ragged batches; sequences of one length lose up to 9 per cent by them."""
+    out = run_checks(tmp_path, r'''
+    for (int pairs = 1; pairs <= 1100; pairs += pairs < 300 ? 1 : 7)
+        for (int n = 2049; n <= 140000; n += step(n))
+            for (bool paged : {false, true}) {
+                const AttnPlan p = plan(n, pairs, 4, ATTN_FULL, paged);
+                const int pieces = pairs >= (paged ? 256 : 192) ? 1 : 512 / pairs;
+                if ((n + 2 * pieces) / (2 * pieces + 1) <= 2048) continue;            // one resident round, or two
+                const int64_t rounds_of_long_ones = (int64_t)((n + 2047) / 2048) * pairs;
+                const int want = paged && rounds_of_long_ones > 512 && rounds_of_long_ones <= 1024 ? (n + 1023) / 1024 : (n + 2047) / 2048;
+                if (p.n_splits > want && p.n_splits <= 128) FAIL("%d pairs of %d, paged %d: %d pieces, not %d", pairs, n, paged, p.n_splits, want);
+            }
+    if (plan(32768, 40, 4, ATTN_FULL, false).n_splits != 16) FAIL("40 pairs of 32768");
+    if (plan(6000, 224, 4, ATTN_FULL, false).n_splits != 3) FAIL("224 pairs of 6000");
+    if (plan(2500, 248, 4, ATTN_FULL, false).n_splits != 2) FAIL("248 pairs of 2500");
+    if (plan(3400, 192, 4, ATTN_FULL, false).n_splits != 3) FAIL("192 pairs of 3400");
+    if (plan(16383, 128, 4, ATTN_FULL, true).n_splits != 16) FAIL("128 paged pairs of 16383");
+''')
+    assert out == "", out
