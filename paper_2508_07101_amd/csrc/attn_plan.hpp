@@ -25,7 +25,7 @@ static_assert(ATTN_SCORE_CHUNK_CAP <= CHUNK_CAP && ATTN_SCORE_CHUNK_CAP_G8 <= CH
               "the split bound assumes it");
 
 struct AttnPlan {
-    int ti;        // row-load instructions per wave iteration (4 or 8; scoring variant 8 or 16)
+    int ti;        // row-load instructions per wave iteration (4 or 8; scoring variant 8 or 16, tiles of 128 or 256 tokens)
     int chunk;     // tokens per workgroup, a multiple of the workgroup tile
     int n_splits;  // grid.x = ceil(n_max / chunk)
 };
@@ -40,6 +40,10 @@ inline float round_share(int n) {
 
 enum AttnKind { ATTN_FULL, ATTN_SPARSE, ATTN_SCORE };
 inline int noalloc_splits(int n_max, int BG);
+
+// Whole tiles of the scoring variant.
+inline int64_t score_tiles(int64_t tokens) { return tokens < 512 ? (tokens + 127) / 128 * 128 : (tokens + 255) / 256 * 256; }
+constexpr int SCORE_START = 64;     // what a workgroup of it costs besides its tokens, in tokens
 
 // Workgroup granularity for n_max tokens per (sequence, KV head).
 // As many even pieces as keep all workgroups resident at once (TARGET_WGS / BG, rounded down: rounded up, the last piece
@@ -58,8 +62,14 @@ inline int noalloc_splits(int n_max, int BG);
 // 1.01; between two and four rounds 0.99 and 1.02, where a draw differs by more than that.  (128 pairs of 601 to 16383 tokens:
 // 106.3 and 96.3 us.)  A contiguous cache holds sequences of one length as a rule: 224 pairs of 6000 tokens, pieces of 2048 107.3 us, of
 // 1280 114.6; 40 of 32768: 105.5 and 114.8.
-// The scoring variant keeps its scores in LDS, hence its own caps, and writes them in bursts, which are
-// better longer (pieces of 2048 against 1024 at 64 pairs of 16384: 121.3 and 123.7 us).
+// The scoring variant keeps its scores in LDS, hence its own caps, writes them in bursts, which are
+// better longer (pieces of 2048 against 1024 at 64 pairs of 16384: 121.3 and 123.7 us), and its tiles are large (128 or 256
+// tokens): it takes 1 / 512 of all tokens, rounded up to whole tiles.  Even pieces as above, rounded to the nearest tile, were
+// 2 per cent slower over 177 selection layers of 8 to 512 pairs of 600 to 40000 tokens, and often by a last round with next
+// to nothing in it (40 pairs of 5000 29.3 us, so 22.9; 24 of 9000 30.7 and 23.6; 128 of 1700 30.5 and 23.9; 256 of 1300 37.7 and
+// 34.0).  Where the last of these pieces would open a second round of workgroups, somewhat longer ones that need one round are taken
+// instead (104 pairs of 5000: 58.8 -> 50.6 us; 160 of 4000 68.4 -> 62.9; 320 of 700 34.3 -> 26.4, which also saves the merge; not where
+// they would be half as long again: 192 of 2600 52.4 -> 55.0).
 // Sparse attention takes one piece of up to SPARSE_CAP tokens (128 sequences of 8 KV heads, lists of 2560: 201 us, cut at 2048 249), but two where
 // a few pairs are left over after every CU has had one, two, ... of the others and those long pieces would run alone (264 pairs of 4096: 118 us,
 // in two pieces 105; 520: 198 and 184; 520 paged: 215 and 192; 384, half a round left over: 128 and 126; from three rounds
@@ -69,29 +79,43 @@ inline int noalloc_splits(int n_max, int BG);
 // (304 pairs of 512, paged: 23.9 -> 20.0 us); shorter runs are faster with 4.
 inline AttnPlan plan_attn(int n_max, int BG, int g, AttnKind kind, bool paged) {
     AttnPlan pl;
-    const bool wide = kind == ATTN_SCORE;
-    const int cap = kind == ATTN_FULL ? CHUNK_CAP : kind == ATTN_SPARSE ? SPARSE_CAP : g >= 8 ? ATTN_SCORE_CHUNK_CAP_G8 : ATTN_SCORE_CHUNK_CAP;
-    int pieces = BG >= (paged ? SINGLE_WGS_PAGED : SINGLE_WGS) ? 1 : TARGET_WGS / BG;
-    if (kind != ATTN_SPARSE && pieces > 1) {
-        for (int more = pieces + 1; more * BG <= 2 * TARGET_WGS && n_max >= more * 512; ++more)
-            if (round_share(more * BG) > round_share(pieces * BG) + 0.05f) pieces = more;
-    }
-    if (kind == ATTN_SPARSE && pieces == 1 && BG > CUS && BG < 3 * CUS && BG % CUS > 0 && BG % CUS < CUS / 2 && n_max >= CHUNK_CAP)
-        pieces = std::min(2, noalloc_splits(n_max, BG));
-    if (!wide && pieces > MERGE_BATCH && n_max <= MERGE_BATCH * 1536) pieces = MERGE_BATCH;
-    int64_t chunk = ((int64_t)n_max + pieces - 1) / pieces;
-    if (chunk > cap) {
-        const int64_t wgs = (int64_t)((n_max + CHUNK_CAP - 1) / CHUNK_CAP) * BG;
-        const bool ragged = kind == ATTN_FULL && paged && wgs > TARGET_WGS && wgs <= 2 * TARGET_WGS;
-        const int even = std::min(CHUNK_CAP, (int)((((int64_t)n_max * BG + TARGET_WGS - 1) / TARGET_WGS + 127) / 128 * 128));
-        const int piece = kind == ATTN_SCORE ? cap : kind == ATTN_SPARSE ? CHUNK_CAP : ragged ? PIECE : even;
-        pieces = (n_max + piece - 1) / piece;
+    int64_t chunk = ((int64_t)n_max * BG + TARGET_WGS - 1) / TARGET_WGS;
+    if (kind == ATTN_SCORE) {
+        const int64_t cap = g >= 8 ? ATTN_SCORE_CHUNK_CAP_G8 : ATTN_SCORE_CHUNK_CAP;
+        chunk = std::min(chunk, cap);
+        pl.ti = chunk >= 512 ? 16 : 8;
+        chunk = score_tiles(chunk);
+        if ((n_max + chunk - 1) / chunk * BG > TARGET_WGS) {
+            int64_t longer = score_tiles(chunk + 1);
+            while (longer <= cap && (n_max + longer - 1) / longer * BG > TARGET_WGS) longer = score_tiles(longer + 1);
+            const int64_t tokens = std::min(longer, (int64_t)n_max);
+            if (longer <= cap && (tokens + SCORE_START) * 10 <= (chunk + SCORE_START) * (longer >= n_max ? 14 : 13)) {
+                chunk = longer;
+                pl.ti = chunk >= 512 ? 16 : 8;
+            }
+        }
+    } else {
+        const int even = (int)std::min((chunk + 127) / 128 * 128, (int64_t)CHUNK_CAP);
+        int pieces = BG >= (paged ? SINGLE_WGS_PAGED : SINGLE_WGS) ? 1 : TARGET_WGS / BG;
+        if (kind == ATTN_FULL && pieces > 1) {
+            for (int more = pieces + 1; more * BG <= 2 * TARGET_WGS && n_max >= more * 512; ++more)
+                if (round_share(more * BG) > round_share(pieces * BG) + 0.05f) pieces = more;
+        }
+        if (kind == ATTN_SPARSE && pieces == 1 && BG > CUS && BG < 3 * CUS && BG % CUS > 0 && BG % CUS < CUS / 2 && n_max >= CHUNK_CAP)
+            pieces = std::min(2, noalloc_splits(n_max, BG));
+        if (pieces > MERGE_BATCH && n_max <= MERGE_BATCH * 1536) pieces = MERGE_BATCH;
         chunk = ((int64_t)n_max + pieces - 1) / pieces;
+        if (chunk > (kind == ATTN_SPARSE ? SPARSE_CAP : CHUNK_CAP)) {
+            const int64_t wgs = (int64_t)((n_max + CHUNK_CAP - 1) / CHUNK_CAP) * BG;
+            const bool ragged = kind == ATTN_FULL && paged && wgs > TARGET_WGS && wgs <= 2 * TARGET_WGS;
+            const int piece = kind == ATTN_SPARSE ? CHUNK_CAP : ragged ? PIECE : even;
+            pieces = (n_max + piece - 1) / piece;
+            chunk = ((int64_t)n_max + pieces - 1) / pieces;
+        }
+        pl.ti = chunk >= 512 ? 8 : 4;
     }
-    pl.ti = wide ? (chunk >= 512 ? 16 : 8) : chunk >= 512 ? 8 : 4;
     const int wg_tile = pl.ti * 4 * ATTN_WAVES;
-    // whole tiles; the scoring variant's are large, so short runs go to the nearest (88 pairs of 743: 128 against 256 tokens)
-    chunk = wide && chunk < 512 && chunk > wg_tile ? (chunk + wg_tile / 2) / wg_tile * wg_tile : (chunk + wg_tile - 1) / wg_tile * wg_tile;
+    chunk = (chunk + wg_tile - 1) / wg_tile * wg_tile;
     if ((n_max + chunk - 1) / chunk > MAX_SPLITS) {
         chunk = ((int64_t)n_max + MAX_SPLITS - 1) / MAX_SPLITS;
         chunk = (chunk + wg_tile - 1) / wg_tile * wg_tile;
@@ -103,13 +127,12 @@ inline AttnPlan plan_attn(int n_max, int BG, int g, AttnKind kind, bool paged) {
 }
 
 // Upper bound of plan_attn(m, BG', ...).n_splits over every m <= n_max and BG' >= BG: a token list is cut into
-// TARGET_WGS / BG pieces (a scoring run rounded down to the nearest tile: at most half as many again), or up to twice as
-// many and one if they have 512 tokens, or into pieces of at least 1024 tokens.  Monotone in n_max, so a workspace sized for a capacity serves every shorter bound.
+// TARGET_WGS / BG pieces, rounded up or down, or up to twice as many and one if they have 512 tokens, or into pieces of at least 1024 tokens.
+// Monotone in n_max, so a workspace sized for a capacity serves every shorter bound.
 inline int max_splits_bound(int n_max, int BG) {
-    const int by_wgs = BG < TARGET_WGS ? TARGET_WGS / BG : 1;
+    const int by_wgs = (TARGET_WGS + BG - 1) / BG;
     const int by_piece = (n_max + 511) / 512 < 2 * by_wgs + 1 ? (n_max + 511) / 512 : std::max(2 * by_wgs + 1, (n_max + 1023) / 1024);
-    const int m = by_wgs + (by_wgs + 1) / 2 > by_piece ? by_wgs + (by_wgs + 1) / 2 : by_piece;
-    return m < MAX_SPLITS ? m : MAX_SPLITS;
+    return std::min(std::max(by_wgs, by_piece), MAX_SPLITS);
 }
 
 // Splits that decide whether cusa_sparse_attn_noalloc takes a problem (a statement to callers: it does not
