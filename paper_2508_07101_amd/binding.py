@@ -141,13 +141,24 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
-def _stream() -> int:
-    """The current device's current stream as a hipStream_t.  (Asked for as the raw handle: the Stream object that
-    torch.cuda.current_stream() builds around it costs 2.6 us of the 11.4 a call to sparse_attn took on the host, more
-    than the GPU needs for its kernels in the smallest cases.)"""
-    if not torch.cuda.is_initialized():
-        return torch.cuda.current_stream().cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+def stream_query(torch_module):
+    """A function that returns the current device's current stream as a hipStream_t.  (Asked for as the raw handle: the Stream
+    object that torch.cuda.current_stream() builds around it costs 2.6 us of the 11.4 a call to sparse_attn took on the host,
+    more than the GPU needs for its kernels in the smallest cases.  The two names are not part of torch's public interface;
+    a torch without them is asked the public way.)"""
+    cuda = torch_module.cuda
+    raw = getattr(torch_module._C, "_cuda_getCurrentRawStream", None)
+    device = getattr(torch_module._C, "_cuda_getDevice", None)
+
+    def public() -> int:
+        return cuda.current_stream().cuda_stream
+
+    if raw is None or device is None:
+        return public
+    return lambda: raw(device()) if cuda.is_initialized() else public()
+
+
+_stream = stream_query(torch)
 
 
 def make_params(batch, n_q_heads, n_kv_heads, budget, window, topk_per_head=0, head_dim=128,
