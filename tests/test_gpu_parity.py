@@ -521,12 +521,12 @@ def test_union_of_agreeing_and_disagreeing_heads(heads, L, K, W, k):
 
 @pytest.mark.parametrize("B,L,K,W,k", [(2, 700, 512, 128, 500), (2, 4200, 1024, 0, 0), (2, 9001, 2048, 512, 2048),
                                         (2, 20011, 3072, 0, 3072), (1, 9000, 8192, 0, 0), (2, 41000, 4096, 1024, 0),
-                                        (1, 140001, 2048, 512, 0), (48, 9700, 3000, 100, 0)])
+                                        (1, 140001, 2048, 512, 0), (48, 9700, 3000, 100, 0), (1, 70001, 8192, 1024, 0)])
 @pytest.mark.parametrize("where", ["one run", "every 16th run of 64", "one position in four"])
 def test_topk_rows_whose_best_scores_cluster(B, L, K, W, k, where):
-    """The top-k's threshold comes from a sample of the row, and a wave's list holds its share of the best only: rows
-    whose best candidates stand together, or where a sample sees all of them or none, lists that overflow, thresholds that
-    let too few through.  All forms: keys in registers, streamed, slices; k up to 8192."""
+    """The top-k's threshold comes from a sample of the row: rows whose best candidates stand together (in one slice, in one
+    wave's part), or where a sample sees all of them or none, and thresholds that let too few through.  All forms: keys in
+    registers, streamed, slices; k up to 8192, in slices up to 7168."""
     w = small("cluster", n_q_heads=8, n_kv_heads=8, batch=B, seq_len=L, lengths=tuple([L] * (B - 1) + [L - 57]), budget=K, window=W,
               topk_per_head=k)
     inp = wl.make_inputs(w, DEV)
@@ -564,6 +564,68 @@ def test_topk_of_rows_whose_scores_repeat(B, L, K, W, k, distinct):
     r = StepRunner(inp)
     r.select(0)
     check_select(inp, r, 0, seqs=[0, B - 1], check_scores=False)
+
+
+@pytest.mark.parametrize("B,L,K,W", [(1, 70001, 8192, 1024), (2, 40000, 5200, 100)])
+def test_widest_topk_of_long_rows_in_slices(B, L, K, W):
+    """k above 4096 on sliced rows: the slices' lists of 14336 entries, 14 composites per thread in the ranking."""
+    w = small("wide", n_q_heads=8, n_kv_heads=8, batch=B, seq_len=L, lengths=tuple([L] * (B - 1) + [L - 57]), budget=K, window=W)
+    inp = wl.make_inputs(w, DEV)
+    r = StepRunner(inp)
+    r.select(0)
+    check_select(inp, r, 0)
+
+
+LENGTHS_OF_ALL_FORMS = [(1, 3000), (2, 6000), (1, 12000), (1, 30000), (1, 40000), (36, 9700)]   # registers, slices, streamed
+
+
+@pytest.mark.parametrize("B,L", LENGTHS_OF_ALL_FORMS)
+@pytest.mark.parametrize("left", ["many", "fewer than k"])
+def test_topk_beside_scores_of_minus_infinity(B, L, left):
+    """A score of -infinity is a candidate like any other, but no threshold lets it through: outside the k best it must not
+    disturb the ranking, and where fewer than k finite scores are left the positions that have it follow in order."""
+    K, W = 700, 150
+    w = small("minusinf", n_q_heads=8, n_kv_heads=8, batch=B, seq_len=L, lengths=tuple([L] * (B - 1) + [L - 57]), budget=K, window=W)
+    inp = wl.make_inputs(w, DEV)
+    lay = inp.layers[0]
+    big = torch.finfo(torch.bfloat16).max
+    lay.q[..., 1] = big                                  # one column decides which scores are -infinity
+    lay.k[..., 1] = 0
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(L)
+    gone = torch.rand(L, generator=gen, device=DEV) < 0.1
+    if left == "fewer than k":
+        gone[:] = True
+        gone[torch.randperm(L - W - 60, generator=gen, device=DEV)[: K - W - 40]] = False
+    lay.k[:, :, gone, 1] = -big
+    r = StepRunner(inp)
+    r.select(0)
+    check_select(inp, r, 0, seqs=[0, B - 1])
+
+
+@pytest.mark.parametrize("B,L", LENGTHS_OF_ALL_FORMS)
+@pytest.mark.parametrize("n_nan", [1, 40, 2000])
+def test_topk_beside_nan_scores_follows_the_keys(B, L, n_nan):
+    """NaN scores have no place among the others but the order of the keys they map to; whatever that is, a row's ranking is that
+    order (ties to the lower position), as with every score."""
+    K, W = 700, 150
+    w = small("nan", n_q_heads=8, n_kv_heads=8, batch=B, seq_len=L, budget=K, window=W)
+    inp = wl.make_inputs(w, DEV)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(n_nan)
+    lay = inp.layers[0]
+    lay.k[:, :, torch.randperm(L - W, generator=gen, device=DEV)[:n_nan], 5] = float("nan")
+    r = StepRunner(inp)
+    r.select(0)
+    torch.cuda.synchronize()
+    for b in {0, B - 1}:
+        bits = r.scores()[b, :, : L - W].cpu().numpy().view(np.uint32)
+        assert np.isnan(bits.view(np.float32)).sum() == 8 * n_nan
+        bits = np.where(bits == 0x80000000, 0, bits).astype(np.uint32)
+        keys = np.where(bits & 0x80000000, ~bits, bits | 0x80000000).astype(np.int64)
+        want = np.argsort(-keys, axis=1, kind="stable")[:, : K - W]
+        got = r.rho_head()[b].cpu().numpy().T
+        assert (got == want).all(), f"seq {b}: {(got != want).sum()} entries"
 
 
 def test_topk_of_scores_that_are_not_finite():
