@@ -19,7 +19,7 @@ constexpr int SINGLE_WGS = 192;     // (sequence, KV head) pairs from which one 
 constexpr int SINGLE_WGS_PAGED = 256;   // the block table's extra round trip per tile wants more of them
 constexpr int CHUNK_CAP = 2048;
 constexpr int SPARSE_CAP = 4096;    // a token set has the same length for nearly all sequences: longer single pieces stay in step
-constexpr int PIECE = 1024;         // tokens per workgroup of a ragged batch that fills the chip once or twice
+constexpr int PIECE = 1280;         // tokens per workgroup of a ragged batch that fills the chip once or twice
 constexpr int MERGE_BATCH = 32;     // splits that the merge of partials asks for at a time
 static_assert(ATTN_SCORE_CHUNK_CAP <= CHUNK_CAP && ATTN_SCORE_CHUNK_CAP_G8 <= CHUNK_CAP && ATTN_SCORE_CHUNK_CAP_G8 >= 1024 && PIECE >= 1024,
               "the split bound assumes it");
@@ -58,9 +58,9 @@ constexpr int SCORE_START = 64;     // what a workgroup of it costs besides its 
 // Lists too long for one piece per workgroup (CHUNK_CAP) take even pieces of about 1 / 512 of all tokens, CHUNK_CAP at most.  A paged cache's sequences
 // are of all lengths as a rule, and many workgroups have nothing to do: where pieces of CHUNK_CAP would fill the chip once or
 // twice if all were of the full length, pieces of about PIECE hold up less at the end.  Mean over 4 draws of lengths and 12
-// sizes, against pieces of CHUNK_CAP: lengths L / 16, L / 4 or L / 2 to L 0.95 of the time (1280 tokens: 0.955, 1536: 0.98), all of length L
-// 1.01; between two and four rounds 0.99 and 1.02, where a draw differs by more than that.  (128 pairs of 601 to 16383 tokens:
-// 106.3 and 96.3 us.)  A contiguous cache holds sequences of one length as a rule: 224 pairs of 6000 tokens, pieces of 2048 107.3 us, of
+// sizes, against pieces of CHUNK_CAP: lengths L / 16, L / 4 or L / 2 to L 0.955 of the time (1024 tokens: 0.95, 1536: 0.98), all of length L
+// 1.02; between two and four rounds 0.99 and 1.01, where a draw differs by more than that.  (128 pairs of 601 to 16383 tokens:
+// 106.3 us, 97.3, in pieces of 1024 99.6.)  A contiguous cache holds sequences of one length as a rule: 224 pairs of 6000 tokens, pieces of 2048 107.3 us, of
 // 1280 114.6; 40 of 32768: 105.5 and 114.8.
 // The scoring variant keeps its scores in LDS, hence its own caps, writes them in bursts, which are
 // better longer (pieces of 2048 against 1024 at 64 pairs of 16384: 121.3 and 123.7 us), and its tiles are large (128 or 256

@@ -83,14 +83,14 @@ def test_long_lists_take_long_pieces_unless_the_batch_is_paged_and_fills_the_chi
                 const int pieces = pairs >= (paged ? 256 : 192) ? 1 : 512 / pairs;
                 if ((n + 2 * pieces) / (2 * pieces + 1) <= 2048) continue;            // one resident round, or two
                 const int64_t rounds_of_long_ones = (int64_t)((n + 2047) / 2048) * pairs;
-                const int want = paged && rounds_of_long_ones > 512 && rounds_of_long_ones <= 1024 ? (n + 1023) / 1024 : (n + 2047) / 2048;
+                const int want = paged && rounds_of_long_ones > 512 && rounds_of_long_ones <= 1024 ? (n + 1279) / 1280 : (n + 2047) / 2048;
                 if (p.n_splits > want && p.n_splits <= 128) FAIL("%d pairs of %d, paged %d: %d pieces, not %d", pairs, n, paged, p.n_splits, want);
             }
     if (plan(32768, 40, 4, ATTN_FULL, false).n_splits != 16) FAIL("40 pairs of 32768");
     if (plan(6000, 224, 4, ATTN_FULL, false).n_splits != 3) FAIL("224 pairs of 6000");
     if (plan(2500, 248, 4, ATTN_FULL, false).n_splits != 2) FAIL("248 pairs of 2500");
     if (plan(3400, 192, 4, ATTN_FULL, false).n_splits != 3) FAIL("192 pairs of 3400");
-    if (plan(16383, 128, 4, ATTN_FULL, true).n_splits != 16) FAIL("128 paged pairs of 16383");
+    if (plan(16383, 128, 4, ATTN_FULL, true).n_splits != 13) FAIL("128 paged pairs of 16383");
 ''')
     assert out == "", out
 
