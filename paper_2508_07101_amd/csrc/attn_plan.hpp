@@ -46,35 +46,38 @@ inline int64_t score_tiles(int64_t tokens) { return tokens < 512 ? (tokens + 127
 constexpr int SCORE_START = 64;     // what a workgroup of it costs besides its tokens, in tokens
 
 // Workgroup granularity for n_max tokens per (sequence, KV head).
-// As many even pieces as keep all workgroups resident at once (TARGET_WGS / BG, rounded down: rounded up, the last piece
-// is a stump and the workgroups no longer fit the chip in one go: 80 pairs of 4096 tokens 39.1 -> 33.9 us, 96 of 5000
-// 51.9 -> 44.2).  From SINGLE_WGS pairs on a piece per pair: what it loses in balance it gains in the merge
-// that falls away (224 pairs of 1024: two pieces 26.3, one 23.0 us; 472 of 832: 42 and 36).
-// Where fewer pairs leave many slots idle (136 pairs: three pieces, 408 workgroups), a pass over all tokens takes more pieces that
-// fill a round and a half or two (144 pairs of 5000, paged: three pieces 0.93 of the time that pieces of 1 / 512 of all tokens take,
-// five 0.88; 192 paged pairs of 3400: two 0.99, three 1.02, four 0.93); with sparse attention's short lists it does not pay.
-// Splits beyond MERGE_BATCH cost the merge a second round trip, so few pairs are cut into MERGE_BATCH pieces while these stay
-// short of 1536 tokens (8 pairs, 64 splits and 32, us: of 16384 15.2 and 13.8, 20000 17.1 and 15.9, 32768 25.1 and 24.0, 49152 34.8 and 33.8).
-// Lists too long for one piece per workgroup (CHUNK_CAP) take even pieces of about 1 / 512 of all tokens, CHUNK_CAP at most.  A paged cache's sequences
-// are of all lengths as a rule, and many workgroups have nothing to do: where pieces of CHUNK_CAP would fill the chip once or
-// twice if all were of the full length, pieces of about PIECE hold up less at the end.  Mean over 4 draws of lengths and 12
-// sizes, against pieces of CHUNK_CAP: lengths L / 16, L / 4 or L / 2 to L 0.955 of the time (1024 tokens: 0.95, 1536: 0.98), all of length L
-// 1.02; between two and four rounds 0.99 and 1.01, where a draw differs by more than that.  (128 pairs of 601 to 16383 tokens:
-// 106.3 us, 97.3, in pieces of 1024 99.6.)  A contiguous cache holds sequences of one length as a rule: 224 pairs of 6000 tokens, pieces of 2048 107.3 us, of
+// As many even pieces as keep all workgroups resident at once (TARGET_WGS / BG, rounded down: rounded up, the last
+// piece is a stump and the workgroups no longer fit the chip in one go: 80 pairs of 4096 tokens 39.1 -> 33.9 us, 96 of
+// 5000 51.9 -> 44.2).  From SINGLE_WGS pairs on a piece per pair: what it loses in balance it gains in the merge that
+// falls away (224 pairs of 1024: two pieces 26.3, one 23.0 us; 472 of 832: 42 and 36).
+// Where fewer pairs leave many slots idle (136 pairs: three pieces, 408 workgroups), a pass over all tokens takes more
+// pieces that fill a round and a half or two (144 pairs of 5000, paged: three pieces 0.93 of the time that pieces of
+// 1/512 of all tokens take, five 0.88; 192 paged pairs of 3400: two 0.99, three 1.02, four 0.93); with sparse
+// attention's short lists it does not pay.
+// Splits beyond MERGE_BATCH cost the merge a second round trip, so few pairs are cut into MERGE_BATCH pieces while
+// these stay short of 1536 tokens (8 pairs, 64 splits and 32, us: of 16384 15.2 and 13.8, 20000 17.1 and 15.9, 32768
+// 25.1 and 24.0, 49152 34.8 and 33.8).
+// Lists too long for one piece per workgroup (CHUNK_CAP) take even pieces of about 1/512 of all tokens, CHUNK_CAP at
+// most.  A paged cache's sequences are of all lengths as a rule, and many workgroups have nothing to do: where pieces
+// of CHUNK_CAP would fill the chip once or twice if all were of the full length, pieces of about PIECE hold up less at
+// the end.  Mean over 4 draws of lengths and 12 sizes, against pieces of CHUNK_CAP: lengths L / 16, L / 4 or L / 2 to L
+// 0.955 of the time (1024 tokens: 0.95, 1536: 0.98), all of length L 1.02; between two and four rounds 0.99 and 1.01,
+// where a draw differs by more than that.  (128 pairs of 601 to 16383 tokens: 106.3 us, 97.3, in pieces of 1024 99.6.)
+// A contiguous cache holds sequences of one length as a rule: 224 pairs of 6000 tokens, pieces of 2048 107.3 us, of
 // 1280 114.6; 40 of 32768: 105.5 and 114.8.
-// The scoring variant keeps its scores in LDS, hence its own caps, writes them in bursts, which are
-// better longer (pieces of 2048 against 1024 at 64 pairs of 16384: 121.3 and 123.7 us), and its tiles are large (128 or 256
-// tokens): it takes 1 / 512 of all tokens, rounded up to whole tiles.  Even pieces as above, rounded to the nearest tile, were
-// 2 per cent slower over 177 selection layers of 8 to 512 pairs of 600 to 40000 tokens, and often by a last round with next
-// to nothing in it (40 pairs of 5000 29.3 us, so 22.9; 24 of 9000 30.7 and 23.6; 128 of 1700 30.5 and 23.9; 256 of 1300 37.7 and
-// 34.0).  Where the last of these pieces would open a second round of workgroups, somewhat longer ones that need one round are taken
-// instead (104 pairs of 5000: 58.8 -> 50.6 us; 160 of 4000 68.4 -> 62.9; 320 of 700 34.3 -> 26.4, which also saves the merge; not where
-// they would be half as long again: 192 of 2600 52.4 -> 55.0).
-// Sparse attention takes one piece of up to SPARSE_CAP tokens (128 sequences of 8 KV heads, lists of 2560: 201 us, cut at 2048 249), but two where
-// a few pairs are left over after every CU has had one, two, ... of the others and those long pieces would run alone (264 pairs of 4096: 118 us,
-// in two pieces 105; 520: 198 and 184; 520 paged: 215 and 192; 384, half a round left over: 128 and 126; from three rounds
-// on it no longer pays: 776 of 2560 172 and 172, of 4096 271 and 268).  It is never cut into more pieces than
-// noalloc_splits says.
+// The scoring variant keeps its scores in LDS, hence its own caps, writes them in bursts, which are better longer
+// (pieces of 2048 against 1024 at 64 pairs of 16384: 121.3 and 123.7 us), and its tiles are large (128 or 256 tokens):
+// it takes 1/512 of all tokens, rounded up to whole tiles.  Even pieces as above, rounded to the nearest tile, were 2
+// per cent slower over 177 selection layers of 8 to 512 pairs of 600 to 40000 tokens, and often by a last round with
+// next to nothing in it (40 pairs of 5000 29.3 us, so 22.9; 24 of 9000 30.7 and 23.6; 128 of 1700 30.5 and 23.9; 256 of
+// 1300 37.7 and 34.0).  Where the last of these pieces would open a second round of workgroups, somewhat longer ones
+// that need one round are taken instead (104 pairs of 5000: 58.8 -> 50.6 us; 160 of 4000 68.4 -> 62.9; 320 of 700 34.3
+// -> 26.4, which also saves the merge; not where they would be half as long again: 192 of 2600 52.4 -> 55.0).
+// Sparse attention takes one piece of up to SPARSE_CAP tokens (128 sequences of 8 KV heads, lists of 2560: 201 us, cut
+// at 2048 249), but two where a few pairs are left over after every CU has had one, two, ... of the others and those
+// long pieces would run alone (264 pairs of 4096: 118 us, in two pieces 105; 520: 198 and 184; 520 paged: 215 and 192;
+// 384, half a round left over: 128 and 126; from three rounds on it no longer pays: 776 of 2560 172 and 172, of 4096
+// 271 and 268).  It is never cut into more pieces than noalloc_splits says.
 // Workgroups whose run is 512 tokens or longer load 8 rows per lane and iteration, which keeps more bytes in flight
 // (304 pairs of 512, paged: 23.9 -> 20.0 us); shorter runs are faster with 4.
 inline AttnPlan plan_attn(int n_max, int BG, int g, AttnKind kind, bool paged) {
@@ -127,7 +130,8 @@ inline AttnPlan plan_attn(int n_max, int BG, int g, AttnKind kind, bool paged) {
 }
 
 // Upper bound of plan_attn(m, BG', ...).n_splits over every m <= n_max and BG' >= BG: a token list is cut into
-// TARGET_WGS / BG pieces, rounded up or down, or up to twice as many and one if they have 512 tokens, or into pieces of at least 1024 tokens.
+// TARGET_WGS / BG pieces, rounded up or down, or up to twice as many and one if they have 512 tokens, or into pieces of
+// at least 1024 tokens.
 // Monotone in n_max, so a workspace sized for a capacity serves every shorter bound.
 inline int max_splits_bound(int n_max, int BG) {
     const int by_wgs = (TARGET_WGS + BG - 1) / BG;

@@ -168,9 +168,9 @@ int plan_topk_slices(int64_t rows, int lc_max, int k) {
     return s < 1 ? 1 : (int)s;
 }
 
+int topk_mtop(int k) { return k <= 1024 ? 1 : k <= 2048 ? 2 : k <= 4096 ? 4 : 8; }   // composites sorted per thread of 1024
 // The same for rows of scores, whose slices are filtered by a threshold of the row (slice_filter_kernel): pieces of
 // about 16384 candidates, no more workgroups than two per CU.
-int topk_mtop(int k) { return k <= 1024 ? 1 : k <= 2048 ? 2 : k <= 4096 ? 4 : 8; }   // composites sorted per thread of 1024
 int plan_filter_slices(int64_t rows, int lc_max) {
     if (lc_max <= 32768) return 1;
     int64_t s = ((int64_t)lc_max + 16383) / 16384;

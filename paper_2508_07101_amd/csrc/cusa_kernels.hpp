@@ -207,9 +207,11 @@ __device__ __forceinline__ float key_score(uint32_t key) {
 //
 // What bounds it: one CU per row, its sixteen waves' instructions (each costs the CU sixteen cycles), the barriers
 // between them and, first, the row's way from memory (3 us of the 14 at 32 K candidates).  Measured before (selection
-// with digit histograms, then ranking) -> after, us: 1 x 32 rows of 3840, k 1024: 9.7 -> 8.5; 32 rows of 32256, k 1536: 20.0
-// -> 14.0; 256 rows of 15360, k 3072: 18.1 -> 15.4; 64 rows of 130048, k 3072, in slices: 50.6 -> 32.0; 576 rows of 11552,
-// k 2304: 57.7 -> 32.9; 1408 rows of 22798, k 3072: 166 -> 89.5.
+// with digit histograms, then ranking) -> after, us, rows still in the last-level cache (in a step they come from memory: 13.6,
+// 15.5 and 33 us for the second, third and fourth size): 32 rows of 3840, k 1024: 7.9 -> 7.7; 32 rows of 32256, k 1536:
+// 16.9 -> 11.9; 256 rows of 15360, k 3072: 16.7 -> 13.5; 64 rows of 130048, k 3072, in slices: 36.5 -> 24.1; 576 rows of
+// 11552, k 2304: 56.8 -> 25.3; 1408 rows of 22798, k 3072: 145 -> 62.1.  Scores that are correlated over 64 positions each
+// take the same times within 1 per cent.
 
 struct SelectState {
     uint32_t prefix;     // digits fixed so far
@@ -608,8 +610,9 @@ __device__ __forceinline__ void mask_scores(f32x4 (&x)[N / 4], Pos pos, int lo, 
 }
 // Hands those of a batch of N scores per thread that are not below theta (a NaN is kept, too) to put(slot, score,
 // position), with the slots of a list that the whole workgroup shares: one LDS atomic per wave and batch reserves them.
-// The counter counts all; a batch that does not fit any more is left out, and what then is in the list is of no use.  (A share of the list per wave would need no atomic, but scores
-// are correlated along the sequence: the best of them are in a few waves' parts of the row.)
+// The counter counts all; a batch that does not fit any more is left out, and what then is in the list is of no use.  (A
+// share of the list per wave would need no atomic, but scores are correlated along the sequence: the best of them are in a
+// few waves' parts of the row.)
 template <int N, typename Val, typename Pos, typename Put>
 __device__ __forceinline__ void list_push(Val val, Pos pos, float theta, int* counter, int cap, Put put) {
     uint64_t mask[N];
