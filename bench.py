@@ -44,7 +44,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 QUOTED = ["c1", "c2", "c3", "c4", "c5"]
-BANDWIDTH_KERNELS = ("attn_kernel<sparse>", "attn_kernel<full+score>", "attn_kernel<full>", "attn_kernel<scores only>")
+BANDWIDTH_KERNELS = ("attn_kernel<sparse>", "attn_kernel<full+filter>", "attn_kernel<full>", "score_kernel", "topk_values_kernel")
 
 
 def parse():
@@ -123,15 +123,18 @@ def cold_step_durations(fn, steps, torch, cb):
     return out
 
 
-def kernel_bytes(w, lens, acc):
+def kernel_bytes(w, lens, acc, layer=True):
     """Algorithmic bytes of ONE launch of each bandwidth-bound kernel (all sequences of the batch)."""
     G, K, W = w.n_kv_heads, w.budget, w.window
     return {
         "attn_kernel<full>": sum(acc.full_attn_bytes(G, L) for L in lens),
         "attn_kernel<sparse>": sum(acc.sparse_attn_bytes(G, K, L) for L in lens),
-        "attn_kernel<scores only>": sum(acc.score_bytes(G, L, K, W) for L in lens),
-        # the selection layer's pass: K and V once, the scores come from the same K rows
-        "attn_kernel<full+score>": sum(acc.full_attn_bytes(G, L) for L in lens),
+        # a selection layer: K once for scores and output (cusa_select on its own: the candidates' only), then V once,
+        # beside the top-k
+        "score_kernel": sum(acc.full_attn_bytes(G, L) // 2 if layer else acc.score_bytes(G, L, K, W) for L in lens),
+        "topk_values_kernel": sum(acc.full_attn_bytes(G, L) // 2 for L in lens),
+        # the same with many scores: K and V once, candidates kept on the way
+        "attn_kernel<full+filter>": sum(acc.full_attn_bytes(G, L) for L in lens),
     }
 
 
@@ -405,10 +408,10 @@ def measure(name, args, torch, acc, cb, wl, StepRunner):
         torch.cuda.synchronize()
         prof = cb.profile_read()
         cb.profile_enable(False)
-        kb = kernel_bytes(w, lens, acc)
+        kb = kernel_bytes(w, lens, acc, args.entry == "step")
         tpath = os.path.join(ROOT, "profiles", f"hbm_traffic_{w.name}.json")
         counted = json.load(open(tpath)).get("hbm_bytes_per_launch", {}) if os.path.exists(tpath) else {}
-        # A selection layer on the filtered fast path launches the scores-only pass and topk_kernel only as the second
+        # A selection layer on the filtered fast path launches score_kernel and topk_kernel only as the second
         # chance of heads whose threshold failed; with none flagged they exit at once and move no bytes.
         fast_path = args.entry == "step" and prof.get("sample_threshold_kernel", {}).get("calls", 0) > 0
         for kname, p in prof.items():
@@ -417,7 +420,7 @@ def measure(name, args, torch, acc, cb, wl, StepRunner):
             avg_us = p["total_ms"] * 1e3 / p["calls"]
             k = {"launches_per_step": p["calls"] // steps, "avg_us": round(avg_us, 3),
                  "us_per_step": round(p["total_ms"] * 1e3 / steps, 3)}
-            if fast_path and kname in ("attn_kernel<scores only>", "topk_kernel"):
+            if fast_path and kname in ("score_kernel", "topk_kernel"):
                 k["role"] = "second chance of the filtered selection (exits at once when no head is flagged)"
             elif kname in kb and kb[kname] > 0:
                 k["bytes_per_launch"] = kb[kname]

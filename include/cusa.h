@@ -207,10 +207,10 @@ cusa_status cusa_full_attn(const cusa_params* params, const void* q, const cusa_
                            void* out, void* ws, size_t ws_bytes, void* stream);
 
 /* A selection layer in one call (the selection branch of Alg. 1): out = FullAttention(q, C[:])
- * and rho = the selection of cusa_select, from one pass over K (the pass that computes the
- * output also writes the scores -- or, for a layer with many scores, only those above a
- * per-head threshold guessed from a sample; heads whose guess fails are scored and ranked again,
- * so the result does not depend on it: cusa_ws_layout.filtered_select).  idx and cnt as in
+ * and rho = the selection of cusa_select, from one pass over K (which writes the scores; the
+ * output is made from them and V while they are ranked -- or, for a layer with many scores, one pass over K
+ * and V keeps those above a per-head threshold guessed from a sample; heads whose guess fails are scored and
+ * ranked again, so the result does not depend on it: cusa_ws_layout.filtered_select).  idx and cnt as in
  * cusa_select (bit for bit the same rho);
  * out as in cusa_full_attn up to binary32 rounding order.  This is what cusa_decode_step runs
  * for a SELECT layer; a caller that drives the layers itself uses it instead of
@@ -221,8 +221,8 @@ cusa_status cusa_select_layer(const cusa_params* params, const void* q, const cu
 /* Attention part of one decode step of Alg. 1 over n_layers layers.
  * layer_kind  host int32[n_layers] of cusa_layer_kind.  FULL: full attention.
  *             SELECT: full attention for this layer's output, then rho is rebuilt
- *             from this layer's q and K (the scores P are written by the same pass
- *             over K that computes the output, bit for bit those of cusa_select;
+ *             from this layer's q and K (K is read once for both; the scores P are
+ *             bit for bit those of cusa_select;
  *             the output agrees with cusa_full_attn up to binary32 rounding order).
  *             SPARSE: sparse attention over the current rho.  A SPARSE layer with no SELECT layer before it in this
  *             call is INVALID_ARG (Alg. 1 starts with rho empty).

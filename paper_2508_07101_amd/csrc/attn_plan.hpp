@@ -7,7 +7,7 @@
 namespace cusa {
 
 constexpr int ATTN_WAVES = 4;       // waves of a workgroup
-// Longest run of tokens a workgroup of the scoring variant may own: its scores wait in LDS (32 KB)
+// Longest run of tokens a workgroup of the filtered form may own: its candidates wait in LDS (32 KB)
 // until the run is done.
 constexpr int ATTN_SCORE_CHUNK_CAP = 2048;
 constexpr int ATTN_SCORE_CHUNK_CAP_G8 = 1024;
@@ -25,7 +25,7 @@ static_assert(ATTN_SCORE_CHUNK_CAP <= CHUNK_CAP && ATTN_SCORE_CHUNK_CAP_G8 <= CH
               "the split bound assumes it");
 
 struct AttnPlan {
-    int ti;        // row-load instructions per wave iteration (4 or 8; scoring variant 8 or 16, tiles of 128 or 256 tokens)
+    int ti;        // row-load instructions per wave iteration (4 or 8; filtered form 8 or 16, tiles of 128 or 256 tokens)
     int chunk;     // tokens per workgroup, a multiple of the workgroup tile
     int n_splits;  // grid.x = ceil(n_max / chunk)
 };
@@ -41,7 +41,7 @@ inline float round_share(int n) {
 enum AttnKind { ATTN_FULL, ATTN_SPARSE, ATTN_SCORE };
 inline int noalloc_splits(int n_max, int BG);
 
-// Whole tiles of the scoring variant.
+// Whole tiles of the filtered form.
 inline int64_t score_tiles(int64_t tokens) { return tokens < 512 ? (tokens + 127) / 128 * 128 : (tokens + 255) / 256 * 256; }
 constexpr int SCORE_START = 64;     // what a workgroup of it costs besides its tokens, in tokens
 
@@ -65,7 +65,7 @@ constexpr int SCORE_START = 64;     // what a workgroup of it costs besides its 
 // where a draw differs by more than that.  (128 pairs of 601 to 16383 tokens: 106.3 us, 97.3, in pieces of 1024 99.6.)
 // A contiguous cache holds sequences of one length as a rule: 224 pairs of 6000 tokens, pieces of 2048 107.3 us, of
 // 1280 114.6; 40 of 32768: 105.5 and 114.8.
-// The scoring variant keeps its scores in LDS, hence its own caps, writes them in bursts, which are better longer
+// The filtered form keeps its candidates in LDS, hence its own caps, writes them in bursts, which are better longer
 // (pieces of 2048 against 1024 at 64 pairs of 16384: 121.3 and 123.7 us), and its tiles are large (128 or 256 tokens):
 // it takes 1/512 of all tokens, rounded up to whole tiles.  Even pieces as above, rounded to the nearest tile, were 2
 // per cent slower over 177 selection layers of 8 to 512 pairs of 600 to 40000 tokens, and often by a last round with
@@ -127,6 +127,40 @@ inline AttnPlan plan_attn(int n_max, int BG, int g, AttnKind kind, bool paged) {
     pl.n_splits = (int)((n_max + chunk - 1) / chunk);
     if (pl.n_splits < 1) pl.n_splits = 1;
     return pl;
+}
+
+// The scoring pass (score_kernel): one workgroup tile a workgroup, of 256 tokens (128 where these would be too few to keep every
+// CU busy twice over); there is no partial result to merge, so nothing bounds their number but the time that idle ones take: the second
+// chance of the filtered selection, which is over at once as a rule, takes runs of 2048.
+inline AttnPlan plan_score(int n_max, int BG, bool second_chance) {
+    const int64_t tokens = (int64_t)n_max * BG;
+    AttnPlan pl;
+    pl.ti = second_chance || tokens > 256 * TARGET_WGS ? 16 : 8;
+    pl.chunk = second_chance ? 2048 : pl.ti * 16;
+    pl.n_splits = (n_max + pl.chunk - 1) / pl.chunk;
+    return pl;
+}
+
+// A selection layer's values (weigh_values): workgroups of 16 waves.
+struct ValuePlan {
+    int chunk;     // tokens per workgroup, a multiple of the workgroup tile
+    int n_splits;
+};
+constexpr int VALUE_TOKENS = 256;   // a tile of 16 for each wave
+// One workgroup to a CU that no row of the top-k starts on (rows: their number) while that makes runs of up to 1536 tokens -- two or
+// three tiles for every wave --, otherwise runs of 1024, which fill the CUs as they become free.  Measured (us for the layer; 256-token steps
+// from 256 to 4096): 8 pairs of 9000 best 22.9, so 23.0; of 16384 26.1 and 26.1; of 32768 36.0 and 36.0; of 65536 59.1, in runs of 1024 60.5;
+// of 131072 109.8 and 109.8; 16 of 16384 36.4 and 36.4; 64 of 16384 108.6 and 109.5; 128 of 3000 to 12000 112.9 and 112.9; 512 of 9000
+// 519.7 and 519.7, in runs of 4096 548.
+inline ValuePlan plan_values(int n_max, int BG, int rows) {
+    const int free = CUS - std::min(rows, 64);
+    int64_t chunk = ((int64_t)n_max * BG + free - 1) / free;
+    chunk = chunk > 1536 ? 1024 : std::max((chunk + VALUE_TOKENS - 1) / VALUE_TOKENS * VALUE_TOKENS, (int64_t)512);
+    if ((n_max + chunk - 1) / chunk > MAX_SPLITS) {
+        chunk = ((int64_t)n_max + MAX_SPLITS - 1) / MAX_SPLITS;
+        chunk = (chunk + VALUE_TOKENS - 1) / VALUE_TOKENS * VALUE_TOKENS;
+    }
+    return {(int)chunk, (int)std::max<int64_t>(1, (n_max + chunk - 1) / chunk)};
 }
 
 // Upper bound of plan_attn(m, BG', ...).n_splits over every m <= n_max and BG' >= BG: a token list is cut into

@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 #include <utility>
@@ -20,13 +21,13 @@ namespace {
 
 // ------------------------------------------------------------------ profiling
 
-enum KernelId { KID_SCORE = 0, KID_TOPK, KID_UNION, KID_ATTN_FULL, KID_ATTN_SPARSE, KID_REDUCE, KID_ATTN_SELECT, KID_ATTN_PER_HEAD, KID_RHO_PER_HEAD, KID_RANK_AGG, KID_RECALL, KID_PROBE, KID_TOPK_SLICE, KID_TOPK_MERGE, KID_PROBE_GATHER, KID_PROBE_RW_SCATTER, KID_PROBE_RW_BURST, KID_SAMPLE_THRESHOLD, KID_TOPK_FILTERED, KID_PROBE_TILES, KID_COUNT };
-const char* const kKernelNames[KID_COUNT] = {"attn_kernel<scores only>", "topk_kernel", "union_kernel",
+enum KernelId { KID_SCORE = 0, KID_TOPK, KID_UNION, KID_ATTN_FULL, KID_ATTN_SPARSE, KID_REDUCE, KID_ATTN_SELECT, KID_ATTN_PER_HEAD, KID_RHO_PER_HEAD, KID_RANK_AGG, KID_RECALL, KID_PROBE, KID_TOPK_SLICE, KID_TOPK_MERGE, KID_PROBE_GATHER, KID_PROBE_RW_SCATTER, KID_PROBE_RW_BURST, KID_SAMPLE_THRESHOLD, KID_TOPK_FILTERED, KID_PROBE_TILES, KID_TOPK_VALUES, KID_COUNT };
+const char* const kKernelNames[KID_COUNT] = {"score_kernel", "topk_kernel", "union_kernel",
                                              "attn_kernel<full>", "attn_kernel<sparse>", "attn_reduce_kernel",
-                                             "attn_kernel<full+score>", "attn_kernel<per-head>", "per_head_rho_kernel",
+                                             "attn_kernel<full+filter>", "attn_kernel<per-head>", "per_head_rho_kernel",
                                              "rank_aggregate_kernel", "recall_kernel", "probe_stream_read_kernel", "topk_kernel<slice>",
                                              "topk_kernel<merge>", "probe_traffic_kernel<gather>", "probe_traffic_kernel<scattered writes>",
-                                             "probe_traffic_kernel<burst writes>", "sample_threshold_kernel", "topk_kernel<filtered>", "probe_traffic_kernel<stream>"};
+                                             "probe_traffic_kernel<burst writes>", "sample_threshold_kernel", "topk_kernel<filtered>", "probe_traffic_kernel<stream>", "topk_values_kernel"};
 
 // With the profiler on, every launch carries a start and a stop event that the runtime fills
 // from the dispatch's own begin and end timestamps (hipExtLaunchKernelGGL), which is what a
@@ -237,7 +238,7 @@ WsLayout make_layout(const cusa_params* p, int max_seq_len) {
     const int BG = p->batch * p->n_kv_heads;
     int64_t lc = (int64_t)max_seq_len - p->window;
     if (lc < 1) lc = 1;
-    w.ldp = (lc + 63) / 64 * 64;
+    w.ldp = ((int64_t)max_seq_len + 63) / 64 * 64;   // a selection layer scores all tokens
     w.k = resolved_k(p);
     if (w.k < 1) w.k = 1;
     w.max_splits = max_splits_bound(max_seq_len > p->budget ? max_seq_len : p->budget, BG);
@@ -306,14 +307,6 @@ cusa_status launch_status() { return hipGetLastError() == hipSuccess ? CUSA_OK :
 
 // ------------------------------------------------------------------ launches
 
-// What a pass over all tokens of a selection layer also emits (scores of the candidate range).
-struct ScoreOut {
-    float* P = nullptr;     // nullptr: plain attention
-    int64_t ldp = 0;
-    int window = 0;
-    FilterState filter = {};   // thr set: the pass keeps the candidates at or above the heads' thresholds instead of writing P
-};
-
 struct AttnArgs {
     bool paged;
     dim3 grid;
@@ -329,52 +322,46 @@ struct AttnArgs {
     uint16_t* out;
     float* lse = nullptr;   // optional: log2 of the softmax denominators, [B][H]
     int n_splits, chunk;
-    ScoreOut score;
+    int window = 0;
+    FilterState filter = {};   // thr set: the pass keeps the candidates at or above the heads' thresholds (all tokens only)
 };
 
-template <int GQ, int TI, bool SPARSE, bool SCORE, bool FILTER = false>
+template <int GQ, int TI, bool SPARSE, bool FILTER = false>
 void launch_attn_partial(const AttnArgs& a) {
-    const int kid = SPARSE ? KID_ATTN_SPARSE : SCORE ? KID_ATTN_SELECT : KID_ATTN_FULL;
+    const int kid = SPARSE ? KID_ATTN_SPARSE : FILTER ? KID_ATTN_SELECT : KID_ATTN_FULL;
     if (a.paged)
-        launch(kid, attn_kernel<GQ, TI, SPARSE, true, SCORE, false, FILTER>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt, a.view.seq_lens, a.q,
-               a.budget, a.n_splits, a.chunk, a.view.G, a.scale, a.pa, a.pm, a.out, a.lse, a.score.P, a.score.ldp, a.score.window, 0, a.score.filter, a.view);
+        launch(kid, attn_kernel<GQ, TI, SPARSE, true, false, FILTER>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt, a.view.seq_lens, a.q,
+               a.budget, a.n_splits, a.chunk, a.view.G, a.scale, a.pa, a.pm, a.out, a.lse, a.window, 0, a.filter, a.view);
     else
-        launch(kid, attn_kernel<GQ, TI, SPARSE, false, SCORE, false, FILTER>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt, a.view.seq_lens, a.q,
-               a.budget, a.n_splits, a.chunk, a.view.G, a.scale, a.pa, a.pm, a.out, a.lse, a.score.P, a.score.ldp, a.score.window, 0, a.score.filter, a.view);
+        launch(kid, attn_kernel<GQ, TI, SPARSE, false, false, FILTER>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt, a.view.seq_lens, a.q,
+               a.budget, a.n_splits, a.chunk, a.view.G, a.scale, a.pa, a.pm, a.out, a.lse, a.window, 0, a.filter, a.view);
 }
 
 // Sparse attention with one token list per query head: grid.y counts query heads.
 template <int TI>
 void launch_attn_per_head(const AttnArgs& a, int H, int hshift) {
     if (a.paged)
-        launch(KID_ATTN_PER_HEAD, attn_kernel<1, TI, true, true, false, true>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt,
-               a.view.seq_lens, a.q, a.budget, a.n_splits, a.chunk, H, a.scale, a.pa, a.pm, a.out, a.lse, nullptr, 0, 0, hshift, FilterState{}, a.view);
+        launch(KID_ATTN_PER_HEAD, attn_kernel<1, TI, true, true, true>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt,
+               a.view.seq_lens, a.q, a.budget, a.n_splits, a.chunk, H, a.scale, a.pa, a.pm, a.out, a.lse, 0, hshift, FilterState{}, a.view);
     else
-        launch(KID_ATTN_PER_HEAD, attn_kernel<1, TI, true, false, false, true>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt,
-               a.view.seq_lens, a.q, a.budget, a.n_splits, a.chunk, H, a.scale, a.pa, a.pm, a.out, a.lse, nullptr, 0, 0, hshift, FilterState{}, a.view);
+        launch(KID_ATTN_PER_HEAD, attn_kernel<1, TI, true, false, true>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt,
+               a.view.seq_lens, a.q, a.budget, a.n_splits, a.chunk, H, a.scale, a.pa, a.pm, a.out, a.lse, 0, hshift, FilterState{}, a.view);
 }
 
 template <int GQ, bool SPARSE>
 void launch_attn_ti(int ti, const AttnArgs& a) {
-    if constexpr (!SPARSE) {
-        if (a.score.P) {                              // the scoring chain repeats work for tiles under 64 tokens: always the wider tile
-            if (a.score.filter.thr) {                 // groups of up to 4 only (filtered_select)
-                if constexpr (GQ <= 4) {
-                    if (ti == 16) launch_attn_partial<GQ, 16, false, true, true>(a);
-                    else launch_attn_partial<GQ, 8, false, true, true>(a);
-                }
-            } else {
-                if (ti == 16) launch_attn_partial<GQ, 16, false, true>(a);
-                else launch_attn_partial<GQ, 8, false, true>(a);
-            }
+    if constexpr (!SPARSE && GQ <= 4) {               // (filtered_select: groups of up to 4)
+        if (a.filter.thr) {                           // the scoring chain repeats work for tiles under 64 tokens: the wider tile where runs allow
+            if (ti == 16) launch_attn_partial<GQ, 16, false, true>(a);
+            else launch_attn_partial<GQ, 8, false, true>(a);
             return;
         }
     }
     if (ti == 8) {
-        launch_attn_partial<GQ, 8, SPARSE, false>(a);
+        launch_attn_partial<GQ, 8, SPARSE>(a);
         return;
     }
-    launch_attn_partial<GQ, 4, SPARSE, false>(a);
+    launch_attn_partial<GQ, 4, SPARSE>(a);
 }
 
 void launch_reduce(const ReduceArgs& r, int H, int B, hipStream_t s) {
@@ -383,14 +370,14 @@ void launch_reduce(const ReduceArgs& r, int H, int B, hipStream_t s) {
 }
 
 // Attention over all tokens (idx == nullptr) or over idx/cnt; n_max bounds the token count.
-// With score.P set (all tokens only) the pass also writes the selection scores.
+// filter (all tokens only): the pass also keeps the selection's candidates.
 // later: the merge of the partials is left to the caller, who gets its arguments (rows 0: nothing to merge).
 template <bool SPARSE>
 cusa_status run_attention(const cusa_params* p, const void* q, const cusa_kv* kv, const int32_t* idx,
                           const int32_t* cnt, int n_max, void* out, void* ws, const WsLayout& w, hipStream_t s,
-                          ScoreOut score = ScoreOut(), float* lse = nullptr, ReduceArgs* later = nullptr) {
+                          const FilterState* filter = nullptr, float* lse = nullptr, ReduceArgs* later = nullptr) {
     const int g = p->n_q_heads / p->n_kv_heads, BG = p->batch * p->n_kv_heads, H = p->n_q_heads;
-    const AttnPlan pl = plan_attn(n_max, BG, g, SPARSE ? ATTN_SPARSE : score.P != nullptr ? ATTN_SCORE : ATTN_FULL,
+    const AttnPlan pl = plan_attn(n_max, BG, g, SPARSE ? ATTN_SPARSE : filter ? ATTN_SCORE : ATTN_FULL,
                                   kv->layout == CUSA_KV_PAGED);
     if (pl.n_splits > w.max_splits) return CUSA_ERR_WORKSPACE_TOO_SMALL;
     AttnArgs a;
@@ -409,7 +396,8 @@ cusa_status run_attention(const cusa_params* p, const void* q, const cusa_kv* kv
     a.lse = lse;
     a.n_splits = pl.n_splits;
     a.chunk = pl.chunk;
-    a.score = score;
+    a.window = p->window;
+    if (filter) a.filter = *filter;
     switch (g) {
         case 1: launch_attn_ti<1, SPARSE>(pl.ti, a); break;
         case 2: launch_attn_ti<2, SPARSE>(pl.ti, a); break;
@@ -491,6 +479,15 @@ bool grant_topk_items() {
            grant_lds(reinterpret_cast<const void*>(topk_kernel<ITEMS, 4, MERGE>), topk_lds_bytes<ITEMS, 4, MERGE>()) &&
            grant_lds(reinterpret_cast<const void*>(topk_kernel<ITEMS, 8, MERGE>), topk_lds_bytes<ITEMS, 8, MERGE>());
 }
+template <int ITEMS, int MTOP>
+bool grant_topk_values_m() {
+    return grant_lds(reinterpret_cast<const void*>(topk_values_kernel<ITEMS, MTOP, false>), std::max(topk_lds_bytes<ITEMS, MTOP>(), value_lds_bytes<4>())) &&
+           grant_lds(reinterpret_cast<const void*>(topk_values_kernel<ITEMS, MTOP, true>), std::max(topk_lds_bytes<ITEMS, MTOP>(), value_lds_bytes<8>()));
+}
+template <int ITEMS>
+bool grant_topk_values() {
+    return grant_topk_values_m<ITEMS, 1>() && grant_topk_values_m<ITEMS, 2>() && grant_topk_values_m<ITEMS, 4>() && grant_topk_values_m<ITEMS, 8>();
+}
 
 // Split-K partials of cusa_sparse_attn_noalloc: device memory that belongs to the library image,
 // one copy per GPU, held until the process ends.  Host code never uses the array's name as an
@@ -520,7 +517,8 @@ bool device_ready() {
     std::lock_guard<std::mutex> lk(mu);
     if (ready[dev]) return true;
     const bool ok = grant_topk_items<4>() && grant_topk_items<8>() && grant_topk_items<16>() && grant_topk_items<32>() &&
-                    grant_topk_items<0>() && grant_topk_items<-1>() && grant_topk_items<4, true>() &&
+                    grant_topk_items<0>() && grant_topk_items<-1>() && grant_topk_values<4>() && grant_topk_values<-1>() &&
+                     grant_topk_items<4, true>() &&
                     grant_topk_items<8, true>() && grant_topk_items<16, true>() && grant_lds(reinterpret_cast<const void*>(union_kernel), SEL_LDS_MAX) &&
                     grant_lds(reinterpret_cast<const void*>(per_head_rho_kernel), SEL_LDS_MAX) && grant_sample<1>() &&
                     grant_sample<2>() && grant_sample<4>();
@@ -619,65 +617,108 @@ cusa_status run_topk(int lc_max, int B, int H, hipStream_t s, const float* P, in
     return launch_topk<16, true>(a);
 }
 
-// P = q.K^T over the candidate range: the selection pass in its scores-only form (no V rows, no output).
-// only_failed / n_failed: the second chance of the filtered selection scores the flagged heads' groups only.
-template <int GQ, int TI>
-void launch_scores_only(const AttnArgs& a) {
-    if (a.paged)
-        launch(KID_SCORE, attn_kernel<GQ, TI, false, true, true, false, false, true>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt, a.view.seq_lens,
-               a.q, a.budget, a.n_splits, a.chunk, a.view.G, a.scale, a.pa, a.pm, a.out, a.lse, a.score.P, a.score.ldp, a.score.window, 0,
-               a.score.filter, a.view);
-    else
-        launch(KID_SCORE, attn_kernel<GQ, TI, false, false, true, false, false, true>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt, a.view.seq_lens,
-               a.q, a.budget, a.n_splits, a.chunk, a.view.G, a.scale, a.pa, a.pm, a.out, a.lse, a.score.P, a.score.ldp, a.score.window, 0,
-               a.score.filter, a.view);
+// The same for the rows of a selection layer, with the layer's values in the launch.  Forms that leave half a CU to the values only: with
+// rows in registers, a workgroup to a CU, the values wait for the rows (us for the launch, 8 sequences of 16384, 32 heads: 61.0
+// and 51.7; where there are few rows, or short ones, it makes no difference).  Rows are never sliced: a long row's walk by one workgroup
+// takes less time than its values.
+constexpr size_t value_lds(bool group8) { return group8 ? value_lds_bytes<8>() : value_lds_bytes<4>(); }
+template <int ITEMS, int MTOP, bool GROUP8>
+cusa_status launch_topk_values_g(const TopkArgs& a, int B, const ValueArgs& v) {
+    const size_t shmem = std::max(topk_lds_bytes<ITEMS, MTOP>(), value_lds(GROUP8));
+    launch(KID_TOPK_VALUES, topk_values_kernel<ITEMS, MTOP, GROUP8>, dim3(a.H * B + v.items), SEL_THREADS, shmem, a.s, a.P, a.ldp, a.seq_lens,
+           a.rho_head, a.H, a.k, a.budget, a.window, a.n_sink, B, v);
+    return launch_status();
 }
-template <int GQ>
-void launch_scores_only_ti(int ti, const AttnArgs& a) {
-    if (ti == 16) launch_scores_only<GQ, 16>(a);
-    else launch_scores_only<GQ, 8>(a);
+template <int ITEMS, int MTOP>
+cusa_status launch_topk_values_m(const TopkArgs& a, int B, const ValueArgs& v) {
+    return v.g == 8 ? launch_topk_values_g<ITEMS, MTOP, true>(a, B, v) : launch_topk_values_g<ITEMS, MTOP, false>(a, B, v);
+}
+template <int ITEMS>
+cusa_status launch_topk_values(const TopkArgs& a, int B, const ValueArgs& v) {
+    switch (topk_mtop(a.k)) {
+        case 1: return launch_topk_values_m<ITEMS, 1>(a, B, v);
+        case 2: return launch_topk_values_m<ITEMS, 2>(a, B, v);
+        case 4: return launch_topk_values_m<ITEMS, 4>(a, B, v);
+        default: return launch_topk_values_m<ITEMS, 8>(a, B, v);
+    }
+}
+cusa_status run_topk_values(int lc_max, int B, int H, hipStream_t s, const float* P, int64_t ldp, const int32_t* seq_lens, int32_t* out, int k,
+                            int budget, int window, int n_sink, const ValueArgs& v) {
+    const TopkArgs a = {dim3(), s, P, ldp, seq_lens, out, H, k, budget, window, 0, n_sink, nullptr, 0, 1};
+    const int items = (lc_max + SEL_THREADS - 1) / SEL_THREADS;
+    return items <= 4 ? launch_topk_values<4>(a, B, v) : launch_topk_values<-1>(a, B, v);
 }
 
-cusa_status run_score(const cusa_params* p, const void* q, const cusa_kv* kv, float* P, int64_t ldp, hipStream_t s,
-                      int32_t* only_failed, int32_t* n_failed) {
+// P = q.K^T.  Scores of this many bytes are left to the caches until the top-k reads them; more would only turn them over and are
+// streamed past them (scores + top-k, us, ordinary and streaming stores: 4 MB 26.9 and 28.0; 17 MB 60.0 and 60.2; 34 MB 84.9 and 86.1; 164 MB
+// 582 and 555).
+constexpr int64_t SCORE_KEEP_BYTES = (int64_t)64 << 20;
+// only_failed / n_failed: the second chance of the filtered selection scores the flagged heads' groups only.
+struct ScoreArgs {
+    bool paged;
+    dim3 grid;
+    hipStream_t s;
+    const uint16_t* q;
+    int budget, window, n_splits, chunk, all, keep;
+    float* P;
+    int64_t ldp;
+    FilterState filter;
+    KvView view;
+};
+template <int GQ, int TI>
+void launch_score(const ScoreArgs& a) {
+    if (a.paged)
+        launch(KID_SCORE, score_kernel<GQ, TI, true>, a.grid, ATTN_THREADS, 0, a.s, a.view.seq_lens, a.q, a.budget, a.window, a.n_splits, a.chunk,
+               a.view.G, a.all, a.keep, a.P, a.ldp, a.filter, a.view);
+    else
+        launch(KID_SCORE, score_kernel<GQ, TI, false>, a.grid, ATTN_THREADS, 0, a.s, a.view.seq_lens, a.q, a.budget, a.window, a.n_splits, a.chunk,
+               a.view.G, a.all, a.keep, a.P, a.ldp, a.filter, a.view);
+}
+template <int GQ>
+void launch_score_ti(int ti, const ScoreArgs& a) {
+    if (ti == 16) launch_score<GQ, 16>(a);
+    else launch_score<GQ, 8>(a);
+}
+
+// all: every token's scores (a selection layer); otherwise those of the candidate range.
+cusa_status run_score(const cusa_params* p, const void* q, const cusa_kv* kv, float* P, int64_t ldp, hipStream_t s, bool all,
+                      int32_t* only_failed = nullptr, int32_t* n_failed = nullptr) {
     const int g = p->n_q_heads / p->n_kv_heads, BG = p->batch * p->n_kv_heads;
-    const int lc_max = kv->max_seq_len - p->window;
-    if (lc_max < 1) return CUSA_OK;
-    const AttnPlan pl = plan_attn(lc_max, BG, g, ATTN_SCORE, kv->layout == CUSA_KV_PAGED);
-    AttnArgs a;
+    const int n_max = all ? kv->max_seq_len : kv->max_seq_len - p->window;
+    if (n_max < 1) return CUSA_OK;
+    ScoreArgs a;
+    const AttnPlan pl = plan_score(n_max, BG, only_failed != nullptr);
     a.paged = kv->layout == CUSA_KV_PAGED;
     a.grid = dim3(pl.n_splits, p->n_kv_heads, p->batch);
     a.s = s;
-    a.view = make_view(p, kv);
     a.q = static_cast<const uint16_t*>(q);
-    a.idx = nullptr;
-    a.cnt = nullptr;
     a.budget = p->budget;
-    a.scale = 0.0f;
-    a.pa = a.pm = nullptr;
-    a.out = nullptr;
+    a.window = p->window;
     a.n_splits = pl.n_splits;
     a.chunk = pl.chunk;
-    a.score.P = P;
-    a.score.ldp = ldp;
-    a.score.window = p->window;
-    a.score.filter.fail = only_failed;                   // nullptr: every group
-    a.score.filter.n_failed = n_failed;
+    a.all = all ? 1 : 0;
+    a.keep = (int64_t)p->batch * p->n_q_heads * n_max * 4 <= SCORE_KEEP_BYTES ? 1 : 0;
+    a.P = P;
+    a.ldp = ldp;
+    a.filter = FilterState{};
+    a.filter.fail = only_failed;                         // nullptr: every group
+    a.filter.n_failed = n_failed;
+    a.view = make_view(p, kv);
     switch (g) {
-        case 1: launch_scores_only_ti<1>(pl.ti, a); break;
-        case 2: launch_scores_only_ti<2>(pl.ti, a); break;
-        case 4: launch_scores_only_ti<4>(pl.ti, a); break;
-        default: launch_scores_only_ti<8>(pl.ti, a); break;
+        case 1: launch_score_ti<1>(pl.ti, a); break;
+        case 2: launch_score_ti<2>(pl.ti, a); break;
+        case 4: launch_score_ti<4>(pl.ti, a); break;
+        default: launch_score_ti<8>(pl.ti, a); break;
     }
     return launch_status();
 }
 
-// scores_ready: P was already written by the layer's attention pass (cusa_decode_step).
+// values: the layer's values, made in the top-k's launch (scores of all tokens).
 // per_head: idx is [B][H][budget], every head keeps its own first K-W picks (head-to-head selection).
 // red: attention partials still to be merged; they go with the union launch (or on their own where there is none).
 cusa_status run_select(const cusa_params* p, const void* q, const cusa_kv* kv, int32_t* idx, int32_t* cnt, void* ws,
-                       const WsLayout& w, hipStream_t s, bool scores_ready = false, bool per_head = false,
-                       const FilterState* redo = nullptr, const ReduceArgs* red = nullptr) {
+                       const WsLayout& w, hipStream_t s, bool per_head = false, const FilterState* redo = nullptr,
+                       const ReduceArgs* red = nullptr, const ValueArgs* values = nullptr) {
     const int H = p->n_q_heads, B = p->batch;
     // redo: the filtered fast path has ranked most heads already; only the flagged ones are scored and ranked here
     int32_t* only_failed = redo ? redo->fail : nullptr;
@@ -687,12 +728,10 @@ cusa_status run_select(const cusa_params* p, const void* q, const cusa_kv* kv, i
 
     if (kv->max_seq_len > p->budget) {            // otherwise no sequence can need scoring
         const int lc_max = kv->max_seq_len - p->window;
-        if (!scores_ready) {
-            const cusa_status st = run_score(p, q, kv, P, w.ldp, s, only_failed, n_failed);
-            if (st != CUSA_OK) return st;
-        }
-        cusa_status st = run_topk(lc_max, B, H, s, P, w.ldp, kv->seq_lens, rho_head, w.k, p->budget, p->window, 0, p->n_sink,
-                                  ws, w, only_failed);
+        cusa_status st = run_score(p, q, kv, P, w.ldp, s, values != nullptr, only_failed, n_failed);
+        if (st != CUSA_OK) return st;
+        st = values ? run_topk_values(lc_max, B, H, s, P, w.ldp, kv->seq_lens, rho_head, w.k, p->budget, p->window, p->n_sink, *values)
+                    : run_topk(lc_max, B, H, s, P, w.ldp, kv->seq_lens, rho_head, w.k, p->budget, p->window, 0, p->n_sink, ws, w, only_failed);
         if (st != CUSA_OK) return st;
     }
     {
@@ -755,19 +794,17 @@ void launch_sample_threshold(const cusa_params* p, const void* q, const cusa_kv*
     }
 }
 
-// A selection layer (Alg. 1): full attention for the layer's output and rho from the same q and K.
-// The pass over all tokens also writes the scores, so K is read once.
+// A selection layer (Alg. 1): full attention for the layer's output and rho from the same q and K, which are read once.
 cusa_status run_select_layer(const cusa_params* p, const void* q, const cusa_kv* kv, void* out, int32_t* idx,
                              int32_t* cnt, void* ws, const WsLayout& w, hipStream_t s) {
-    ScoreOut score;
     ReduceArgs red = {};
-    if (kv->max_seq_len > p->budget) {
-        score.P = ws_ptr<float>(ws, w.scores);
-        score.ldp = w.ldp;
-        score.window = p->window;
+    // rho is every token of every sequence; or tokens lie too far apart for the values' kernel
+    if (kv->max_seq_len <= p->budget || (kv->layout == CUSA_KV_CONTIGUOUS && kv->stride_token > VALUE_MAX_STEP)) {
+        const cusa_status st = run_attention<false>(p, q, kv, nullptr, nullptr, kv->max_seq_len, out, ws, w, s, nullptr, nullptr, &red);
+        return st != CUSA_OK ? st : run_select(p, q, kv, idx, cnt, ws, w, s, false, nullptr, &red);
     }
-    if (score.P && w.filter_cap > 0 && filtered_select(p, kv->max_seq_len)) {
-        // The filtered fast path: thresholds from a sample, the pass keeps the candidates above them, the
+    if (w.filter_cap > 0 && filtered_select(p, kv->max_seq_len)) {
+        // The filtered fast path: thresholds from a sample, the pass over K and V keeps the candidates above them, the
         // top-k ranks among those, and whatever the guess failed for is scored and ranked the ordinary way.
         const int H = p->n_q_heads, B = p->batch;
         FilterState f;
@@ -781,8 +818,7 @@ cusa_status run_select_layer(const cusa_params* p, const void* q, const cusa_kv*
         const SamplePlan sp = plan_sample((int64_t)kv->max_seq_len - p->window);
         launch_sample_threshold(p, q, kv, sp, f, w.k, s);
         if (launch_status() != CUSA_OK) return CUSA_ERR_LAUNCH;
-        score.filter = f;
-        cusa_status st = run_attention<false>(p, q, kv, nullptr, nullptr, kv->max_seq_len, out, ws, w, s, score, nullptr, &red);
+        cusa_status st = run_attention<false>(p, q, kv, nullptr, nullptr, kv->max_seq_len, out, ws, w, s, &f, nullptr, &red);
         if (st != CUSA_OK) return st;
         TopkArgs a = {dim3(H, B), s, nullptr, 0, kv->seq_lens, ws_ptr<int32_t>(ws, w.rho_head), H, w.k, p->budget, p->window, 0,
                       p->n_sink, nullptr, 0, 1};
@@ -790,11 +826,26 @@ cusa_status run_select_layer(const cusa_params* p, const void* q, const cusa_kv*
         const int items = (f.cap + SEL_THREADS - 1) / SEL_THREADS;
         st = items <= 4 ? launch_topk<4, true>(a) : items <= 8 ? launch_topk<8, true>(a) : launch_topk<16, true>(a);
         if (st != CUSA_OK) return st;
-        return run_select(p, q, kv, idx, cnt, ws, w, s, false, false, &f, &red);
+        return run_select(p, q, kv, idx, cnt, ws, w, s, false, &f, &red);
     }
-    cusa_status st = run_attention<false>(p, q, kv, nullptr, nullptr, kv->max_seq_len, out, ws, w, s, score, nullptr, &red);
-    if (st != CUSA_OK) return st;
-    return run_select(p, q, kv, idx, cnt, ws, w, s, score.P != nullptr, false, nullptr, &red);
+    // Otherwise the scores of all tokens first; the values are made while the top-k runs.
+    ValueArgs v;
+    const ValuePlan pl = plan_values(kv->max_seq_len, p->batch * p->n_kv_heads, p->batch * p->n_q_heads);
+    if (pl.n_splits > w.max_splits) return CUSA_ERR_WORKSPACE_TOO_SMALL;
+    v.P = ws_ptr<float>(ws, w.scores);
+    v.ldp = w.ldp;
+    v.scale_log2e = p->sm_scale * 1.4426950408889634f;
+    v.part_acc = ws_ptr<float>(ws, w.part_acc);
+    v.part_ml = ws_ptr<float>(ws, w.part_ml);
+    v.out = static_cast<uint16_t*>(out);
+    v.n_splits = pl.n_splits;
+    v.chunk = pl.chunk;
+    v.g = p->n_q_heads / p->n_kv_heads;
+    v.paged = kv->layout == CUSA_KV_PAGED ? 1 : 0;
+    v.items = pl.n_splits * p->batch * p->n_kv_heads;
+    v.kv = make_view(p, kv);
+    red = {v.part_acc, v.part_ml, v.out, kv->seq_lens, 0x7fffffff, pl.n_splits, pl.chunk, nullptr, pl.n_splits > 1 ? p->n_q_heads * p->batch : 0};
+    return run_select(p, q, kv, idx, cnt, ws, w, s, false, nullptr, &red, &v);
 }
 
 }  // namespace
@@ -915,7 +966,7 @@ cusa_status cusa_select_per_head(const cusa_params* params, const void* q, const
     if ((st = check_select_length(params, kv)) != CUSA_OK) return st;
     const WsLayout w = make_layout(params, kv->max_seq_len);
     if ((st = check_ws(w, ws, ws_bytes)) != CUSA_OK) return st;
-    return run_select(params, q, kv, idx_head, cnt, ws, w, static_cast<hipStream_t>(stream), false, true);
+    return run_select(params, q, kv, idx_head, cnt, ws, w, static_cast<hipStream_t>(stream), true);
 }
 
 cusa_status cusa_sparse_attn_per_head(const cusa_params* params, const void* q, const cusa_kv* kv,
@@ -946,9 +997,9 @@ cusa_status cusa_attention_recall(const cusa_params* params, const void* q, cons
     void* out_tmp = ws_ptr<uint16_t>(ws, w.out_tmp);
     const int n_max = params->budget < kv->max_seq_len ? params->budget : kv->max_seq_len;
     if (idx_per_head) st = run_attention_per_head(params, q, kv, idx, cnt, out_tmp, ws, w, s, lse_set);
-    else st = run_attention<true>(params, q, kv, idx, cnt, n_max, out_tmp, ws, w, s, ScoreOut(), lse_set);
+    else st = run_attention<true>(params, q, kv, idx, cnt, n_max, out_tmp, ws, w, s, nullptr, lse_set);
     if (st != CUSA_OK) return st;
-    st = run_attention<false>(params, q, kv, nullptr, nullptr, kv->max_seq_len, out_tmp, ws, w, s, ScoreOut(), lse_all);
+    st = run_attention<false>(params, q, kv, nullptr, nullptr, kv->max_seq_len, out_tmp, ws, w, s, nullptr, lse_all);
     if (st != CUSA_OK) return st;
     launch(KID_RECALL, recall_kernel, (n + 255) / 256, 256, 0, s, lse_set, lse_all, recall, n);
     return launch_status();

@@ -6,11 +6,13 @@
 //   slice_filter_kernel the same threshold on slices of few long rows
 //   union_kernel        cross-head union, first-occurrence global rank, cut at
 //                       K-W, recency window (Sec. 3.2, 3.3) -> ascending rho
+//   score_kernel        P = q.K^T (Alg. 1, selection layer): one lane per key row, K staged
+//                       through LDS, products accumulated by k = 1 MFMA in column order
+//   topk_values_kernel  a selection layer's top-k and, on the rest of the chip, its output
+//                       softmax(P) V from those scores
 //   attn_kernel         split-K flash-decode over all tokens or over rho
-//                       (Eq. 1 / SparseAttention of Alg. 1), GQA group in registers; its
-//                       scoring forms also make P = q.K^T over the candidate range (Alg. 1,
-//                       selection layer): one lane per key row, K staged through LDS,
-//                       products accumulated by k = 1 MFMA in column order
+//                       (Eq. 1 / SparseAttention of Alg. 1), GQA group in registers; its filtered
+//                       form also keeps the selection's candidates above a threshold
 //   sample_threshold_kernel   per-head thresholds from a sample of the scores (filtered selection)
 //   attn_reduce_kernel  merges the split-K partials and writes bf16
 //   per_head_rho_kernel, rank_aggregate_kernel, recall_kernel   the head-to-head variant, the other
@@ -66,6 +68,11 @@ __device__ __forceinline__ u32x4 row_load(const uint16_t* p) {
     return SHARED_ROWS ? *reinterpret_cast<const u32x4*>(p) : stream_load(p);
 }
 
+// A value at a wave-uniform address that no kernel of the launch writes: a scalar load.
+__device__ __forceinline__ int32_t uniform_load(const int32_t* p) {
+    return *(const __attribute__((address_space(4))) int32_t*)(uintptr_t)p;
+}
+
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
@@ -85,8 +92,8 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
 
 // ---------------------------------------------------------------- scoring
 //
-// The selection scores P = q.K^T are made by the attention kernel's scoring forms (attn_kernel with
-// SCORE; ONLY_SCORES for cusa_select and the second chance).  Their bit-exactness rests on the product
+// The selection scores P = q.K^T are made by score_kernel and, where only candidates above a threshold are kept, by
+// attn_kernel's filtered form.  Their bit-exactness rests on the product
 // chain: V_MFMA_F32_4X4X1_16B_F32 takes, per lane, one binary32 element of q (head = lane % 4) and one
 // of K (the lane's row) and adds the 4 heads x 64 rows of single products to the accumulators.  With
 // k = 1 there is exactly one product (exact: bf16 x bf16 has a 16-bit significand) and one rounded
@@ -673,14 +680,14 @@ constexpr float SLICE_Z = 6.0f;                         // instead of FAST_Z: a 
 // slice selects its own k best and leaves their composites, unsorted and padded with zeros, in
 // parts[row][slice][k]; the k best of a row are among the k best of its slices, so a second launch (MERGE) selects
 // and ranks among those n_slices * k composites instead of the row.  MERGE also ranks what a filtered pass kept.
-template <int ITEMS, int MTOP, bool MERGE = false>
-__global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS > 0 && ITEMS <= 8))) ? 8 : 4) void topk_kernel(const float* __restrict__ P, int64_t ldp,
-                                                            const int32_t* __restrict__ seq_lens,
-                                                            int32_t* __restrict__ rho_head, int H, int k,
-                                                            int budget, int window, int raw_keys, int n_sink,
-                                                            uint64_t* __restrict__ parts, int slice_len, int n_slices,
-                                                            const int32_t* __restrict__ only_rows, FilterState flt,
-                                                            SliceLists sl) {
+//
+// lin: number of the row (and with it of the workgroup) among the B * H; z: its slice.
+template <int ITEMS, int MTOP, bool MERGE>
+__device__ __forceinline__ void topk_row(const int lin, const int z, const int B, const float* __restrict__ P, int64_t ldp,
+                                         const int32_t* __restrict__ seq_lens, int32_t* __restrict__ rho_head, int H, int k,
+                                         int budget, int window, int raw_keys, int n_sink, uint64_t* __restrict__ parts,
+                                         int slice_len, int n_slices, const int32_t* __restrict__ only_rows, FilterState flt,
+                                         SliceLists sl) {
     static_assert(!MERGE || ITEMS > 0, "the composites of a merge are held in registers");
     constexpr int NSORT = MTOP * SEL_THREADS;         // k <= NSORT
     constexpr int CAP = topk_list_cap(ITEMS, MTOP);
@@ -699,14 +706,11 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
     // heads of a sequence are put on one XCD, whose L2 then merges their 4-byte stores into whole
     // lines instead of each XCD writing its own fragments of every line (c5: 104 MB written for a 13 MB
     // output before).
-    int h = blockIdx.x, b = blockIdx.y;
-    {
-        const int B = gridDim.y, lin = blockIdx.x + H * blockIdx.y;
-        if (lin < (B / 8) * 8 * H) {
-            const int within = lin % (8 * H);
-            b = (lin / (8 * H)) * 8 + (within & 7);
-            h = within >> 3;
-        }
+    int h = lin % H, b = lin / H;
+    if (lin < (B / 8) * 8 * H) {
+        const int within = lin % (8 * H);
+        b = (lin / (8 * H)) * 8 + (within & 7);
+        h = within >> 3;
     }
     // only_rows: the second chance of the filtered fast path ranks the flagged heads only
     if (only_rows && only_rows[(int64_t)b * H + h] == 0) return;
@@ -716,9 +720,9 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
     // this workgroup's candidates: the positions [t_lo, t_hi) of the row (a slice of it), or -- MERGE --
     // the composites the slices left, or (flt.thr set) those the filtered pass kept for this head
     const bool slice = !MERGE && parts != nullptr;
-    const int t_lo = slice ? (int)blockIdx.z * slice_len : 0;
+    const int t_lo = slice ? z * slice_len : 0;
     const int t_hi = slice ? min(Lc, t_lo + slice_len) : Lc;
-    uint64_t* const my_parts = parts + (((int64_t)b * H + h) * n_slices + (slice ? (int)blockIdx.z : 0)) * k;
+    uint64_t* const my_parts = parts + (((int64_t)b * H + h) * n_slices + (slice ? z : 0)) * k;
     // the first n_sink positions are kept in rho anyway and are no candidates (key 0, like the padding)
     const int k_eff = MERGE ? min(k, Lc - n_sink) : min(k, t_hi - max(t_lo, n_sink));
     if (slice && k_eff <= 0) {                        // nothing of the row falls into this slice
@@ -923,7 +927,7 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
             if constexpr (ITEMS == 0) {               // a long row whose slices have been filtered already
                 if (sl.cand) {
                     const int64_t r0 = ((int64_t)b * H + h) * sl.n_slices;
-                    for (int z = 0; z < sl.n_slices; ++z) n += min(sl.cnt[r0 + z], FCAP + 1);
+                    for (int y = 0; y < sl.n_slices; ++y) n += min(sl.cnt[r0 + y], FCAP + 1);
                     go = n < k_eff || n > FCAP;
                     if (!go) {
                         s_lo = sl.s_lo[(int64_t)b * H + h];
@@ -932,12 +936,12 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
                             int i = tid + j * SEL_THREADS;
                             lv[j] = 0;
                             if (i < n) {
-                                int z = 0;
-                                for (int c = sl.cnt[r0]; i >= c; c = sl.cnt[r0 + z]) {
+                                int y = 0;
+                                for (int c = sl.cnt[r0]; i >= c; c = sl.cnt[r0 + y]) {
                                     i -= c;
-                                    ++z;
+                                    ++y;
                                 }
-                                lv[j] = sl.cand[(r0 + z) * sl.cap + i];
+                                lv[j] = sl.cand[(r0 + y) * sl.cap + i];
                             }
                         }
                         lds_barrier();                // the cleared areas
@@ -1216,6 +1220,21 @@ __global__ __launch_bounds__(SEL_THREADS, (MTOP <= 4 && (ITEMS == -1 || (ITEMS >
     int32_t* __restrict__ out = rho_head + (int64_t)b * k * H + h;
     for (int j = threadIdx.x; j < k_eff; j += SEL_THREADS)
         out[(int64_t)j * H] = (int32_t)~(uint32_t)sort_buf[j];
+}
+
+// Forms that leave room for a second workgroup on the CU.
+constexpr bool topk_lean(int items, int mtop) { return mtop <= 4 && (items == -1 || (items > 0 && items <= 8)); }
+
+template <int ITEMS, int MTOP, bool MERGE = false>
+__global__ __launch_bounds__(SEL_THREADS, topk_lean(ITEMS, MTOP) ? 8 : 4) void topk_kernel(const float* __restrict__ P, int64_t ldp,
+                                                            const int32_t* __restrict__ seq_lens,
+                                                            int32_t* __restrict__ rho_head, int H, int k,
+                                                            int budget, int window, int raw_keys, int n_sink,
+                                                            uint64_t* __restrict__ parts, int slice_len, int n_slices,
+                                                            const int32_t* __restrict__ only_rows, FilterState flt,
+                                                            SliceLists sl) {
+    topk_row<ITEMS, MTOP, MERGE>((int)(blockIdx.x + H * blockIdx.y), (int)blockIdx.z, (int)gridDim.y, P, ldp, seq_lens, rho_head, H, k, budget,
+                                 window, raw_keys, n_sink, parts, slice_len, n_slices, only_rows, flt, sl);
 }
 
 // Few long rows: one workgroup would walk a row on one CU while most of the chip idles, so a row is cut into slices
@@ -1581,7 +1600,7 @@ __global__ __launch_bounds__(UNION_THREADS) void union_kernel(const int32_t* __r
 // compacted per head) and the top-k ranks among them.  theta is only a guess, so everything that
 // depends on it is checked: a head whose kept candidates turn out fewer than k (theta too high) or more
 // than the buffers hold (theta too low, or many equal scores) is flagged, and the flagged heads are
-// scored and ranked again the ordinary way (the scores-only pass and topk_kernel in their flagged-only forms).
+// scored and ranked again the ordinary way (score_kernel and topk_kernel in their flagged-only forms).
 // The result never depends on theta; only the time does.
 //
 // The sample of a head has n_s candidates out of n (every position in a sampled tile that is a
@@ -1980,9 +1999,8 @@ __device__ __forceinline__ float lane_value(float v, int lane) {
 
 __device__ __forceinline__ int wave_base_of(unsigned tid) { return (int)(tid >> 6); }
 
-// SCORE (selection layer, all tokens): the scores of the candidate range [0, L - window) are also
-// written to P[b][head][t] (row stride ldp), so the layer's K is read once for both (Alg. 1 computes
-// the layer's output and P from the same K).  q.k then runs as the k = 1 MFMA chain -- the pinned
+// FILTER (selection layer with many scores, all tokens): the candidates of [0, L - window) whose scores reach their head's threshold
+// are kept (sample_threshold_kernel has the account).  q.k then runs as the k = 1 MFMA chain -- the pinned
 // left-to-right binary32 sum (see "scoring" above) -- instead of the k = 4 bf16 MFMA, and the softmax
 // uses those same values.
 //
@@ -1993,20 +2011,14 @@ __device__ __forceinline__ int wave_base_of(unsigned tid) { return (int)(tid >> 
 // -- the head-to-head selection the paper compares with (Sec. 3.2, the generalization figure) --
 // so a workgroup serves one query head, blockIdx.y counts query heads (G of them) and head y reads
 // KV head y >> hshift.  Nothing is shared inside a GQA group: each head fetches its own rows.
-//
-// ONLY_SCORES (a form of SCORE): the scores and nothing else -- no V rows, no softmax, no output.  This
-// is cusa_select's scoring pass and the second chance of the filtered selection: with flt.fail set, only
-// the groups that have a flagged head are scored, and nothing at all when the counter *flt.n_failed is 0.
-template <int GQ, int TI, bool SPARSE, bool PAGED, bool SCORE = false, bool PER_HEAD = false, bool FILTER = false,
-          bool ONLY_SCORES = false>
+template <int GQ, int TI, bool SPARSE, bool PAGED, bool PER_HEAD = false, bool FILTER = false>
 __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt, const int32_t* __restrict__ seq_lens,
     const uint16_t* __restrict__ q, int budget, int n_splits, int chunk, int G, float scale_log2e,
     float* __restrict__ part_acc, float* __restrict__ part_ml, uint16_t* __restrict__ out, float* __restrict__ lse,
-    float* __restrict__ P, int64_t ldp, int window, int hshift, FilterState flt, KvView kv) {
-    static_assert(!(SCORE && SPARSE), "scores are emitted by the pass over all tokens");
-    static_assert(!FILTER || SCORE, "the filter is a form of the scoring variant");
-    static_assert(!ONLY_SCORES || (SCORE && !FILTER), "scores only: the dense scoring variant without the attention");
+    int window, int hshift, FilterState flt, KvView kv) {
+    static_assert(!(FILTER && SPARSE), "candidates are kept by the pass over all tokens");
+    static_assert(!FILTER || GQ <= 4, "the filtered pass of a group of 8 does not fit the register file");
     static_assert(!PER_HEAD || (SPARSE && GQ == 1), "per-head token lists: one query head per workgroup");
     constexpr int TILE = TI * 4;                      // tokens per wave iteration (<= 64)
     constexpr int WG_TILE = TILE * ATTN_WAVES;
@@ -2014,15 +2026,15 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     constexpr int QSB = 136;                          // padded head stride of q in LDS (bf16 elements)
     // A wave's K tile buffer (TILE rows of 256 bytes) also carries its partial accumulators
     // (GQ x 128 floats) into the final merge.
-    // The scoring variant parks a tile's K rows in two halves of 64 columns, one after the other (its
-    // product chain walks the columns in order anyway), which leaves LDS for the scores of the
-    // workgroup's whole run (pstage below).
-    constexpr int KSLOTS = SCORE ? 8 : 16;            // 16-byte slots of a K row held in LDS at a time
+    // The filtered form parks a tile's K rows in two halves of 64 columns, one after the other (its
+    // product chain walks the columns in order anyway), which leaves LDS for the candidates of the
+    // workgroup's whole run (cstage below).
+    constexpr int KSLOTS = FILTER ? 8 : 16;            // 16-byte slots of a K row held in LDS at a time
     constexpr int WAVE_LDS = TILE * KSLOTS * 16;      // bytes of a wave's tile buffer
     static_assert(WAVE_LDS >= GQ * D * 4, "the K tile buffer must hold a wave's partial accumulators");
     __shared__ __attribute__((aligned(16))) unsigned char smem_raw[ATTN_WAVES * WAVE_LDS];
     // this wave's K rows: chunk c of row r at slot c ^ (r & 7) (a swizzle over all sixteen slots, c ^ (r & 15),
-    // removes the remaining two-way bank conflicts and was measured: no faster); scoring variant: chunk c
+    // removes the remaining two-way bank conflicts and was measured: no faster); filtered form: chunk c
     // (of the half) at slot c ^ ((r >> 1) & 7)
     u32x4* const ktile = reinterpret_cast<u32x4*>(smem_raw) + wave_base_of(threadIdx.x) * (TILE * KSLOTS);
     __shared__ float sm_m[ATTN_WAVES][GQ];
@@ -2033,31 +2045,23 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     // together (rows 4ig .. 4ig+3 of its row group) are one 8-byte word.
     static_assert(TI % 4 == 0 && WAVE_LDS >= TI * SETS * 32, "the numerators must fit the K tile buffer");
     __bf16* const pbuf16 = reinterpret_cast<__bf16*>(ktile);
-    // q in LDS: a private bf16 copy per wave, or -- in the scoring variant, whose product chain takes
+    // q in LDS: a private bf16 copy per wave, or -- in the filtered form, whose product chain takes
     // binary32 operands -- one binary32 copy for the workgroup (every wave writes all of it with the
     // same values, so a wave depends on its own writes only and no workgroup barrier is needed).
     constexpr int QSF = 132;                          // padded head stride of the binary32 copy (floats)
-    __shared__ __attribute__((aligned(16))) uint16_t qlds_all[SCORE ? 1 : ATTN_WAVES][SCORE ? 8 : SETS * 4 * QSB];
-    __shared__ __attribute__((aligned(16))) float qf32[SCORE ? SETS * 4 * QSF : 4];
-    // scoring variant: the scores of the workgroup's run (of its last STAGE_IT iterations, should a run be
-    // longer: the host caps it at STAGE_TOK tokens), [head][token], on their way to P
-    constexpr int STAGE_TOK = GQ >= 8 ? ATTN_SCORE_CHUNK_CAP_G8 : ATTN_SCORE_CHUNK_CAP;   // 32 KB at groups of 4 and 8
-    constexpr int STAGE_IT = STAGE_TOK / WG_TILE;
-    __shared__ __attribute__((aligned(16))) float pstage[SCORE ? GQ * STAGE_TOK : 4];
-    // Filtered form of the scoring variant (FILTER; see sample_threshold_kernel): instead of every score,
-    // the buffer takes the (score key, position) composites of the candidates at or above the head's
-    // threshold, compacted per head -- STAGE_CAND of them per head at most, or the head is flagged.
-    constexpr int STAGE_CAND = STAGE_TOK / 2;         // composites are twice a score's size
-    uint64_t* const cstage = reinterpret_cast<uint64_t*>(pstage);
-    __shared__ int cand_n[SCORE ? GQ : 1], cand_base[SCORE ? GQ : 1];
-    __shared__ uint32_t thr_lds[SCORE ? GQ : 1];
-    constexpr bool filtered = FILTER;
+    __shared__ __attribute__((aligned(16))) uint16_t qlds_all[FILTER ? 1 : ATTN_WAVES][FILTER ? 8 : SETS * 4 * QSB];
+    __shared__ __attribute__((aligned(16))) float qf32[FILTER ? SETS * 4 * QSF : 4];
+    // FILTER: the (score key, position) composites of the run's candidates (of its last STAGE_IT iterations' ones, should a run
+    // be longer: the host caps it at ATTN_SCORE_CHUNK_CAP tokens) at or above the head's threshold, compacted per head --
+    // STAGE_CAND of them per head at most, or the head is flagged -- on their way to the head's list.
+    constexpr int STAGE_IT = ATTN_SCORE_CHUNK_CAP / WG_TILE;
+    constexpr int STAGE_CAND = ATTN_SCORE_CHUNK_CAP / 2;
+    __shared__ __attribute__((aligned(16))) uint64_t cstage[FILTER ? GQ * STAGE_CAND : 2];
+    __shared__ int cand_n[FILTER ? GQ : 1], cand_base[FILTER ? GQ : 1];
+    __shared__ uint32_t thr_lds[FILTER ? GQ : 1];
     // Workgroups go to the 8 XCDs round-robin in launch order (blockIdx.x fastest).  With ragged
     // lengths the low splits are the busy ones; starting each (sequence, KV head) at a different
     // block spreads them evenly over the XCDs instead of loading the first ones.
-    if constexpr (ONLY_SCORES) {                         // the second chance with nothing flagged: out before any other load is asked for
-        if (flt.fail && *flt.n_failed == 0) return;
-    }
     const int gy = blockIdx.y, b = blockIdx.z, H = G * GQ;
     const int kvh = PER_HEAD ? gy >> hshift : gy;
     const int split = (int)((blockIdx.x + gy + G * b) % (unsigned)n_splits);
@@ -2084,7 +2088,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     // Every wave keeps its own bf16 copy of q in LDS (no workgroup barrier on the way in): lane l
     // fetches 16 bytes of head l / 16 per set now and parks them once the first tile's loads are
     // under way.  Heads beyond GQ score zero.
-    uint16_t* const qlds = qlds_all[SCORE ? 0 : wave];
+    uint16_t* const qlds = qlds_all[FILTER ? 0 : wave];
     u32x4 qv[SETS];
 #pragma unroll
     for (int s = 0; s < SETS; ++s) {
@@ -2094,16 +2098,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     }
     bool q_parked = false;
     const int L = seq_lens[b];
-    if constexpr (ONLY_SCORES) {
-        if (L <= budget) return;                         // rho is every token: nothing is scored
-        if (flt.fail) {                                  // the second chance: flagged heads' groups only
-            int any = 0;
-#pragma unroll
-            for (int h = 0; h < GQ; ++h) any |= flt.fail[head0 + h];
-            if (!any) return;
-        }
-    }
-    const int n = SPARSE ? min(cnt[b], budget) : ONLY_SCORES ? L - window : L;   // scores only: the candidate range
+    const int n = SPARSE ? min(cnt[b], budget) : L;
     // Everything the first tile's addresses depend on is requested above and has to be here
     // before the first branch; otherwise the compiler sinks each load behind the branch that
     // precedes its first use and the kernel starts with a chain of dependent memory round trips.
@@ -2137,12 +2132,12 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     // Rows past the end of the run read some token of the sequence (a valid row) so that all
     // loads are unconditional and issue back to back; their scores are masked below.
     // The next tile's K rows are requested as soon as this tile's are parked in LDS, i.e. before
-    // this tile's arithmetic (not in the scoring variant, whose 64-token tiles leave no registers
+    // this tile's arithmetic (not in the filtered form, whose 64-token tiles leave no registers
     // for it; there the rows are requested at the top of the tile's own iteration).
-    constexpr bool PREFETCH = !SCORE;
-    // The scoring variant of a group of 8 has no registers for K and V rows at once (64 each at 64-token
-    // tiles, beside 64 accumulators): its V rows are requested once the K rows are parked in LDS.
-    constexpr bool V_LATE = !ONLY_SCORES && SCORE && (GQ >= 8 || (FILTER && GQ >= 4));
+    constexpr bool PREFETCH = !FILTER;
+    // The filtered form of a group of 4 has no registers for K and V rows at once (64 each at 64-token
+    // tiles): its V rows are requested once the K rows are parked in LDS.
+    constexpr bool V_LATE = FILTER && GQ >= 4;
     u32x4 kreg[TI], vreg[TI];
     int64_t off[TI];
     // a valid position for row load i of the tile that starts at list entry t_ (an index outside the
@@ -2188,35 +2183,6 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
         request_k();
         advance(tile0);
     }
-    // Scoring variant: the scores go to P through a staging buffer in LDS that the whole workgroup
-    // writes out in one burst.  A few per cent of small writes scattered
-    // through a streaming read cost this machine a sixth of its read rate; the same bytes written in
-    // workgroup-sized bursts cost a third of that (measured with plain read / write kernels).  The
-    // burst is issued at the end of the workgroup's run (the host caps a run at STAGE_TOK tokens; a
-    // longer one would take a burst every STAGE_IT iterations, before the next tile's rows are
-    // requested).  Measured on the selection pass, us without stores / scattered stores / bursts:
-    // c3 95 / 106 / 99, c4 100 / 121 / 106, c5 867 / 1036 / 1008.  Giving every workgroup its own
-    // burst phase, so that the chip's bursts do not coincide, was measured too and is slower.
-    auto flush_scores = [&](int g0, int n_tok) {       // staged tokens [g0, g0 + n_tok) of this workgroup's run
-        if constexpr (SCORE) {
-            const int lim = min(end, L - window);      // candidates only; L <= budget: rho is every token, nothing is scored
-            if (L > budget && g0 < lim) {
-                const int quads = n_tok >> 2;
-                for (int i = tid; i < GQ * quads; i += ATTN_THREADS) {
-                    const int h = i / quads, w4 = (i - h * quads) * 4, t = g0 + w4;
-                    const f32x4 v = *reinterpret_cast<const f32x4*>(&pstage[h * STAGE_TOK + w4]);
-                    float* const dst = &P[(head0 + h) * ldp + t];
-                    if (t + 3 < lim) {
-                        __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(dst));
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (t + e < lim) dst[e] = v[e];
-                    }
-                }
-            }
-        }
-    };
     // filtered form: the staged candidates of every head go to the head's list in memory, one reservation
     // per head and workgroup.  The reservation is a device-scope atomic whose answer takes microseconds:
     // reserve_candidates asks (thread h for head h; returns the answer, -1 if there is nothing to copy),
@@ -2224,7 +2190,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     // and writes its attention partials in between.  Both are called by the whole workgroup.
     auto reserve_candidates = [&]() -> int {
         int base = -1;
-        if constexpr (SCORE) {
+        if constexpr (FILTER) {
             lds_barrier();                               // every wave's candidates are staged
             if (tid < GQ) {
                 const int n_h = cand_n[tid];
@@ -2235,7 +2201,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
         return base;
     };
     auto copy_candidates = [&](int base) {
-        if constexpr (SCORE) {
+        if constexpr (FILTER) {
             if (tid < GQ) {
                 if (base >= 0 && base + cand_n[tid] > flt.cap) {   // the head's list is full (the count stays above cap: the ranking sees it too)
                     flag_failed(flt, head0 + tid);
@@ -2269,23 +2235,15 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     int it = 0;                                          // iterations of the workgroup so far
     for (int w0 = begin; w0 < end; w0 += WG_TILE, ++it) {
         const int t0 = w0 + wave * TILE;
-        // Only the scoring variant has workgroup barriers inside the loop; there a wave whose tile lies
+        // Only the filtered form has workgroup barriers inside the loop; there a wave whose tile lies
         // past the run's end still takes part in them.
         const bool active = t0 < end;
-        // workgroup-uniform; the buffer holds STAGE_IT iterations at most
-        const bool burst_due = SCORE && it - it_staged == STAGE_IT;
-        if (burst_due) {
-            if (filtered) {
-                copy_candidates(reserve_candidates());
-            } else {
-                lds_barrier();                           // every wave's scores since the last burst are staged
-                flush_scores(begin + it_staged * WG_TILE, (it - it_staged) * WG_TILE);
-                lds_barrier();                           // ... and read, before the buffer is written again
-            }
+        if (FILTER && it - it_staged == STAGE_IT) {      // workgroup-uniform
+            copy_candidates(reserve_candidates());
             it_staged = it;
         }
         if (!active) {
-            if constexpr (!SCORE) break;
+            if constexpr (!FILTER) break;
             continue;
         }
         if constexpr (!PREFETCH) {
@@ -2294,7 +2252,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
             // order, so the scores are under way while the V rows are still arriving.
             request_k();
         }
-        if constexpr (!V_LATE && !ONLY_SCORES) {
+        if constexpr (!V_LATE) {
 #pragma unroll
             for (int i = 0; i < TI; ++i) vreg[i] = row_load<PER_HEAD>(kv.v + off[i]);
         }
@@ -2303,7 +2261,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
         if (!q_parked) {
 #pragma unroll
             for (int s = 0; s < SETS; ++s) {
-                if constexpr (SCORE) {
+                if constexpr (FILTER) {
                     float qf[8];
                     unpack8(make_uint4(qv[s].x, qv[s].y, qv[s].z, qv[s].w), qf);
                     float* const dst = &qf32[(s * 4 + r) * QSF + c * 8];
@@ -2315,7 +2273,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
             }
             q_parked = true;
         }
-        if constexpr (!SCORE) {
+        if constexpr (!FILTER) {
 #pragma unroll
             for (int i = 0; i < TI; ++i) {
                 const int row = i * 4 + r;
@@ -2333,7 +2291,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
         f32x4 sc[SETS];
 #pragma unroll
         for (int s = 0; s < SETS; ++s) sc[s] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        if constexpr (SCORE) {
+        if constexpr (FILTER) {
             // columns 0..63, then 64..127: the lanes holding that half of a row park it, every lane then
             // walks its own token's 64 columns in order
 #pragma unroll
@@ -2383,7 +2341,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
                             sc[s] = __builtin_amdgcn_mfma_f32_4x4x1f32(qf[s][e], kf[e], sc[s], 0, 0, 0);
                 }
             }
-            if (filtered) {
+            {
                 const int t = t0 + tl;
                 const bool is_cand = lane < TILE && t >= flt.n_sink && t < min(end, L - window);
 #pragma unroll
@@ -2400,9 +2358,6 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
                     }
                     asm volatile("" ::: "memory");       // one head at a time: nothing of the next is fetched early
                 }
-            } else if (lane < TILE) {
-#pragma unroll
-                for (int h = 0; h < GQ; ++h) pstage[h * STAGE_TOK + (it - it_staged) * WG_TILE + wave * TILE + tl] = sc[h >> 2][h & 3];
             }
         } else {
 #pragma unroll
@@ -2419,10 +2374,6 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
                     }
                 }
             }
-        }
-        if constexpr (ONLY_SCORES) {
-            wave_lds_sync();                              // the tile buffer is rewritten next iteration
-            continue;
         }
         const bool valid = t0 + tl < end;
         float corr[GQ];
@@ -2478,15 +2429,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
         wave_lds_sync();                              // the tile buffers are rewritten next iteration
     }
     int cand_reserved = -1;
-    if constexpr (SCORE) {
-        if (filtered) {
-            cand_reserved = reserve_candidates();        // used after the merge below
-        } else if (it > it_staged) {                   // the iterations staged since the last burst
-            lds_barrier();
-            flush_scores(begin + it_staged * WG_TILE, (it - it_staged) * WG_TILE);
-        }
-    }
-    if constexpr (ONLY_SCORES) return;
+    if constexpr (FILTER) cand_reserved = reserve_candidates();   // used after the merge below
     // Merge.  Inside the wave the four row groups are folded with lane swaps: of the N = 8 GQ
     // values of a lane, two folds leave N / 4 complete sums, those with flat index (head * 8 +
     // column) v0 .. v0 + N/4 - 1 where v0 depends on the row group.  The wave parks them in its
@@ -2552,6 +2495,398 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
         }
     }
     if constexpr (FILTER) copy_candidates(cand_reserved);
+}
+
+// ---------------------------------------------------------------- scoring pass
+//
+// P[b][h][t] = q_h . K_t, grid (n_splits, G, B), 256 threads.  A workgroup takes the tokens of its run (chunk) of one
+// (sequence, KV head) a workgroup tile at a time, a wave TI * 4 of them.  A K row is read by 16 lanes with one 16-byte load each;
+// the wave parks its rows in LDS in two halves of 64 columns (8 KB instead of 16 per 64 tokens: the product chain walks the
+// columns in order anyway) and every lane reads its own token's columns back.  The tile's scores take the place of its rows and are
+// written by the whole workgroup, 1 KB of a head at a time.
+//
+// What bounds it is memory, if enough loads are in flight while tiles are worked on.  Nothing is requested ahead inside a
+// workgroup: runs are one tile long and four workgroups share a CU, 256 KB of rows, whose waits and arithmetic overlap.
+// Measured against two workgroups with runs of 512 to 2048 tokens, q in registers and the next tile's rows on their way
+// (us; 8 pairs of 32768, 64 of 16384, 8 of 131072 with groups of 8): 16.1, 47.2, 63.3 -> 14.5, 46.2, 53.0; with both tiles' rows
+// in registers 17.3, 49.6, 61.2.
+//
+// all: every token of every sequence is scored (a selection layer, whose values weigh them all); otherwise the
+// candidate range [0, L - window) of the sequences longer than the budget (cusa_select, the filtered selection's second
+// chance: with flt.fail set only the groups that have a flagged head, and nothing when the counter is 0).
+// keep: P is small enough for the last-level cache to hold until the top-k reads it (ordinary stores, SCORE_KEEP_BYTES).
+template <int GQ, int TI, bool PAGED>
+__global__ __launch_bounds__(ATTN_THREADS, 4) void score_kernel(const int32_t* __restrict__ seq_lens, const uint16_t* __restrict__ q,
+                                                                 int budget, int window, int n_splits, int chunk, int G, int all,
+                                                                 int keep, float* __restrict__ P, int64_t ldp, FilterState flt, KvView kv) {
+    constexpr int TILE = TI * 4, WG_TILE = TILE * ATTN_WAVES;
+    constexpr int SETS = (GQ + 3) / 4;
+    constexpr int QSF = 132;                          // padded head stride of q in LDS (floats)
+    static_assert(GQ * TILE * 4 <= TILE * 128, "a tile's scores take the place of its rows");
+    __shared__ __attribute__((aligned(16))) u32x4 ktile_all[ATTN_WAVES][TILE * 8];   // chunk c of a row's half at slot c ^ ((row >> 1) & 7)
+    __shared__ __attribute__((aligned(16))) float qf32[SETS * 4 * QSF];   // binary32; every wave writes all of it, no barrier
+    if (!all && flt.fail && *flt.n_failed == 0) return;
+    const int kvh = blockIdx.y, b = blockIdx.z;
+    // workgroups go to the 8 XCDs round-robin: short sequences' idle ones are spread over them
+    const int split = (int)((blockIdx.x + kvh + G * b) % (unsigned)n_splits);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t head0 = ((int64_t)b * G + kvh) * GQ;
+    const int begin = split * chunk;
+    const int L = uniform_load(seq_lens + b);
+    if (!all) {
+        if (L <= budget) return;                      // rho is every token: nothing is scored
+        if (flt.fail) {
+            int any = 0;
+#pragma unroll
+            for (int h = 0; h < GQ; ++h) any |= flt.fail[head0 + h];
+            if (!any) return;
+        }
+    }
+    const int n = all ? L : L - window;
+    if (begin >= n) return;
+    const int last = min(begin + chunk, n) - 1;
+    u32x4* const ktile = ktile_all[wave];
+    float* const stage = reinterpret_cast<float*>(ktile);   // [GQ][TILE]
+    int my_lane = lane;
+    for (int w0 = begin; w0 <= last; w0 += WG_TILE) {
+        const int t0 = w0 + wave * TILE;
+        asm volatile("" : "+v"(my_lane));             // what is made of it is made where it is needed: there are no registers to keep it
+        const int r = my_lane >> 4, c = my_lane & 15;
+        u32x4 qv[SETS];                               // lane: 16 bytes of head 4s + r; heads beyond the group score zero
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) {
+            const int h = s * 4 + r;
+            qv[s] = *reinterpret_cast<const u32x4*>(q + (head0 + (h < GQ ? h : 0)) * D + c * 8);
+            if (h >= GQ) qv[s] = u32x4{0u, 0u, 0u, 0u};
+        }
+        // rows past the end of the run are its last token's; their scores are not written
+        u32x4 kreg[TI];
+#pragma unroll
+        for (int ig = 0; ig < TI / 4; ++ig) {         // 16 rows: one page
+            if constexpr (PAGED) {
+                const int first = min(t0 + 16 * ig, last & ~15), rows = last - first;
+                const int64_t page = uniform_load(kv.bt + (int64_t)b * kv.max_pages + (first >> 4));
+                const uint16_t* const at = kv.k + (page * kv.G + kvh) * (PAGE * D);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) kreg[4 * ig + i] = stream_load(at + (uint32_t)(min(i * 4 + r, rows) * D + c * 8));
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int pos = min(t0 + (4 * ig + i) * 4 + r, last);
+                    kreg[4 * ig + i] = stream_load(kv.k + ((int64_t)b * kv.sb + (int64_t)kvh * kv.sh + (int64_t)pos * kv.st + c * 8));
+                }
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) {              // (again for every tile, with the same values: a run is one as a rule)
+            float qf[8];
+            unpack8(make_uint4(qv[s].x, qv[s].y, qv[s].z, qv[s].w), qf);
+            float* const dst = &qf32[(s * 4 + r) * QSF + c * 8];
+            *reinterpret_cast<f32x4*>(dst) = f32x4{qf[0], qf[1], qf[2], qf[3]};
+            *reinterpret_cast<f32x4*>(dst + 4) = f32x4{qf[4], qf[5], qf[6], qf[7]};
+        }
+        const int tl = my_lane % TILE;                // the token of the tile that this lane scores
+        f32x4 sc[SETS];
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) sc[s] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            if (half) wave_lds_sync();                // the first half has been read
+            if ((c >> 3) == half) {
+#pragma unroll
+                for (int i = 0; i < TI; ++i) {
+                    const int row = i * 4 + r;
+                    ktile[row * 8 + ((c & 7) ^ ((row >> 1) & 7))] = kreg[i];
+                }
+            }
+            wave_lds_sync();
+#pragma unroll
+            for (int c8 = 0; c8 < 8; ++c8) {
+                const int cc = half * 8 + c8;
+                const u32x4 kw = ktile[tl * 8 + (c8 ^ ((tl >> 1) & 7))];
+                float kf[8];
+                unpack8(make_uint4(kw.x, kw.y, kw.z, kw.w), kf);
+                float qf[SETS][8];
+#pragma unroll
+                for (int s = 0; s < SETS; ++s) {
+                    const float* const src = &qf32[(s * 4 + (my_lane & 3)) * QSF + cc * 8];
+                    const f32x4 qa = *reinterpret_cast<const f32x4*>(src), qb = *reinterpret_cast<const f32x4*>(src + 4);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        qf[s][e] = qa[e];
+                        qf[s][4 + e] = qb[e];
+                    }
+                }
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+#pragma unroll
+                    for (int s = 0; s < SETS; ++s) sc[s] = __builtin_amdgcn_mfma_f32_4x4x1f32(qf[s][e], kf[e], sc[s], 0, 0, 0);
+                if (SETS == 2 || (c8 & 1)) __builtin_amdgcn_sched_barrier(0);   // (no further ahead: registers)
+            }
+        }
+        wave_lds_sync();                              // the rows have been read
+        asm volatile("" : "+v"(my_lane));
+        if (my_lane < TILE) {
+#pragma unroll
+            for (int h = 0; h < GQ; ++h) stage[h * TILE + my_lane] = sc[h >> 2][h & 3];
+        }
+        lds_barrier();
+        constexpr int QUADS = WG_TILE / 4;
+        for (int i = wave * 64 + my_lane; i < GQ * QUADS; i += ATTN_THREADS) {
+            const int h = i / QUADS, w4 = (i % QUADS) * 4, t = w0 + w4;
+            const f32x4 v = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(ktile_all[w4 / TILE]) + h * TILE + w4 % TILE);
+            float* const dst = &P[(head0 + h) * ldp + t];
+            if (t + 3 <= last) {
+                if (keep) *reinterpret_cast<f32x4*>(dst) = v;   // uniform
+                else __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(dst));
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (t + e <= last) dst[e] = v[e];
+            }
+        }
+        if (w0 + WG_TILE <= last) lds_barrier();      // read, before the tile buffers are written again
+    }
+}
+
+// ---------------------------------------------------------------- a selection layer's values
+//
+// out = softmax(scale * P) V for the scores P that score_kernel left: the second half of a selection layer's full attention.
+// It does not enter the selection, so its workgroups share a launch with the top-k's (topk_values_kernel): those keep a CU
+// each busy with latencies, these stream V meanwhile.
+//
+// A workgroup of 16 waves owns a run of tokens of one (sequence, KV head); a wave takes tiles of 16 tokens: 16 lanes per 256-byte
+// row, four row loads.  Lane (row group r, t) weighs token t for the r-th part of the group's heads; the weights go through LDS, as
+// bf16, into the A operand of V_MFMA_F32_16X16X16_BF16, one instruction for each of the lane's eight columns: after two V_PERM_B32 a lane
+// holds one column of its four rows.  A tile's scores are requested before its rows (loads return in order), so that the weights are made while
+// the rows arrive.  The weights are 2^x as the hardware has it: what it flushes to zero is below 2^-126 of the largest.
+//
+// What bounds it is memory and, for that, bytes in flight: a CU has at most about 64 KB of misses on their way, so half of the CUs do not saturate
+// the memory (128 of them: 4.5 TB/s of 6.5).  Hence 64 registers, tiles of 4 KB for each of 16 waves, and two workgroups to a CU, so that a row
+// of the top-k and a run of values share one (8 sequences of 16384, 32 heads: values in 128 registers, alone on their CUs, 57 - 61 us
+// for the launch, so 51; the values alone 49, the rows alone 14).
+// Measured (us for the layer; one pass for scores and output, then the top-k -> so): 1 sequence, 32 heads, of 4096 21.7 -> 19.6, of 32768
+// 50.1 -> 38.9; 8 of 16384 119.1 -> 115.5; 64 heads of 131072 144.6 -> 124.0.
+struct ValueArgs {
+    const float* P;
+    int64_t ldp;
+    float scale_log2e;
+    float* part_acc;
+    float* part_ml;
+    uint16_t* out;
+    int n_splits, chunk;      // chunk: a multiple of VALUE_WG_TILE tokens
+    int g, paged;             // g: query heads per KV head
+    int items;                // workgroups
+    KvView kv;
+};
+constexpr int VALUE_TILE = 16;
+constexpr int64_t VALUE_MAX_STEP = (int64_t)1 << 26;   // elements between tokens: a lane's distance from its group's first row fits 32 bits
+constexpr int VALUE_WG_TILE = VALUE_TILE * SEL_WAVES;
+struct ValueLds {
+    float m[SEL_WAVES][8], l[SEL_WAVES][8];
+};
+template <int GQ>
+constexpr size_t value_lds_bytes() { return (size_t)SEL_WAVES * GQ * D * 4; }
+
+template <int GQ>
+__device__ __forceinline__ void weigh_values(const ValueArgs& a, int item, float* sums_lds, ValueLds& st) {
+    constexpr int TI = VALUE_TILE / 4;
+    constexpr int HPL = GQ >= 4 ? GQ / 4 : 1;         // heads a lane weighs: those from head (row group % ROWS_USED) * HPL on
+    constexpr int HROWS = GQ / HPL;                   // row groups that weigh different heads
+    const int wave = __builtin_amdgcn_readfirstlane(wave_id());
+    const int pair = item / a.n_splits;
+    const int kvh = pair % a.kv.G, b = pair / a.kv.G;
+    const int split = (item + pair) % a.n_splits;     // short sequences' idle workgroups: spread over the XCDs
+    const int L = uniform_load(a.kv.seq_lens + b);
+    const int begin = split * a.chunk;
+    if (split > 0 && begin >= L) return;
+    const int last = min(begin + a.chunk, L) - 1;
+    const int64_t head0 = ((int64_t)b * a.kv.G + kvh) * GQ;
+    float* const wsum = sums_lds + wave * (GQ * D);   // [GQ][D], this wave's; before that its weights:
+    __bf16* const wbuf = reinterpret_cast<__bf16*>(wsum);   // [head][row group][row load], the A operand's order
+    int my_lane = lane_id();
+    const float* const prow = a.P + head0 * a.ldp;
+    float m[HPL], l[HPL], p[HPL];
+    f32x4 acc[8];                                     // column 8c + e; heads 4r .. 4r+3
+#pragma unroll
+    for (int j = 0; j < HPL; ++j) {
+        m[j] = -INFINITY;
+        l[j] = 0.0f;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    // A tile is 16 rows (a page): the address of its first row is uniform, a lane adds its row's distance from it, rows
+    // past the end of the run that of its last token.
+    const uint32_t row_bytes = 2u * (uint32_t)(a.paged ? D : a.kv.st);   // (VALUE_MAX_STEP)
+    u32x4 v[TI];
+    int pg = 0;                                       // page of the tile to be requested next
+    auto page_load = [&](int t_) {
+        if (a.paged) pg = uniform_load(a.kv.bt + (int64_t)b * a.kv.max_pages + (min(t_, last) >> 4));
+    };
+    auto request_p = [&](int t_) {
+        asm volatile("" : "+v"(my_lane));             // (no registers for what can be made of it)
+        const uint32_t heads = (uint32_t)((my_lane >> 4) & (HROWS - 1)) * (uint32_t)(HPL * a.ldp);   // (a sequence's length is capped by the host)
+        const uint32_t at = 4u * (heads + (uint32_t)min(t_ + (my_lane & 15), last));
+#pragma unroll
+        for (int j = 0; j < HPL; ++j) {
+            uint64_t base = reinterpret_cast<uint64_t>(prow + j * a.ldp);
+            asm volatile("" : "+s"(base));            // (scalar base and 32-bit distance: no 64-bit sums in vector registers)
+            p[j] = *reinterpret_cast<const __attribute__((address_space(1))) float*>(reinterpret_cast<const __attribute__((address_space(1))) char*>(base) + at);
+        }
+    };
+    auto request_v = [&](int t_) {
+        asm volatile("" : "+v"(my_lane));
+        const int rows = last - t_;
+        const int64_t off = a.paged ? ((int64_t)pg * a.kv.G + kvh) * (PAGE * D) : (int64_t)b * a.kv.sb + (int64_t)kvh * a.kv.sh + (int64_t)t_ * a.kv.st;
+        const char* const at = reinterpret_cast<const char*>(a.kv.v + off);
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+            v[i] = stream_load(reinterpret_cast<const uint16_t*>(at + ((uint32_t)min(i * 4 + (my_lane >> 4), rows) * row_bytes + 16u * (uint32_t)(my_lane & 15))));
+    };
+    int t0 = begin + wave * VALUE_TILE;
+    page_load(t0);
+    if (t0 <= last) {
+        request_p(t0);
+        request_v(t0);
+        page_load(t0 + VALUE_WG_TILE);
+    }
+    for (; t0 <= last; t0 += VALUE_WG_TILE) {
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" : "+v"(my_lane));
+        // lane (r, t) weighs token t; token t is row load t / 4 of row group t % 4
+        const int t = my_lane & 15, r = my_lane >> 4;
+        __bf16* const put = wbuf + (r & (HROWS - 1)) * (HPL * VALUE_TILE) + (t & 3) * TI + (t >> 2);
+        float corr[HPL];
+        bool same = true;
+#pragma unroll
+        for (int j = 0; j < HPL; ++j) {
+            const float z = t0 + t <= last ? p[j] * a.scale_log2e : -INFINITY;
+            const float m_new = fmaxf(m[j], row_max16(z));   // finite: the tile's first token is valid
+            corr[j] = __builtin_amdgcn_exp2f(m[j] - m_new);
+            same = same && __ballot(m_new != m[j]) == 0;
+            m[j] = m_new;
+            // the weight enters numerator and denominator as the same bf16 value
+            const __bf16 pb = (__bf16)__builtin_amdgcn_exp2f(z - m_new);
+            put[j * VALUE_TILE] = pb;                 // (row groups that repeat a head's weights write the same)
+            l[j] = l[j] * corr[j] + (float)pb;
+        }
+        const bool more = t0 + VALUE_WG_TILE <= last;
+        // ahead of the rows: the weights are made while these arrive (a group of 8 has no registers for that so early)
+        if (GQ < 8 && more) request_p(t0 + VALUE_WG_TILE);
+        if (!same) {                                  // uniform; rare after the first tiles
+#pragma unroll
+            for (int hh = 0; hh < (GQ < 4 ? GQ : 4); ++hh) {
+                // head 4r + hh: its factor is with the lanes that weigh it
+                const float f0 = lane_value(corr[hh % HPL], (hh / HPL) * 16);
+                const float f1 = GQ == 8 ? lane_value(corr[hh % HPL], (hh / HPL) * 16 + 32) : f0;
+                const float g = r & 1 ? f1 : f0;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[e][hh] *= g;
+            }
+        }
+        wave_lds_sync();
+        // rows of A beyond the group repeat its heads
+        const s16x4 wa = *reinterpret_cast<const s16x4*>(wbuf + (my_lane & (GQ - 1)) * VALUE_TILE + r * TI);
+        // the same column of the lane's four rows
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const uint32_t pick = e & 1 ? 0x07060302u : 0x05040100u;
+            const uint2 col = make_uint2(__builtin_amdgcn_perm(v[1][e >> 1], v[0][e >> 1], pick), __builtin_amdgcn_perm(v[3][e >> 1], v[2][e >> 1], pick));
+            acc[e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wa, __builtin_bit_cast(s16x4, col), acc[e], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (more) {
+            if (GQ >= 8) request_p(t0 + VALUE_WG_TILE);
+            request_v(t0 + VALUE_WG_TILE);
+            page_load(t0 + 2 * VALUE_WG_TILE);
+        }
+        wave_lds_sync();                              // the weights are rewritten next time
+    }
+    asm volatile("" : "+v"(my_lane));
+    const int tid = wave * 64 + my_lane;
+    // The waves' sums meet in LDS: lanes of row group r hold heads 4r .. 4r+3.
+    {
+        const int r = (tid >> 4) & 3, c = tid & 15;
+        if (4 * r < GQ) {
+#pragma unroll
+            for (int hh = 0; hh < (GQ < 4 ? GQ : 4); ++hh) {
+                float* const dst = wsum + (4 * r + hh) * D + c * 8;
+                *reinterpret_cast<f32x4*>(dst) = f32x4{acc[0][hh], acc[1][hh], acc[2][hh], acc[3][hh]};
+                *reinterpret_cast<f32x4*>(dst + 4) = f32x4{acc[4][hh], acc[5][hh], acc[6][hh], acc[7][hh]};
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < HPL; ++j) {
+        const float ls = row_sum16(l[j]);
+        const int r = (tid >> 4) & 3;
+        if ((tid & 15) == 0 && r < HROWS) {
+            st.m[wave][r * HPL + j] = m[j];
+            st.l[wave][r * HPL + j] = ls;
+        }
+    }
+    __syncthreads();
+    for (int o = tid; o < GQ * D; o += SEL_THREADS) {
+        const int h = o / D, col = o % D;
+        float M = st.m[0][h];
+#pragma unroll
+        for (int wv = 1; wv < SEL_WAVES; ++wv) M = fmaxf(M, st.m[wv][h]);
+        float A = 0.0f, Ls = 0.0f;
+#pragma unroll 4
+        for (int wv = 0; wv < SEL_WAVES; ++wv) {
+            const float mw = st.m[wv][h];
+            const float f = (mw == -INFINITY) ? 0.0f : exp2f(mw - M);
+            A = __builtin_fmaf(sums_lds[wv * (GQ * D) + o], f, A);
+            Ls = __builtin_fmaf(st.l[wv][h], f, Ls);
+        }
+        if (L <= a.chunk) {                           // this workgroup saw all tokens
+            a.out[(head0 + h) * D + col] = f32_to_bf16_rne(Ls > 0.0f ? A / Ls : 0.0f);
+        } else {
+            const int64_t p_ = (head0 + h) * a.n_splits + split;
+            a.part_acc[p_ * D + col] = A;
+            if (col == 0) {
+                a.part_ml[p_ * 2] = M;
+                a.part_ml[p_ * 2 + 1] = Ls;
+            }
+        }
+    }
+}
+
+// The top-k over whole rows and the values in one launch, 1-D grid of n_topk + va.items workgroups.  Rows and runs take turns of 256, a
+// workgroup for every CU (where there are as many), what is left of either comes at the end: the dispatcher hands out workgroups strictly in order
+// and in turn to the shader engines, so with a shorter turn all rows meet in a few engines and what follows them waits for a place elsewhere
+// (turns of 8: 120 CUs idle for 18 of 64 us).
+template <int ITEMS, int MTOP, bool GROUP8>
+__global__ __launch_bounds__(SEL_THREADS, topk_lean(ITEMS, MTOP) ? 8 : 4) void topk_values_kernel(const float* __restrict__ P, int64_t ldp,
+                                                                      const int32_t* __restrict__ seq_lens,
+                                                                      int32_t* __restrict__ rho_head, int H, int k, int budget,
+                                                                      int window, int n_sink, int B, ValueArgs va) {
+    extern __shared__ uint64_t sort_buf[];
+    const int n_topk = H * B, x = blockIdx.x, turns = min(n_topk, va.items) / 256 * 256;
+    int i = x - turns;                                // past the alternating part: first the rest of the one, then of the other kind
+    bool values = i >= n_topk;
+    if (x < 2 * turns) {
+        values = (x >> 8) & 1;
+        i = (x >> 9) * 256 + (x & 255);
+    } else if (values) {
+        i -= n_topk - turns;
+    }
+    if (!values) {
+        topk_row<ITEMS, MTOP, false>(i, 0, B, P, ldp, seq_lens, rho_head, H, k, budget, window, 0, n_sink, nullptr, 0, 1, nullptr,
+                                     FilterState{}, SliceLists{});
+        return;
+    }
+    __shared__ ValueLds st;
+    float* const lds = reinterpret_cast<float*>(sort_buf);
+    if constexpr (GROUP8) {                           // (its registers are too few beside the other groups' code)
+        weigh_values<8>(va, i, lds, st);
+    } else {
+        if (va.g == 4) weigh_values<4>(va, i, lds, st);   // uniform
+        else if (va.g == 2) weigh_values<2>(va, i, lds, st);
+        else weigh_values<1>(va, i, lds, st);
+    }
 }
 
 // Merge of the split-K partials of one (sequence, head) row whose sequence kept more than one workgroup

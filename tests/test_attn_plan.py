@@ -115,3 +115,27 @@ def test_scoring_passes_open_no_round_for_next_to_nothing(tmp_path):
             }
 ''')
     assert out == "", out
+
+
+def test_selection_layer_runs_cover_the_tokens_and_fit_the_workspace(tmp_path):
+    """Runs of the scoring pass and of the values: whole tiles, the list covered, no run empty; the values' partials fit a workspace
+    laid out for any longer bound and any smaller number of pairs."""
+    out = run_checks(tmp_path, r'''
+    (void)plan;
+    for (int pairs = 1; pairs <= 1100; pairs += pairs < 80 ? 1 : 7)
+        for (int n = 1; n <= 1300000; n += step(n)) {
+            for (int rows : {pairs, 2 * pairs, 8 * pairs}) {
+                const ValuePlan v = plan_values(n, pairs, rows);
+                if (v.chunk % VALUE_TOKENS || (int64_t)v.chunk * v.n_splits < n || (v.n_splits > 1 && (int64_t)v.chunk * (v.n_splits - 1) >= n))
+                    FAIL("values of %d pairs of %d: %d runs of %d", pairs, n, v.n_splits, v.chunk);
+                for (int fewer : {pairs, (pairs + 1) / 2, (pairs + 7) / 8})
+                    if (v.n_splits > max_splits_bound(n, fewer)) FAIL("values of %d pairs of %d: %d runs, bound %d", pairs, n, v.n_splits, max_splits_bound(n, fewer));
+            }
+            for (bool second : {false, true}) {
+                const AttnPlan p = plan_score(n, pairs, second);
+                if ((p.ti != 8 && p.ti != 16) || p.chunk % (p.ti * 4 * ATTN_WAVES) || (int64_t)p.chunk * p.n_splits < n || (int64_t)p.chunk * (p.n_splits - 1) >= n)
+                    FAIL("scores of %d pairs of %d: %d runs of %d", pairs, n, p.n_splits, p.chunk);
+            }
+        }
+''')
+    assert out == "", out

@@ -698,6 +698,44 @@ def _kernel_calls(fn):
     return {k: v["calls"] for k, v in prof.items()}
 
 
+def _attention64_and_bound(inp, layer_pos, b):
+    """Full attention of sequence b in 64 bits, and how far a correct kernel may be from it: the output's rounding to bf16 and that of every
+    softmax weight (2^-9 relative each, in the product and in the denominator), which binary32 sums do not add to at this size."""
+    q, K, V = host_view(inp, layer_pos, b)
+    to = lambda x: torch.from_numpy(np.asarray(x).astype(np.int32) << 16).view(torch.float32).to(DEV).double()   # noqa: E731
+    q, K, V = to(q), to(K), to(V)
+    p = torch.softmax((q.view(K.shape[0], -1, 128) @ K.transpose(1, 2).contiguous()) / 128 ** 0.5, dim=-1)
+    out, mag = (p @ V).view(-1, 128), (p @ V.abs()).view(-1, 128)
+    return out, 2.0 ** -8 * out.abs() + 2.0 ** -8 * mag + 1e-6
+
+
+@pytest.mark.parametrize("H,layout", [(8, "head_major"), (16, "paged"), (32, "token_major"), (32, "paged"), (64, "head_major"), (64, "paged")])
+@pytest.mark.parametrize("lens", [
+    (17, 5, 31, 32, 33, 255, 256, 257, 511, 512, 513, 1537),      # rows of a tile, tiles of a workgroup, the scoring pass's tiles
+    (20001,),                                                     # one sequence: many runs, the last one short
+    (2049, 1024, 1025, 2048, 900) * 8,                            # runs of 1024: one, exactly one, one and a token
+    (300, 16, 257, 290)])                                         # one run for every sequence: no merge
+def test_selection_layer_values_at_the_edges_of_tiles_and_runs(H, layout, lens):
+    """The selection layer's two passes (scores of all tokens; values beside the top-k) for every group size and layout."""
+    w = small(f"values_{H}_{layout}_{len(lens)}", batch=len(lens), n_q_heads=H, seq_len=max(lens), lengths=lens, budget=16, window=4,
+              n_layers=1, schedule=(LAYER_SELECT,), paged=layout == "paged", n_sink=1)
+    inp = wl.make_inputs(w, DEV)
+    if layout == "token_major":
+        for lay in inp.layers:
+            lay.k = lay.k.transpose(1, 2).contiguous().transpose(1, 2)
+            lay.v = lay.v.transpose(1, 2).contiguous().transpose(1, 2)
+    r = StepRunner(inp)
+    _say(f"{w.name}: lens {lens[:6]}")
+    r.outs[0].fill_(float("nan"))
+    r.ws.fill_(0xff)                                     # NaN wherever something is read that was not written
+    r.run()
+    check_select(inp, r, 0, seqs=range(0, len(lens), max(1, len(lens) // 6)))
+    for b in range(min(len(lens), 12)):
+        want, bound = _attention64_and_bound(inp, 0, b)
+        err = (r.outs[0][b].double() - want).abs()
+        assert (err <= bound).all(), f"seq {b} of {lens[b]} tokens: {(err / bound).max().item():.2f} of the bound"
+
+
 def test_filtered_selection_layer_fast_path_and_its_second_chance():
     """A selection layer with many scores keeps only the candidates above a sampled threshold.  The result must
     not depend on the guess: random scores (the guess holds), massive ties (far more candidates than the lists
