@@ -129,16 +129,19 @@ inline AttnPlan plan_attn(int n_max, int BG, int g, AttnKind kind, bool paged) {
     return pl;
 }
 
-// The scoring pass (score_kernel): one workgroup tile a workgroup, of 256 tokens (128 where these would be too few to keep every
-// CU busy twice over); there is no partial result to merge, so nothing bounds their number but the time that idle ones take: the second
-// chance of the filtered selection, which is over at once as a rule, takes runs of 2048.
-inline AttnPlan plan_score(int n_max, int BG, bool second_chance) {
-    const int64_t tokens = (int64_t)n_max * BG;
-    AttnPlan pl;
-    pl.ti = second_chance || tokens > 256 * TARGET_WGS ? 16 : 8;
-    pl.chunk = second_chance ? 2048 : pl.ti * 16;
-    pl.n_splits = (n_max + pl.chunk - 1) / pl.chunk;
-    return pl;
+// The scoring pass (score_kernel): a workgroup for every workgroup tile, of 256 tokens (128 where these would be too few to keep every
+// CU busy twice over); there is no partial result to merge, so nothing bounds their number but the time that idle ones take.  The second chance of
+// the filtered selection finds nothing to do as a rule, so it has at most about 8192 workgroups, which take a (sequence, KV head)'s tiles in turn
+// (64 sequences of 8192 to 32768, no head flagged: 65536 workgroups are gone after 20.5 us, 32768 after 10.7, 8192 after 4.0; 31 sequences of 4119 to
+// 16478, the heads of the short ones flagged: in runs of 2048 tokens 54 us, in turn 22).
+struct ScorePlan {
+    int ti;        // row-load instructions of a wave: tiles of 128 or 256 tokens
+    int n_splits;  // workgroups per (sequence, KV head)
+};
+inline ScorePlan plan_score(int n_max, int BG, bool second_chance) {
+    const int ti = second_chance || (int64_t)n_max * BG > 256 * TARGET_WGS ? 16 : 8, tile = ti * 4 * ATTN_WAVES;
+    const int tiles = (n_max + tile - 1) / tile;
+    return {ti, second_chance ? std::min(tiles, std::max(8, 8192 / BG)) : tiles};
 }
 
 // A selection layer's values (weigh_values): workgroups of 16 waves.

@@ -659,7 +659,7 @@ struct ScoreArgs {
     dim3 grid;
     hipStream_t s;
     const uint16_t* q;
-    int budget, window, n_splits, chunk, all, keep;
+    int budget, window, n_splits, all, keep;
     float* P;
     int64_t ldp;
     FilterState filter;
@@ -668,11 +668,11 @@ struct ScoreArgs {
 template <int GQ, int TI>
 void launch_score(const ScoreArgs& a) {
     if (a.paged)
-        launch(KID_SCORE, score_kernel<GQ, TI, true>, a.grid, ATTN_THREADS, 0, a.s, a.view.seq_lens, a.q, a.budget, a.window, a.n_splits, a.chunk,
-               a.view.G, a.all, a.keep, a.P, a.ldp, a.filter, a.view);
+        launch(KID_SCORE, score_kernel<GQ, TI, true>, a.grid, ATTN_THREADS, 0, a.s, a.view.seq_lens, a.q, a.budget, a.window, a.n_splits, a.view.G,
+               a.all, a.keep, a.P, a.ldp, a.filter, a.view);
     else
-        launch(KID_SCORE, score_kernel<GQ, TI, false>, a.grid, ATTN_THREADS, 0, a.s, a.view.seq_lens, a.q, a.budget, a.window, a.n_splits, a.chunk,
-               a.view.G, a.all, a.keep, a.P, a.ldp, a.filter, a.view);
+        launch(KID_SCORE, score_kernel<GQ, TI, false>, a.grid, ATTN_THREADS, 0, a.s, a.view.seq_lens, a.q, a.budget, a.window, a.n_splits, a.view.G,
+               a.all, a.keep, a.P, a.ldp, a.filter, a.view);
 }
 template <int GQ>
 void launch_score_ti(int ti, const ScoreArgs& a) {
@@ -687,7 +687,7 @@ cusa_status run_score(const cusa_params* p, const void* q, const cusa_kv* kv, fl
     const int n_max = all ? kv->max_seq_len : kv->max_seq_len - p->window;
     if (n_max < 1) return CUSA_OK;
     ScoreArgs a;
-    const AttnPlan pl = plan_score(n_max, BG, only_failed != nullptr);
+    const ScorePlan pl = plan_score(n_max, BG, only_failed != nullptr);
     a.paged = kv->layout == CUSA_KV_PAGED;
     a.grid = dim3(pl.n_splits, p->n_kv_heads, p->batch);
     a.s = s;
@@ -695,7 +695,6 @@ cusa_status run_score(const cusa_params* p, const void* q, const cusa_kv* kv, fl
     a.budget = p->budget;
     a.window = p->window;
     a.n_splits = pl.n_splits;
-    a.chunk = pl.chunk;
     a.all = all ? 1 : 0;
     a.keep = (int64_t)p->batch * p->n_q_heads * n_max * 4 <= SCORE_KEEP_BYTES ? 1 : 0;
     a.P = P;

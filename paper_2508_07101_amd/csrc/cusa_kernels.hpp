@@ -2499,14 +2499,14 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
 
 // ---------------------------------------------------------------- scoring pass
 //
-// P[b][h][t] = q_h . K_t, grid (n_splits, G, B), 256 threads.  A workgroup takes the tokens of its run (chunk) of one
-// (sequence, KV head) a workgroup tile at a time, a wave TI * 4 of them.  A K row is read by 16 lanes with one 16-byte load each;
+// P[b][h][t] = q_h . K_t, grid (n_splits, G, B), 256 threads.  A workgroup takes every n_splits-th workgroup tile -- one, as a
+// rule -- of a (sequence, KV head), a wave TI * 4 tokens of it.  A K row is read by 16 lanes with one 16-byte load each;
 // the wave parks its rows in LDS in two halves of 64 columns (8 KB instead of 16 per 64 tokens: the product chain walks the
 // columns in order anyway) and every lane reads its own token's columns back.  The tile's scores take the place of its rows and are
 // written by the whole workgroup, 1 KB of a head at a time.
 //
 // What bounds it is memory, if enough loads are in flight while tiles are worked on.  Nothing is requested ahead inside a
-// workgroup: runs are one tile long and four workgroups share a CU, 256 KB of rows, whose waits and arithmetic overlap.
+// workgroup: it has one tile and four workgroups share a CU, 256 KB of rows, whose waits and arithmetic overlap.
 // Measured against two workgroups with runs of 512 to 2048 tokens, q in registers and the next tile's rows on their way
 // (us; 8 pairs of 32768, 64 of 16384, 8 of 131072 with groups of 8): 16.1, 47.2, 63.3 -> 14.5, 46.2, 53.0; with both tiles' rows
 // in registers 17.3, 49.6, 61.2.
@@ -2517,8 +2517,8 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
 // keep: P is small enough for the last-level cache to hold until the top-k reads it (ordinary stores, SCORE_KEEP_BYTES).
 template <int GQ, int TI, bool PAGED>
 __global__ __launch_bounds__(ATTN_THREADS, 4) void score_kernel(const int32_t* __restrict__ seq_lens, const uint16_t* __restrict__ q,
-                                                                 int budget, int window, int n_splits, int chunk, int G, int all,
-                                                                 int keep, float* __restrict__ P, int64_t ldp, FilterState flt, KvView kv) {
+                                                                 int budget, int window, int n_splits, int G, int all, int keep,
+                                                                 float* __restrict__ P, int64_t ldp, FilterState flt, KvView kv) {
     constexpr int TILE = TI * 4, WG_TILE = TILE * ATTN_WAVES;
     constexpr int SETS = (GQ + 3) / 4;
     constexpr int QSF = 132;                          // padded head stride of q in LDS (floats)
@@ -2532,7 +2532,6 @@ __global__ __launch_bounds__(ATTN_THREADS, 4) void score_kernel(const int32_t* _
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t head0 = ((int64_t)b * G + kvh) * GQ;
-    const int begin = split * chunk;
     const int L = uniform_load(seq_lens + b);
     if (!all) {
         if (L <= budget) return;                      // rho is every token: nothing is scored
@@ -2544,12 +2543,11 @@ __global__ __launch_bounds__(ATTN_THREADS, 4) void score_kernel(const int32_t* _
         }
     }
     const int n = all ? L : L - window;
-    if (begin >= n) return;
-    const int last = min(begin + chunk, n) - 1;
+    const int last = n - 1;
     u32x4* const ktile = ktile_all[wave];
     float* const stage = reinterpret_cast<float*>(ktile);   // [GQ][TILE]
     int my_lane = lane;
-    for (int w0 = begin; w0 <= last; w0 += WG_TILE) {
+    for (int w0 = split * WG_TILE; w0 <= last; w0 += n_splits * WG_TILE) {
         const int t0 = w0 + wave * TILE;
         asm volatile("" : "+v"(my_lane));             // what is made of it is made where it is needed: there are no registers to keep it
         const int r = my_lane >> 4, c = my_lane & 15;
@@ -2560,7 +2558,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 4) void score_kernel(const int32_t* _
             qv[s] = *reinterpret_cast<const u32x4*>(q + (head0 + (h < GQ ? h : 0)) * D + c * 8);
             if (h >= GQ) qv[s] = u32x4{0u, 0u, 0u, 0u};
         }
-        // rows past the end of the run are its last token's; their scores are not written
+        // rows past the end are the last token's; their scores are not written
         u32x4 kreg[TI];
 #pragma unroll
         for (int ig = 0; ig < TI / 4; ++ig) {         // 16 rows: one page
@@ -2580,7 +2578,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 4) void score_kernel(const int32_t* _
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int s = 0; s < SETS; ++s) {              // (again for every tile, with the same values: a run is one as a rule)
+        for (int s = 0; s < SETS; ++s) {              // (again for every tile, with the same values: there is one as a rule)
             float qf[8];
             unpack8(make_uint4(qv[s].x, qv[s].y, qv[s].z, qv[s].w), qf);
             float* const dst = &qf32[(s * 4 + r) * QSF + c * 8];
@@ -2647,7 +2645,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 4) void score_kernel(const int32_t* _
                     if (t + e <= last) dst[e] = v[e];
             }
         }
-        if (w0 + WG_TILE <= last) lds_barrier();      // read, before the tile buffers are written again
+        if (w0 + n_splits * WG_TILE <= last) lds_barrier();   // read, before the tile buffers are written again
     }
 }
 

@@ -118,8 +118,8 @@ def test_scoring_passes_open_no_round_for_next_to_nothing(tmp_path):
 
 
 def test_selection_layer_runs_cover_the_tokens_and_fit_the_workspace(tmp_path):
-    """Runs of the scoring pass and of the values: whole tiles, the list covered, no run empty; the values' partials fit a workspace
-    laid out for any longer bound and any smaller number of pairs."""
+    """Runs of the values: whole tiles, the list covered, no run empty; their partials fit a workspace laid out for any longer bound and
+    any smaller number of pairs.  The scoring pass has a workgroup for every tile, the second chance no more than that."""
     out = run_checks(tmp_path, r'''
     (void)plan;
     for (int pairs = 1; pairs <= 1100; pairs += pairs < 80 ? 1 : 7)
@@ -132,9 +132,10 @@ def test_selection_layer_runs_cover_the_tokens_and_fit_the_workspace(tmp_path):
                     if (v.n_splits > max_splits_bound(n, fewer)) FAIL("values of %d pairs of %d: %d runs, bound %d", pairs, n, v.n_splits, max_splits_bound(n, fewer));
             }
             for (bool second : {false, true}) {
-                const AttnPlan p = plan_score(n, pairs, second);
-                if ((p.ti != 8 && p.ti != 16) || p.chunk % (p.ti * 4 * ATTN_WAVES) || (int64_t)p.chunk * p.n_splits < n || (int64_t)p.chunk * (p.n_splits - 1) >= n)
-                    FAIL("scores of %d pairs of %d: %d runs of %d", pairs, n, p.n_splits, p.chunk);
+                const ScorePlan p = plan_score(n, pairs, second);
+                const int tile = p.ti * 4 * ATTN_WAVES, tiles = (n + tile - 1) / tile;
+                if ((p.ti != 8 && p.ti != 16) || p.n_splits < 1 || p.n_splits > tiles || (!second && p.n_splits != tiles))
+                    FAIL("scores of %d pairs of %d: %d workgroups for %d tiles", pairs, n, p.n_splits, tiles);
             }
         }
 ''')
