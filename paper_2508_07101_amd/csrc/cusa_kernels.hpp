@@ -73,6 +73,10 @@ __device__ __forceinline__ int32_t uniform_load(const int32_t* p) {
     return *(const __attribute__((address_space(4))) int32_t*)(uintptr_t)p;
 }
 
+// Where a running maximum of scores starts: no score of a tile needs to be finite.  (From -infinity, a first tile whose scores are all
+// -infinity makes NaN of its weights; from here they are 2^-infinity = 0.)
+constexpr float LOWEST = -3.402823466e38f;
+
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
@@ -2710,7 +2714,7 @@ __device__ __forceinline__ void weigh_values(const ValueArgs& a, int item, float
     f32x4 acc[8];                                     // column 8c + e; heads 4r .. 4r+3
 #pragma unroll
     for (int j = 0; j < HPL; ++j) {
-        m[j] = -INFINITY;
+        m[j] = LOWEST;
         l[j] = 0.0f;
     }
 #pragma unroll
@@ -2761,7 +2765,7 @@ __device__ __forceinline__ void weigh_values(const ValueArgs& a, int item, float
 #pragma unroll
         for (int j = 0; j < HPL; ++j) {
             const float z = t0 + t <= last ? p[j] * a.scale_log2e : -INFINITY;
-            const float m_new = fmaxf(m[j], row_max16(z));   // finite: the tile's first token is valid
+            const float m_new = fmaxf(m[j], row_max16(z));
             corr[j] = __builtin_amdgcn_exp2f(m[j] - m_new);
             same = same && __ballot(m_new != m[j]) == 0;
             m[j] = m_new;
@@ -2834,8 +2838,7 @@ __device__ __forceinline__ void weigh_values(const ValueArgs& a, int item, float
         float A = 0.0f, Ls = 0.0f;
 #pragma unroll 4
         for (int wv = 0; wv < SEL_WAVES; ++wv) {
-            const float mw = st.m[wv][h];
-            const float f = (mw == -INFINITY) ? 0.0f : exp2f(mw - M);
+            const float f = exp2f(st.m[wv][h] - M);
             A = __builtin_fmaf(sums_lds[wv * (GQ * D) + o], f, A);
             Ls = __builtin_fmaf(st.l[wv][h], f, Ls);
         }

@@ -736,6 +736,45 @@ def test_selection_layer_values_at_the_edges_of_tiles_and_runs(H, layout, lens):
         assert (err <= bound).all(), f"seq {b} of {lens[b]} tokens: {(err / bound).max().item():.2f} of the bound"
 
 
+def _minus_infinity_scores(inp, runs):
+    """The tokens of these runs of positions score -infinity with every head of every layer (one column's product overflows)."""
+    big = torch.finfo(torch.bfloat16).max
+    for lay in inp.layers:
+        lay.q[..., 1] = big
+        lay.k[..., 1] = 0
+        for lo, hi in runs:
+            if inp.block_table is None:
+                lay.k[:, :, lo:hi, 1] = -big
+                continue
+            for b, L in enumerate(inp.seq_lens_host):
+                t = torch.arange(min(lo, L), min(hi, L), device=DEV)
+                lay.k[inp.block_table[b][t // 16].long(), :, t % 16, 1] = -big
+
+
+def _check_outputs64(inp, r, layer_pos):
+    torch.cuda.synchronize()
+    for b, L in enumerate(inp.seq_lens_host):
+        want, bound = _attention64_and_bound(inp, layer_pos, b)
+        err = (r.outs[layer_pos][b].double() - want).abs()
+        assert (err <= bound).all(), f"seq {b} of {L} tokens: {(err / bound).max().item():.2f} of the bound"
+
+
+@pytest.mark.parametrize("H", [8, 16, 32, 64])
+@pytest.mark.parametrize("paged", [False, True])
+def test_selection_layer_output_beside_scores_of_minus_infinity(H, paged):
+    """A score of -infinity weighs nothing, wherever it stands: the first tile of a wave or of the sequence, a whole run, the last tokens."""
+    lens = (5003, 900, 2100)
+    w = small(f"values_minusinf_{H}", batch=len(lens), n_q_heads=H, seq_len=max(lens), lengths=lens, budget=300, window=60, n_layers=1,
+              schedule=(LAYER_SELECT,), paged=paged)
+    inp = wl.make_inputs(w, DEV)
+    _minus_infinity_scores(inp, [(0, 16), (48, 64), (560, 600), (850, 900), (1024, 2048), (2085, 2100), (2304, 2367), (4990, 5003)])
+    r = StepRunner(inp)
+    r.outs[0].fill_(float("nan"))
+    r.run()
+    check_select(inp, r, 0)
+    _check_outputs64(inp, r, 0)
+
+
 def test_filtered_selection_layer_fast_path_and_its_second_chance():
     """A selection layer with many scores keeps only the candidates above a sampled threshold.  The result must
     not depend on the guess: random scores (the guess holds), massive ties (far more candidates than the lists
