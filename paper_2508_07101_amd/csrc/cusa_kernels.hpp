@@ -2125,7 +2125,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     f32x4 acc[SETS][8];                               // [set][column e of the lane's 8]: the four heads of the set
 #pragma unroll
     for (int h = 0; h < GQ; ++h) {
-        m[h] = -INFINITY;
+        m[h] = LOWEST;
         l[h] = 0.0f;
     }
 #pragma unroll
@@ -2387,7 +2387,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
             float mt = row_max16(z);                  // lanes TILE apart hold the same token
             if (TILE > 16) mt = max_with_row_neighbour(mt);
             if (TILE > 32) mt = max_with_other_half(mt);
-            const float m_new = fmaxf(m[h], mt);      // finite: token t0 of this tile is valid
+            const float m_new = fmaxf(m[h], mt);
             corr[h] = exp2f(m[h] - m_new);
             m[h] = m_new;
             // the weight enters numerator and denominator as the same bf16 value
@@ -2481,8 +2481,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
         float A = 0.0f, Ls = 0.0f;
 #pragma unroll
         for (int wv = 0; wv < ATTN_WAVES; ++wv) {
-            const float mw = sm_m[wv][h];
-            const float f = (mw == -INFINITY) ? 0.0f : exp2f(mw - M);
+            const float f = exp2f(sm_m[wv][h] - M);
             A = __builtin_fmaf(sums[wv * (WAVE_LDS / 4) + o], f, A);
             Ls = __builtin_fmaf(sm_l[wv][h], f, Ls);
         }

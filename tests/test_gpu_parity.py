@@ -698,12 +698,14 @@ def _kernel_calls(fn):
     return {k: v["calls"] for k, v in prof.items()}
 
 
-def _attention64_and_bound(inp, layer_pos, b):
-    """Full attention of sequence b in 64 bits, and how far a correct kernel may be from it: the output's rounding to bf16 and that of every
+def _attention64_and_bound(inp, layer_pos, b, tokens=None):
+    """Attention of sequence b over all tokens (or these) in 64 bits, and how far a correct kernel may be from it: the output's rounding to bf16 and that of every
     softmax weight (2^-9 relative each, in the product and in the denominator), which binary32 sums do not add to at this size."""
     q, K, V = host_view(inp, layer_pos, b)
     to = lambda x: torch.from_numpy(np.asarray(x).astype(np.int32) << 16).view(torch.float32).to(DEV).double()   # noqa: E731
     q, K, V = to(q), to(K), to(V)
+    if tokens is not None:
+        K, V = K[:, tokens], V[:, tokens]
     p = torch.softmax((q.view(K.shape[0], -1, 128) @ K.transpose(1, 2).contiguous()) / 128 ** 0.5, dim=-1)
     out, mag = (p @ V).view(-1, 128), (p @ V.abs()).view(-1, 128)
     return out, 2.0 ** -8 * out.abs() + 2.0 ** -8 * mag + 1e-6
@@ -751,10 +753,10 @@ def _minus_infinity_scores(inp, runs):
                 lay.k[inp.block_table[b][t // 16].long(), :, t % 16, 1] = -big
 
 
-def _check_outputs64(inp, r, layer_pos):
+def _check_outputs64(inp, r, layer_pos, tokens=None):
     torch.cuda.synchronize()
     for b, L in enumerate(inp.seq_lens_host):
-        want, bound = _attention64_and_bound(inp, layer_pos, b)
+        want, bound = _attention64_and_bound(inp, layer_pos, b, tokens and tokens[b])
         err = (r.outs[layer_pos][b].double() - want).abs()
         assert (err <= bound).all(), f"seq {b} of {L} tokens: {(err / bound).max().item():.2f} of the bound"
 
@@ -773,6 +775,36 @@ def test_selection_layer_output_beside_scores_of_minus_infinity(H, paged):
     r.run()
     check_select(inp, r, 0)
     _check_outputs64(inp, r, 0)
+
+
+@pytest.mark.parametrize("H", [8, 16, 32, 64])
+@pytest.mark.parametrize("paged", [False, True])
+def test_attention_passes_beside_scores_of_minus_infinity(H, paged):
+    """The same for the passes over all tokens, over rho (K - W of the candidates are finite, and all of the window is not) and over lists
+    per head: tiles of 16, 32 and 64 tokens."""
+    lens = (5003, 900, 2100)
+    w = small(f"minusinf_{H}", batch=len(lens), n_q_heads=H, seq_len=max(lens), lengths=lens, budget=600, window=100, n_layers=2,
+              schedule=(LAYER_FULL, LAYER_SPARSE), paged=paged)
+    inp = wl.make_inputs(w, DEV)
+    _minus_infinity_scores(inp, [(0, 64), (128, 192), (560, 700), (750, 900), (1024, 2100), (2304, 2367), (2500, 3100), (4800, 5003)])
+    r = StepRunner(inp)
+    idx = torch.zeros((len(lens), 600), dtype=torch.int32, device=DEV)
+    for b, L in enumerate(lens):                         # every other token from the end back: runs of -infinity in it, the window's among them
+        idx[b, : min(600, L)] = torch.arange(L - 1, -1, -1, device=DEV, dtype=torch.int32)[:: 1 if L <= 1200 else 2][: 600].flip(0)
+    r.idx.copy_(idx)
+    r.cnt.fill_(600)
+    per_head = idx.unsqueeze(1).expand(-1, H, -1).contiguous()
+    out_head = torch.empty_like(r.outs[1])
+    for o in r.outs:
+        o.fill_(float("nan"))
+    r.full(0)
+    r.sparse(1)
+    cb.sparse_attn_per_head(r.params, inp.layers[1].q, r.kvs[1], per_head, r.cnt, out_head, r.ws)
+    _check_outputs64(inp, r, 0)
+    rho = [idx[b].long() for b in range(len(lens))]
+    _check_outputs64(inp, r, 1, rho)
+    r.outs[1].copy_(out_head)
+    _check_outputs64(inp, r, 1, rho)
 
 
 def test_filtered_selection_layer_fast_path_and_its_second_chance():
