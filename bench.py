@@ -44,7 +44,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 QUOTED = ["c1", "c2", "c3", "c4", "c5"]
-BANDWIDTH_KERNELS = ("attn_kernel<sparse>", "attn_kernel<full+filter>", "attn_kernel<full>", "score_kernel", "topk_values_kernel")
+BANDWIDTH_KERNELS = ("attn_kernel<sparse>", "attn_kernel<full+filter>", "attn_kernel<full+score>", "attn_kernel<full>", "score_kernel", "topk_values_kernel")
 
 
 def parse():
@@ -135,6 +135,8 @@ def kernel_bytes(w, lens, acc, layer=True):
         "topk_values_kernel": sum(acc.full_attn_bytes(G, L) // 2 for L in lens),
         # the same with many scores: K and V once, candidates kept on the way
         "attn_kernel<full+filter>": sum(acc.full_attn_bytes(G, L) for L in lens),
+        # and in one pass over K and V
+        "attn_kernel<full+score>": sum(acc.full_attn_bytes(G, L) for L in lens),
     }
 
 

@@ -7,7 +7,7 @@
 namespace cusa {
 
 constexpr int ATTN_WAVES = 4;       // waves of a workgroup
-// Longest run of tokens a workgroup of the filtered form may own: its candidates wait in LDS (32 KB)
+// Longest run of tokens a workgroup of the scoring variant may own: its scores wait in LDS (32 KB)
 // until the run is done.
 constexpr int ATTN_SCORE_CHUNK_CAP = 2048;
 constexpr int ATTN_SCORE_CHUNK_CAP_G8 = 1024;
@@ -25,7 +25,7 @@ static_assert(ATTN_SCORE_CHUNK_CAP <= CHUNK_CAP && ATTN_SCORE_CHUNK_CAP_G8 <= CH
               "the split bound assumes it");
 
 struct AttnPlan {
-    int ti;        // row-load instructions per wave iteration (4 or 8; filtered form 8 or 16, tiles of 128 or 256 tokens)
+    int ti;        // row-load instructions per wave iteration (4 or 8; scoring variant 8 or 16, tiles of 128 or 256 tokens)
     int chunk;     // tokens per workgroup, a multiple of the workgroup tile
     int n_splits;  // grid.x = ceil(n_max / chunk)
 };
@@ -41,7 +41,7 @@ inline float round_share(int n) {
 enum AttnKind { ATTN_FULL, ATTN_SPARSE, ATTN_SCORE };
 inline int noalloc_splits(int n_max, int BG);
 
-// Whole tiles of the filtered form.
+// Whole tiles of the scoring variant.
 inline int64_t score_tiles(int64_t tokens) { return tokens < 512 ? (tokens + 127) / 128 * 128 : (tokens + 255) / 256 * 256; }
 constexpr int SCORE_START = 64;     // what a workgroup of it costs besides its tokens, in tokens
 
@@ -65,7 +65,7 @@ constexpr int SCORE_START = 64;     // what a workgroup of it costs besides its 
 // where a draw differs by more than that.  (128 pairs of 601 to 16383 tokens: 106.3 us, 97.3, in pieces of 1024 99.6.)
 // A contiguous cache holds sequences of one length as a rule: 224 pairs of 6000 tokens, pieces of 2048 107.3 us, of
 // 1280 114.6; 40 of 32768: 105.5 and 114.8.
-// The filtered form keeps its candidates in LDS, hence its own caps, writes them in bursts, which are better longer
+// The scoring variant keeps its scores in LDS, hence its own caps, writes them in bursts, which are better longer
 // (pieces of 2048 against 1024 at 64 pairs of 16384: 121.3 and 123.7 us), and its tiles are large (128 or 256 tokens):
 // it takes 1/512 of all tokens, rounded up to whole tiles.  Even pieces as above, rounded to the nearest tile, were 2
 // per cent slower over 177 selection layers of 8 to 512 pairs of 600 to 40000 tokens, and often by a last round with
@@ -164,6 +164,25 @@ inline ValuePlan plan_values(int n_max, int BG, int rows) {
         chunk = (chunk + VALUE_TOKENS - 1) / VALUE_TOKENS * VALUE_TOKENS;
     }
     return {(int)chunk, (int)std::max<int64_t>(1, (n_max + chunk - 1) / chunk)};
+}
+
+// Whether a row of the workspace's scores has room for every token, not just the candidates: see values_beside_topk, which asks for it.  Once true
+// it stays true for longer bounds, so a workspace laid out for a capacity serves every shorter bound, and rows stay under 5 / 3 of the candidates.
+inline bool scores_of_all_tokens(int window, int max_seq_len) { return (int64_t)window * 5 <= (int64_t)max_seq_len * 2; }
+
+// Whether a selection layer that is not filtered scores all tokens first and makes its output from those scores while the top-k runs (score_kernel,
+// topk_values_kernel); otherwise one pass over K and V makes the output and writes the candidates' scores (attn_kernel's scoring variant).
+// rows: batch * query heads.
+inline bool values_beside_topk(int64_t rows, int BG, int window, int max_seq_len, int64_t token_step) {
+    // the rows and runs are workgroups of 1024 threads of a one-dimensional launch: fewer than 2^32 threads
+    if (rows + (int64_t)BG * plan_values(max_seq_len, BG, (int)std::min(rows, (int64_t)CUS)).n_splits >= 1 << 22) return false;
+    // a lane's distance from the first row of its 16 fits 32 bits (elements between tokens; 0: paged)
+    if (token_step > 1 << 26) return false;
+    // The scores of a window are written and read for the output alone: 4 g bytes for the 256 of a row.  From two fifths of the tokens on the one pass
+    // is faster (8 sequences of 16384, 8 KV heads, us, one pass and so, window 0.4, 0.5, 0.9 of the tokens: groups of 4 105.5 and 104.1, 102.6 and 104.4,
+    // 99.1 and 104.5; of 8 117.1 and 117.6, 112.8 and 117.0, 108.9 and 119.0).  (With at most UNION_MAX_POSITIONS candidates this also keeps the score
+    // rows of a group's heads within 32 bits of each other.)
+    return scores_of_all_tokens(window, max_seq_len);
 }
 
 // Upper bound of plan_attn(m, BG', ...).n_splits over every m <= n_max and BG' >= BG: a token list is cut into

@@ -21,13 +21,13 @@ namespace {
 
 // ------------------------------------------------------------------ profiling
 
-enum KernelId { KID_SCORE = 0, KID_TOPK, KID_UNION, KID_ATTN_FULL, KID_ATTN_SPARSE, KID_REDUCE, KID_ATTN_SELECT, KID_ATTN_PER_HEAD, KID_RHO_PER_HEAD, KID_RANK_AGG, KID_RECALL, KID_PROBE, KID_TOPK_SLICE, KID_TOPK_MERGE, KID_PROBE_GATHER, KID_PROBE_RW_SCATTER, KID_PROBE_RW_BURST, KID_SAMPLE_THRESHOLD, KID_TOPK_FILTERED, KID_PROBE_TILES, KID_TOPK_VALUES, KID_COUNT };
+enum KernelId { KID_SCORE = 0, KID_TOPK, KID_UNION, KID_ATTN_FULL, KID_ATTN_SPARSE, KID_REDUCE, KID_ATTN_SELECT, KID_ATTN_PER_HEAD, KID_RHO_PER_HEAD, KID_RANK_AGG, KID_RECALL, KID_PROBE, KID_TOPK_SLICE, KID_TOPK_MERGE, KID_PROBE_GATHER, KID_PROBE_RW_SCATTER, KID_PROBE_RW_BURST, KID_SAMPLE_THRESHOLD, KID_TOPK_FILTERED, KID_PROBE_TILES, KID_TOPK_VALUES, KID_ATTN_FILTER, KID_COUNT };
 const char* const kKernelNames[KID_COUNT] = {"score_kernel", "topk_kernel", "union_kernel",
                                              "attn_kernel<full>", "attn_kernel<sparse>", "attn_reduce_kernel",
-                                             "attn_kernel<full+filter>", "attn_kernel<per-head>", "per_head_rho_kernel",
+                                             "attn_kernel<full+score>", "attn_kernel<per-head>", "per_head_rho_kernel",
                                              "rank_aggregate_kernel", "recall_kernel", "probe_stream_read_kernel", "topk_kernel<slice>",
                                              "topk_kernel<merge>", "probe_traffic_kernel<gather>", "probe_traffic_kernel<scattered writes>",
-                                             "probe_traffic_kernel<burst writes>", "sample_threshold_kernel", "topk_kernel<filtered>", "probe_traffic_kernel<stream>", "topk_values_kernel"};
+                                             "probe_traffic_kernel<burst writes>", "sample_threshold_kernel", "topk_kernel<filtered>", "probe_traffic_kernel<stream>", "topk_values_kernel", "attn_kernel<full+filter>"};
 
 // With the profiler on, every launch carries a start and a stop event that the runtime fills
 // from the dispatch's own begin and end timestamps (hipExtLaunchKernelGGL), which is what a
@@ -238,7 +238,7 @@ WsLayout make_layout(const cusa_params* p, int max_seq_len) {
     const int BG = p->batch * p->n_kv_heads;
     int64_t lc = (int64_t)max_seq_len - p->window;
     if (lc < 1) lc = 1;
-    w.ldp = ((int64_t)max_seq_len + 63) / 64 * 64;   // a selection layer scores all tokens
+    w.ldp = ((scores_of_all_tokens(p->window, max_seq_len) ? max_seq_len : lc) + 63) / 64 * 64;
     w.k = resolved_k(p);
     if (w.k < 1) w.k = 1;
     w.max_splits = max_splits_bound(max_seq_len > p->budget ? max_seq_len : p->budget, BG);
@@ -307,6 +307,14 @@ cusa_status launch_status() { return hipGetLastError() == hipSuccess ? CUSA_OK :
 
 // ------------------------------------------------------------------ launches
 
+// What a pass over all tokens of a selection layer also emits (scores of the candidate range).
+struct ScoreOut {
+    float* P = nullptr;     // nullptr: plain attention
+    int64_t ldp = 0;
+    int window = 0;
+    FilterState filter = {};   // thr set: the pass keeps the candidates at or above the heads' thresholds instead of writing P
+};
+
 struct AttnArgs {
     bool paged;
     dim3 grid;
@@ -322,46 +330,52 @@ struct AttnArgs {
     uint16_t* out;
     float* lse = nullptr;   // optional: log2 of the softmax denominators, [B][H]
     int n_splits, chunk;
-    int window = 0;
-    FilterState filter = {};   // thr set: the pass keeps the candidates at or above the heads' thresholds (all tokens only)
+    ScoreOut score;
 };
 
-template <int GQ, int TI, bool SPARSE, bool FILTER = false>
+template <int GQ, int TI, bool SPARSE, bool SCORE, bool FILTER = false>
 void launch_attn_partial(const AttnArgs& a) {
-    const int kid = SPARSE ? KID_ATTN_SPARSE : FILTER ? KID_ATTN_SELECT : KID_ATTN_FULL;
+    const int kid = SPARSE ? KID_ATTN_SPARSE : FILTER ? KID_ATTN_FILTER : SCORE ? KID_ATTN_SELECT : KID_ATTN_FULL;
     if (a.paged)
-        launch(kid, attn_kernel<GQ, TI, SPARSE, true, false, FILTER>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt, a.view.seq_lens, a.q,
-               a.budget, a.n_splits, a.chunk, a.view.G, a.scale, a.pa, a.pm, a.out, a.lse, a.window, 0, a.filter, a.view);
+        launch(kid, attn_kernel<GQ, TI, SPARSE, true, SCORE, false, FILTER>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt, a.view.seq_lens, a.q,
+               a.budget, a.n_splits, a.chunk, a.view.G, a.scale, a.pa, a.pm, a.out, a.lse, a.score.P, a.score.ldp, a.score.window, 0, a.score.filter, a.view);
     else
-        launch(kid, attn_kernel<GQ, TI, SPARSE, false, false, FILTER>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt, a.view.seq_lens, a.q,
-               a.budget, a.n_splits, a.chunk, a.view.G, a.scale, a.pa, a.pm, a.out, a.lse, a.window, 0, a.filter, a.view);
+        launch(kid, attn_kernel<GQ, TI, SPARSE, false, SCORE, false, FILTER>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt, a.view.seq_lens, a.q,
+               a.budget, a.n_splits, a.chunk, a.view.G, a.scale, a.pa, a.pm, a.out, a.lse, a.score.P, a.score.ldp, a.score.window, 0, a.score.filter, a.view);
 }
 
 // Sparse attention with one token list per query head: grid.y counts query heads.
 template <int TI>
 void launch_attn_per_head(const AttnArgs& a, int H, int hshift) {
     if (a.paged)
-        launch(KID_ATTN_PER_HEAD, attn_kernel<1, TI, true, true, true>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt,
-               a.view.seq_lens, a.q, a.budget, a.n_splits, a.chunk, H, a.scale, a.pa, a.pm, a.out, a.lse, 0, hshift, FilterState{}, a.view);
+        launch(KID_ATTN_PER_HEAD, attn_kernel<1, TI, true, true, false, true>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt,
+               a.view.seq_lens, a.q, a.budget, a.n_splits, a.chunk, H, a.scale, a.pa, a.pm, a.out, a.lse, nullptr, 0, 0, hshift, FilterState{}, a.view);
     else
-        launch(KID_ATTN_PER_HEAD, attn_kernel<1, TI, true, false, true>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt,
-               a.view.seq_lens, a.q, a.budget, a.n_splits, a.chunk, H, a.scale, a.pa, a.pm, a.out, a.lse, 0, hshift, FilterState{}, a.view);
+        launch(KID_ATTN_PER_HEAD, attn_kernel<1, TI, true, false, false, true>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt,
+               a.view.seq_lens, a.q, a.budget, a.n_splits, a.chunk, H, a.scale, a.pa, a.pm, a.out, a.lse, nullptr, 0, 0, hshift, FilterState{}, a.view);
 }
 
 template <int GQ, bool SPARSE>
 void launch_attn_ti(int ti, const AttnArgs& a) {
-    if constexpr (!SPARSE && GQ <= 4) {               // (filtered_select: groups of up to 4)
-        if (a.filter.thr) {                           // the scoring chain repeats work for tiles under 64 tokens: the wider tile where runs allow
-            if (ti == 16) launch_attn_partial<GQ, 16, false, true>(a);
-            else launch_attn_partial<GQ, 8, false, true>(a);
+    if constexpr (!SPARSE) {
+        if (a.score.P) {                              // the scoring chain repeats work for tiles under 64 tokens: always the wider tile
+            if (a.score.filter.thr) {                 // groups of up to 4 only (filtered_select)
+                if constexpr (GQ <= 4) {
+                    if (ti == 16) launch_attn_partial<GQ, 16, false, true, true>(a);
+                    else launch_attn_partial<GQ, 8, false, true, true>(a);
+                }
+            } else {
+                if (ti == 16) launch_attn_partial<GQ, 16, false, true>(a);
+                else launch_attn_partial<GQ, 8, false, true>(a);
+            }
             return;
         }
     }
     if (ti == 8) {
-        launch_attn_partial<GQ, 8, SPARSE>(a);
+        launch_attn_partial<GQ, 8, SPARSE, false>(a);
         return;
     }
-    launch_attn_partial<GQ, 4, SPARSE>(a);
+    launch_attn_partial<GQ, 4, SPARSE, false>(a);
 }
 
 void launch_reduce(const ReduceArgs& r, int H, int B, hipStream_t s) {
@@ -370,14 +384,14 @@ void launch_reduce(const ReduceArgs& r, int H, int B, hipStream_t s) {
 }
 
 // Attention over all tokens (idx == nullptr) or over idx/cnt; n_max bounds the token count.
-// filter (all tokens only): the pass also keeps the selection's candidates.
+// With score.P set (all tokens only) the pass also writes the selection scores.
 // later: the merge of the partials is left to the caller, who gets its arguments (rows 0: nothing to merge).
 template <bool SPARSE>
 cusa_status run_attention(const cusa_params* p, const void* q, const cusa_kv* kv, const int32_t* idx,
                           const int32_t* cnt, int n_max, void* out, void* ws, const WsLayout& w, hipStream_t s,
-                          const FilterState* filter = nullptr, float* lse = nullptr, ReduceArgs* later = nullptr) {
+                          ScoreOut score = ScoreOut(), float* lse = nullptr, ReduceArgs* later = nullptr) {
     const int g = p->n_q_heads / p->n_kv_heads, BG = p->batch * p->n_kv_heads, H = p->n_q_heads;
-    const AttnPlan pl = plan_attn(n_max, BG, g, SPARSE ? ATTN_SPARSE : filter ? ATTN_SCORE : ATTN_FULL,
+    const AttnPlan pl = plan_attn(n_max, BG, g, SPARSE ? ATTN_SPARSE : score.P != nullptr ? ATTN_SCORE : ATTN_FULL,
                                   kv->layout == CUSA_KV_PAGED);
     if (pl.n_splits > w.max_splits) return CUSA_ERR_WORKSPACE_TOO_SMALL;
     AttnArgs a;
@@ -396,8 +410,7 @@ cusa_status run_attention(const cusa_params* p, const void* q, const cusa_kv* kv
     a.lse = lse;
     a.n_splits = pl.n_splits;
     a.chunk = pl.chunk;
-    a.window = p->window;
-    if (filter) a.filter = *filter;
+    a.score = score;
     switch (g) {
         case 1: launch_attn_ti<1, SPARSE>(pl.ti, a); break;
         case 2: launch_attn_ti<2, SPARSE>(pl.ti, a); break;
@@ -712,12 +725,13 @@ cusa_status run_score(const cusa_params* p, const void* q, const cusa_kv* kv, fl
     return launch_status();
 }
 
+// scores_ready: P was already written by the layer's attention pass.
 // values: the layer's values, made in the top-k's launch (scores of all tokens).
 // per_head: idx is [B][H][budget], every head keeps its own first K-W picks (head-to-head selection).
 // red: attention partials still to be merged; they go with the union launch (or on their own where there is none).
 cusa_status run_select(const cusa_params* p, const void* q, const cusa_kv* kv, int32_t* idx, int32_t* cnt, void* ws,
-                       const WsLayout& w, hipStream_t s, bool per_head = false, const FilterState* redo = nullptr,
-                       const ReduceArgs* red = nullptr, const ValueArgs* values = nullptr) {
+                       const WsLayout& w, hipStream_t s, bool scores_ready = false, bool per_head = false,
+                       const FilterState* redo = nullptr, const ReduceArgs* red = nullptr, const ValueArgs* values = nullptr) {
     const int H = p->n_q_heads, B = p->batch;
     // redo: the filtered fast path has ranked most heads already; only the flagged ones are scored and ranked here
     int32_t* only_failed = redo ? redo->fail : nullptr;
@@ -727,7 +741,7 @@ cusa_status run_select(const cusa_params* p, const void* q, const cusa_kv* kv, i
 
     if (kv->max_seq_len > p->budget) {            // otherwise no sequence can need scoring
         const int lc_max = kv->max_seq_len - p->window;
-        cusa_status st = run_score(p, q, kv, P, w.ldp, s, values != nullptr, only_failed, n_failed);
+        cusa_status st = scores_ready ? CUSA_OK : run_score(p, q, kv, P, w.ldp, s, values != nullptr, only_failed, n_failed);
         if (st != CUSA_OK) return st;
         st = values ? run_topk_values(lc_max, B, H, s, P, w.ldp, kv->seq_lens, rho_head, w.k, p->budget, p->window, p->n_sink, *values)
                     : run_topk(lc_max, B, H, s, P, w.ldp, kv->seq_lens, rho_head, w.k, p->budget, p->window, 0, p->n_sink, ws, w, only_failed);
@@ -797,12 +811,13 @@ void launch_sample_threshold(const cusa_params* p, const void* q, const cusa_kv*
 cusa_status run_select_layer(const cusa_params* p, const void* q, const cusa_kv* kv, void* out, int32_t* idx,
                              int32_t* cnt, void* ws, const WsLayout& w, hipStream_t s) {
     ReduceArgs red = {};
-    // rho is every token of every sequence; or tokens lie too far apart for the values' kernel
-    if (kv->max_seq_len <= p->budget || (kv->layout == CUSA_KV_CONTIGUOUS && kv->stride_token > VALUE_MAX_STEP)) {
-        const cusa_status st = run_attention<false>(p, q, kv, nullptr, nullptr, kv->max_seq_len, out, ws, w, s, nullptr, nullptr, &red);
-        return st != CUSA_OK ? st : run_select(p, q, kv, idx, cnt, ws, w, s, false, nullptr, &red);
+    ScoreOut score;
+    if (kv->max_seq_len > p->budget) {                // otherwise rho is every token of every sequence
+        score.P = ws_ptr<float>(ws, w.scores);
+        score.ldp = w.ldp;
+        score.window = p->window;
     }
-    if (w.filter_cap > 0 && filtered_select(p, kv->max_seq_len)) {
+    if (score.P && w.filter_cap > 0 && filtered_select(p, kv->max_seq_len)) {
         // The filtered fast path: thresholds from a sample, the pass over K and V keeps the candidates above them, the
         // top-k ranks among those, and whatever the guess failed for is scored and ranked the ordinary way.
         const int H = p->n_q_heads, B = p->batch;
@@ -817,7 +832,8 @@ cusa_status run_select_layer(const cusa_params* p, const void* q, const cusa_kv*
         const SamplePlan sp = plan_sample((int64_t)kv->max_seq_len - p->window);
         launch_sample_threshold(p, q, kv, sp, f, w.k, s);
         if (launch_status() != CUSA_OK) return CUSA_ERR_LAUNCH;
-        cusa_status st = run_attention<false>(p, q, kv, nullptr, nullptr, kv->max_seq_len, out, ws, w, s, &f, nullptr, &red);
+        score.filter = f;
+        cusa_status st = run_attention<false>(p, q, kv, nullptr, nullptr, kv->max_seq_len, out, ws, w, s, score, nullptr, &red);
         if (st != CUSA_OK) return st;
         TopkArgs a = {dim3(H, B), s, nullptr, 0, kv->seq_lens, ws_ptr<int32_t>(ws, w.rho_head), H, w.k, p->budget, p->window, 0,
                       p->n_sink, nullptr, 0, 1};
@@ -825,7 +841,12 @@ cusa_status run_select_layer(const cusa_params* p, const void* q, const cusa_kv*
         const int items = (f.cap + SEL_THREADS - 1) / SEL_THREADS;
         st = items <= 4 ? launch_topk<4, true>(a) : items <= 8 ? launch_topk<8, true>(a) : launch_topk<16, true>(a);
         if (st != CUSA_OK) return st;
-        return run_select(p, q, kv, idx, cnt, ws, w, s, false, &f, &red);
+        return run_select(p, q, kv, idx, cnt, ws, w, s, false, false, &f, &red);
+    }
+    if (!score.P || !values_beside_topk((int64_t)p->batch * p->n_q_heads, p->batch * p->n_kv_heads, p->window, kv->max_seq_len,
+                                        kv->layout == CUSA_KV_PAGED ? 0 : kv->stride_token)) {
+        const cusa_status st = run_attention<false>(p, q, kv, nullptr, nullptr, kv->max_seq_len, out, ws, w, s, score, nullptr, &red);
+        return st != CUSA_OK ? st : run_select(p, q, kv, idx, cnt, ws, w, s, score.P != nullptr, false, nullptr, &red);
     }
     // Otherwise the scores of all tokens first; the values are made while the top-k runs.
     ValueArgs v;
@@ -844,7 +865,7 @@ cusa_status run_select_layer(const cusa_params* p, const void* q, const cusa_kv*
     v.items = pl.n_splits * p->batch * p->n_kv_heads;
     v.kv = make_view(p, kv);
     red = {v.part_acc, v.part_ml, v.out, kv->seq_lens, 0x7fffffff, pl.n_splits, pl.chunk, nullptr, pl.n_splits > 1 ? p->n_q_heads * p->batch : 0};
-    return run_select(p, q, kv, idx, cnt, ws, w, s, false, nullptr, &red, &v);
+    return run_select(p, q, kv, idx, cnt, ws, w, s, false, false, nullptr, &red, &v);
 }
 
 }  // namespace
@@ -965,7 +986,7 @@ cusa_status cusa_select_per_head(const cusa_params* params, const void* q, const
     if ((st = check_select_length(params, kv)) != CUSA_OK) return st;
     const WsLayout w = make_layout(params, kv->max_seq_len);
     if ((st = check_ws(w, ws, ws_bytes)) != CUSA_OK) return st;
-    return run_select(params, q, kv, idx_head, cnt, ws, w, static_cast<hipStream_t>(stream), true);
+    return run_select(params, q, kv, idx_head, cnt, ws, w, static_cast<hipStream_t>(stream), false, true);
 }
 
 cusa_status cusa_sparse_attn_per_head(const cusa_params* params, const void* q, const cusa_kv* kv,
@@ -996,9 +1017,9 @@ cusa_status cusa_attention_recall(const cusa_params* params, const void* q, cons
     void* out_tmp = ws_ptr<uint16_t>(ws, w.out_tmp);
     const int n_max = params->budget < kv->max_seq_len ? params->budget : kv->max_seq_len;
     if (idx_per_head) st = run_attention_per_head(params, q, kv, idx, cnt, out_tmp, ws, w, s, lse_set);
-    else st = run_attention<true>(params, q, kv, idx, cnt, n_max, out_tmp, ws, w, s, nullptr, lse_set);
+    else st = run_attention<true>(params, q, kv, idx, cnt, n_max, out_tmp, ws, w, s, ScoreOut(), lse_set);
     if (st != CUSA_OK) return st;
-    st = run_attention<false>(params, q, kv, nullptr, nullptr, kv->max_seq_len, out_tmp, ws, w, s, nullptr, lse_all);
+    st = run_attention<false>(params, q, kv, nullptr, nullptr, kv->max_seq_len, out_tmp, ws, w, s, ScoreOut(), lse_all);
     if (st != CUSA_OK) return st;
     launch(KID_RECALL, recall_kernel, (n + 255) / 256, 256, 0, s, lse_set, lse_all, recall, n);
     return launch_status();

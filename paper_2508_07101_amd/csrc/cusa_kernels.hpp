@@ -11,8 +11,8 @@
 //   topk_values_kernel  a selection layer's top-k and, on the rest of the chip, its output
 //                       softmax(P) V from those scores
 //   attn_kernel         split-K flash-decode over all tokens or over rho
-//                       (Eq. 1 / SparseAttention of Alg. 1), GQA group in registers; its filtered
-//                       form also keeps the selection's candidates above a threshold
+//                       (Eq. 1 / SparseAttention of Alg. 1), GQA group in registers; its scoring
+//                       forms also write the candidates' scores, or keep those above a threshold
 //   sample_threshold_kernel   per-head thresholds from a sample of the scores (filtered selection)
 //   attn_reduce_kernel  merges the split-K partials and writes bf16
 //   per_head_rho_kernel, rank_aggregate_kernel, recall_kernel   the head-to-head variant, the other
@@ -96,8 +96,8 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
 
 // ---------------------------------------------------------------- scoring
 //
-// The selection scores P = q.K^T are made by score_kernel and, where only candidates above a threshold are kept, by
-// attn_kernel's filtered form.  Their bit-exactness rests on the product
+// The selection scores P = q.K^T are made by score_kernel and, in the same pass as a selection layer's output or where only candidates above a
+// threshold are kept, by attn_kernel's scoring forms.  Their bit-exactness rests on the product
 // chain: V_MFMA_F32_4X4X1_16B_F32 takes, per lane, one binary32 element of q (head = lane % 4) and one
 // of K (the lane's row) and adds the 4 heads x 64 rows of single products to the accumulators.  With
 // k = 1 there is exactly one product (exact: bf16 x bf16 has a 16-bit significand) and one rounded
@@ -2003,8 +2003,9 @@ __device__ __forceinline__ float lane_value(float v, int lane) {
 
 __device__ __forceinline__ int wave_base_of(unsigned tid) { return (int)(tid >> 6); }
 
-// FILTER (selection layer with many scores, all tokens): the candidates of [0, L - window) whose scores reach their head's threshold
-// are kept (sample_threshold_kernel has the account).  q.k then runs as the k = 1 MFMA chain -- the pinned
+// SCORE (selection layer, all tokens): the scores of the candidate range [0, L - window) are also
+// written to P[b][head][t] (row stride ldp), so the layer's K is read once for both (Alg. 1 computes
+// the layer's output and P from the same K).  q.k then runs as the k = 1 MFMA chain -- the pinned
 // left-to-right binary32 sum (see "scoring" above) -- instead of the k = 4 bf16 MFMA, and the softmax
 // uses those same values.
 //
@@ -2015,14 +2016,14 @@ __device__ __forceinline__ int wave_base_of(unsigned tid) { return (int)(tid >> 
 // -- the head-to-head selection the paper compares with (Sec. 3.2, the generalization figure) --
 // so a workgroup serves one query head, blockIdx.y counts query heads (G of them) and head y reads
 // KV head y >> hshift.  Nothing is shared inside a GQA group: each head fetches its own rows.
-template <int GQ, int TI, bool SPARSE, bool PAGED, bool PER_HEAD = false, bool FILTER = false>
+template <int GQ, int TI, bool SPARSE, bool PAGED, bool SCORE = false, bool PER_HEAD = false, bool FILTER = false>
 __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt, const int32_t* __restrict__ seq_lens,
     const uint16_t* __restrict__ q, int budget, int n_splits, int chunk, int G, float scale_log2e,
     float* __restrict__ part_acc, float* __restrict__ part_ml, uint16_t* __restrict__ out, float* __restrict__ lse,
-    int window, int hshift, FilterState flt, KvView kv) {
-    static_assert(!(FILTER && SPARSE), "candidates are kept by the pass over all tokens");
-    static_assert(!FILTER || GQ <= 4, "the filtered pass of a group of 8 does not fit the register file");
+    float* __restrict__ P, int64_t ldp, int window, int hshift, FilterState flt, KvView kv) {
+    static_assert(!(SCORE && SPARSE), "scores are emitted by the pass over all tokens");
+    static_assert(!FILTER || SCORE, "the filter is a form of the scoring variant");
     static_assert(!PER_HEAD || (SPARSE && GQ == 1), "per-head token lists: one query head per workgroup");
     constexpr int TILE = TI * 4;                      // tokens per wave iteration (<= 64)
     constexpr int WG_TILE = TILE * ATTN_WAVES;
@@ -2030,15 +2031,15 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     constexpr int QSB = 136;                          // padded head stride of q in LDS (bf16 elements)
     // A wave's K tile buffer (TILE rows of 256 bytes) also carries its partial accumulators
     // (GQ x 128 floats) into the final merge.
-    // The filtered form parks a tile's K rows in two halves of 64 columns, one after the other (its
-    // product chain walks the columns in order anyway), which leaves LDS for the candidates of the
-    // workgroup's whole run (cstage below).
-    constexpr int KSLOTS = FILTER ? 8 : 16;            // 16-byte slots of a K row held in LDS at a time
+    // The scoring variant parks a tile's K rows in two halves of 64 columns, one after the other (its
+    // product chain walks the columns in order anyway), which leaves LDS for the scores of the
+    // workgroup's whole run (pstage below).
+    constexpr int KSLOTS = SCORE ? 8 : 16;            // 16-byte slots of a K row held in LDS at a time
     constexpr int WAVE_LDS = TILE * KSLOTS * 16;      // bytes of a wave's tile buffer
     static_assert(WAVE_LDS >= GQ * D * 4, "the K tile buffer must hold a wave's partial accumulators");
     __shared__ __attribute__((aligned(16))) unsigned char smem_raw[ATTN_WAVES * WAVE_LDS];
     // this wave's K rows: chunk c of row r at slot c ^ (r & 7) (a swizzle over all sixteen slots, c ^ (r & 15),
-    // removes the remaining two-way bank conflicts and was measured: no faster); filtered form: chunk c
+    // removes the remaining two-way bank conflicts and was measured: no faster); scoring variant: chunk c
     // (of the half) at slot c ^ ((r >> 1) & 7)
     u32x4* const ktile = reinterpret_cast<u32x4*>(smem_raw) + wave_base_of(threadIdx.x) * (TILE * KSLOTS);
     __shared__ float sm_m[ATTN_WAVES][GQ];
@@ -2049,20 +2050,25 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     // together (rows 4ig .. 4ig+3 of its row group) are one 8-byte word.
     static_assert(TI % 4 == 0 && WAVE_LDS >= TI * SETS * 32, "the numerators must fit the K tile buffer");
     __bf16* const pbuf16 = reinterpret_cast<__bf16*>(ktile);
-    // q in LDS: a private bf16 copy per wave, or -- in the filtered form, whose product chain takes
+    // q in LDS: a private bf16 copy per wave, or -- in the scoring variant, whose product chain takes
     // binary32 operands -- one binary32 copy for the workgroup (every wave writes all of it with the
     // same values, so a wave depends on its own writes only and no workgroup barrier is needed).
     constexpr int QSF = 132;                          // padded head stride of the binary32 copy (floats)
-    __shared__ __attribute__((aligned(16))) uint16_t qlds_all[FILTER ? 1 : ATTN_WAVES][FILTER ? 8 : SETS * 4 * QSB];
-    __shared__ __attribute__((aligned(16))) float qf32[FILTER ? SETS * 4 * QSF : 4];
-    // FILTER: the (score key, position) composites of the run's candidates (of its last STAGE_IT iterations' ones, should a run
-    // be longer: the host caps it at ATTN_SCORE_CHUNK_CAP tokens) at or above the head's threshold, compacted per head --
-    // STAGE_CAND of them per head at most, or the head is flagged -- on their way to the head's list.
-    constexpr int STAGE_IT = ATTN_SCORE_CHUNK_CAP / WG_TILE;
-    constexpr int STAGE_CAND = ATTN_SCORE_CHUNK_CAP / 2;
-    __shared__ __attribute__((aligned(16))) uint64_t cstage[FILTER ? GQ * STAGE_CAND : 2];
-    __shared__ int cand_n[FILTER ? GQ : 1], cand_base[FILTER ? GQ : 1];
-    __shared__ uint32_t thr_lds[FILTER ? GQ : 1];
+    __shared__ __attribute__((aligned(16))) uint16_t qlds_all[SCORE ? 1 : ATTN_WAVES][SCORE ? 8 : SETS * 4 * QSB];
+    __shared__ __attribute__((aligned(16))) float qf32[SCORE ? SETS * 4 * QSF : 4];
+    // scoring variant: the scores of the workgroup's run (of its last STAGE_IT iterations, should a run be
+    // longer: the host caps it at STAGE_TOK tokens), [head][token], on their way to P
+    constexpr int STAGE_TOK = GQ >= 8 ? ATTN_SCORE_CHUNK_CAP_G8 : ATTN_SCORE_CHUNK_CAP;   // 32 KB at groups of 4 and 8
+    constexpr int STAGE_IT = STAGE_TOK / WG_TILE;
+    __shared__ __attribute__((aligned(16))) float pstage[SCORE ? GQ * STAGE_TOK : 4];
+    // Filtered form of the scoring variant (FILTER; see sample_threshold_kernel): instead of every score,
+    // the buffer takes the (score key, position) composites of the candidates at or above the head's
+    // threshold, compacted per head -- STAGE_CAND of them per head at most, or the head is flagged.
+    constexpr int STAGE_CAND = STAGE_TOK / 2;         // composites are twice a score's size
+    uint64_t* const cstage = reinterpret_cast<uint64_t*>(pstage);
+    __shared__ int cand_n[SCORE ? GQ : 1], cand_base[SCORE ? GQ : 1];
+    __shared__ uint32_t thr_lds[SCORE ? GQ : 1];
+    constexpr bool filtered = FILTER;
     // Workgroups go to the 8 XCDs round-robin in launch order (blockIdx.x fastest).  With ragged
     // lengths the low splits are the busy ones; starting each (sequence, KV head) at a different
     // block spreads them evenly over the XCDs instead of loading the first ones.
@@ -2092,7 +2098,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     // Every wave keeps its own bf16 copy of q in LDS (no workgroup barrier on the way in): lane l
     // fetches 16 bytes of head l / 16 per set now and parks them once the first tile's loads are
     // under way.  Heads beyond GQ score zero.
-    uint16_t* const qlds = qlds_all[FILTER ? 0 : wave];
+    uint16_t* const qlds = qlds_all[SCORE ? 0 : wave];
     u32x4 qv[SETS];
 #pragma unroll
     for (int s = 0; s < SETS; ++s) {
@@ -2136,12 +2142,12 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     // Rows past the end of the run read some token of the sequence (a valid row) so that all
     // loads are unconditional and issue back to back; their scores are masked below.
     // The next tile's K rows are requested as soon as this tile's are parked in LDS, i.e. before
-    // this tile's arithmetic (not in the filtered form, whose 64-token tiles leave no registers
+    // this tile's arithmetic (not in the scoring variant, whose 64-token tiles leave no registers
     // for it; there the rows are requested at the top of the tile's own iteration).
-    constexpr bool PREFETCH = !FILTER;
-    // The filtered form of a group of 4 has no registers for K and V rows at once (64 each at 64-token
-    // tiles): its V rows are requested once the K rows are parked in LDS.
-    constexpr bool V_LATE = FILTER && GQ >= 4;
+    constexpr bool PREFETCH = !SCORE;
+    // The scoring variant of a group of 8 has no registers for K and V rows at once (64 each at 64-token
+    // tiles, beside 64 accumulators): its V rows are requested once the K rows are parked in LDS.
+    constexpr bool V_LATE = SCORE && (GQ >= 8 || (FILTER && GQ >= 4));
     u32x4 kreg[TI], vreg[TI];
     int64_t off[TI];
     // a valid position for row load i of the tile that starts at list entry t_ (an index outside the
@@ -2187,6 +2193,35 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
         request_k();
         advance(tile0);
     }
+    // Scoring variant: the scores go to P through a staging buffer in LDS that the whole workgroup
+    // writes out in one burst.  A few per cent of small writes scattered
+    // through a streaming read cost this machine a sixth of its read rate; the same bytes written in
+    // workgroup-sized bursts cost a third of that (measured with plain read / write kernels).  The
+    // burst is issued at the end of the workgroup's run (the host caps a run at STAGE_TOK tokens; a
+    // longer one would take a burst every STAGE_IT iterations, before the next tile's rows are
+    // requested).  Measured on the selection pass, us without stores / scattered stores / bursts:
+    // c3 95 / 106 / 99, c4 100 / 121 / 106, c5 867 / 1036 / 1008.  Giving every workgroup its own
+    // burst phase, so that the chip's bursts do not coincide, was measured too and is slower.
+    auto flush_scores = [&](int g0, int n_tok) {       // staged tokens [g0, g0 + n_tok) of this workgroup's run
+        if constexpr (SCORE) {
+            const int lim = min(end, L - window);      // candidates only; L <= budget: rho is every token, nothing is scored
+            if (L > budget && g0 < lim) {
+                const int quads = n_tok >> 2;
+                for (int i = tid; i < GQ * quads; i += ATTN_THREADS) {
+                    const int h = i / quads, w4 = (i - h * quads) * 4, t = g0 + w4;
+                    const f32x4 v = *reinterpret_cast<const f32x4*>(&pstage[h * STAGE_TOK + w4]);
+                    float* const dst = &P[(head0 + h) * ldp + t];
+                    if (t + 3 < lim) {
+                        __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(dst));
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (t + e < lim) dst[e] = v[e];
+                    }
+                }
+            }
+        }
+    };
     // filtered form: the staged candidates of every head go to the head's list in memory, one reservation
     // per head and workgroup.  The reservation is a device-scope atomic whose answer takes microseconds:
     // reserve_candidates asks (thread h for head h; returns the answer, -1 if there is nothing to copy),
@@ -2194,7 +2229,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     // and writes its attention partials in between.  Both are called by the whole workgroup.
     auto reserve_candidates = [&]() -> int {
         int base = -1;
-        if constexpr (FILTER) {
+        if constexpr (SCORE) {
             lds_barrier();                               // every wave's candidates are staged
             if (tid < GQ) {
                 const int n_h = cand_n[tid];
@@ -2205,7 +2240,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
         return base;
     };
     auto copy_candidates = [&](int base) {
-        if constexpr (FILTER) {
+        if constexpr (SCORE) {
             if (tid < GQ) {
                 if (base >= 0 && base + cand_n[tid] > flt.cap) {   // the head's list is full (the count stays above cap: the ranking sees it too)
                     flag_failed(flt, head0 + tid);
@@ -2239,15 +2274,23 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     int it = 0;                                          // iterations of the workgroup so far
     for (int w0 = begin; w0 < end; w0 += WG_TILE, ++it) {
         const int t0 = w0 + wave * TILE;
-        // Only the filtered form has workgroup barriers inside the loop; there a wave whose tile lies
+        // Only the scoring variant has workgroup barriers inside the loop; there a wave whose tile lies
         // past the run's end still takes part in them.
         const bool active = t0 < end;
-        if (FILTER && it - it_staged == STAGE_IT) {      // workgroup-uniform
-            copy_candidates(reserve_candidates());
+        // workgroup-uniform; the buffer holds STAGE_IT iterations at most
+        const bool burst_due = SCORE && it - it_staged == STAGE_IT;
+        if (burst_due) {
+            if (filtered) {
+                copy_candidates(reserve_candidates());
+            } else {
+                lds_barrier();                           // every wave's scores since the last burst are staged
+                flush_scores(begin + it_staged * WG_TILE, (it - it_staged) * WG_TILE);
+                lds_barrier();                           // ... and read, before the buffer is written again
+            }
             it_staged = it;
         }
         if (!active) {
-            if constexpr (!FILTER) break;
+            if constexpr (!SCORE) break;
             continue;
         }
         if constexpr (!PREFETCH) {
@@ -2265,7 +2308,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
         if (!q_parked) {
 #pragma unroll
             for (int s = 0; s < SETS; ++s) {
-                if constexpr (FILTER) {
+                if constexpr (SCORE) {
                     float qf[8];
                     unpack8(make_uint4(qv[s].x, qv[s].y, qv[s].z, qv[s].w), qf);
                     float* const dst = &qf32[(s * 4 + r) * QSF + c * 8];
@@ -2277,7 +2320,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
             }
             q_parked = true;
         }
-        if constexpr (!FILTER) {
+        if constexpr (!SCORE) {
 #pragma unroll
             for (int i = 0; i < TI; ++i) {
                 const int row = i * 4 + r;
@@ -2295,7 +2338,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
         f32x4 sc[SETS];
 #pragma unroll
         for (int s = 0; s < SETS; ++s) sc[s] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        if constexpr (FILTER) {
+        if constexpr (SCORE) {
             // columns 0..63, then 64..127: the lanes holding that half of a row park it, every lane then
             // walks its own token's 64 columns in order
 #pragma unroll
@@ -2345,7 +2388,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
                             sc[s] = __builtin_amdgcn_mfma_f32_4x4x1f32(qf[s][e], kf[e], sc[s], 0, 0, 0);
                 }
             }
-            {
+            if (filtered) {
                 const int t = t0 + tl;
                 const bool is_cand = lane < TILE && t >= flt.n_sink && t < min(end, L - window);
 #pragma unroll
@@ -2362,6 +2405,9 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
                     }
                     asm volatile("" ::: "memory");       // one head at a time: nothing of the next is fetched early
                 }
+            } else if (lane < TILE) {
+#pragma unroll
+                for (int h = 0; h < GQ; ++h) pstage[h * STAGE_TOK + (it - it_staged) * WG_TILE + wave * TILE + tl] = sc[h >> 2][h & 3];
             }
         } else {
 #pragma unroll
@@ -2433,7 +2479,14 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
         wave_lds_sync();                              // the tile buffers are rewritten next iteration
     }
     int cand_reserved = -1;
-    if constexpr (FILTER) cand_reserved = reserve_candidates();   // used after the merge below
+    if constexpr (SCORE) {
+        if (filtered) {
+            cand_reserved = reserve_candidates();        // used after the merge below
+        } else if (it > it_staged) {                   // the iterations staged since the last burst
+            lds_barrier();
+            flush_scores(begin + it_staged * WG_TILE, (it - it_staged) * WG_TILE);
+        }
+    }
     // Merge.  Inside the wave the four row groups are folded with lane swaps: of the N = 8 GQ
     // values of a lane, two folds leave N / 4 complete sums, those with flat index (head * 8 +
     // column) v0 .. v0 + N/4 - 1 where v0 depends on the row group.  The wave parks them in its
@@ -2683,7 +2736,6 @@ struct ValueArgs {
     KvView kv;
 };
 constexpr int VALUE_TILE = 16;
-constexpr int64_t VALUE_MAX_STEP = (int64_t)1 << 26;   // elements between tokens: a lane's distance from its group's first row fits 32 bits
 constexpr int VALUE_WG_TILE = VALUE_TILE * SEL_WAVES;
 struct ValueLds {
     float m[SEL_WAVES][8], l[SEL_WAVES][8];
@@ -2720,7 +2772,7 @@ __device__ __forceinline__ void weigh_values(const ValueArgs& a, int item, float
     for (int e = 0; e < 8; ++e) acc[e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     // A tile is 16 rows (a page): the address of its first row is uniform, a lane adds its row's distance from it, rows
     // past the end of the run that of its last token.
-    const uint32_t row_bytes = 2u * (uint32_t)(a.paged ? D : a.kv.st);   // (VALUE_MAX_STEP)
+    const uint32_t row_bytes = 2u * (uint32_t)(a.paged ? D : a.kv.st);   // (32 bits: values_beside_topk)
     u32x4 v[TI];
     int pg = 0;                                       // page of the tile to be requested next
     auto page_load = [&](int t_) {
@@ -2728,7 +2780,7 @@ __device__ __forceinline__ void weigh_values(const ValueArgs& a, int item, float
     };
     auto request_p = [&](int t_) {
         asm volatile("" : "+v"(my_lane));             // (no registers for what can be made of it)
-        const uint32_t heads = (uint32_t)((my_lane >> 4) & (HROWS - 1)) * (uint32_t)(HPL * a.ldp);   // (a sequence's length is capped by the host)
+        const uint32_t heads = (uint32_t)((my_lane >> 4) & (HROWS - 1)) * (uint32_t)(HPL * a.ldp);   // (32 bits: values_beside_topk)
         const uint32_t at = 4u * (heads + (uint32_t)min(t_ + (my_lane & 15), last));
 #pragma unroll
         for (int j = 0; j < HPL; ++j) {

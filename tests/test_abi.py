@@ -144,6 +144,20 @@ def test_workspace_bytes_never_shrink_with_capacity(B, H, G, K, W):
         prev = n
 
 
+@pytest.mark.parametrize("B,H,G,K,W,k", [(8, 64, 8, 40000, 36000, 4096), (64, 32, 8, 9000, 8000, 0), (1, 8, 8, 300, 200, 0)])
+def test_workspace_bytes_never_shrink_with_capacity_and_wide_windows(B, H, G, K, W, k):
+    """The same where the scores' rows hold the candidates only, up to a bound: windows of most of the tokens."""
+    p = cb.make_params(B, H, G, K, W, k)
+    at = W * 5 // 2
+    prev = 0
+    for m in sorted(set([W + 1, W + 63, K, K + 1, at - 65, at - 64, at - 1, at, at + 1, at + 64, at + 65] + list(range(W + 1, W * 4 + 9000, 997)))):
+        n = cb.workspace_bytes(p, m)
+        assert n >= prev, f"workspace shrinks from {prev} to {n} at max_seq_len {m}"
+        prev = n
+    lay = cb.workspace_layout(p, K + 100)
+    assert lay.ld_scores < 2 * (K + 100 - W) + 64, "a row of scores grows with the window"
+
+
 def test_layout_reports_the_filtered_fast_path():
     """The layout says whether a selection layer of this size keeps only the scores that can matter: many scores,
     groups of at most four heads, the default ranking, a sample dense enough for the longest sequence."""

@@ -140,3 +140,35 @@ def test_selection_layer_runs_cover_the_tokens_and_fit_the_workspace(tmp_path):
         }
 ''')
     assert out == "", out
+
+
+def test_the_selection_layers_values_stay_within_their_kernels_limits(tmp_path):
+    """Where the values are made beside the top-k: fewer than 2^32 threads in the launch, rows of V and of scores within 32 bits of bytes of each
+    other, room for every token's score; for all that the selection accepts (up to 1179648 candidates, windows of any length)."""
+    out = run_checks(tmp_path, r'''
+    (void)plan;
+    const int MAX_POSITIONS = 1179648;
+    long taken = 0;
+    for (int pairs : {1, 2, 7, 64, 1000, 65535, 524280, 4000000})
+        for (int g : {1, 2, 4, 8})
+            for (int64_t cand = 1; cand <= MAX_POSITIONS; cand += cand < 3000 ? 97 : cand / 3)
+                for (int64_t window : {(int64_t)0, cand / 8, cand / 2, cand * 2 / 3, cand, 5 * cand, (int64_t)134217728, (int64_t)160000000, (int64_t)2000000000})
+                    for (int64_t step : {(int64_t)0, (int64_t)128, (int64_t)1 << 26, ((int64_t)1 << 26) + 8, (int64_t)1 << 31}) {
+                        if (cand + window > 2147483647) continue;
+                        const int n = (int)(cand + window);
+                        const int64_t rows = (int64_t)pairs * g;
+                        if (!values_beside_topk(rows, pairs, (int)window, n, step)) continue;
+                        ++taken;
+                        const ValuePlan v = plan_values(n, pairs, (int)rows);
+                        const int64_t ldp = ((int64_t)n + 63) / 64 * 64;
+                        if ((rows + (int64_t)pairs * v.n_splits) * 1024 >= (int64_t)1 << 32) FAIL("%d pairs of %d, groups of %d: threads", pairs, n, g);
+                        if (((g - 1) * ldp + n) * 4 >= (int64_t)1 << 32) FAIL("%d tokens, groups of %d: scores", n, g);
+                        if (step * 2 * 15 >= (int64_t)1 << 32) FAIL("%lld elements between tokens", (long long)step);
+                        if (!scores_of_all_tokens((int)window, n)) FAIL("no room for the scores of %d tokens", n);
+                    }
+    if (taken < 5000) FAIL("only %ld taken", taken);
+    for (int window : {0, 100, 12345, 1000000})                  // a workspace for a capacity serves every shorter bound
+        for (int n = window + 1; n < window + 1179648; n += step(n))
+            if (scores_of_all_tokens(window, n) && !scores_of_all_tokens(window, n + 1)) FAIL("window %d at %d", window, n);
+''')
+    assert out == "", out

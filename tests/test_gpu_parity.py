@@ -807,6 +807,55 @@ def test_attention_passes_beside_scores_of_minus_infinity(H, paged):
     _check_outputs64(inp, r, 1, rho)
 
 
+@pytest.mark.parametrize("H,layout", [(8, "head_major"), (16, "paged"), (32, "token_major"), (64, "paged"), (64, "head_major")])
+@pytest.mark.parametrize("lens,K,W", [((1500, 1100, 1024, 1300), 1100, 1000),      # the window is most of the tokens
+                                      ((3000, 3000), 2040, 2000), ((20011,), 19000, 18500)])
+def test_selection_layers_with_a_wide_window_take_one_pass(H, layout, lens, K, W):
+    """Few candidates beside a long window: the pass over K and V writes their scores, and its workspace has no room for the window's."""
+    w = small(f"wide_window_{H}_{layout}", batch=len(lens), n_q_heads=H, seq_len=max(lens), lengths=lens, budget=K, window=W,
+              n_layers=1, schedule=(LAYER_SELECT,), paged=layout == "paged", n_sink=1)
+    inp = wl.make_inputs(w, DEV)
+    if layout == "token_major":
+        for lay in inp.layers:
+            lay.k = lay.k.transpose(1, 2).contiguous().transpose(1, 2)
+            lay.v = lay.v.transpose(1, 2).contiguous().transpose(1, 2)
+    r = StepRunner(inp)
+    r.outs[0].fill_(float("nan"))
+    r.ws.fill_(0xff)
+    calls = _kernel_calls(r.run)
+    assert calls["attn_kernel<full+score>"] == 1 and not calls.get("score_kernel") and not calls.get("topk_values_kernel"), calls
+    check_select(inp, r, 0)
+    _check_outputs64(inp, r, 0)
+
+
+def test_selection_layer_over_tokens_far_apart_in_memory():
+    """2^26 + 8 elements between tokens: beyond what the values' kernel reaches with 32 bits; a cache of 40 tokens, one KV head."""
+    L, step = 40, (1 << 26) + 8
+    base = torch.zeros((2, (L - 1) * step + 128), dtype=torch.bfloat16, device=DEV)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(5)
+    rows = torch.randn((2, L, 128), generator=gen, device=DEV).to(torch.bfloat16)
+    far = torch.as_strided(base, (2, 1, 1, L, 128), (base.shape[1], base.shape[1], base.shape[1], step, 1))
+    far.copy_(rows.view(2, 1, 1, L, 128))
+    near = rows.view(2, 1, 1, L, 128).contiguous()
+    q = torch.randn((1, 8, 128), generator=gen, device=DEV).to(torch.bfloat16)
+    p = cb.make_params(1, 8, 1, 20, 4)
+    lens = torch.tensor([L], dtype=torch.int32, device=DEV)
+    got = []
+    for k, v in (near, far):
+        ws = cb.alloc_workspace(p, L, DEV)
+        out, idx = torch.empty_like(q), torch.zeros((1, 20), dtype=torch.int32, device=DEV)
+        cnt = torch.zeros((1,), dtype=torch.int32, device=DEV)
+        cb.select_layer(p, q, cb.KvCache(k, v, lens, L), out, idx, cnt, ws)
+        full = torch.empty_like(q)
+        cb.full_attn(p, q, cb.KvCache(k, v, lens, L), full, ws)
+        got.append((out, idx, cnt, full))
+    torch.cuda.synchronize()
+    for a, b in zip(got[0][1:], got[1][1:]):
+        assert torch.equal(a, b)
+    assert torch.allclose(got[0][0].float(), got[1][0].float(), rtol=2.0 ** -7, atol=2.0 ** -7)
+
+
 def test_filtered_selection_layer_fast_path_and_its_second_chance():
     """A selection layer with many scores keeps only the candidates above a sampled threshold.  The result must
     not depend on the guess: random scores (the guess holds), massive ties (far more candidates than the lists
