@@ -685,9 +685,9 @@ constexpr float SLICE_Z = 6.0f;                         // instead of FAST_Z: a 
 // parts[row][slice][k]; the k best of a row are among the k best of its slices, so a second launch (MERGE) selects
 // and ranks among those n_slices * k composites instead of the row.  MERGE also ranks what a filtered pass kept.
 //
-// lin: number of the row (and with it of the workgroup) among the B * H; z: its slice.
+// h, b: the workgroup's place among the H heads of B sequences, heads first; z: its slice.
 template <int ITEMS, int MTOP, bool MERGE>
-__device__ __forceinline__ void topk_row(const int lin, const int z, const int B, const float* __restrict__ P, int64_t ldp,
+__device__ __forceinline__ void topk_row(int h, int b, const int z, const int B, const float* __restrict__ P, int64_t ldp,
                                          const int32_t* __restrict__ seq_lens, int32_t* __restrict__ rho_head, int H, int k,
                                          int budget, int window, int raw_keys, int n_sink, uint64_t* __restrict__ parts,
                                          int slice_len, int n_slices, const int32_t* __restrict__ only_rows, FilterState flt,
@@ -710,11 +710,13 @@ __device__ __forceinline__ void topk_row(const int lin, const int z, const int B
     // heads of a sequence are put on one XCD, whose L2 then merges their 4-byte stores into whole
     // lines instead of each XCD writing its own fragments of every line (c5: 104 MB written for a 13 MB
     // output before).
-    int h = lin % H, b = lin / H;
-    if (lin < (B / 8) * 8 * H) {
-        const int within = lin % (8 * H);
-        b = (lin / (8 * H)) * 8 + (within & 7);
-        h = within >> 3;
+    {
+        const int lin = h + H * b;
+        if (lin < (B / 8) * 8 * H) {
+            const int within = lin % (8 * H);
+            b = (lin / (8 * H)) * 8 + (within & 7);
+            h = within >> 3;
+        }
     }
     // only_rows: the second chance of the filtered fast path ranks the flagged heads only
     if (only_rows && only_rows[(int64_t)b * H + h] == 0) return;
@@ -1237,7 +1239,7 @@ __global__ __launch_bounds__(SEL_THREADS, topk_lean(ITEMS, MTOP) ? 8 : 4) void t
                                                             uint64_t* __restrict__ parts, int slice_len, int n_slices,
                                                             const int32_t* __restrict__ only_rows, FilterState flt,
                                                             SliceLists sl) {
-    topk_row<ITEMS, MTOP, MERGE>((int)(blockIdx.x + H * blockIdx.y), (int)blockIdx.z, (int)gridDim.y, P, ldp, seq_lens, rho_head, H, k, budget,
+    topk_row<ITEMS, MTOP, MERGE>((int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z, (int)gridDim.y, P, ldp, seq_lens, rho_head, H, k, budget,
                                  window, raw_keys, n_sink, parts, slice_len, n_slices, only_rows, flt, sl);
 }
 
@@ -2926,7 +2928,7 @@ __global__ __launch_bounds__(SEL_THREADS, topk_lean(ITEMS, MTOP) ? 8 : 4) void t
         i -= n_topk - turns;
     }
     if (!values) {
-        topk_row<ITEMS, MTOP, false>(i, 0, B, P, ldp, seq_lens, rho_head, H, k, budget, window, 0, n_sink, nullptr, 0, 1, nullptr,
+        topk_row<ITEMS, MTOP, false>(i % H, i / H, 0, B, P, ldp, seq_lens, rho_head, H, k, budget, window, 0, n_sink, nullptr, 0, 1, nullptr,
                                      FilterState{}, SliceLists{});
         return;
     }
