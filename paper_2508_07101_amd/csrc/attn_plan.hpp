@@ -129,27 +129,41 @@ inline AttnPlan plan_attn(int n_max, int BG, int g, AttnKind kind, bool paged) {
     return pl;
 }
 
+// Workgroups per pair for n pieces each of BG pairs: about `limit` in all at most, all with as many pieces (some with one less).
+inline int in_turn(int n, int BG, int limit) {
+    const int64_t rounds = ((int64_t)n * BG + limit - 1) / limit;
+    return (int)std::max<int64_t>(1, (n + rounds - 1) / rounds);
+}
+
 // The scoring pass (score_kernel): a workgroup for every workgroup tile, of 256 tokens (128 where these would be too few to keep every
-// CU busy twice over); there is no partial result to merge, so nothing bounds their number but the time that idle ones take.  The second chance of
-// the filtered selection finds nothing to do as a rule, so it has at most about 8192 workgroups, which take a (sequence, KV head)'s tiles in turn
-// (64 sequences of 8192 to 32768, no head flagged: 65536 workgroups are gone after 20.5 us, 32768 after 10.7, 8192 after 4.0; 31 sequences of 4119 to
-// 16478, the heads of the short ones flagged: in runs of 2048 tokens 54 us, in turn 22).
+// CU busy twice over); there is no partial result to merge, so nothing bounds their number but the time that idle ones take: where the bound is
+// far above the lengths, which are not known here, nearly all have nothing to do (64 sequences of 8 KV heads, no tile to be scored: 65536
+// workgroups are gone after 20.5 us, 32768 after 10.7, 8192 after 4.0).  Beyond SCORE_WGS of them each takes several of a (sequence, KV
+// head)'s tiles in turn (32 sequences of 4096, 64 heads, bound 1000000, cusa_select, us: a workgroup for every tile 418, at most 131072 125, 65536
+// 115, 32768 110; 64 of 32768 and no more 974, 974, 975, 991).  The second chance of the filtered selection finds nothing to do as a rule
+// and has at most about 8192 (31 sequences of 4119 to 16478, the heads of the short ones flagged: in runs of 2048 tokens 54 us, in turn 22).
 struct ScorePlan {
     int ti;        // row-load instructions of a wave: tiles of 128 or 256 tokens
     int n_splits;  // workgroups per (sequence, KV head)
 };
+constexpr int SCORE_WGS = 65536;
 inline ScorePlan plan_score(int n_max, int BG, bool second_chance) {
     const int ti = second_chance || (int64_t)n_max * BG > 256 * TARGET_WGS ? 16 : 8, tile = ti * 4 * ATTN_WAVES;
     const int tiles = (n_max + tile - 1) / tile;
-    return {ti, second_chance ? std::min(tiles, std::max(8, 8192 / BG)) : tiles};
+    return {ti, second_chance ? std::min(tiles, std::max(8, 8192 / BG)) : in_turn(tiles, BG, SCORE_WGS)};
 }
 
 // A selection layer's values (weigh_values): workgroups of 16 waves.
 struct ValuePlan {
-    int chunk;     // tokens per workgroup, a multiple of the workgroup tile
-    int n_splits;
+    int chunk;     // tokens of a run, a multiple of the workgroup tile
+    int n_splits;  // runs per (sequence, KV head)
+    int wgs;       // workgroups that take them in turn
 };
 constexpr int VALUE_TOKENS = 256;   // a tile of 16 for each wave
+// A workgroup of 16 waves that has nothing to do takes 2.6 ns of all CUs' time, one of four waves 0.3: beyond VALUE_WGS of them each takes several runs
+// (us for the layer, a workgroup for every run and so: 64 sequences of 4096, 64 heads, bound 131072 506 and 318, one pass 338; 128 of 3000 888 and
+// 547, 535; 32 of 4096, bound 1000000 644 and 192, 363.  64 of 9000 and no more 524; in 2048 workgroups 537, in 1024 552).
+constexpr int VALUE_WGS = 4096;
 // One workgroup to a CU that no row of the top-k starts on (rows: their number) while that makes runs of up to 1536 tokens -- two or
 // three tiles for every wave --, otherwise runs of 1024, which fill the CUs as they become free.  Measured (us for the layer; 256-token steps
 // from 256 to 4096): 8 pairs of 9000 best 22.9, so 23.0; of 16384 26.1 and 26.1; of 32768 36.0 and 36.0; of 65536 59.1, in runs of 1024 60.5;
@@ -163,7 +177,8 @@ inline ValuePlan plan_values(int n_max, int BG, int rows) {
         chunk = ((int64_t)n_max + MAX_SPLITS - 1) / MAX_SPLITS;
         chunk = (chunk + VALUE_TOKENS - 1) / VALUE_TOKENS * VALUE_TOKENS;
     }
-    return {(int)chunk, (int)std::max<int64_t>(1, (n_max + chunk - 1) / chunk)};
+    const int n = (int)std::max<int64_t>(1, (n_max + chunk - 1) / chunk);
+    return {(int)chunk, n, in_turn(n, BG, VALUE_WGS)};
 }
 
 // Whether a row of the workspace's scores has room for every token, not just the candidates: see values_beside_topk, which asks for it.  Once true
@@ -175,7 +190,7 @@ inline bool scores_of_all_tokens(int window, int max_seq_len) { return (int64_t)
 // rows: batch * query heads.
 inline bool values_beside_topk(int64_t rows, int BG, int window, int max_seq_len, int64_t token_step) {
     // the rows and runs are workgroups of 1024 threads of a one-dimensional launch: fewer than 2^32 threads
-    if (rows + (int64_t)BG * plan_values(max_seq_len, BG, (int)std::min(rows, (int64_t)CUS)).n_splits >= 1 << 22) return false;
+    if (rows + BG + VALUE_WGS >= 1 << 22) return false;
     // a lane's distance from the first row of its 16 fits 32 bits (elements between tokens; 0: paged)
     if (token_step > 1 << 26) return false;
     // The scores of a window are written and read for the output alone: 4 g bytes for the 256 of a row.  From two fifths of the tokens on the one pass

@@ -861,9 +861,28 @@ cusa_status run_select_layer(const cusa_params* p, const void* q, const cusa_kv*
     v.n_splits = pl.n_splits;
     v.chunk = pl.chunk;
     v.g = p->n_q_heads / p->n_kv_heads;
-    v.paged = kv->layout == CUSA_KV_PAGED ? 1 : 0;
-    v.items = pl.n_splits * p->batch * p->n_kv_heads;
-    v.kv = make_view(p, kv);
+    v.wgs = pl.wgs;
+    v.pairs = p->batch * p->n_kv_heads;
+    v.items = pl.wgs * v.pairs;
+    v.v = static_cast<const uint16_t*>(kv->v);
+    v.seq_lens = kv->seq_lens;
+    v.G = p->n_kv_heads;
+    if (kv->layout == CUSA_KV_PAGED) {
+        v.table = kv->block_table;
+        v.table_step = kv->max_pages;
+        v.paged = -1;
+        v.seq_step = 0;
+        v.head_step = PAGE * D;
+        v.group_step = (int64_t)p->n_kv_heads * (PAGE * D);
+        v.row_bytes = 2 * D;
+    } else {
+        v.table = kv->seq_lens;
+        v.table_step = v.paged = 0;
+        v.seq_step = kv->stride_batch;
+        v.head_step = kv->stride_head;
+        v.group_step = kv->stride_token;
+        v.row_bytes = (uint32_t)(2 * kv->stride_token);   // (32 bits: values_beside_topk)
+    }
     red = {v.part_acc, v.part_ml, v.out, kv->seq_lens, 0x7fffffff, pl.n_splits, pl.chunk, nullptr, pl.n_splits > 1 ? p->n_q_heads * p->batch : 0};
     return run_select(p, q, kv, idx, cnt, ws, w, s, false, false, nullptr, &red, &v);
 }

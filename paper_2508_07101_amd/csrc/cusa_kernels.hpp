@@ -2717,7 +2717,8 @@ __global__ __launch_bounds__(ATTN_THREADS, 4) void score_kernel(const int32_t* _
 // row, four row loads.  Lane (row group r, t) weighs token t for the r-th part of the group's heads; the weights go through LDS, as
 // bf16, into the A operand of V_MFMA_F32_16X16X16_BF16, one instruction for each of the lane's eight columns: after two V_PERM_B32 a lane
 // holds one column of its four rows.  A tile's scores are requested before its rows (loads return in order), so that the weights are made while
-// the rows arrive.  The weights are 2^x as the hardware has it: what it flushes to zero is below 2^-126 of the largest.
+// the rows arrive.  The weights, and the waves' factors when their sums meet, are 2^x as the hardware has it: what it flushes to zero is below
+// 2^-126 of the largest.
 //
 // What bounds it is memory and, for that, bytes in flight: a CU has at most about 64 KB of misses on their way, so half of the CUs do not saturate
 // the memory (128 of them: 4.5 TB/s of 6.5).  Hence 64 registers, tiles of 4 KB for each of 16 waves, and two workgroups to a CU, so that a row
@@ -2732,10 +2733,18 @@ struct ValueArgs {
     float* part_acc;
     float* part_ml;
     uint16_t* out;
-    int n_splits, chunk;      // chunk: a multiple of VALUE_WG_TILE tokens
-    int g, paged;             // g: query heads per KV head
+    int n_splits, chunk;      // runs per (sequence, KV head); chunk: a multiple of VALUE_WG_TILE tokens
+    int wgs, pairs;           // workgroups that take them in turn; (sequence, KV head) pairs
+    int g;                    // query heads per KV head
     int items;                // workgroups
-    KvView kv;
+    // V without a case distinction, which would cost the loop over runs registers: 16 rows start seq_step * b + head_step * kvh + group_step * n
+    // from v, where n is their page, or the first one's token (paged: all bits, or none), and are row_bytes apart
+    const uint16_t* v;
+    const int32_t* seq_lens;
+    const int32_t* table;     // [b][table_step]; not paged: an address that can be read, table_step 0
+    int64_t seq_step, head_step, group_step;
+    int G, table_step, paged;
+    uint32_t row_bytes;
 };
 constexpr int VALUE_TILE = 16;
 constexpr int VALUE_WG_TILE = VALUE_TILE * SEL_WAVES;
@@ -2746,22 +2755,18 @@ template <int GQ>
 constexpr size_t value_lds_bytes() { return (size_t)SEL_WAVES * GQ * D * 4; }
 
 template <int GQ>
-__device__ __forceinline__ void weigh_values(const ValueArgs& a, int item, float* sums_lds, ValueLds& st) {
+__device__ __forceinline__ void weigh_values(const ValueArgs& a, int pair, int split, int L, int wave, float* sums_lds, ValueLds& st) {
     constexpr int TI = VALUE_TILE / 4;
-    constexpr int HPL = GQ >= 4 ? GQ / 4 : 1;         // heads a lane weighs: those from head (row group % ROWS_USED) * HPL on
+    constexpr int HPL = GQ >= 4 ? GQ / 4 : 1;         // heads a lane weighs: those from head (row group % HROWS) * HPL on
     constexpr int HROWS = GQ / HPL;                   // row groups that weigh different heads
-    const int wave = __builtin_amdgcn_readfirstlane(wave_id());
-    const int pair = item / a.n_splits;
-    const int kvh = pair % a.kv.G, b = pair / a.kv.G;
-    const int split = (item + pair) % a.n_splits;     // short sequences' idle workgroups: spread over the XCDs
-    const int L = uniform_load(a.kv.seq_lens + b);
-    const int begin = split * a.chunk;
-    if (split > 0 && begin >= L) return;
-    const int last = min(begin + a.chunk, L) - 1;
-    const int64_t head0 = ((int64_t)b * a.kv.G + kvh) * GQ;
+    const int kvh = pair % a.G, b = pair / a.G;
+    const int64_t head0 = ((int64_t)b * a.G + kvh) * GQ;
     float* const wsum = sums_lds + wave * (GQ * D);   // [GQ][D], this wave's; before that its weights:
     __bf16* const wbuf = reinterpret_cast<__bf16*>(wsum);   // [head][row group][row load], the A operand's order
-    int my_lane = lane_id();
+    int my_lane;                                      // (made here: not kept from run to run)
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(my_lane));
+    const int begin = split * a.chunk;
+    const int last = min(begin + a.chunk, L) - 1;
     const float* const prow = a.P + head0 * a.ldp;
     float m[HPL], l[HPL], p[HPL];
     f32x4 acc[8];                                     // column 8c + e; heads 4r .. 4r+3
@@ -2774,11 +2779,12 @@ __device__ __forceinline__ void weigh_values(const ValueArgs& a, int item, float
     for (int e = 0; e < 8; ++e) acc[e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     // A tile is 16 rows (a page): the address of its first row is uniform, a lane adds its row's distance from it, rows
     // past the end of the run that of its last token.
-    const uint32_t row_bytes = 2u * (uint32_t)(a.paged ? D : a.kv.st);   // (32 bits: values_beside_topk)
     u32x4 v[TI];
-    int pg = 0;                                       // page of the tile to be requested next
+    const int32_t* const table = a.table + (int64_t)b * a.table_step;
+    const uint16_t* const origin = a.v + ((int64_t)b * a.seq_step + (int64_t)kvh * a.head_step);
+    int group = 0;                                    // page, or first token, of the tile to be requested next
     auto page_load = [&](int t_) {
-        if (a.paged) pg = uniform_load(a.kv.bt + (int64_t)b * a.kv.max_pages + (min(t_, last) >> 4));
+        group = (uniform_load(table + ((min(t_, last) >> 4) & a.paged)) & a.paged) | (t_ & ~a.paged);
     };
     auto request_p = [&](int t_) {
         asm volatile("" : "+v"(my_lane));             // (no registers for what can be made of it)
@@ -2794,11 +2800,10 @@ __device__ __forceinline__ void weigh_values(const ValueArgs& a, int item, float
     auto request_v = [&](int t_) {
         asm volatile("" : "+v"(my_lane));
         const int rows = last - t_;
-        const int64_t off = a.paged ? ((int64_t)pg * a.kv.G + kvh) * (PAGE * D) : (int64_t)b * a.kv.sb + (int64_t)kvh * a.kv.sh + (int64_t)t_ * a.kv.st;
-        const char* const at = reinterpret_cast<const char*>(a.kv.v + off);
+        const char* const at = reinterpret_cast<const char*>(origin + (int64_t)group * a.group_step);
 #pragma unroll
         for (int i = 0; i < TI; ++i)
-            v[i] = stream_load(reinterpret_cast<const uint16_t*>(at + ((uint32_t)min(i * 4 + (my_lane >> 4), rows) * row_bytes + 16u * (uint32_t)(my_lane & 15))));
+            v[i] = stream_load(reinterpret_cast<const uint16_t*>(at + ((uint32_t)min(i * 4 + (my_lane >> 4), rows) * a.row_bytes + 16u * (uint32_t)(my_lane & 15))));
     };
     int t0 = begin + wave * VALUE_TILE;
     page_load(t0);
@@ -2891,7 +2896,7 @@ __device__ __forceinline__ void weigh_values(const ValueArgs& a, int item, float
         float A = 0.0f, Ls = 0.0f;
 #pragma unroll 4
         for (int wv = 0; wv < SEL_WAVES; ++wv) {
-            const float f = exp2f(st.m[wv][h] - M);
+            const float f = __builtin_amdgcn_exp2f(st.m[wv][h] - M);
             A = __builtin_fmaf(sums_lds[wv * (GQ * D) + o], f, A);
             Ls = __builtin_fmaf(st.l[wv][h], f, Ls);
         }
@@ -2908,7 +2913,8 @@ __device__ __forceinline__ void weigh_values(const ValueArgs& a, int item, float
     }
 }
 
-// The top-k over whole rows and the values in one launch, 1-D grid of n_topk + va.items workgroups.  Rows and runs take turns of 256, a
+// The top-k over whole rows and the values in one launch, 1-D grid of n_topk + va.items workgroups.  Workgroup i of the values takes the runs
+// i / pairs, i / pairs + wgs, ... of pair i % pairs: where sequences are shorter than the bound, the workgroups with work come first.  Rows and runs take turns of 256, a
 // workgroup for every CU (where there are as many), what is left of either comes at the end: the dispatcher hands out workgroups strictly in order
 // and in turn to the shader engines, so with a shorter turn all rows meet in a few engines and what follows them waits for a place elsewhere
 // (turns of 8: 120 CUs idle for 18 of 64 us).
@@ -2934,12 +2940,19 @@ __global__ __launch_bounds__(SEL_THREADS, topk_lean(ITEMS, MTOP) ? 8 : 4) void t
     }
     __shared__ ValueLds st;
     float* const lds = reinterpret_cast<float*>(sort_buf);
-    if constexpr (GROUP8) {                           // (its registers are too few beside the other groups' code)
-        weigh_values<8>(va, i, lds, st);
-    } else {
-        if (va.g == 4) weigh_values<4>(va, i, lds, st);   // uniform
-        else if (va.g == 2) weigh_values<2>(va, i, lds, st);
-        else weigh_values<1>(va, i, lds, st);
+    int wave = __builtin_amdgcn_readfirstlane(wave_id()), pair = i % va.pairs;
+    const int L = uniform_load(va.seq_lens + pair / va.G);
+#pragma clang loop unroll(disable)
+    for (int run = i / va.pairs; run * va.chunk < L; run += va.wgs) {
+        asm volatile("" : "+s"(pair), "+s"(wave));    // (scalar registers: every run makes what it needs of them anew)
+        if constexpr (GROUP8) {                       // (its registers are too few beside the other groups' code)
+            weigh_values<8>(va, pair, run, L, wave, lds, st);
+        } else {
+            if (va.g == 4) weigh_values<4>(va, pair, run, L, wave, lds, st);   // uniform
+            else if (va.g == 2) weigh_values<2>(va, pair, run, L, wave, lds, st);
+            else weigh_values<1>(va, pair, run, L, wave, lds, st);
+        }
+        lds_barrier();                                // read, before the next run writes
     }
 }
 

@@ -119,7 +119,8 @@ def test_scoring_passes_open_no_round_for_next_to_nothing(tmp_path):
 
 def test_selection_layer_runs_cover_the_tokens_and_fit_the_workspace(tmp_path):
     """Runs of the values: whole tiles, the list covered, no run empty; their partials fit a workspace laid out for any longer bound and
-    any smaller number of pairs.  The scoring pass has a workgroup for every tile, the second chance no more than that."""
+    any smaller number of pairs.  The scoring pass has a workgroup for every tile, the second chance no more than that; of neither, nor of the values,
+    are there more than what the idle ones of sequences far below the bound may cost."""
     out = run_checks(tmp_path, r'''
     (void)plan;
     for (int pairs = 1; pairs <= 1100; pairs += pairs < 80 ? 1 : 7)
@@ -128,14 +129,17 @@ def test_selection_layer_runs_cover_the_tokens_and_fit_the_workspace(tmp_path):
                 const ValuePlan v = plan_values(n, pairs, rows);
                 if (v.chunk % VALUE_TOKENS || (int64_t)v.chunk * v.n_splits < n || (v.n_splits > 1 && (int64_t)v.chunk * (v.n_splits - 1) >= n))
                     FAIL("values of %d pairs of %d: %d runs of %d", pairs, n, v.n_splits, v.chunk);
+                if (v.wgs < 1 || v.wgs > v.n_splits || v.wgs * (int64_t)pairs > VALUE_WGS + pairs || (v.n_splits * (int64_t)pairs <= VALUE_WGS && v.wgs != v.n_splits))
+                    FAIL("values of %d pairs of %d: %d workgroups for %d runs", pairs, n, v.wgs, v.n_splits);
                 for (int fewer : {pairs, (pairs + 1) / 2, (pairs + 7) / 8})
                     if (v.n_splits > max_splits_bound(n, fewer)) FAIL("values of %d pairs of %d: %d runs, bound %d", pairs, n, v.n_splits, max_splits_bound(n, fewer));
             }
             for (bool second : {false, true}) {
                 const ScorePlan p = plan_score(n, pairs, second);
                 const int tile = p.ti * 4 * ATTN_WAVES, tiles = (n + tile - 1) / tile;
-                if ((p.ti != 8 && p.ti != 16) || p.n_splits < 1 || p.n_splits > tiles || (!second && p.n_splits != tiles))
+                if ((p.ti != 8 && p.ti != 16) || p.n_splits < 1 || p.n_splits > tiles || (!second && tiles * (int64_t)pairs <= SCORE_WGS && p.n_splits != tiles))
                     FAIL("scores of %d pairs of %d: %d workgroups for %d tiles", pairs, n, p.n_splits, tiles);
+                if (p.n_splits * (int64_t)pairs > SCORE_WGS + pairs) FAIL("scores of %d pairs of %d: %d workgroups", pairs, n, p.n_splits * pairs);
             }
         }
 ''')
@@ -161,7 +165,7 @@ def test_the_selection_layers_values_stay_within_their_kernels_limits(tmp_path):
                         ++taken;
                         const ValuePlan v = plan_values(n, pairs, (int)rows);
                         const int64_t ldp = ((int64_t)n + 63) / 64 * 64;
-                        if ((rows + (int64_t)pairs * v.n_splits) * 1024 >= (int64_t)1 << 32) FAIL("%d pairs of %d, groups of %d: threads", pairs, n, g);
+                        if ((rows + (int64_t)pairs * v.wgs) * 1024 >= (int64_t)1 << 32) FAIL("%d pairs of %d, groups of %d: threads", pairs, n, g);
                         if (((g - 1) * ldp + n) * 4 >= (int64_t)1 << 32) FAIL("%d tokens, groups of %d: scores", n, g);
                         if (step * 2 * 15 >= (int64_t)1 << 32) FAIL("%lld elements between tokens", (long long)step);
                         if (!scores_of_all_tokens((int)window, n)) FAIL("no room for the scores of %d tokens", n);
