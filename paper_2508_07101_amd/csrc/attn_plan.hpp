@@ -164,15 +164,22 @@ constexpr int VALUE_TOKENS = 256;   // a tile of 16 for each wave
 // (us for the layer, a workgroup for every run and so: 64 sequences of 4096, 64 heads, bound 131072 506 and 318, one pass 338; 128 of 3000 888 and
 // 547, 535; 32 of 4096, bound 1000000 644 and 192, 363.  64 of 9000 and no more 524; in 2048 workgroups 537, in 1024 552).
 constexpr int VALUE_WGS = 4096;
-// One workgroup to a CU that no row of the top-k starts on (rows: their number) while that makes runs of up to 1536 tokens -- two or
-// three tiles for every wave --, otherwise runs of 1024, which fill the CUs as they become free.  Measured (us for the layer; 256-token steps
-// from 256 to 4096): 8 pairs of 9000 best 22.9, so 23.0; of 16384 26.1 and 26.1; of 32768 36.0 and 36.0; of 65536 59.1, in runs of 1024 60.5;
-// of 131072 109.8 and 109.8; 16 of 16384 36.4 and 36.4; 64 of 16384 108.6 and 109.5; 128 of 3000 to 12000 112.9 and 112.9; 512 of 9000
-// 519.7 and 519.7, in runs of 4096 548.
+// The runs of at most 1536 tokens -- two to six tiles for every wave -- that give every CU one workgroup.  Beside fewer rows of the top-k (rows: their
+// number) than CUs, those CUs that a row starts on are left out, 64 at most (8 pairs of 9000 tokens, us for the layer: best of 256-token steps from
+// 256 to 4096 22.9, so 23.0; of 16384 26.1 and 26.1; of 32768 36.0 and 36.0; of 131072 109.8 and 109.8; 16 of 16384 36.4 and 36.4).  More rows share all
+// CUs with the runs anyway (64 pairs of 1562, groups of 4: runs for 192 CUs 27.7, for 256 26.1; of 3125 36.5 and 34.9; of 5156 48.8 and 43.9).
+// Where that would make longer runs or leave CUs without, many short runs that fill the CUs as they become free: of 768 tokens in layers of up to half
+// a million, of 1024 in larger ones (over 150 layers of 32 to 128 pairs and 280000 to 1000000 tokens, runs of 512, 768, 1024, 1280, 1536, against the
+// one pass: 0.964, 0.956, 0.963, 0.974, 0.980); of 1536 from 192 pairs on, which are one to three to a pair and have little left over (108 layers of 192
+// to 512 pairs of 1560 to 3300, runs of 512 to 2048: 0.919, 0.919, 0.914, 0.911, 0.904, 0.915; 256 pairs of 2031, groups of 2: 1024 1.06, 1536 0.99).
 inline ValuePlan plan_values(int n_max, int BG, int rows) {
-    const int free = CUS - std::min(rows, 64);
-    int64_t chunk = ((int64_t)n_max * BG + free - 1) / free;
-    chunk = chunk > 1536 ? 1024 : std::max((chunk + VALUE_TOKENS - 1) / VALUE_TOKENS * VALUE_TOKENS, (int64_t)512);
+    const int64_t tokens = (int64_t)n_max * BG;
+    const int per_pair = CUS / BG;
+    int64_t chunk = 1536 + 1;
+    if (rows < CUS) chunk = (tokens + CUS - std::min(rows, 64) - 1) / (CUS - std::min(rows, 64));
+    else if (per_pair * BG >= CUS - 32) chunk = ((int64_t)n_max + per_pair - 1) / per_pair;
+    if (chunk > 1536) chunk = BG >= 192 ? 1536 : tokens < 1 << 19 ? 768 : 1024;
+    chunk = std::max((chunk + VALUE_TOKENS - 1) / VALUE_TOKENS * VALUE_TOKENS, (int64_t)512);
     if ((n_max + chunk - 1) / chunk > MAX_SPLITS) {
         chunk = ((int64_t)n_max + MAX_SPLITS - 1) / MAX_SPLITS;
         chunk = (chunk + VALUE_TOKENS - 1) / VALUE_TOKENS * VALUE_TOKENS;
