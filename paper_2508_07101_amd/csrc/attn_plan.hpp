@@ -189,22 +189,35 @@ inline ValuePlan plan_values(int n_max, int BG, int rows) {
 }
 
 // Whether a row of the workspace's scores has room for every token, not just the candidates: see values_beside_topk, which asks for it.  Once true
-// it stays true for longer bounds, so a workspace laid out for a capacity serves every shorter bound, and rows stay under 5 / 3 of the candidates.
-inline bool scores_of_all_tokens(int window, int max_seq_len) { return (int64_t)window * 5 <= (int64_t)max_seq_len * 2; }
+// it stays true for longer bounds, so a workspace laid out for a capacity serves every shorter bound, and rows stay under 3 / 2 of the candidates.
+inline bool scores_of_all_tokens(int64_t rows, int k, int window, int max_seq_len) {
+    return !(k > 4096 && rows > 192) && (int64_t)window * 3 <= max_seq_len;
+}
 
 // Whether a selection layer that is not filtered scores all tokens first and makes its output from those scores while the top-k runs (score_kernel,
 // topk_values_kernel); otherwise one pass over K and V makes the output and writes the candidates' scores (attn_kernel's scoring variant).
 // rows: batch * query heads.
-inline bool values_beside_topk(int64_t rows, int BG, int window, int max_seq_len, int64_t token_step) {
+inline bool values_beside_topk(int64_t rows, int BG, int k, int window, int max_seq_len, int64_t token_step) {
+    const int64_t tokens = (int64_t)BG * max_seq_len;
     // the rows and runs are workgroups of 1024 threads of a one-dimensional launch: fewer than 2^32 threads
     if (rows + BG + VALUE_WGS >= 1 << 22) return false;
     // a lane's distance from the first row of its 16 fits 32 bits (elements between tokens; 0: paged)
     if (token_step > 1 << 26) return false;
-    // The scores of a window are written and read for the output alone: 4 g bytes for the 256 of a row.  From two fifths of the tokens on the one pass
-    // is faster (8 sequences of 16384, 8 KV heads, us, one pass and so, window 0.4, 0.5, 0.9 of the tokens: groups of 4 105.5 and 104.1, 102.6 and 104.4,
-    // 99.1 and 104.5; of 8 117.1 and 117.6, 112.8 and 117.0, 108.9 and 119.0).  (With at most UNION_MAX_POSITIONS candidates this also keeps the score
-    // rows of a group's heads within 32 bits of each other.)
-    return scores_of_all_tokens(window, max_seq_len);
+    // A sort of more than 4096 picks needs 94 registers and 130 KB of LDS, and the runs in its launch, a workgroup to a CU with it, wait for the rows:
+    // beside more than 192 rows the one pass and a launch of the rows are faster (us, K 8192, one pass and so: 8 sequences of 10000, 256 rows 93.6
+    // and 103.8, of 16384 126.5 and 136.7, of 32000 226.4 and 226.9; 6 of 16384, 192 rows, 107.8 and 107.5; 4 82.3 and 75.3).
+    // (scores_of_all_tokens)
+    // Layers that large take long enough for the one pass to fill the chip as well, and read P once less (64 sequences of 32768, groups of 8: 1747 and
+    // 1816, 16 of 65536 859 and 858, 64 of 9000 561 and 525).
+    if (tokens >= 8 << 20) return false;
+    // Groups of 8: the one pass, in runs of at most 1024 tokens, is at its best where these fill its 512 resident workgroups once, most of them
+    // (64 pairs of 5625: 54.4 and 56.3; 128 of 3125 66.8 and 69.3; 48 of 6875 54.0 and 55.6; 48 of 5833 51.5 and 51.1, of 8333 61.4 and 58.5).
+    if (rows == 8 * (int64_t)BG && BG >= 48 && BG < 192 && tokens >= 9 << 15 && tokens < 13 << 15) return false;
+    // The scores of a window are written and read for the output alone: 4 g bytes for the 256 of a row.  From a third of the tokens on the one pass
+    // is as fast (8 sequences of 16384, 8 KV heads, us, one pass and so, window 0.3, 0.4, 0.5, 0.9 of the tokens: groups of 4 106.7 and 103.7, 105.5 and
+    // 104.1, 102.6 and 104.4, 99.1 and 104.5; of 8 117.4 and 117.1, 117.1 and 117.6, 112.8 and 117.0, 108.9 and 119.0).  (With at most
+    // UNION_MAX_POSITIONS candidates this also keeps the score rows of a group's heads within 32 bits of each other.)
+    return scores_of_all_tokens(rows, k, window, max_seq_len);
 }
 
 // Upper bound of plan_attn(m, BG', ...).n_splits over every m <= n_max and BG' >= BG: a token list is cut into

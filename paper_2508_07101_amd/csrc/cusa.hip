@@ -238,9 +238,9 @@ WsLayout make_layout(const cusa_params* p, int max_seq_len) {
     const int BG = p->batch * p->n_kv_heads;
     int64_t lc = (int64_t)max_seq_len - p->window;
     if (lc < 1) lc = 1;
-    w.ldp = ((scores_of_all_tokens(p->window, max_seq_len) ? max_seq_len : lc) + 63) / 64 * 64;
     w.k = resolved_k(p);
     if (w.k < 1) w.k = 1;
+    w.ldp = ((scores_of_all_tokens(B * H, w.k, p->window, max_seq_len) ? max_seq_len : lc) + 63) / 64 * 64;
     w.max_splits = max_splits_bound(max_seq_len > p->budget ? max_seq_len : p->budget, BG);
     size_t off = 0;
     w.scores = off;    off += align256((size_t)(B * H * w.ldp) * 4);
@@ -843,7 +843,7 @@ cusa_status run_select_layer(const cusa_params* p, const void* q, const cusa_kv*
         if (st != CUSA_OK) return st;
         return run_select(p, q, kv, idx, cnt, ws, w, s, false, false, &f, &red);
     }
-    if (!score.P || !values_beside_topk((int64_t)p->batch * p->n_q_heads, p->batch * p->n_kv_heads, p->window, kv->max_seq_len,
+    if (!score.P || !values_beside_topk((int64_t)p->batch * p->n_q_heads, p->batch * p->n_kv_heads, w.k, p->window, kv->max_seq_len,
                                         kv->layout == CUSA_KV_PAGED ? 0 : kv->stride_token)) {
         const cusa_status st = run_attention<false>(p, q, kv, nullptr, nullptr, kv->max_seq_len, out, ws, w, s, score, nullptr, &red);
         return st != CUSA_OK ? st : run_select(p, q, kv, idx, cnt, ws, w, s, score.P != nullptr, false, nullptr, &red);

@@ -148,7 +148,7 @@ def test_workspace_bytes_never_shrink_with_capacity(B, H, G, K, W):
 def test_workspace_bytes_never_shrink_with_capacity_and_wide_windows(B, H, G, K, W, k):
     """The same where the scores' rows hold the candidates only, up to a bound: windows of most of the tokens."""
     p = cb.make_params(B, H, G, K, W, k)
-    at = W * 5 // 2
+    at = W * 3
     prev = 0
     for m in sorted(set([W + 1, W + 63, K, K + 1, at - 65, at - 64, at - 1, at, at + 1, at + 64, at + 65] + list(range(W + 1, W * 4 + 9000, 997)))):
         n = cb.workspace_bytes(p, m)

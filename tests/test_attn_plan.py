@@ -156,23 +156,38 @@ def test_the_selection_layers_values_stay_within_their_kernels_limits(tmp_path):
     for (int pairs : {1, 2, 7, 64, 1000, 65535, 524280, 4000000})
         for (int g : {1, 2, 4, 8})
             for (int64_t cand = 1; cand <= MAX_POSITIONS; cand += cand < 3000 ? 97 : cand / 3)
-                for (int64_t window : {(int64_t)0, cand / 8, cand / 2, cand * 2 / 3, cand, 5 * cand, (int64_t)134217728, (int64_t)160000000, (int64_t)2000000000})
+                for (int64_t window : {(int64_t)0, cand / 8, cand / 3, cand / 2, cand, 5 * cand, (int64_t)134217728, (int64_t)160000000, (int64_t)2000000000})
                     for (int64_t step : {(int64_t)0, (int64_t)128, (int64_t)1 << 26, ((int64_t)1 << 26) + 8, (int64_t)1 << 31}) {
                         if (cand + window > 2147483647) continue;
                         const int n = (int)(cand + window);
                         const int64_t rows = (int64_t)pairs * g;
-                        if (!values_beside_topk(rows, pairs, (int)window, n, step)) continue;
+                        if (!values_beside_topk(rows, pairs, 512, (int)window, n, step)) continue;
                         ++taken;
                         const ValuePlan v = plan_values(n, pairs, (int)rows);
                         const int64_t ldp = ((int64_t)n + 63) / 64 * 64;
                         if ((rows + (int64_t)pairs * v.wgs) * 1024 >= (int64_t)1 << 32) FAIL("%d pairs of %d, groups of %d: threads", pairs, n, g);
                         if (((g - 1) * ldp + n) * 4 >= (int64_t)1 << 32) FAIL("%d tokens, groups of %d: scores", n, g);
                         if (step * 2 * 15 >= (int64_t)1 << 32) FAIL("%lld elements between tokens", (long long)step);
-                        if (!scores_of_all_tokens((int)window, n)) FAIL("no room for the scores of %d tokens", n);
+                        if (!scores_of_all_tokens(rows, 512, (int)window, n)) FAIL("no room for the scores of %d tokens", n);
                     }
-    if (taken < 5000) FAIL("only %ld taken", taken);
+    if (taken < 2000) FAIL("only %ld taken", taken);
     for (int window : {0, 100, 12345, 1000000})                  // a workspace for a capacity serves every shorter bound
         for (int n = window + 1; n < window + 1179648; n += step(n))
-            if (scores_of_all_tokens(window, n) && !scores_of_all_tokens(window, n + 1)) FAIL("window %d at %d", window, n);
+            if (scores_of_all_tokens(256, 5000, window, n) || (scores_of_all_tokens(256, 512, window, n) && !scores_of_all_tokens(256, 512, window, n + 1))) FAIL("window %d at %d", window, n);
+''')
+    assert out == "", out
+
+
+def test_selection_layers_that_one_pass_serves_faster(tmp_path):
+    """Where the former pass over K and V beats the two of the values: many picks to sort beside many rows, wide windows, the largest layers (sizes that
+    were measured 4 to 10 per cent slower)."""
+    out = run_checks(tmp_path, r'''
+    (void)plan;
+    struct { int rows, pairs, k, window, n; bool beside; } const sizes[] = {
+        {256, 64, 8192, 0, 16384, false}, {512, 64, 7168, 1024, 10000, false}, {128, 32, 8192, 0, 16384, true}, {256, 64, 4096, 1024, 16384, true},
+        {512, 64, 600, 8500, 16384, false}, {32, 8, 500, 1100, 3300, true}, {4096, 512, 1536, 512, 32768, false}, {4096, 512, 1536, 512, 9000, true},
+        {512, 64, 768, 256, 5625, false}, {512, 64, 768, 256, 8125, true}, {256, 64, 768, 256, 5625, true}, {64, 8, 768, 256, 45000, true}};
+    for (const auto& s : sizes)
+        if (values_beside_topk(s.rows, s.pairs, s.k, s.window, s.n, 128) != s.beside) FAIL("%d rows, %d pairs of %d, k %d", s.rows, s.pairs, s.n, s.k);
 ''')
     assert out == "", out

@@ -739,10 +739,11 @@ def test_selection_layer_values_at_the_edges_of_tiles_and_runs(H, layout, lens):
 
 
 @pytest.mark.parametrize("H,paged", [(8, False), (32, True), (64, False), (64, True)])
-@pytest.mark.parametrize("B,lens,bound", [(40, (3100, 700, 1024, 1500, 2049), 70000),        # three runs to a workgroup, some without any
-                                          (2, (40000, 35001), 1100000),                      # runs of 4352 tokens
-                                          (64, (1500, 900, 601), 600000)])                   # 32 runs to a workgroup, 10 tiles
-def test_selection_layer_under_a_bound_far_above_the_lengths(H, paged, B, lens, bound):
+@pytest.mark.parametrize("B,lens,bound,two_passes", [(16, (3100, 700, 1024, 1500, 2049), 60000, True),     # two runs to a workgroup, some without any
+                                                     (64, (4000, 900, 601, 1536, 1537), 16000, True),
+                                                     (2, (40000, 35001), 500000, True),               # runs of 2048 tokens
+                                                     (64, (1500, 900, 601), 600000, False)])          # 19 tiles of cusa_select to a workgroup
+def test_selection_under_a_bound_far_above_the_lengths(H, paged, B, lens, bound, two_passes):
     """Workgroups of the scoring pass and of the values that take several tiles and runs in turn, or have nothing to do."""
     lens = tuple(lens[i % len(lens)] for i in range(B))
     w = small(f"far_bound_{B}_{H}", batch=B, n_q_heads=H, seq_len=max(lens), lengths=lens, budget=300, window=60, n_layers=1,
@@ -752,12 +753,16 @@ def test_selection_layer_under_a_bound_far_above_the_lengths(H, paged, B, lens, 
         table = torch.zeros((B, (bound + 15) // 16), dtype=torch.int32, device=DEV)
         table[:, : inp.block_table.shape[1]] = inp.block_table
         inp.block_table = table
-    r = StepRunner(inp, rank_mode=cb.RANK_FIRST_OCCURRENCE if H == 64 else cb.RANK_VOTES, max_len=bound)   # (not filtered)
+    mode = cb.RANK_FIRST_OCCURRENCE if H == 64 else cb.RANK_VOTES   # (not filtered)
+    r = StepRunner(inp, rank_mode=mode, max_len=bound)
     r.outs[0].fill_(float("nan"))
     calls = _kernel_calls(r.run)
-    assert calls.get("topk_values_kernel") == 1, calls
-    check_select(inp, r, 0, seqs=range(min(B, 5)), rank_mode=r.params.rank_mode)
+    assert calls.get("topk_values_kernel" if two_passes else "attn_kernel<full+score>") == 1, calls
+    check_select(inp, r, 0, seqs=range(min(B, 5)), rank_mode=mode)
     _check_outputs64(inp, r, 0)
+    r.idx.fill_(-1)
+    r.select(0)
+    check_select(inp, r, 0, seqs=range(min(B, 5)), rank_mode=mode)
 
 
 def _minus_infinity_scores(inp, runs):
