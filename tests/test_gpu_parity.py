@@ -143,9 +143,24 @@ def _with_keys(w, fn, rank_mode=0):
     inp = wl.make_inputs(w, DEV)
     fn(inp.layers[0].k)
     r = StepRunner(inp, rank_mode=rank_mode)
-    r.run()
-    check_select(inp, r, 0, rank_mode=rank_mode)
+    check_both_selections(inp, r, rank_mode=rank_mode)
     return inp, r
+
+
+def check_both_selections(inp, r, check=check_select, **kw):
+    """Layer 0's selection by cusa_select, whose rows have launches of their own (in registers, streamed, in slices where they are few and long), and as a
+    selection layer, which ranks them beside its values; the kernels that ran, and rho after each."""
+    w = inp.workload
+    if r.max_len > w.budget:
+        calls = _kernel_calls(lambda: r.select(0))
+        n_cand, rows = r.max_len - w.window, w.batch * w.n_q_heads
+        sliced = n_cand > 32768 and rows <= 256
+        assert calls.get("topk_kernel") and not calls.get("topk_values_kernel") and bool(calls.get("topk_kernel<slice>")) == sliced, calls
+        check(inp, r, 0, **kw)
+    r.idx.fill_(-1)
+    calls = _kernel_calls(lambda: r.select_layer(0))
+    assert r.max_len <= w.budget or calls.get("topk_values_kernel") == 1, calls
+    check(inp, r, 0, **kw)
 
 
 def test_ties_duplicated_keys_go_to_lowest_position():
@@ -543,9 +558,7 @@ def test_topk_rows_whose_best_scores_cluster(B, L, K, W, k, where):
     rows = lay.k[:, :, at].float()
     q = lay.q.float()[:, :, None, :]                     # one query head per KV head
     lay.k[:, :, at] = (0.3 * rows + 0.5 * q).to(torch.bfloat16)
-    r = StepRunner(inp)
-    r.run()
-    check_select(inp, r, 0, seqs=[0, B - 1], check_scores=False)
+    check_both_selections(inp, StepRunner(inp), seqs=[0, B - 1], check_scores=False)
 
 
 @pytest.mark.parametrize("B,L,K,W,k", [(2, 4000, 1300, 276, 1024), (2, 7000, 1000, 100, 0), (2, 9000, 2560, 512, 0),
@@ -561,9 +574,7 @@ def test_topk_of_rows_whose_scores_repeat(B, L, K, W, k, distinct):
     gen = torch.Generator(device=DEV)
     gen.manual_seed(distinct)
     lay.k.copy_(lay.k[:, :, torch.randint(distinct, (L,), generator=gen, device=DEV)].clone())
-    r = StepRunner(inp)
-    r.select(0)
-    check_select(inp, r, 0, seqs=[0, B - 1], check_scores=False)
+    check_both_selections(inp, StepRunner(inp), seqs=[0, B - 1], check_scores=False)
 
 
 @pytest.mark.parametrize("B,L,K,W", [(1, 70001, 8192, 1024), (2, 40000, 5200, 100)])
@@ -571,9 +582,7 @@ def test_widest_topk_of_long_rows_in_slices(B, L, K, W):
     """k above 4096 on sliced rows: the slices' lists of 14336 entries, 14 composites per thread in the ranking."""
     w = small("wide", n_q_heads=8, n_kv_heads=8, batch=B, seq_len=L, lengths=tuple([L] * (B - 1) + [L - 57]), budget=K, window=W)
     inp = wl.make_inputs(w, DEV)
-    r = StepRunner(inp)
-    r.select(0)
-    check_select(inp, r, 0)
+    check_both_selections(inp, StepRunner(inp))
 
 
 LENGTHS_OF_ALL_FORMS = [(1, 3000), (2, 6000), (1, 12000), (1, 30000), (1, 40000), (36, 9700)]   # registers, slices, streamed
@@ -598,9 +607,7 @@ def test_topk_beside_scores_of_minus_infinity(B, L, left):
         gone[:] = True
         gone[torch.randperm(L - W - 60, generator=gen, device=DEV)[: K - W - 40]] = False
     lay.k[:, :, gone, 1] = -big
-    r = StepRunner(inp)
-    r.select(0)
-    check_select(inp, r, 0, seqs=[0, B - 1])
+    check_both_selections(inp, StepRunner(inp), seqs=[0, B - 1])
 
 
 @pytest.mark.parametrize("B,L", LENGTHS_OF_ALL_FORMS)
@@ -615,17 +622,19 @@ def test_topk_beside_nan_scores_follows_the_keys(B, L, n_nan):
     gen.manual_seed(n_nan)
     lay = inp.layers[0]
     lay.k[:, :, torch.randperm(L - W, generator=gen, device=DEV)[:n_nan], 5] = float("nan")
-    r = StepRunner(inp)
-    r.select(0)
-    torch.cuda.synchronize()
-    for b in {0, B - 1}:
-        bits = r.scores()[b, :, : L - W].cpu().numpy().view(np.uint32)
-        assert np.isnan(bits.view(np.float32)).sum() == 8 * n_nan
-        bits = np.where(bits == 0x80000000, 0, bits).astype(np.uint32)
-        keys = np.where(bits & 0x80000000, ~bits, bits | 0x80000000).astype(np.int64)
-        want = np.argsort(-keys, axis=1, kind="stable")[:, : K - W]
-        got = r.rho_head()[b].cpu().numpy().T
-        assert (got == want).all(), f"seq {b}: {(got != want).sum()} entries"
+
+    def check(inp, r, layer_pos):
+        torch.cuda.synchronize()
+        for b in {0, B - 1}:
+            bits = r.scores()[b, :, : L - W].cpu().numpy().view(np.uint32)
+            assert np.isnan(bits.view(np.float32)).sum() == 8 * n_nan
+            bits = np.where(bits == 0x80000000, 0, bits).astype(np.uint32)
+            keys = np.where(bits & 0x80000000, ~bits, bits | 0x80000000).astype(np.int64)
+            want = np.argsort(-keys, axis=1, kind="stable")[:, : K - W]
+            got = r.rho_head()[b].cpu().numpy().T
+            assert (got == want).all(), f"seq {b}: {(got != want).sum()} entries"
+
+    check_both_selections(inp, StepRunner(inp), check=check)
 
 
 def test_topk_of_scores_that_are_not_finite():
@@ -641,9 +650,7 @@ def test_topk_of_scores_that_are_not_finite():
         lay.k[:, :, 100:164, 0] = big                    # +inf
         lay.k[:, :, 200:1500, 0] = torch.linspace(0.1, 0.9, 1300, device=DEV).to(torch.bfloat16)
         lay.k[:, :, 2000:2010, 0] = -big                 # -inf
-        r = StepRunner(inp)
-        r.select(0)
-        check_select(inp, r, 0)
+        check_both_selections(inp, StepRunner(inp))
 
 
 @pytest.mark.parametrize("B,L,K,paged,min_len", [(24, 1100, 512, False, 0), (24, 2100, 1000, True, 900), (26, 2060, 640, False, 700),
@@ -736,6 +743,23 @@ def test_selection_layer_values_at_the_edges_of_tiles_and_runs(H, layout, lens):
         want, bound = _attention64_and_bound(inp, 0, b)
         err = (r.outs[0][b].double() - want).abs()
         assert (err <= bound).all(), f"seq {b} of {lens[b]} tokens: {(err / bound).max().item():.2f} of the bound"
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("H", [32, 64])
+@pytest.mark.parametrize("L,K,W", [(3900, 1500, 100), (3900, 3500, 100), (9001, 2000, 100), (9001, 4000, 500), (9001, 8000, 300)])
+def test_selection_layer_with_wide_sorts_beside_its_values(H, L, K, W, paged):
+    """1025 to 8192 picks per head, rows in registers and streamed, with the weights' area and the sort's in one workgroup's LDS."""
+    lens = (L, L - 333)
+    w = small(f"wide_values_{H}_{paged}", batch=2, n_q_heads=H, seq_len=L, lengths=lens, budget=K, window=W, n_layers=1, schedule=(LAYER_SELECT,),
+              paged=paged)
+    inp = wl.make_inputs(w, DEV)
+    r = StepRunner(inp)
+    r.outs[0].fill_(float("nan"))
+    calls = _kernel_calls(r.run)
+    assert calls.get("topk_values_kernel") == 1, calls
+    check_select(inp, r, 0)
+    _check_outputs64(inp, r, 0)
 
 
 @pytest.mark.parametrize("H,paged", [(8, False), (32, True), (64, False), (64, True)])
@@ -964,6 +988,7 @@ def test_many_rows_take_the_lean_streamed_topk():
     w = small("manyrows", batch=16, seq_len=9700, min_seq_len=8400, budget=512, window=128, n_planted=7)
     inp, r, sched = run_and_check(w)
     check_attention(inp, r, 1, LAYER_SPARSE, seqs=[0, 9])
+    check_both_selections(inp, r)
 
 
 def test_decode_step_with_different_length_bounds_per_layer():

@@ -10,9 +10,10 @@ pytestmark = pytest.mark.gpu
 DEV, D, G = "cuda", 128, 8
 
 
-def _topk_us(B, H, L, K, W, k, span=0, distinct=0):
-    """Fastest of five means of ten calls.  span: each span of that many positions has an offset of its own, as wide as the
-    scores are spread; distinct: that many different keys."""
+def _topk_us(B, H, L, K, W, k, span=0, distinct=0, layer=False):
+    """Fastest of five means of ten calls of cusa_select, or (layer) of a selection layer, whose values share the top-k's launch.
+    span: each span of that many positions has an offset of its own, as wide as the scores are spread; distinct: that many
+    different keys."""
     gen = torch.Generator(device=DEV)
     gen.manual_seed(11)
     q = torch.randn((B, H, D), generator=gen, device=DEV, dtype=torch.bfloat16)
@@ -30,7 +31,15 @@ def _topk_us(B, H, L, K, W, k, span=0, distinct=0):
     idx = torch.zeros((B, K), dtype=torch.int32, device=DEV)
     cnt = torch.zeros((B,), dtype=torch.int32, device=DEV)
     ws = cb.alloc_workspace(p, L, DEV)
-    cb.select(p, q, kv, idx, cnt, ws)
+    out = torch.empty_like(q)
+
+    def call():
+        if layer:
+            cb.select_layer(p, q, kv, out, idx, cnt, ws)
+        else:
+            cb.select(p, q, kv, idx, cnt, ws)
+
+    call()
     torch.cuda.synchronize()
     best = float("inf")
     cb.profile_enable(True)
@@ -38,7 +47,7 @@ def _topk_us(B, H, L, K, W, k, span=0, distinct=0):
         for _ in range(5):
             cb.profile_reset()
             for _ in range(10):
-                cb.select(p, q, kv, idx, cnt, ws)
+                call()
             prof = cb.profile_read()
             best = min(best, sum(v["total_ms"] for name, v in prof.items() if name.startswith("topk")) * 100.0)
     finally:
@@ -47,33 +56,37 @@ def _topk_us(B, H, L, K, W, k, span=0, distinct=0):
     return best
 
 
+LAYER = pytest.mark.parametrize("layer", [False, True])
 SIZES = [(1, 32, 32768, 2048, 512, 0), (8, 32, 16384, 4096, 1024, 0), (16, 32, 16384, 2048, 512, 0),
          (1, 64, 131072, 4096, 1024, 0)]
 
 
+@LAYER
 @pytest.mark.parametrize("size", SIZES)
-def test_scores_correlated_along_the_sequence_take_no_longer(size):
+def test_scores_correlated_along_the_sequence_take_no_longer(size, layer):
     """One list for the whole row: where its best candidates stand does not matter.  (With a sixteenth of the list for
     each wave these took 2.5 to 6 times as long as independent scores.)"""
-    plain, clustered = _topk_us(*size), _topk_us(*size, span=256)
-    print(f"[time] {size}: independent {plain:.1f} us, correlated {clustered:.1f} us", flush=True)
+    plain, clustered = _topk_us(*size, layer=layer), _topk_us(*size, span=256, layer=layer)
+    print(f"[time] {'layer' if layer else 'select'} {size}: independent {plain:.1f} us, correlated {clustered:.1f} us", flush=True)
     assert clustered < 1.5 * plain
 
 
+@LAYER
 @pytest.mark.parametrize("size,span", [((1, 32, 30512, 2560, 512, 0), 256), ((1, 32, 30512, 2560, 512, 0), 64),
                                        ((1, 64, 131072, 2048, 512, 0), 64), ((1, 32, 60512, 2560, 512, 0), 64)])
-def test_the_sample_speaks_for_rows_correlated_along_the_sequence(size, span):
+def test_the_sample_speaks_for_rows_correlated_along_the_sequence(size, span, layer):
     """The threshold's sample is spread over the row in short runs and a second threshold goes by what the first let through.
     (Half the row in 256-key pieces, or 64-key runs, and twice as many the second time: 1.6 to 4 times as long.)"""
-    plain, clustered = _topk_us(*size), _topk_us(*size, span=span)
-    print(f"[time] {size} spans of {span}: independent {plain:.1f} us, correlated {clustered:.1f} us", flush=True)
+    plain, clustered = _topk_us(*size, layer=layer), _topk_us(*size, span=span, layer=layer)
+    print(f"[time] {'layer' if layer else 'select'} {size} spans of {span}: independent {plain:.1f} us, correlated {clustered:.1f} us", flush=True)
     assert clustered < 1.4 * plain
 
 
+@LAYER
 @pytest.mark.parametrize("size", SIZES[:2])
-def test_scores_that_repeat_are_sorted_instead_of_walked(size):
+def test_scores_that_repeat_are_sorted_instead_of_walked(size, layer):
     """Many equal scores: their segments are not walked entry by entry (4.3 to 5 times as long), and the list is sorted without
     a selection."""
-    plain, ties = _topk_us(*size), _topk_us(*size, distinct=64)
-    print(f"[time] {size}: independent {plain:.1f} us, 64 different keys {ties:.1f} us", flush=True)
+    plain, ties = _topk_us(*size, layer=layer), _topk_us(*size, distinct=64, layer=layer)
+    print(f"[time] {'layer' if layer else 'select'} {size}: independent {plain:.1f} us, 64 different keys {ties:.1f} us", flush=True)
     assert ties < 3.5 * plain
