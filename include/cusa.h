@@ -207,12 +207,12 @@ cusa_status cusa_full_attn(const cusa_params* params, const void* q, const cusa_
                            void* out, void* ws, size_t ws_bytes, void* stream);
 
 /* A selection layer in one call (the selection branch of Alg. 1): out = FullAttention(q, C[:])
- * and rho = the selection of cusa_select, from one pass over K (which writes the scores; the
- * output is made from them and V while they are ranked -- or, for a layer with many scores, one pass over K
- * and V keeps those above a per-head threshold guessed from a sample; heads whose guess fails are scored and
- * ranked again, so the result does not depend on it: cusa_ws_layout.filtered_select).  idx and cnt as in
- * cusa_select (bit for bit the same rho);
- * out as in cusa_full_attn up to binary32 rounding order.  This is what cusa_decode_step runs
+ * and rho = the selection of cusa_select, from one pass over K: that pass writes the scores, and the output is made
+ * from them and V while they are ranked, or it reads V as well and makes the output itself.  For a layer with many
+ * scores it keeps only those above a per-head threshold guessed from a sample; heads whose guess fails are scored and
+ * ranked again, so the result does not depend on it (cusa_ws_layout.filtered_select).  idx and cnt as in cusa_select
+ * (bit for bit the same rho); out as in cusa_full_attn up to the order of binary32 sums and the rounding of the softmax
+ * weights to bf16 (2^-9 relative each, taken against another running maximum).  This is what cusa_decode_step runs
  * for a SELECT layer; a caller that drives the layers itself uses it instead of
  * cusa_full_attn followed by cusa_select, which read K twice. */
 cusa_status cusa_select_layer(const cusa_params* params, const void* q, const cusa_kv* kv, void* out,
@@ -222,8 +222,7 @@ cusa_status cusa_select_layer(const cusa_params* params, const void* q, const cu
  * layer_kind  host int32[n_layers] of cusa_layer_kind.  FULL: full attention.
  *             SELECT: full attention for this layer's output, then rho is rebuilt
  *             from this layer's q and K (K is read once for both; the scores P are
- *             bit for bit those of cusa_select;
- *             the output agrees with cusa_full_attn up to binary32 rounding order).
+ *             bit for bit those of cusa_select; the output as in cusa_select_layer).
  *             SPARSE: sparse attention over the current rho.  A SPARSE layer with no SELECT layer before it in this
  *             call is INVALID_ARG (Alg. 1 starts with rho empty).
  * q_layers    host array of n_layers device pointers, each bf16 [batch][H][128].

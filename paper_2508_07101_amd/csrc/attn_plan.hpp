@@ -194,6 +194,9 @@ inline bool scores_of_all_tokens(int64_t rows, int k, int window, int max_seq_le
     return !(k > 4096 && rows > 192) && (int64_t)window * 3 <= max_seq_len;
 }
 
+// At most so many rows of the top-k are cut into slices where they are long and have a launch of their own (plan_filter_slices).
+constexpr int MAX_SLICED_ROWS = 256;
+
 // Whether a selection layer that is not filtered scores all tokens first and makes its output from those scores while the top-k runs (score_kernel,
 // topk_values_kernel); otherwise one pass over K and V makes the output and writes the candidates' scores (attn_kernel's scoring variant).
 // rows: batch * query heads.
@@ -210,6 +213,9 @@ inline bool values_beside_topk(int64_t rows, int BG, int k, int window, int max_
     // Layers that large take long enough for the one pass to fill the chip as well, and read P once less (64 sequences of 32768, groups of 8: 1747 and
     // 1816, 16 of 65536 859 and 858, 64 of 9000 561 and 525).
     if (tokens >= 8 << 20) return false;
+    // One workgroup ranks a row beside the values.  The longer it is, the less its sample says about so few picks: too many pass the threshold, and the
+    // row is ranked the general way, five times as slowly, while rows that the top-k's own launch cuts into slices rarely are.
+    if (rows <= MAX_SLICED_ROWS && max_seq_len - window > 131072) return false;
     // Groups of 8: the one pass, in runs of at most 1024 tokens, is at its best where these fill its 512 resident workgroups once, most of them
     // (64 pairs of 5625: 54.4 and 56.3; 128 of 3125 66.8 and 69.3; 48 of 6875 54.0 and 55.6; 48 of 5833 51.5 and 51.1, of 8333 61.4 and 58.5).
     if (rows == 8 * (int64_t)BG && BG >= 48 && BG < 192 && tokens >= 9 << 15 && tokens < 13 << 15) return false;

@@ -630,10 +630,10 @@ cusa_status run_topk(int lc_max, int B, int H, hipStream_t s, const float* P, in
     return launch_topk<16, true>(a);
 }
 
-// The same for the rows of a selection layer, with the layer's values in the launch.  Forms that leave half a CU to the values only: with
-// rows in registers, a workgroup to a CU, the values wait for the rows (us for the launch, 8 sequences of 16384, 32 heads: 61.0
-// and 51.7; where there are few rows, or short ones, it makes no difference).  Rows are never sliced: a long row's walk by one workgroup
-// takes less time than its values.
+// The same for the rows of a selection layer, with the layer's values in the launch.  Forms that leave half a CU to the values for up to 4096
+// picks: with rows in registers, a workgroup to a CU, the values wait for the rows (us for the launch, 8 sequences of 16384, 32 heads: 61.0
+// and 51.7; where there are few rows, or short ones, it makes no difference).  Wider sorts need 94 registers and 130 KB of LDS, whatever the form
+// (values_beside_topk has when they are made here all the same).  Rows are not sliced: where that would be needed the values are not made here.
 constexpr size_t value_lds(bool group8) { return group8 ? value_lds_bytes<8>() : value_lds_bytes<4>(); }
 template <int ITEMS, int MTOP, bool GROUP8>
 cusa_status launch_topk_values_g(const TopkArgs& a, int B, const ValueArgs& v) {

@@ -672,6 +672,9 @@ struct SliceLists {
     int cap, n_slices, slice_len;
 };
 constexpr int SLICE_SAMPLE = 8;                         // sampled keys per thread
+// Rows longer than this that one workgroup walks are sampled like sliced ones: of 4096 keys so few are among the k best that the threshold, where
+// scores are correlated along the sequence, often lets more through than the list holds.
+constexpr int LONG_ROW = 65536;
 constexpr float SLICE_Z = 6.0f;                         // instead of FAST_Z: a second walk is that of a whole row by one workgroup
 
 // ITEMS == -1 is the streamed kernel in a register-lean form (half the keys in flight, compiled for two
@@ -967,8 +970,10 @@ __device__ __forceinline__ void topk_row(int h, int b, const int z, const int B,
                     asm volatile("" : "+v"(my_tid));
                 };
                 if constexpr (ITEMS > 0) mask_row();
-                uint32_t sk[FAST_SAMPLE];
+                constexpr bool EXACT = ITEMS > 0 && ITEMS <= FAST_SAMPLE;
+                RowSample rs;
                 if constexpr (ITEMS > 0) {
+                    uint32_t sk[FAST_SAMPLE];
 #pragma unroll
                     for (int i = 0; i < FAST_SAMPLE; ++i) {
                         const int it = QUADS >= 4 ? 5 * i : QUADS == 2 ? (i < 2 ? 2 * i : 2 * i + 1) : i;   // (5 i: element i of quad i)
@@ -976,16 +981,25 @@ __device__ __forceinline__ void topk_row(int h, int b, const int z, const int B,
                         const float s = QUADS == 8 && (lane & 1) ? x[(it >> 2) + (QUADS == 8 ? 4 : 0)][it & 3] : x[it >> 2][it & 3];
                         sk[i] = s == -INFINITY ? 0u : score_key(s);
                     }
+                    go = sample_row(sk, shist, &sample_st, &rs);
                 } else {
-                    static_assert(FAST_SAMPLE == 4, "one 16-byte load");
-                    const int t = sample_quad<FAST_SAMPLE * SEL_THREADS>(tid, t_hi);
-                    const f32x4 y = *reinterpret_cast<const f32x4*>(row + min(t, (int)ldp - 4));
+                    auto sample_streamed = [&](auto keys_per_thread) {   // 16-byte loads
+                        constexpr int S = decltype(keys_per_thread)::value;
+                        f32x4 y[S / 4];
+                        uint32_t sk[S];
 #pragma unroll
-                    for (int i = 0; i < FAST_SAMPLE; ++i) sk[i] = t + i < t_hi && t + i >= n_sink ? score_key(y[i]) : 0u;
+                        for (int i = 0; i < S / 4; ++i)
+                            y[i] = *reinterpret_cast<const f32x4*>(row + min(sample_quad<S * SEL_THREADS>(i * SEL_THREADS + tid, t_hi), (int)ldp - 4));
+#pragma unroll
+                        for (int i = 0; i < S; ++i) {
+                            const int t = sample_quad<S * SEL_THREADS>((i >> 2) * SEL_THREADS + tid, t_hi) + (i & 3);
+                            sk[i] = t < t_hi && t >= n_sink ? score_key(y[i >> 2][i & 3]) : 0u;
+                        }
+                        return sample_row(sk, shist, &sample_st, &rs);
+                    };
+                    if (ITEMS == -1 && t_hi > LONG_ROW) go = sample_streamed(std::integral_constant<int, SLICE_SAMPLE>());   // uniform
+                    else go = sample_streamed(std::integral_constant<int, FAST_SAMPLE>());
                 }
-                constexpr bool EXACT = ITEMS > 0 && ITEMS <= FAST_SAMPLE;
-                RowSample rs;
-                go = sample_row(sk, shist, &sample_st, &rs);
                 // (slices that failed have told how many reach a threshold like the first)
                 for (int attempt = ITEMS == 0 && sl.cand ? 1 : 0; go; ++attempt) {
                     int j = EXACT ? k_eff : sample_rank_wanted(k_eff, t_hi - max(t_lo, n_sink), rs.n_s, FAST_Z);
