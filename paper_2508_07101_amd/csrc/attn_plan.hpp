@@ -214,8 +214,11 @@ inline bool values_beside_topk(int64_t rows, int BG, int k, int window, int max_
     // 1816, 16 of 65536 859 and 858, 64 of 9000 561 and 525).
     if (tokens >= 8 << 20) return false;
     // One workgroup ranks a row beside the values.  The longer it is, the less its sample says about so few picks: too many pass the threshold, and the
-    // row is ranked the general way, five times as slowly, while rows that the top-k's own launch cuts into slices rarely are.
-    if (rows <= MAX_SLICED_ROWS && max_seq_len - window > 131072) return false;
+    // row is ranked the general way, five times as slowly, while rows that the top-k's own launch cuts into slices rarely are; and of one or two pairs
+    // the values take less time than the row.  (1 to 32 pairs, groups of 1, 4, 8, 300 to 7680 picks, scores independent or correlated over 64 tokens,
+    // against the one pass: geometric mean and worst of 100000 tokens 0.89 and 1.02, 131072 0.94 and 1.03, 150000 0.91 and 1.03, 180000 0.93 and 1.03,
+    // 220000 0.94 and 1.11, 262144 0.99 and 1.63; from 360000 to 1048576, with samples of 4096 keys, 1.11 to 1.77 and 6.1.)
+    if (rows <= MAX_SLICED_ROWS && max_seq_len - window > 3 * 65536) return false;
     // Groups of 8: the one pass, in runs of at most 1024 tokens, is at its best where these fill its 512 resident workgroups once, most of them
     // (64 pairs of 5625: 54.4 and 56.3; 128 of 3125 66.8 and 69.3; 48 of 6875 54.0 and 55.6; 48 of 5833 51.5 and 51.1, of 8333 61.4 and 58.5).
     if (rows == 8 * (int64_t)BG && BG >= 48 && BG < 192 && tokens >= 9 << 15 && tokens < 13 << 15) return false;

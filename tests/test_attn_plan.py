@@ -180,14 +180,14 @@ def test_the_selection_layers_values_stay_within_their_kernels_limits(tmp_path):
 
 def test_selection_layers_that_one_pass_serves_faster(tmp_path):
     """Where the former pass over K and V beats the two of the values: many picks to sort beside many rows, wide windows, the largest layers, few
-    rows of more than 131072 candidates (sizes that were measured 4 to 10 per cent slower)."""
+    rows of more than 196608 candidates (sizes that were measured 4 to 10 per cent slower)."""
     out = run_checks(tmp_path, r'''
     (void)plan;
     struct { int rows, pairs, k, window, n; bool beside; } const sizes[] = {
         {256, 64, 8192, 0, 16384, false}, {512, 64, 7168, 1024, 10000, false}, {128, 32, 8192, 0, 16384, true}, {256, 64, 4096, 1024, 16384, true},
         {512, 64, 600, 8500, 16384, false}, {32, 8, 500, 1100, 3300, true}, {4096, 512, 1536, 512, 32768, false}, {4096, 512, 1536, 512, 9000, true},
         {512, 64, 768, 256, 5625, false}, {512, 64, 768, 256, 8125, true}, {256, 64, 768, 256, 5625, true}, {64, 8, 768, 256, 45000, true},
-        {64, 8, 3072, 1024, 132096, true}, {64, 8, 3072, 1024, 132097, false}, {1, 1, 1792, 256, 1048576, false}, {320, 40, 1792, 256, 180000, true}};
+        {64, 8, 3072, 1024, 197632, true}, {64, 8, 3072, 1024, 197633, false}, {1, 1, 1792, 256, 1048576, false}, {320, 40, 1792, 256, 200000, true}};
     for (const auto& s : sizes)
         if (values_beside_topk(s.rows, s.pairs, s.k, s.window, s.n, 128) != s.beside) FAIL("%d rows, %d pairs of %d, k %d", s.rows, s.pairs, s.n, s.k);
 ''')

@@ -536,7 +536,7 @@ def test_union_of_agreeing_and_disagreeing_heads(heads, L, K, W, k):
 
 @pytest.mark.parametrize("B,L,K,W,k", [(2, 700, 512, 128, 500), (2, 4200, 1024, 0, 0), (2, 9001, 2048, 512, 2048),
                                         (2, 20011, 3072, 0, 3072), (1, 9000, 8192, 0, 0), (2, 41000, 4096, 1024, 0),
-                                        (1, 140001, 2048, 512, 0), (48, 9700, 3000, 100, 0), (1, 70001, 8192, 1024, 0)])
+                                        (1, 140001, 2048, 512, 0), (48, 9700, 3000, 100, 0), (1, 70001, 8192, 1024, 0), (1, 200701, 2048, 512, 0)])
 @pytest.mark.parametrize("where", ["one run", "every 16th run of 64", "one position in four"])
 def test_topk_rows_whose_best_scores_cluster(B, L, K, W, k, where):
     """The top-k's threshold comes from a sample of the row: rows whose best candidates stand together (in one slice, in one
@@ -558,7 +558,7 @@ def test_topk_rows_whose_best_scores_cluster(B, L, K, W, k, where):
     rows = lay.k[:, :, at].float()
     q = lay.q.float()[:, :, None, :]                     # one query head per KV head
     lay.k[:, :, at] = (0.3 * rows + 0.5 * q).to(torch.bfloat16)
-    check_both_selections(inp, StepRunner(inp), values=L - W <= 131072, seqs=[0, B - 1], check_scores=False)
+    check_both_selections(inp, StepRunner(inp), values=L - W <= 196608, seqs=[0, B - 1], check_scores=False)
 
 
 @pytest.mark.parametrize("B,L,K,W,k", [(2, 4000, 1300, 276, 1024), (2, 7000, 1000, 100, 0), (2, 9000, 2560, 512, 0),
@@ -765,7 +765,7 @@ def test_selection_layer_with_wide_sorts_beside_its_values(H, L, K, W, paged):
 @pytest.mark.parametrize("H,paged", [(8, False), (32, True), (64, False), (64, True)])
 @pytest.mark.parametrize("B,lens,bound,two_passes", [(16, (3100, 700, 1024, 1500, 2049), 60000, True),     # two runs to a workgroup, some without any
                                                      (64, (4000, 900, 601, 1536, 1537), 16000, True),
-                                                     (2, (40000, 35001), 131132, True),               # the longest rows that are ranked beside the values
+                                                     (2, (40000, 35001), 196668, True),               # the longest rows that are ranked beside the values
                                                      (64, (1500, 900, 601), 600000, False)])          # 19 tiles of cusa_select to a workgroup
 def test_selection_under_a_bound_far_above_the_lengths(H, paged, B, lens, bound, two_passes):
     """Workgroups of the scoring pass and of the values that take several tiles and runs in turn, or have nothing to do."""
