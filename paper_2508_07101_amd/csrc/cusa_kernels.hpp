@@ -2763,6 +2763,7 @@ struct ValueArgs {
 };
 constexpr int VALUE_TILE = 16;
 constexpr int VALUE_WG_TILE = VALUE_TILE * SEL_WAVES;
+constexpr int VALUE_PAIRS_IN_ORDER = 64;
 struct ValueLds {
     float m[SEL_WAVES][8], l[SEL_WAVES][8];
 };
@@ -2929,7 +2930,10 @@ __device__ __forceinline__ void weigh_values(const ValueArgs& a, int pair, int s
 }
 
 // The top-k over whole rows and the values in one launch, 1-D grid of n_topk + va.items workgroups.  Workgroup i of the values takes the runs
-// i / pairs, i / pairs + wgs, ... of pair i % pairs: where sequences are shorter than the bound, the workgroups with work come first.  Rows and runs take turns of 256, a
+// i / pairs, i / pairs + wgs, ... of pair i % pairs: where sequences are shorter than the bound, the workgroups with work come first.  Of few pairs the
+// runs of one come together, if a workgroup has no more than one of them (us for the layer, first runs first and so: 8 pairs of 131072, groups of 8, 125.5
+// and 119.7; 64 of 16384 110.3 and 108.4; 16 of 131072, paged, 211.3 and 209.0; 32 of 16384, paged, 62.1 and 62.3; 128 of 9000, paged, 123.9 and 124.5; 256 of
+// 8192 206.2 and 207.5). Rows and runs take turns of 256, a
 // workgroup for every CU (where there are as many), what is left of either comes at the end: the dispatcher hands out workgroups strictly in order
 // and in turn to the shader engines, so with a shorter turn all rows meet in a few engines and what follows them waits for a place elsewhere
 // (turns of 8: 120 CUs idle for 18 of 64 us).
@@ -2955,10 +2959,14 @@ __global__ __launch_bounds__(SEL_THREADS, topk_lean(ITEMS, MTOP) ? 8 : 4) void t
     }
     __shared__ ValueLds st;
     float* const lds = reinterpret_cast<float*>(sort_buf);
-    int wave = __builtin_amdgcn_readfirstlane(wave_id()), pair = i % va.pairs;
+    int wave = __builtin_amdgcn_readfirstlane(wave_id()), pair = i % va.pairs, first = i / va.pairs;
+    if (va.wgs == va.n_splits && va.pairs <= VALUE_PAIRS_IN_ORDER) {
+        pair = i / va.n_splits;
+        first = (i + pair) % va.n_splits;             // short sequences' idle workgroups: spread over the XCDs
+    }
     const int L = uniform_load(va.seq_lens + pair / va.G);
 #pragma clang loop unroll(disable)
-    for (int run = i / va.pairs; run * va.chunk < L; run += va.wgs) {
+    for (int run = first; run * va.chunk < L; run += va.wgs) {
         asm volatile("" : "+s"(pair), "+s"(wave));    // (scalar registers: every run makes what it needs of them anew)
         if constexpr (GROUP8) {                       // (its registers are too few beside the other groups' code)
             weigh_values<8>(va, pair, run, L, wave, lds, st);
