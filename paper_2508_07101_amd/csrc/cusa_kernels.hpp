@@ -182,7 +182,10 @@ struct FilterState {              // device memory of the fast path, all per (se
     int32_t* cand_cnt;            // candidates kept so far
     int32_t* fail;                // 1: this head takes the second chance
     int32_t* n_failed;            // number of flagged heads
-    uint64_t* cand;               // [row][cap] composites (score key << 32 | ~position), in any order
+    union {
+        uint64_t* cand;           // [row][cap] composites (score key << 32 | ~position), in any order
+        float* scores;            // attn_kernel's scoring variant without the filter: P, rows of cap scores.  (Arguments of their own, which
+    };                            // every form of the kernel would load: 0.2 us per launch, 401 -> 408 for a step of 36 layers.)
     int32_t cap;
     int32_t n_sink;
 };
@@ -2038,7 +2041,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt, const int32_t* __restrict__ seq_lens,
     const uint16_t* __restrict__ q, int budget, int n_splits, int chunk, int G, float scale_log2e,
     float* __restrict__ part_acc, float* __restrict__ part_ml, uint16_t* __restrict__ out, float* __restrict__ lse,
-    float* __restrict__ P, int64_t ldp, int window, int hshift, FilterState flt, KvView kv) {
+    int window, int hshift, FilterState flt, KvView kv) {
     static_assert(!(SCORE && SPARSE), "scores are emitted by the pass over all tokens");
     static_assert(!FILTER || SCORE, "the filter is a form of the scoring variant");
     static_assert(!PER_HEAD || (SPARSE && GQ == 1), "per-head token lists: one query head per workgroup");
@@ -2227,7 +2230,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
                 for (int i = tid; i < GQ * quads; i += ATTN_THREADS) {
                     const int h = i / quads, w4 = (i - h * quads) * 4, t = g0 + w4;
                     const f32x4 v = *reinterpret_cast<const f32x4*>(&pstage[h * STAGE_TOK + w4]);
-                    float* const dst = &P[(head0 + h) * ldp + t];
+                    float* const dst = &flt.scores[(head0 + h) * flt.cap + t];
                     if (t + 3 < lim) {
                         __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(dst));
                     } else {
