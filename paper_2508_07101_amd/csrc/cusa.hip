@@ -369,10 +369,8 @@ void launch_attn_ti(int ti, const AttnArgs& a) {
     if constexpr (!SPARSE) {
         if (a.score.P) {                              // the scoring chain repeats work for tiles under 64 tokens: always the wider tile
             if (a.score.filter.thr) {                 // groups of up to 4 only (filtered_select)
-                if constexpr (GQ <= 4) {
-                    if (ti == 16) launch_attn_partial<GQ, 16, false, true, true>(a);
-                    else launch_attn_partial<GQ, 8, false, true, true>(a);
-                }
+                // (so many scores, FILTER_MIN_SCORES, that a workgroup's run is always the longest)
+                if constexpr (GQ <= 4) launch_attn_partial<GQ, 16, false, true, true>(a);
             } else {
                 if (ti == 16) launch_attn_partial<GQ, 16, false, true>(a);
                 else launch_attn_partial<GQ, 8, false, true>(a);

@@ -192,3 +192,19 @@ def test_selection_layers_that_one_pass_serves_faster(tmp_path):
         if (values_beside_topk(s.rows, s.pairs, s.k, s.window, s.n, 128) != s.beside) FAIL("%d rows, %d pairs of %d, k %d", s.rows, s.pairs, s.n, s.k);
 ''')
     assert out == "", out
+
+
+def test_filtered_layers_take_the_wide_tile(tmp_path):
+    """Layers of 8 Mi scores and more in groups of up to 4, which is what the filtered pass is for: runs in tiles of 256 tokens, whatever the window."""
+    out = run_checks(tmp_path, r'''
+    (void)plan;
+    for (int64_t pairs = 1; pairs <= 65535; pairs += pairs < 80 ? 1 : pairs / 7)
+        for (int g : {1, 2, 4})
+            for (int64_t n = ((int64_t)8 << 20) / (pairs * g); n <= 4000000; n += n / 5 + 1)
+                for (bool paged : {false, true}) {
+                    if (n < 64) continue;
+                    const AttnPlan p = plan_attn((int)n, (int)pairs, g, ATTN_SCORE, paged);
+                    if (p.ti != 16 || p.chunk % 256) FAIL("%lld pairs of %lld, groups of %d: ti %d, runs of %d", (long long)pairs, (long long)n, g, p.ti, p.chunk);
+                }
+''')
+    assert out == "", out
