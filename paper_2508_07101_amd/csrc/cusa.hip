@@ -347,10 +347,10 @@ void launch_attn_partial(const AttnArgs& a) {
     const int kid = SPARSE ? KID_ATTN_SPARSE : FILTER ? KID_ATTN_FILTER : SCORE ? KID_ATTN_SELECT : KID_ATTN_FULL;
     if (a.paged)
         launch(kid, attn_kernel<GQ, TI, SPARSE, true, SCORE, false, FILTER>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt, a.view.seq_lens, a.q,
-               a.budget, a.n_splits, a.chunk, a.view.G, a.scale, a.pa, a.pm, a.out, a.lse, a.score.window, 0, a.score.dest(), a.view);
+               a.budget, a.n_splits, a.chunk, a.view.G, 0xffffffffu / (uint32_t)a.n_splits, a.scale, a.pa, a.pm, a.out, a.lse, a.score.window, 0, a.score.dest(), a.view);
     else
         launch(kid, attn_kernel<GQ, TI, SPARSE, false, SCORE, false, FILTER>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt, a.view.seq_lens, a.q,
-               a.budget, a.n_splits, a.chunk, a.view.G, a.scale, a.pa, a.pm, a.out, a.lse, a.score.window, 0, a.score.dest(), a.view);
+               a.budget, a.n_splits, a.chunk, a.view.G, 0xffffffffu / (uint32_t)a.n_splits, a.scale, a.pa, a.pm, a.out, a.lse, a.score.window, 0, a.score.dest(), a.view);
 }
 
 // Sparse attention with one token list per query head: grid.y counts query heads.
@@ -358,10 +358,10 @@ template <int TI>
 void launch_attn_per_head(const AttnArgs& a, int H, int hshift) {
     if (a.paged)
         launch(KID_ATTN_PER_HEAD, attn_kernel<1, TI, true, true, false, true>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt,
-               a.view.seq_lens, a.q, a.budget, a.n_splits, a.chunk, H, a.scale, a.pa, a.pm, a.out, a.lse, 0, hshift, FilterState{}, a.view);
+               a.view.seq_lens, a.q, a.budget, a.n_splits, a.chunk, H, 0xffffffffu / (uint32_t)a.n_splits, a.scale, a.pa, a.pm, a.out, a.lse, 0, hshift, FilterState{}, a.view);
     else
         launch(KID_ATTN_PER_HEAD, attn_kernel<1, TI, true, false, false, true>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt,
-               a.view.seq_lens, a.q, a.budget, a.n_splits, a.chunk, H, a.scale, a.pa, a.pm, a.out, a.lse, 0, hshift, FilterState{}, a.view);
+               a.view.seq_lens, a.q, a.budget, a.n_splits, a.chunk, H, 0xffffffffu / (uint32_t)a.n_splits, a.scale, a.pa, a.pm, a.out, a.lse, 0, hshift, FilterState{}, a.view);
 }
 
 template <int GQ, bool SPARSE>

@@ -2039,7 +2039,7 @@ __device__ __forceinline__ int wave_base_of(unsigned tid) { return (int)(tid >> 
 template <int GQ, int TI, bool SPARSE, bool PAGED, bool SCORE = false, bool PER_HEAD = false, bool FILTER = false>
 __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt, const int32_t* __restrict__ seq_lens,
-    const uint16_t* __restrict__ q, int budget, int n_splits, int chunk, int G, float scale_log2e,
+    const uint16_t* __restrict__ q, int budget, int n_splits, int chunk, int G, uint32_t inv_splits, float scale_log2e,
     float* __restrict__ part_acc, float* __restrict__ part_ml, uint16_t* __restrict__ out, float* __restrict__ lse,
     int window, int hshift, FilterState flt, KvView kv) {
     static_assert(!(SCORE && SPARSE), "scores are emitted by the pass over all tokens");
@@ -2058,9 +2058,8 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     constexpr int WAVE_LDS = TILE * KSLOTS * 16;      // bytes of a wave's tile buffer
     static_assert(WAVE_LDS >= GQ * D * 4, "the K tile buffer must hold a wave's partial accumulators");
     __shared__ __attribute__((aligned(16))) unsigned char smem_raw[ATTN_WAVES * WAVE_LDS];
-    // this wave's K rows: chunk c of row r at slot c ^ (r & 7) (a swizzle over all sixteen slots, c ^ (r & 15),
-    // removes the remaining two-way bank conflicts and was measured: no faster); scoring variant: chunk c
-    // (of the half) at slot c ^ ((r >> 1) & 7)
+    // this wave's K rows: chunk c of row r at slot c ^ (r & 15) (no bank conflicts in either direction); scoring
+    // variant: chunk c (of the half) at slot c ^ ((r >> 1) & 7)
     u32x4* const ktile = reinterpret_cast<u32x4*>(smem_raw) + wave_base_of(threadIdx.x) * (TILE * KSLOTS);
     __shared__ float sm_m[ATTN_WAVES][GQ];
     __shared__ float sm_l[ATTN_WAVES][GQ];
@@ -2094,8 +2093,13 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     // block spreads them evenly over the XCDs instead of loading the first ones.
     const int gy = blockIdx.y, b = blockIdx.z, H = G * GQ;
     const int kvh = PER_HEAD ? gy >> hshift : gy;
-    const int split = (int)((blockIdx.x + gy + G * b) % (unsigned)n_splits);
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r = lane >> 4, c = lane & 15;
+    // (blockIdx.x + pair) % n_splits: inv_splits = (2^32 - 1) / n_splits rounded down, so the quotient is right or one short
+    const uint32_t pair = (uint32_t)gy + (uint32_t)G * (uint32_t)b;
+    uint32_t turned = blockIdx.x + (pair - __umulhi(pair, inv_splits) * (uint32_t)n_splits);
+    if (turned >= (uint32_t)n_splits) turned -= n_splits;
+    if (turned >= (uint32_t)n_splits) turned -= n_splits;
+    const int split = (int)turned;
+    const int tid = threadIdx.x, wave = SCORE ? tid >> 6 : __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r = lane >> 4, c = lane & 15;
     const int begin = split * chunk;
     const int32_t* __restrict__ my_idx = idx + (PER_HEAD ? (int64_t)b * G + gy : (int64_t)b) * budget;
     const int64_t head0 = (int64_t)b * H + gy * GQ;      // first query head of this group
@@ -2107,13 +2111,13 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     // entries past the count are masked below like every row past the run's end.
     const int tile0 = begin + wave * TILE;
     int posA[TI], pgA[TI];
-    auto idx_load = [&](int t_, int* p) {
+    auto idx_load = [&](int t_, int last, int* p) {
         if (SPARSE) {
 #pragma unroll
-            for (int i = 0; i < TI; ++i) p[i] = my_idx[min(t_ + i * 4 + r, budget - 1)];
+            for (int i = 0; i < TI; ++i) p[i] = my_idx[min(t_ + i * 4 + r, last)];
         }
     };
-    idx_load(tile0, posA);
+    idx_load(tile0, budget - 1, posA);
 
     // Every wave keeps its own bf16 copy of q in LDS (no workgroup barrier on the way in): lane l
     // fetches 16 bytes of head l / 16 per set now and parks them once the first tile's loads are
@@ -2127,43 +2131,75 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
         if (h >= GQ) qv[s] = u32x4{0u, 0u, 0u, 0u};
     }
     bool q_parked = false;
+    f32x4 acc[SETS][8];                               // [set][column e of the lane's 8]: the four heads of the set
+#pragma unroll
+    for (int s = 0; s < SETS; ++s)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            acc[s][e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            if (!SCORE) asm volatile("" : "+v"(acc[s][e]));   // here, while the token list is on its way, not between the rows' requests
+        }
     const int L = seq_lens[b];
     const int n = SPARSE ? min(cnt[b], budget) : L;
     // Everything the first tile's addresses depend on is requested above and has to be here
     // before the first branch; otherwise the compiler sinks each load behind the branch that
     // precedes its first use and the kernel starts with a chain of dependent memory round trips.
     asm volatile("" ::"s"(L), "s"(n), "s"(kv.k), "s"(H));
+    // ... nor fetch the arguments that are used later when they are (a round trip each; in the scoring variant the registers they
+    // would occupy cost more: 979 -> 983 us for 64 sequences)
+    if (!SCORE) asm volatile("" ::"s"(kv.v), "s"(kv.st), "s"(part_acc), "s"(part_ml), "s"(out), "s"(lse), "s"(scale_log2e));
     if (SPARSE) {
 #pragma unroll
         for (int i = 0; i < TI; ++i) asm volatile("" ::"v"(posA[i]));
     }
-    if (split > 0 && begin >= n) return;                 // split >= attn_active_splits(n, chunk)
+    if (!SCORE) {
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) asm volatile("" ::"v"(qv[s]));
+    }
+    if (__builtin_expect(begin >= n, 0)) {               // split >= attn_active_splits(n, chunk), or an empty list:
+        if (split == 0) {                                // nothing to attend to
+            for (int o = tid; o < GQ * D; o += ATTN_THREADS) out[head0 * D + o] = 0;
+            if (lse && tid < GQ) lse[head0 + tid] = -INFINITY;
+        }
+        return;
+    }
     const int end = (begin + chunk < n) ? begin + chunk : n;
 
     // Scores come from V_MFMA_F32_4X4X4_16B_BF16: per lane four bf16 of q (head = lane % 4)
-    // and four of K (the lane's token); after 32 instructions lane t holds q_h . k_t for the
-    // heads of each set.  Lane t scores token t % TILE of the tile.
+    // and four of K (the lane's token).  A tile of fewer than 64 tokens has 64 / TILE = PARTS lanes to a token: lane t
+    // multiplies part t / TILE of the columns of token t % TILE (32 / PARTS instructions), and two folds over the
+    // lane's upper bits add the parts up and leave every lane the whole scores of NZ = 4 SETS / PARTS heads, head0_z
+    // onwards -- one (token, head) per lane at 16 tokens and a group of 4, so that the tile's maxima and weights take one
+    // chain of operations instead of four and K and q a quarter of the LDS reads.  (When all lanes of a token
+    // walked the whole row, reading K and q was what a short run's arithmetic waited for: 4 waves x 16 + 16 reads of 1 KB.  Layer
+    // of one sequence, 32 heads, list of 2048: 7.75 -> 7.2 us; 8 sequences, lists of 4096: 27.1 -> 26.6.)
+    // The scoring variant's sums run over the columns in order: one part, every lane all heads (lanes beyond TILE repeat a token
+    // and add nothing to l).
+    constexpr int PARTS = SCORE ? 1 : 64 / TILE;
+    constexpr int NV = SETS * 4, NZ = PARTS == 1 ? GQ : NV / PARTS;
+    static_assert(PARTS == 1 || PARTS == 2 || PARTS == 4, "tiles of 16, 32 or 64 tokens");
     const int tl = lane % TILE;
-    const bool owner = lane < TILE;                   // lanes beyond TILE repeat a token; they add nothing to l
+    const bool owner = PARTS > 1 || lane < TILE;
+    const int head0_z = PARTS == 1 ? 0 : PARTS == 2 ? (lane >> 5) * (NV / 2) : (lane >> 5) * (NV / 2) + ((lane >> 4) & 1) * (NV / 4);
     // token tl is row load (tl / 4) of row group (tl % 4): where its numerators go (bf16 elements)
-    const int p_slot = (((tl & 3) * (TI / 4) + (tl >> 4)) * SETS * 4) * 4 + ((tl >> 2) & 3);
-    float m[GQ], l[GQ];
-    f32x4 acc[SETS][8];                               // [set][column e of the lane's 8]: the four heads of the set
+    const int p_slot = (((tl & 3) * (TI / 4) + (tl >> 4)) * SETS * 4 + head0_z) * 4 + ((tl >> 2) & 3);
+    float m[NZ], l[NZ];                               // of the lane's heads
 #pragma unroll
-    for (int h = 0; h < GQ; ++h) {
-        m[h] = LOWEST;
-        l[h] = 0.0f;
+    for (int v = 0; v < NZ; ++v) {
+        m[v] = LOWEST;
+        l[v] = 0.0f;
     }
-#pragma unroll
-    for (int s = 0; s < SETS; ++s)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[s][e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
     // Rows past the end of the run read some token of the sequence (a valid row) so that all
     // loads are unconditional and issue back to back; their scores are masked below.
     // The next tile's K rows are requested as soon as this tile's are parked in LDS, i.e. before
-    // this tile's arithmetic (not in the scoring variant, whose 64-token tiles leave no registers
-    // for it; there the rows are requested at the top of the tile's own iteration).
+    // this tile's arithmetic (not in the scoring variant, whose
+    // 64-token tiles leave no registers for it; there the rows are requested at the top of the tile's own iteration).
+    // The K rows are requested whether there is a next tile or not (rows past the run's end are the run's last): loads return
+    // in order, a wait counts those that may still be under way, and behind a branch the compiler cannot count them -- it
+    // waited for the next tile's K rows before it multiplied this tile's V rows.  (With that, the accumulators cleared while the
+    // token list is on its way and the tail's arguments fetched at the start: list of 2048 7.2 -> 6.95 us, 64 heads and 4096 9.6 ->
+    // 8.4; all of 32768 tokens, 32 heads, 26.2 -> 25.3; 8 sequences of 16384 86.8 -> 84.9.)
     constexpr bool PREFETCH = !SCORE;
     // The scoring variant of a group of 8 has no registers for K and V rows at once (64 each at 64-token
     // tiles, beside 64 accumulators): its V rows are requested once the K rows are parked in LDS.
@@ -2173,7 +2209,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     // a valid position for row load i of the tile that starts at list entry t_ (an index outside the
     // sequence is a caller error; never fault on it)
     auto tile_pos = [&](int t_, int i, const int* p) {
-        return SPARSE ? min(max(p[i], 0), L - 1) : min(t_ + i * 4 + r, end - 1);
+        return (uint32_t)(SPARSE ? max(min(p[i], L - 1), 0) : min(t_ + i * 4 + r, end - 1));
     };
     // Pool pages of the tile's rows.  A pass over all tokens walks the table in order: tiles start at
     // multiples of 16 tokens, so row loads 4ig .. 4ig+3 of every lane fall into one page, entry
@@ -2193,7 +2229,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
         if constexpr (SPARSE && PAGED) page_load(t_, p, g);
 #pragma unroll
         for (int i = 0; i < TI; ++i) {
-            const int pos = tile_pos(t_, i, p);
+            const uint32_t pos = tile_pos(t_, i, p);
             if (PAGED) off[i] = (((int64_t)g[SPARSE ? i : i >> 2] * kv.G + kvh) * PAGE + (pos & (PAGE - 1))) * D + c * 8;
             else off[i] = (int64_t)b * kv.sb + (int64_t)kvh * kv.sh + (int64_t)pos * kv.st + c * 8;
         }
@@ -2202,16 +2238,36 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
 #pragma unroll
         for (int i = 0; i < TI; ++i) kreg[i] = row_load<PER_HEAD>(kv.k + off[i]);
     };
+    auto request_v = [&]() {
+#pragma unroll
+        for (int i = 0; i < TI; ++i) vreg[i] = row_load<PER_HEAD>(kv.v + off[i]);
+    };
     // After the rows of the tile at t_ have been requested: the lookups for the tile after it.
     auto advance = [&](int t_) {
-        idx_load(t_ + WG_TILE, posA);
+        idx_load(t_ + WG_TILE, end - 1, posA);           // (past the run's end: its last row, not rows of the next run)
         if constexpr (!SPARSE) page_load(t_ + WG_TILE, posA, pgA);   // sparse: looked up where the offsets are made
     };
     if constexpr (!SPARSE) page_load(tile0, posA, pgA);
-    if (PREFETCH && tile0 < end) {
+    auto park_q = [&]() {
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) {
+            if constexpr (SCORE) {
+                float qf[8];
+                unpack8(make_uint4(qv[s].x, qv[s].y, qv[s].z, qv[s].w), qf);
+                float* const dst = &qf32[(s * 4 + r) * QSF + c * 8];
+                *reinterpret_cast<f32x4*>(dst) = f32x4{qf[0], qf[1], qf[2], qf[3]};
+                *reinterpret_cast<f32x4*>(dst + 4) = f32x4{qf[4], qf[5], qf[6], qf[7]};
+            } else {
+                *reinterpret_cast<u32x4*>(&qlds[(s * 4 + r) * QSB + c * 8]) = qv[s];
+            }
+        }
+    };
+    if constexpr (PREFETCH) {
         make_off(tile0, posA, pgA);
         request_k();
         advance(tile0);
+        __builtin_amdgcn_sched_barrier(0);
+        park_q();
     }
     // Scoring variant: the scores go to P through a staging buffer in LDS that the whole workgroup
     // writes out in one burst.  A few per cent of small writes scattered
@@ -2292,8 +2348,9 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     int t_opaque = 0;                                    // always zero, unknown to the compiler
     int it_staged = 0;                                   // first iteration whose scores are still in the staging buffer
     int it = 0;                                          // iterations of the workgroup so far
-    for (int w0 = begin; w0 < end; w0 += WG_TILE, ++it) {
-        const int t0 = w0 + wave * TILE;
+    // (Without the scoring variant's barriers every wave leaves when its own tiles are done.)
+    for (int w0 = SCORE ? begin : tile0; w0 < end; w0 += WG_TILE, ++it) {
+        const int t0 = SCORE ? w0 + wave * TILE : w0;
         // Only the scoring variant has workgroup barriers inside the loop; there a wave whose tile lies
         // past the run's end still takes part in them.
         const bool active = t0 < end;
@@ -2309,46 +2366,29 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
             }
             it_staged = it;
         }
-        if (!active) {
-            if constexpr (!SCORE) break;
-            continue;
-        }
+        if (SCORE && !active) continue;
         if constexpr (!PREFETCH) {
             make_off(t0, posA, pgA);
             // K rows first: they are needed first (parked in LDS and scored), and loads return in
             // order, so the scores are under way while the V rows are still arriving.
             request_k();
         }
-        if constexpr (!V_LATE) {
-#pragma unroll
-            for (int i = 0; i < TI; ++i) vreg[i] = row_load<PER_HEAD>(kv.v + off[i]);
-        }
+        if constexpr (!V_LATE) request_v();
         if constexpr (!PREFETCH && !V_LATE) advance(t0);
         __builtin_amdgcn_sched_barrier(0);               // keep every load above the arithmetic
-        if (!q_parked) {
-#pragma unroll
-            for (int s = 0; s < SETS; ++s) {
-                if constexpr (SCORE) {
-                    float qf[8];
-                    unpack8(make_uint4(qv[s].x, qv[s].y, qv[s].z, qv[s].w), qf);
-                    float* const dst = &qf32[(s * 4 + r) * QSF + c * 8];
-                    *reinterpret_cast<f32x4*>(dst) = f32x4{qf[0], qf[1], qf[2], qf[3]};
-                    *reinterpret_cast<f32x4*>(dst + 4) = f32x4{qf[4], qf[5], qf[6], qf[7]};
-                } else {
-                    *reinterpret_cast<u32x4*>(&qlds[(s * 4 + r) * QSB + c * 8]) = qv[s];
-                }
-            }
+        if (SCORE && !q_parked) {
+            park_q();
             q_parked = true;
         }
         if constexpr (!SCORE) {
 #pragma unroll
             for (int i = 0; i < TI; ++i) {
                 const int row = i * 4 + r;
-                ktile[row * 16 + (c ^ (row & 7))] = kreg[i];
+                ktile[row * 16 + (c ^ (row & 15))] = kreg[i];
             }
             wave_lds_sync();
         }
-        if (PREFETCH && t0 + WG_TILE < end) {
+        if constexpr (PREFETCH) {
             make_off(t0 + WG_TILE, posA, pgA);
             request_k();
             advance(t0 + WG_TILE);
@@ -2378,8 +2418,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
                         // the compiler must not see that they are the same values, or it keeps them
                         asm volatile("" : "+v"(t_opaque));
                         make_off(t0 + t_opaque, posA, pgA);
-#pragma unroll
-                        for (int i = 0; i < TI; ++i) vreg[i] = row_load<PER_HEAD>(kv.v + off[i]);
+                        request_v();
                         advance(t0);
                         __builtin_amdgcn_sched_barrier(0);
                     }
@@ -2430,48 +2469,64 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
                 for (int h = 0; h < GQ; ++h) pstage[h * STAGE_TOK + (it - it_staged) * WG_TILE + wave * TILE + tl] = sc[h >> 2][h & 3];
             }
         } else {
+            // this lane's part of the columns; the two halves of a chunk into sums of their own (shorter chains)
+            constexpr int CHUNKS = 16 / PARTS;
+            const int part0 = (lane / TILE) * CHUNKS, slot0 = part0 ^ (tl & 15);
+            f32x4 sc2[SETS];
 #pragma unroll
-            for (int cc = 0; cc < 16; ++cc) {
-                const u32x4 kw = ktile[tl * 16 + (cc ^ (tl & 7))];
+            for (int s = 0; s < SETS; ++s) sc2[s] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-                for (int half = 0; half < 2; ++half) {
-                    const uint2 kb = half == 0 ? make_uint2(kw.x, kw.y) : make_uint2(kw.z, kw.w);
-                    const s16x4 bq = __builtin_bit_cast(s16x4, kb);
+            for (int j = 0; j < CHUNKS; ++j) {
+                const u32x4 kw = ktile[tl * 16 + (slot0 ^ j)];
+                const s16x4 klo = __builtin_bit_cast(s16x4, make_uint2(kw.x, kw.y)), khi = __builtin_bit_cast(s16x4, make_uint2(kw.z, kw.w));
 #pragma unroll
-                    for (int s = 0; s < SETS; ++s) {
-                        const s16x4 aq = *reinterpret_cast<const s16x4*>(&qlds[(s * 4 + (lane & 3)) * QSB + cc * 8 + half * 4]);
-                        sc[s] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(aq, bq, sc[s], 0, 0, 0);
-                    }
+                for (int s = 0; s < SETS; ++s) {
+                    const u32x4 qw = *reinterpret_cast<const u32x4*>(&qlds[(s * 4 + (lane & 3)) * QSB + (part0 + j) * 8]);
+                    sc[s] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(s16x4, make_uint2(qw.x, qw.y)), klo, sc[s], 0, 0, 0);
+                    sc2[s] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(s16x4, make_uint2(qw.z, qw.w)), khi, sc2[s], 0, 0, 0);
                 }
+            }
+#pragma unroll
+            for (int s = 0; s < SETS; ++s) sc[s] += sc2[s];
+        }
+        float z[NZ];                                  // the lane's scores: token tl, heads head0_z ...
+        if constexpr (PARTS == 1) {
+#pragma unroll
+            for (int v = 0; v < NZ; ++v) z[v] = sc[v >> 2][v & 3];
+        } else {
+            float y[NV / 2];
+#pragma unroll
+            for (int v = 0; v < NV / 2; ++v) y[v] = fold_halves(sc[v >> 2][v & 3], sc[(v + NV / 2) >> 2][(v + NV / 2) & 3]);
+#pragma unroll
+            for (int v = 0; v < NZ; ++v) {
+                if constexpr (PARTS == 2) z[v] = y[v];
+                else z[v] = fold_rows(y[v], y[v + NV / 4]);
             }
         }
         const bool valid = t0 + tl < end;
-        float corr[GQ];
+        float corr[NZ];
 #pragma unroll
-        for (int h = 0; h < GQ; ++h) {
-            const float z = valid ? sc[h >> 2][h & 3] * scale_log2e : -INFINITY;
-            float mt = row_max16(z);                  // lanes TILE apart hold the same token
+        for (int v = 0; v < NZ; ++v) {
+            const float zs = valid ? z[v] * scale_log2e : -INFINITY;
+            float mt = row_max16(zs);                 // over the lanes that hold the same heads
             if (TILE > 16) mt = max_with_row_neighbour(mt);
-            if (TILE > 32) mt = max_with_other_half(mt);
-            const float m_new = fmaxf(m[h], mt);
-            corr[h] = exp2f(m[h] - m_new);
-            m[h] = m_new;
+            if (TILE > 32 || PARTS == 1) mt = max_with_other_half(mt);
+            const float m_new = fmaxf(m[v], mt);
+            corr[v] = __builtin_amdgcn_exp2f(m[v] - m_new);   // (below 2^-126 beside a largest weight of 1: zero)
+            m[v] = m_new;
             // the weight enters numerator and denominator as the same bf16 value
-            const __bf16 pb = (__bf16)exp2f(z - m_new);
-            pbuf16[p_slot + h * 4] = pb;
-            l[h] = l[h] * corr[h] + (owner ? (float)pb : 0.0f);
+            const __bf16 pb = (__bf16)__builtin_amdgcn_exp2f(zs - m_new);
+            pbuf16[p_slot + v * 4] = pb;
+            l[v] = l[v] * corr[v] + (owner ? (float)pb : 0.0f);
         }
 #pragma unroll
-        for (int s = 0; s < SETS; ++s)
+        for (int h = 0; h < GQ; ++h) {
+            const float ch = PARTS == 1 ? corr[h] : lane_value(corr[h % NZ], h / NZ * (64 / PARTS));
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                f32x4 a = acc[s][e];
-#pragma unroll
-                for (int hh = 0; hh < 4; ++hh)
-                    if (s * 4 + hh < GQ) a[hh] *= corr[s * 4 + hh];
-                acc[s][e] = a;
-            }
+            for (int e = 0; e < 8; ++e) acc[h >> 2][e][h & 3] *= ch;
+        }
         wave_lds_sync();
+        __builtin_amdgcn_sched_barrier(0);               // nothing waits for V rows before the weights are made
         // P.V on the matrix cores, four tokens per instruction.  A lane holds columns 8c .. 8c+7 of the
         // rows i*4 + r; the same column of four of its rows (4ig .. 4ig+3) is gathered into one bf16
         // quadruple (V_PERM_B32), which is this lane's column of the 4 x 4 B operand; the A operand is
@@ -2534,40 +2589,58 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
         }
     }
 #pragma unroll
-    for (int h = 0; h < GQ; ++h) {
-        float ls = row_sum16(l[h]);                      // only lanes below TILE carry a sum
-        float lt = lane_value(ls, 0);
-        if (TILE > 16) lt += lane_value(ls, 16);
-        if (TILE > 32) lt += lane_value(ls, 32) + lane_value(ls, 48);
-        if (lane == 0) {
-            sm_m[wave][h] = m[h];
-            sm_l[wave][h] = lt;
+    for (int v = 0; v < NZ; ++v) {
+        float ls = row_sum16(l[v]);
+        if (TILE > 16) ls = fold_rows(ls, ls);
+        if (PARTS == 1) ls = fold_halves(ls, ls);
+        const int h = head0_z + v;
+        if (lane % (64 / PARTS) == 0 && (PARTS == 1 || h < GQ)) {
+            sm_m[wave][h] = m[v];
+            sm_l[wave][h] = ls;
         }
     }
     __syncthreads();
     const float* const sums = reinterpret_cast<const float*>(smem_raw);
-    for (int o = tid; o < GQ * D; o += ATTN_THREADS) {
-        const int h = o / D, col = o % D;
-        float M = sm_m[0][h];
-#pragma unroll
-        for (int wv = 1; wv < ATTN_WAVES; ++wv) M = fmaxf(M, sm_m[wv][h]);
-        float A = 0.0f, Ls = 0.0f;
+    // a thread has PER consecutive columns of a head (threads beyond GQ * D / PER: none)
+    constexpr int PER = GQ * D >= ATTN_THREADS ? GQ * D / ATTN_THREADS : 1;
+    typedef float f32_per __attribute__((ext_vector_type(PER)));
+    typedef uint16_t u16_per __attribute__((ext_vector_type(PER)));
+    if (tid * PER < GQ * D) {
+        const int o = tid * PER, h = o / D, col = o % D;
+        f32_per part[ATTN_WAVES];
+        float mw[ATTN_WAVES], lw[ATTN_WAVES];
 #pragma unroll
         for (int wv = 0; wv < ATTN_WAVES; ++wv) {
-            const float f = exp2f(sm_m[wv][h] - M);
-            A = __builtin_fmaf(sums[wv * (WAVE_LDS / 4) + o], f, A);
-            Ls = __builtin_fmaf(sm_l[wv][h], f, Ls);
+            mw[wv] = sm_m[wv][h];
+            lw[wv] = sm_l[wv][h];
+            part[wv] = *reinterpret_cast<const f32_per*>(&sums[wv * (WAVE_LDS / 4) + o]);
+        }
+        const float M = fmaxf(fmaxf(mw[0], mw[1]), fmaxf(mw[2], mw[3]));
+        f32_per A = part[0] * __builtin_amdgcn_exp2f(mw[0] - M);
+        float Ls = lw[0] * __builtin_amdgcn_exp2f(mw[0] - M);
+#pragma unroll
+        for (int wv = 1; wv < ATTN_WAVES; ++wv) {
+            const float f = __builtin_amdgcn_exp2f(mw[wv] - M);
+#pragma unroll
+            for (int e = 0; e < PER; ++e) A[e] = __builtin_fmaf(part[wv][e], f, A[e]);
+            Ls = __builtin_fmaf(lw[wv], f, Ls);
         }
         if (n <= chunk) {                                // this workgroup saw the whole token list
-            out[(head0 + h) * D + col] = f32_to_bf16_rne(Ls > 0.0f ? A / Ls : 0.0f);
+            u16_per res;
+#pragma unroll
+            for (int e = 0; e < PER; ++e) res[e] = f32_to_bf16_rne(Ls > 0.0f ? A[e] / Ls : 0.0f);
+            uint16_t* const dst = out + (head0 + h) * D + col;
+            if ((uintptr_t)out % sizeof(u16_per) == 0) {
+                *reinterpret_cast<u16_per*>(dst) = res;
+            } else {
+#pragma unroll
+                for (int e = 0; e < PER; ++e) dst[e] = res[e];
+            }
             if (lse && col == 0) lse[head0 + h] = M + log2f(Ls);
         } else {
             const int64_t p = (head0 + h) * n_splits + split;
-            part_acc[p * D + col] = A;
-            if (col == 0) {
-                part_ml[p * 2] = M;
-                part_ml[p * 2 + 1] = Ls;
-            }
+            *reinterpret_cast<f32_per*>(&part_acc[p * D + col]) = A;
+            if (col == 0) *reinterpret_cast<f32x2*>(&part_ml[p * 2]) = f32x2{M, Ls};
         }
     }
     if constexpr (FILTER) copy_candidates(cand_reserved);

@@ -1,0 +1,100 @@
+"""The attention passes at the edges of their tiles: lists that end inside, at and just behind a wave's tile, a workgroup's tile and a
+piece, empty lists, outputs at addresses that take no wide store -- against softmax(q K^T / sqrt d) V in float64.
+
+The tolerance is derived: a weight is rounded to bf16 (2^-9 of it), in the numerator as in the denominator, which makes at most 2^-8 of the
+weighted mean of |v|; the output is rounded to bf16 (2^-9 of it); sums are binary32.
+"""
+import math
+
+import pytest
+import torch
+
+from paper_2508_07101_amd import binding as cb
+
+pytestmark = pytest.mark.gpu
+DEV, D, G = "cuda", 128, 2
+LENGTHS = (1, 15, 16, 17, 63, 64, 65, 127, 128, 129, 511, 513, 1025, 2049)
+
+
+def _cache(lens, layout, gen):
+    n, B = max(lens), len(lens)
+    k = torch.randn((B, G, n, D), generator=gen, device=DEV).bfloat16()
+    v = torch.randn((B, G, n, D), generator=gen, device=DEV).bfloat16()
+    seq_lens = torch.tensor(lens, dtype=torch.int32, device=DEV)
+    if layout != "paged":
+        if layout == "token_major":
+            return k, v, cb.KvCache(k.transpose(1, 2).contiguous().transpose(1, 2), v.transpose(1, 2).contiguous().transpose(1, 2), seq_lens, n)
+        return k, v, cb.KvCache(k, v, seq_lens, n)
+    pages = (n + 15) // 16
+    table = torch.randperm(B * pages, generator=gen, device=DEV).to(torch.int32).view(B, pages)
+
+    def pool(x):
+        x = torch.nn.functional.pad(x, (0, 0, 0, pages * 16 - n)).view(B, G, pages, 16, D).transpose(1, 2).reshape(B * pages, G, 16, D)
+        p = torch.empty_like(x)
+        p[table.flatten().long()] = x
+        return p
+    return k, v, cb.KvCache(pool(k), pool(v), seq_lens, n, table)
+
+
+def _check(got, q, k, v, tokens, what):
+    """One sequence: got and q [H][D], k and v [G][n][D]."""
+    if len(tokens) == 0:
+        assert (got == 0).all(), what
+        return
+    q64, g = q.cpu().double(), q.shape[0] // G
+    for h in range(q.shape[0]):
+        kk, vv = k[h // g, tokens].cpu().double(), v[h // g, tokens].cpu().double()
+        p = torch.softmax(kk @ q64[h] / math.sqrt(D), 0)
+        want, mean_abs = p @ vv, p @ vv.abs()
+        err = (got[h].cpu().double() - want).abs()
+        bad = err > 2.0 ** -9 * want.abs() + 2.0 ** -8 * mean_abs + 1e-5
+        assert not bad.any(), f"{what}, head {h}: {err.max().item()}"
+
+
+@pytest.mark.parametrize("g", [1, 2, 4, 8])
+@pytest.mark.parametrize("layout", ["head_major", "token_major", "paged"])
+@pytest.mark.parametrize("shift", [0, 1])                  # elements the outputs stand behind an aligned address
+def test_lists_that_end_at_the_edges_of_tiles(g, layout, shift):
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(100 * g + shift)
+    lens, H = list(LENGTHS), G * g
+    B, budget = len(lens), 700
+    k, v, kv = _cache(lens, layout, gen)
+    q = torch.randn((B, H, D), generator=gen, device=DEV).bfloat16()
+    params = cb.make_params(B, H, G, budget, budget // 4)
+    ws = cb.alloc_workspace(params, max(lens), DEV)
+    out = torch.full((B * H * D + 8,), 7.0, dtype=torch.bfloat16, device=DEV)
+    view = out[shift: shift + B * H * D].view(B, H, D)
+    cb.full_attn(params, q, kv, view, ws)
+    for b, n in enumerate(lens):
+        _check(view[b], q[b], k[b], v[b], torch.arange(n, device=DEV), f"full, {n} tokens")
+    # token lists of every length that fits, one of them empty
+    counts = [min(n, budget) for n in lens]
+    counts[-1], counts[-2] = 0, 257
+    idx = torch.zeros((B, budget), dtype=torch.int32, device=DEV)
+    for b, n in enumerate(counts):
+        idx[b, :n] = torch.randperm(lens[b], generator=gen, device=DEV)[:n].sort().values.to(torch.int32)
+    cnt = torch.tensor(counts, dtype=torch.int32, device=DEV)
+    cb.sparse_attn(params, q, kv, idx, cnt, view, ws)
+    for b, n in enumerate(counts):
+        _check(view[b], q[b], k[b], v[b], idx[b, :n].long(), f"sparse, {n} of {lens[b]} tokens")
+    assert (out[:shift] == 7.0).all() and (out[shift + B * H * D:] == 7.0).all(), "written beside the outputs"
+
+
+@pytest.mark.parametrize("g", [1, 2, 4, 8])
+@pytest.mark.parametrize("n", [60, 64, 250, 1000, 2050, 9000])
+def test_few_sequences_in_pieces(g, n):
+    """One sequence, cut into as many pieces as fill the chip: whole tiles, remainders, a single token in the last piece."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(n + g)
+    for length in (n, n + 1):
+        k, v, kv = _cache([length], "head_major", gen)
+        q = torch.randn((1, G * g, D), generator=gen, device=DEV).bfloat16()
+        params = cb.make_params(1, G * g, G, length, length // 4)
+        ws = cb.alloc_workspace(params, length, DEV)
+        out = torch.empty_like(q)
+        idx = torch.arange(length, dtype=torch.int32, device=DEV)[None]
+        cb.full_attn(params, q, kv, out, ws)
+        _check(out[0], q[0], k[0], v[0], torch.arange(length, device=DEV), f"full, {length} tokens")
+        cb.sparse_attn(params, q, kv, idx, torch.tensor([length], dtype=torch.int32, device=DEV), out, ws)
+        _check(out[0], q[0], k[0], v[0], torch.arange(length, device=DEV), f"sparse, {length} tokens")
