@@ -135,6 +135,18 @@ inline int in_turn(int n, int BG, int limit) {
     return (int)std::max<int64_t>(1, (n + rounds - 1) / rounds);
 }
 
+// Whether an attention launch merges its pieces itself (merge_tagged) instead of leaving them to a second launch: where the host, 3 us a launch,
+// takes longer than the GPU, that is where runs are short, and where the partial sums, written past the caches in twice the bytes, are few.
+// rows: batch * query heads; in_step: one layer of several that are enqueued together, so that the GPU is behind the host.
+// (Layer of one sequence, us, GPU alone / calls one after the other from Python, two launches and so: 32 heads, list of 1024, 512 rows of partial
+// sums, 6.3 / 9.8 and 6.0 / 6.9; of 2048, 1024 rows, 6.87 / 9.8 and 7.04 / 7.15; all of 4096 tokens, 1024, 7.9 / 9.9 and 8.0 / 8.2; 64 heads, 4096,
+// 2048 rows, 8.4 / 9.7 and 9.2 / 9.3.  Runs of 512 tokens: 8 sequences, lists of 4096, 26.2 and 27.1, the waiting costs more than a launch.)
+constexpr int MERGE_ROWS_MAX = 256;
+constexpr int MERGE_RUN = 128;
+inline bool merges_itself(const AttnPlan& pl, int64_t rows, bool in_step) {
+    return pl.n_splits > 1 && pl.chunk <= MERGE_RUN && rows <= MERGE_ROWS_MAX && rows * pl.n_splits <= (in_step ? 512 : 1024);
+}
+
 // The scoring pass (score_kernel): a workgroup for every workgroup tile, of 256 tokens (128 where these would be too few to keep every
 // CU busy twice over); there is no partial result to merge, so nothing bounds their number but the time that idle ones take: where the bound is
 // far above the lengths, which are not known here, nearly all have nothing to do (64 sequences of 8 KV heads, no tile to be scored: 65536

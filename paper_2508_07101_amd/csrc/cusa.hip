@@ -8,7 +8,9 @@
 
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <mutex>
+#include <random>
 #include <utility>
 #include <vector>
 
@@ -226,6 +228,7 @@ bool filtered_select(const cusa_params* p, int max_seq_len) {
 struct WsLayout {
     size_t scores, rho_head, part_acc, part_ml, agg, rho_rank, lse, out_tmp, topk_parts, slice_cnt, slice_lo, total;
     size_t f_thr, f_cnt, f_fail, f_nfailed, f_cand;           // the selection's filtered fast path
+    size_t part_bytes;                                        // of part_acc and part_ml, which follow each other
     int filter_cap;                                           // 0: not laid out
     int64_t ldp;
     int k;
@@ -247,6 +250,9 @@ WsLayout make_layout(const cusa_params* p, int max_seq_len) {
     w.rho_head = off;  off += align256((size_t)(B * w.k * H) * 4);
     w.part_acc = off;  off += align256((size_t)(B * H * w.max_splits * D) * 4);
     w.part_ml = off;   off += align256((size_t)(B * H * w.max_splits * 2) * 4);
+    // room for the words of a launch that merges its pieces itself (no more where the pieces are not few)
+    if (B * H <= MERGE_ROWS_MAX) off = std::max(off, w.part_acc + align256((size_t)(B * H * MERGE_BATCH * (D / 2 + D / MERGE_COLS)) * 16));
+    w.part_bytes = off - w.part_acc;
     w.agg = w.rho_rank = off;
     if (p->rank_mode != CUSA_RANK_FIRST_OCCURRENCE) {   // per-position ranking keys and the unified ranked list
         w.agg = off;       off += align256((size_t)(B * 2 * w.ldp) * 4);
@@ -338,19 +344,32 @@ struct AttnArgs {
     float* pm;
     uint16_t* out;
     float* lse = nullptr;   // optional: log2 of the softmax denominators, [B][H]
-    int n_splits, chunk;
+    int n_splits, chunk, n_seqs;
+    uint64_t tag = 0;       // of the launch's partial sums, where it merges them itself
+    uint32_t tagged_bytes = 0;
     ScoreOut score;
 };
+
+// A tag that no other call of this or an earlier process is likely to have had: a random start, then steps by an odd constant,
+// which come back to a value after 2^64 of them.  (0 means no tag.)
+uint64_t new_tag() {
+    static std::atomic<uint64_t> state{[] {
+        std::random_device rd;
+        return ((uint64_t)rd() << 32 | rd()) ^ (uint64_t)std::chrono::steady_clock::now().time_since_epoch().count();
+    }()};
+    const uint64_t t = state.fetch_add(0x9E3779B97F4A7C15ull, std::memory_order_relaxed);
+    return t ? t : 1;
+}
 
 template <int GQ, int TI, bool SPARSE, bool SCORE, bool FILTER = false>
 void launch_attn_partial(const AttnArgs& a) {
     const int kid = SPARSE ? KID_ATTN_SPARSE : FILTER ? KID_ATTN_FILTER : SCORE ? KID_ATTN_SELECT : KID_ATTN_FULL;
     if (a.paged)
         launch(kid, attn_kernel<GQ, TI, SPARSE, true, SCORE, false, FILTER>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt, a.view.seq_lens, a.q,
-               a.budget, a.n_splits, a.chunk, a.view.G, 0xffffffffu / (uint32_t)a.n_splits, a.scale, a.pa, a.pm, a.out, a.lse, a.score.window, 0, a.score.dest(), a.view);
+               a.budget, a.n_splits, a.chunk, a.view.G, 0xffffffffu / (uint32_t)a.n_splits, a.n_seqs, a.scale, a.pa, a.pm, a.out, a.lse, a.tag, a.tagged_bytes, a.score.window, 0, a.score.dest(), a.view);
     else
         launch(kid, attn_kernel<GQ, TI, SPARSE, false, SCORE, false, FILTER>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt, a.view.seq_lens, a.q,
-               a.budget, a.n_splits, a.chunk, a.view.G, 0xffffffffu / (uint32_t)a.n_splits, a.scale, a.pa, a.pm, a.out, a.lse, a.score.window, 0, a.score.dest(), a.view);
+               a.budget, a.n_splits, a.chunk, a.view.G, 0xffffffffu / (uint32_t)a.n_splits, a.n_seqs, a.scale, a.pa, a.pm, a.out, a.lse, a.tag, a.tagged_bytes, a.score.window, 0, a.score.dest(), a.view);
 }
 
 // Sparse attention with one token list per query head: grid.y counts query heads.
@@ -358,10 +377,10 @@ template <int TI>
 void launch_attn_per_head(const AttnArgs& a, int H, int hshift) {
     if (a.paged)
         launch(KID_ATTN_PER_HEAD, attn_kernel<1, TI, true, true, false, true>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt,
-               a.view.seq_lens, a.q, a.budget, a.n_splits, a.chunk, H, 0xffffffffu / (uint32_t)a.n_splits, a.scale, a.pa, a.pm, a.out, a.lse, 0, hshift, FilterState{}, a.view);
+               a.view.seq_lens, a.q, a.budget, a.n_splits, a.chunk, H, 0xffffffffu / (uint32_t)a.n_splits, a.n_seqs, a.scale, a.pa, a.pm, a.out, a.lse, a.tag, a.tagged_bytes, 0, hshift, FilterState{}, a.view);
     else
         launch(KID_ATTN_PER_HEAD, attn_kernel<1, TI, true, false, false, true>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt,
-               a.view.seq_lens, a.q, a.budget, a.n_splits, a.chunk, H, 0xffffffffu / (uint32_t)a.n_splits, a.scale, a.pa, a.pm, a.out, a.lse, 0, hshift, FilterState{}, a.view);
+               a.view.seq_lens, a.q, a.budget, a.n_splits, a.chunk, H, 0xffffffffu / (uint32_t)a.n_splits, a.n_seqs, a.scale, a.pa, a.pm, a.out, a.lse, a.tag, a.tagged_bytes, 0, hshift, FilterState{}, a.view);
 }
 
 template <int GQ, bool SPARSE>
@@ -391,12 +410,12 @@ void launch_reduce(const ReduceArgs& r, int H, int B, hipStream_t s) {
 }
 
 // Attention over all tokens (idx == nullptr) or over idx/cnt; n_max bounds the token count.
-// With score.P set (all tokens only) the pass also writes the selection scores.
+// With score.P set (all tokens only) the pass also writes the selection scores.  in_step: see merges_itself.
 // later: the merge of the partials is left to the caller, who gets its arguments (rows 0: nothing to merge).
 template <bool SPARSE>
 cusa_status run_attention(const cusa_params* p, const void* q, const cusa_kv* kv, const int32_t* idx,
                           const int32_t* cnt, int n_max, void* out, void* ws, const WsLayout& w, hipStream_t s,
-                          ScoreOut score = ScoreOut(), float* lse = nullptr, ReduceArgs* later = nullptr) {
+                          ScoreOut score = ScoreOut(), float* lse = nullptr, ReduceArgs* later = nullptr, bool in_step = false) {
     const int g = p->n_q_heads / p->n_kv_heads, BG = p->batch * p->n_kv_heads, H = p->n_q_heads;
     const AttnPlan pl = plan_attn(n_max, BG, g, SPARSE ? ATTN_SPARSE : score.P != nullptr ? ATTN_SCORE : ATTN_FULL,
                                   kv->layout == CUSA_KV_PAGED);
@@ -417,7 +436,15 @@ cusa_status run_attention(const cusa_params* p, const void* q, const cusa_kv* kv
     a.lse = lse;
     a.n_splits = pl.n_splits;
     a.chunk = pl.chunk;
+    a.n_seqs = p->batch;
     a.score = score;
+    const int64_t words = (int64_t)p->batch * H * pl.n_splits * (D / 2 + D / MERGE_COLS);
+    if (merges_itself(pl, (int64_t)p->batch * H, in_step) && !score.P && !later && words * 16 <= (int64_t)w.part_bytes) {
+        a.tag = new_tag();
+        a.tagged_bytes = (uint32_t)(words * 16);
+        const int per_slice = pl.n_splits * p->n_kv_heads, items = p->batch * H * (D / MERGE_COLS);
+        a.grid.z += (items + per_slice - 1) / per_slice;
+    }
     switch (g) {
         case 1: launch_attn_ti<1, SPARSE>(pl.ti, a); break;
         case 2: launch_attn_ti<2, SPARSE>(pl.ti, a); break;
@@ -428,7 +455,7 @@ cusa_status run_attention(const cusa_params* p, const void* q, const cusa_kv* kv
     const ReduceArgs red = {a.pa, a.pm, a.out, SPARSE ? cnt : kv->seq_lens, SPARSE ? p->budget : 0x7fffffff, pl.n_splits,
                             pl.chunk, lse, pl.n_splits > 1 ? H * p->batch : 0};
     if (later) *later = red;
-    else if (red.rows > 0) launch_reduce(red, H, p->batch, s);
+    else if (red.rows > 0 && !a.tag) launch_reduce(red, H, p->batch, s);
     return launch_status();
 }
 
@@ -456,6 +483,7 @@ cusa_status run_attention_per_head(const cusa_params* p, const void* q, const cu
     a.lse = lse;
     a.n_splits = pl.n_splits;
     a.chunk = pl.chunk;
+    a.n_seqs = p->batch;
     const int hshift = g == 1 ? 0 : g == 2 ? 1 : g == 4 ? 2 : 3;
     if (pl.ti == 8) launch_attn_per_head<8>(a, H, hshift);
     else launch_attn_per_head<4>(a, H, hshift);
@@ -966,6 +994,7 @@ cusa_status cusa_sparse_attn_noalloc(const cusa_params* params, const void* q, c
     w.part_acc = 0;
     w.part_ml = align256(rows * D * 4);
     w.total = w.part_ml + align256(rows * 2 * 4);
+    w.part_bytes = NOALLOC_SCRATCH_BYTES;
     if (w.total > NOALLOC_SCRATCH_BYTES) return CUSA_ERR_UNSUPPORTED;   // beyond the static scratch
     if (!device_ready()) return CUSA_ERR_LAUNCH;
     int dev = 0;
@@ -1107,11 +1136,12 @@ cusa_status cusa_decode_step(const cusa_params* params, int32_t n_layers, const 
         const cusa_kv* kv = &kv_layers[i];
         if (layer_kind[i] == CUSA_LAYER_SPARSE) {
             const int n_max = params->budget < kv->max_seq_len ? params->budget : kv->max_seq_len;
-            st = run_attention<true>(params, q_layers[i], kv, idx, cnt, n_max, out_layers[i], ws, w, s);
+            st = run_attention<true>(params, q_layers[i], kv, idx, cnt, n_max, out_layers[i], ws, w, s, ScoreOut(), nullptr, nullptr, n_layers > 1);
         } else if (layer_kind[i] == CUSA_LAYER_SELECT) {
             st = run_select_layer(params, q_layers[i], kv, out_layers[i], idx, cnt, ws, w, s);
         } else {
-            st = run_attention<false>(params, q_layers[i], kv, nullptr, nullptr, kv->max_seq_len, out_layers[i], ws, w, s);
+            st = run_attention<false>(params, q_layers[i], kv, nullptr, nullptr, kv->max_seq_len, out_layers[i], ws, w, s, ScoreOut(), nullptr, nullptr,
+                                      n_layers > 1);
         }
         if (st != CUSA_OK) return st;
     }

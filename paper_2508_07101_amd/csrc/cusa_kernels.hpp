@@ -2023,6 +2023,177 @@ __device__ __forceinline__ float lane_value(float v, int lane) {
 
 __device__ __forceinline__ int wave_base_of(unsigned tid) { return (int)(tid >> 6); }
 
+// ---- merge of a pair's pieces inside the attention launch
+//
+// Where a layer's pieces are short, the second launch that merges them costs the host as much as the first (3 us each) and the GPU the
+// time between two kernels.  There the merge is done by further workgroups of the same launch, dispatched behind all pieces: a
+// piece leaves its partial sums as words of 16 bytes, two values with the two halves of the launch's tag between them, written past the
+// caches (agent scope), and a merging workgroup reads the words of its row until all carry the tag.  No flag, counter or fence is
+// needed, a word says itself whether it is there (flags behind the data cost a further way to memory and back: for
+// 256 pieces that read 8 MB, us, two launches 4.9, by flags 5.3, by tagged words 4.7).  What bounds it is that way, once there and once
+// back.  Words that have come are not asked for again (0.3 us), and the merge is run once over nothing beforehand: its
+// instructions come from memory the first time (0.3 us).  Where it is used: merges_itself, with both sides' times.
+//
+// Every wait ends: a merging workgroup waits only for pieces of its own launch, which wait for nobody and are dispatched before it, and
+// even out of order it could not keep them out (at most MERGE_ROWS_MAX * 2 waiting workgroups, two to a CU).  Should a wait
+// ever exceed MERGE_POLLS looks (some seconds), the output is made NaN.
+//
+// The tag is 64 random-looking bits that the host draws anew for every call, so whatever the workspace held before is taken for a word of this launch with
+// a probability of 2^-64 per word.  A launch captured into a graph is replayed with the same tag; therefore the words are cleared once they are read, each by
+// its only reader.  A lane's aligned 16 bytes are written and read in one access.
+constexpr int MERGE_COLS = 64;                        // columns of a merging workgroup: two per row (one or four: 0.3, 0.1 us more)
+constexpr int MERGE_POLLS = 1 << 23;
+constexpr int MERGE_LDS_FLOATS = 8 * MERGE_COLS + 16;
+constexpr int CACHE_AGENT = 16;                       // cache policy of a buffer access: agent scope (sc1)
+
+__device__ __forceinline__ auto tagged_words(float* base, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00020000);   // accesses past `bytes` are dropped
+}
+template <typename Rsrc>
+__device__ __forceinline__ void store_tagged(Rsrc words, uint32_t at, u32x4 w) {
+    __builtin_amdgcn_raw_buffer_store_b128(w, words, at, 0, CACHE_AGENT);
+}
+
+// One step of the merge: the pieces a thread asked for together join its running (maximum, sum, columns).
+template <int U, typename Cols>
+__device__ __forceinline__ void fold_pieces(const Cols (&a)[U], const float (&m)[U], const float (&l)[U], const bool (&there)[U], float& mo, float& lo, Cols& ao) {
+    float mb = mo;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (there[u]) mb = fmaxf(mb, m[u]);
+    if (mb == -INFINITY) return;                     // nothing but empty pieces so far
+    const float f0 = (mo == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(mo - mb);
+    ao *= f0;
+    lo *= f0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        // dropped by select, never by a multiplication: a slot without a piece holds whatever was there before
+        const bool live = there[u] && m[u] != -INFINITY;
+        const float f = live ? __builtin_amdgcn_exp2f(m[u] - mb) : 0.0f;
+        const Cols au = live ? a[u] : Cols(0.0f);
+        ao += au * f;
+        lo = __builtin_fmaf(live ? l[u] : 0.0f, f, lo);
+    }
+    mo = mb;
+}
+
+// The eight running merges of a row, one column: their maximum; A and Ls get the column and the sum.
+template <typename Col>
+__device__ __forceinline__ float meet_in_lds(const float* m, const float* l, Col col, float& A, float& Ls) {
+    float M = m[0];
+#pragma unroll
+    for (int j = 1; j < 8; ++j) M = fmaxf(M, m[j]);
+    A = Ls = 0.0f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const float f = (m[j] == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(m[j] - M);
+        A = __builtin_fmaf(col(j), f, A);
+        Ls = __builtin_fmaf(l[j], f, Ls);
+    }
+    return M;
+}
+
+// 256 threads: thread (c, sr) has columns 2c, 2c + 1 of the workgroup's and the pieces sr, sr + 8, ...; the eight meet in LDS.
+__device__ __forceinline__ void merge_tagged(float* base, uint32_t bytes, uint64_t tag, int item, int rows, int H, const int32_t* __restrict__ n_tok,
+                                             int n_clip, int n_splits, int chunk, uint16_t* __restrict__ out, float* __restrict__ lse, float* lds) {
+    constexpr int PARTS = D / MERGE_COLS, WORDS = MERGE_COLS / 2, U = 4;
+    const int row = item / PARTS, part = item % PARTS;
+    if (row >= rows) return;
+    const int n = min(n_tok[row / H], n_clip);
+    const int pieces = attn_active_splits(n, chunk);
+    if (pieces <= 1) return;                             // the only piece wrote the result itself
+    const int tid = threadIdx.x, c = tid % WORDS, sr = tid / WORDS;
+    const uint32_t lo = (uint32_t)tag, hi = (uint32_t)(tag >> 32);
+    const auto words = tagged_words(base, bytes);
+    const uint32_t ml0 = (uint32_t)rows * n_splits * (D / 2);
+    float(*const la)[MERGE_COLS] = reinterpret_cast<float(*)[MERGE_COLS]>(lds);
+    float* const lm = lds + 8 * MERGE_COLS;
+    // Once over nothing, while the pieces are being made, so that the instructions are in the cache when the words are there.
+#pragma nounroll
+    for (int dry = 1; dry >= 0; --dry) {
+        asm volatile("" : "+s"(dry));
+        const int todo = dry ? 1 : pieces;
+        float m = -INFINITY, l = 0.0f;
+        f32x2 a = {0.0f, 0.0f};
+        bool lost = false;
+        for (int s0 = sr; s0 - sr < todo; s0 += 8 * U) {
+            u32x4 wa[U], wm[U];
+            uint32_t at_a[U], at_m[U];
+            bool there[U], got[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int s = s0 + 8 * u;
+                there[u] = dry || s < pieces;
+                got[u] = dry || s >= pieces;
+                const uint32_t p = (uint32_t)row * n_splits + s;
+                at_a[u] = (p * (D / 2) + part * WORDS + c) * 16u;
+                at_m[u] = (ml0 + p * PARTS + part) * 16u;
+                wa[u] = wm[u] = u32x4{0u, 0u, 0u, 0u};
+            }
+            bool ready = false;
+            for (int look = 0; look < MERGE_POLLS && !ready; ++look) {
+                asm volatile("" ::: "memory");           // read again
+                u32x4 na[U], nm[U];
+                // what is there (or does not exist) is not asked for again: an address past the buffer's end is no access
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    na[u] = __builtin_amdgcn_raw_buffer_load_b128(words, got[u] ? 0xfffffff0u : at_a[u], 0, CACHE_AGENT);
+                    nm[u] = __builtin_amdgcn_raw_buffer_load_b128(words, got[u] ? 0xfffffff0u : at_m[u], 0, CACHE_AGENT);
+                }
+                bool mine = true;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (!got[u]) {
+                        wa[u] = na[u];
+                        wm[u] = nm[u];
+                        got[u] = wa[u].y == lo && wa[u].w == hi && wm[u].y == lo && wm[u].w == hi;
+                    }
+                    mine = mine && got[u];
+                }
+                ready = __all(mine);
+            }
+            lost = lost || !ready;
+            float mu[U], lu[U];
+            f32x2 au[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                au[u] = f32x2{__uint_as_float(wa[u].x), __uint_as_float(wa[u].z)};
+                mu[u] = __uint_as_float(wm[u].x);
+                lu[u] = __uint_as_float(wm[u].z);
+            }
+            fold_pieces<U>(au, mu, lu, there, m, l, a);
+            // cleared by its only reader (every column's word; the maximum's and sum's by the first of the 32 lanes, which read it together)
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (there[u] && !dry) {
+                    store_tagged(words, at_a[u], u32x4{0u, 0u, 0u, 0u});
+                    if (c == 0) store_tagged(words, at_m[u], u32x4{0u, 0u, 0u, 0u});
+                }
+        }
+        *reinterpret_cast<f32x2*>(&la[sr][2 * c]) = a;
+        if (c == 0) {
+            lm[sr] = lost ? NAN : m;
+            lm[8 + sr] = l;
+        }
+        lds_barrier();
+        if (tid < MERGE_COLS) {
+            float A, Ls;
+            const float M = meet_in_lds(lm, lm + 8, [&](int j) { return la[j][tid]; }, A, Ls);
+            bool bad = false;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) bad = bad || lm[j] != lm[j];
+            const uint16_t res = bad ? 0x7fc0 : f32_to_bf16_rne(Ls > 0.0f ? A / Ls : 0.0f);
+            if (!dry) {
+                out[(int64_t)row * D + part * MERGE_COLS + tid] = res;
+                if (lse && part == 0 && tid == 0) lse[row] = bad ? NAN : M + log2f(Ls);
+            } else {
+                asm volatile("" ::"v"((uint32_t)res));
+            }
+        }
+        lds_barrier();                                   // read, before the second time round writes
+    }
+}
+
 // SCORE (selection layer, all tokens): the scores of the candidate range [0, L - window) are also
 // written to P[b][head][t] (row stride ldp), so the layer's K is read once for both (Alg. 1 computes
 // the layer's output and P from the same K).  q.k then runs as the k = 1 MFMA chain -- the pinned
@@ -2039,9 +2210,9 @@ __device__ __forceinline__ int wave_base_of(unsigned tid) { return (int)(tid >> 
 template <int GQ, int TI, bool SPARSE, bool PAGED, bool SCORE = false, bool PER_HEAD = false, bool FILTER = false>
 __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt, const int32_t* __restrict__ seq_lens,
-    const uint16_t* __restrict__ q, int budget, int n_splits, int chunk, int G, uint32_t inv_splits, float scale_log2e,
+    const uint16_t* __restrict__ q, int budget, int n_splits, int chunk, int G, uint32_t inv_splits, int n_seqs, float scale_log2e,
     float* __restrict__ part_acc, float* __restrict__ part_ml, uint16_t* __restrict__ out, float* __restrict__ lse,
-    int window, int hshift, FilterState flt, KvView kv) {
+    uint64_t tag, uint32_t tagged_bytes, int window, int hshift, FilterState flt, KvView kv) {
     static_assert(!(SCORE && SPARSE), "scores are emitted by the pass over all tokens");
     static_assert(!FILTER || SCORE, "the filter is a form of the scoring variant");
     static_assert(!PER_HEAD || (SPARSE && GQ == 1), "per-head token lists: one query head per workgroup");
@@ -2092,6 +2263,15 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     // lengths the low splits are the busy ones; starting each (sequence, KV head) at a different
     // block spreads them evenly over the XCDs instead of loading the first ones.
     const int gy = blockIdx.y, b = blockIdx.z, H = G * GQ;
+    static_assert(sizeof(smem_raw) >= MERGE_LDS_FLOATS * 4, "the merge's sums must fit the tile buffers");
+    if constexpr (!SCORE && !PER_HEAD) {
+        if (__builtin_expect(b >= n_seqs, 0)) {          // behind all pieces: the workgroups that merge them
+            const int item = ((b - n_seqs) * G + gy) * (int)gridDim.x + (int)blockIdx.x;
+            merge_tagged(part_acc, tagged_bytes, tag, item, n_seqs * H, H, SPARSE ? cnt : seq_lens, SPARSE ? budget : 0x7fffffff, n_splits, chunk,
+                         out, lse, reinterpret_cast<float*>(smem_raw));
+            return;
+        }
+    }
     const int kvh = PER_HEAD ? gy >> hshift : gy;
     // (blockIdx.x + pair) % n_splits: inv_splits = (2^32 - 1) / n_splits rounded down, so the quotient is right or one short
     const uint32_t pair = (uint32_t)gy + (uint32_t)G * (uint32_t)b;
@@ -2602,7 +2782,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     __syncthreads();
     const float* const sums = reinterpret_cast<const float*>(smem_raw);
     // a thread has PER consecutive columns of a head (threads beyond GQ * D / PER: none)
-    constexpr int PER = GQ * D >= ATTN_THREADS ? GQ * D / ATTN_THREADS : 1;
+    constexpr int PER = GQ * D >= 2 * ATTN_THREADS ? GQ * D / ATTN_THREADS : 2;
     typedef float f32_per __attribute__((ext_vector_type(PER)));
     typedef uint16_t u16_per __attribute__((ext_vector_type(PER)));
     if (tid * PER < GQ * D) {
@@ -2637,6 +2817,15 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
                 for (int e = 0; e < PER; ++e) dst[e] = res[e];
             }
             if (lse && col == 0) lse[head0 + h] = M + log2f(Ls);
+        } else if (!SCORE && !PER_HEAD && tag) {         // for a merging workgroup of this launch
+            const auto words = tagged_words(part_acc, tagged_bytes);
+            const uint32_t p = (uint32_t)((head0 + h) * n_splits + split), lo = (uint32_t)tag, hi = (uint32_t)(tag >> 32);
+#pragma unroll
+            for (int e = 0; e < PER; e += 2)
+                store_tagged(words, (p * (D / 2) + (col + e) / 2) * 16u, u32x4{__float_as_uint(A[e]), lo, __float_as_uint(A[e + 1]), hi});
+            if (col % MERGE_COLS == 0)                   // every merging workgroup of the row has maximum and sum to itself
+                store_tagged(words, (uint32_t)((int64_t)n_seqs * H * n_splits * (D / 2) + p * (D / MERGE_COLS) + col / MERGE_COLS) * 16u,
+                             u32x4{__float_as_uint(M), lo, __float_as_uint(Ls), hi});
         } else {
             const int64_t p = (head0 + h) * n_splits + split;
             *reinterpret_cast<f32_per*>(&part_acc[p * D + col]) = A;
@@ -3098,24 +3287,15 @@ __device__ __forceinline__ void reduce_row(const ReduceArgs& r, int row, int seq
                 vml[u] = *reinterpret_cast<const f32x2*>(&r.part_ml[p * 2]);
             }
         }
-        float mb = mo;
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (s0 + 8 * u < n_splits) mb = fmaxf(mb, vml[u].x);
-        if (mb == -INFINITY) continue;               // nothing but empty splits so far
-        const float f0 = (mo == -INFINITY) ? 0.0f : exp2f(mo - mb);
-        ao *= f0;
-        lo *= f0;
+        float mu[U], lu[U];
+        bool there[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const float mu = vml[u].x;
-            const bool live = s0 + 8 * u < n_splits && mu != -INFINITY;
-            const float f = live ? exp2f(mu - mb) : 0.0f;
-            const f32x4 a = live ? va[u] : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-            ao += a * f;
-            lo = __builtin_fmaf(live ? vml[u].y : 0.0f, f, lo);
+            mu[u] = vml[u].x;
+            lu[u] = vml[u].y;
+            there[u] = s0 + 8 * u < n_splits;
         }
-        mo = mb;
+        fold_pieces<U>(va, mu, lu, there, mo, lo, ao);
     }
     *reinterpret_cast<f32x4*>(&lds.a[sr][c4 * 4]) = ao;
     if (c4 == 0) {
@@ -3124,17 +3304,8 @@ __device__ __forceinline__ void reduce_row(const ReduceArgs& r, int row, int seq
     }
     __syncthreads();
     if (merge && tid < D) {
-        float M = lds.m[0];
-#pragma unroll
-        for (int j = 1; j < 8; ++j) M = fmaxf(M, lds.m[j]);
-        float A = 0.0f, Ls = 0.0f;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const float mj = lds.m[j];
-            const float f = (mj == -INFINITY) ? 0.0f : exp2f(mj - M);
-            A = __builtin_fmaf(lds.a[j][tid], f, A);
-            Ls = __builtin_fmaf(lds.l[j], f, Ls);
-        }
+        float A, Ls;
+        const float M = meet_in_lds(lds.m, lds.l, [&](int j) { return lds.a[j][tid]; }, A, Ls);
         r.out[(int64_t)row * D + tid] = f32_to_bf16_rne(Ls > 0.0f ? A / Ls : 0.0f);
         if (r.lse && tid == 0) r.lse[row] = M + log2f(Ls);
     }

@@ -98,3 +98,83 @@ def test_few_sequences_in_pieces(g, n):
         _check(out[0], q[0], k[0], v[0], torch.arange(length, device=DEV), f"full, {length} tokens")
         cb.sparse_attn(params, q, kv, idx, torch.tensor([length], dtype=torch.int32, device=DEV), out, ws)
         _check(out[0], q[0], k[0], v[0], torch.arange(length, device=DEV), f"sparse, {length} tokens")
+
+
+def _layer(b, H, Gk, L, K, seed):
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(seed)
+    k = torch.randn((b, Gk, L, D), generator=gen, device=DEV).bfloat16()
+    v = torch.randn((b, Gk, L, D), generator=gen, device=DEV).bfloat16()
+    q = torch.randn((b, H, D), generator=gen, device=DEV).bfloat16()
+    kv = cb.KvCache(k, v, torch.full((b,), L, dtype=torch.int32, device=DEV), L)
+    idx = torch.stack([torch.randperm(L, generator=gen, device=DEV)[:K].sort().values for _ in range(b)]).to(torch.int32)
+    return q, kv, idx, torch.full((b,), K, dtype=torch.int32, device=DEV), cb.make_params(b, H, Gk, K, K // 4)
+
+
+@pytest.mark.parametrize("b,H,Gk,L,K", [(1, 32, 8, 4096, 1024), (1, 32, 8, 4096, 2048), (1, 8, 8, 3000, 300), (2, 8, 1, 900, 700), (4, 16, 2, 2100, 512)])
+def test_pieces_merged_in_the_launch_whatever_the_workspace_held(b, H, Gk, L, K):
+    """The same bits from a workspace of random words, of ones, of an earlier call's words or a selection's, in a decode step (which
+    may merge with a second launch), without a workspace, and in a graph replayed beside other work."""
+    q, kv, idx, cnt, params = _layer(b, H, Gk, L, K, 5)
+    ws = cb.alloc_workspace(params, L, DEV)
+    want = torch.empty_like(q)
+    # an order of its own for the first bits: two launches
+    kinds = [cb.LAYER_SELECT, cb.LAYER_SPARSE, cb.LAYER_FULL]
+    outs = [torch.empty_like(q) for _ in kinds]
+    rho, n_rho = torch.zeros_like(idx), torch.zeros_like(cnt)
+    step = cb.DecodeStep(params, kinds, [q] * 3, [kv] * 3, outs, rho, n_rho, ws)
+    step.run()
+    full = torch.empty_like(q)
+    for fill in ("random", "ones", "earlier", "earlier", "selection"):
+        if fill == "random":
+            ws.random_(0, 256)
+        elif fill == "ones":
+            ws.fill_(255)
+        elif fill == "selection":
+            cb.select(params, q, kv, rho, n_rho, ws)
+        got = torch.zeros_like(q)
+        cb.sparse_attn(params, q, kv, rho, n_rho, got, ws)
+        assert torch.equal(got, outs[1]), f"sparse, workspace: {fill}"
+        cb.full_attn(params, q, kv, full, ws)
+        assert torch.equal(full, outs[2]), f"full, workspace: {fill}"
+    cb.sparse_attn_noalloc(params, q, kv, rho, n_rho, want)
+    assert torch.equal(want, outs[1])
+    q2, got = q.clone(), torch.zeros_like(q)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        cb.sparse_attn(params, q2, kv, idx, cnt, got, ws)
+        cb.full_attn(params, q2, kv, full, ws)
+    for rep in range(5):
+        q2.copy_(torch.randn(q.shape, device=DEV).bfloat16())
+        g.replay()
+        torch.cuda.synchronize()
+        now = (got.clone(), full.clone())
+        if rep == 2:
+            ws.random_(0, 256)
+        cb.full_attn(params, q2, kv, full, ws)
+        assert torch.equal(now[1], full), f"replay {rep}, full"
+        cb.sparse_attn(params, q2, kv, idx, cnt, want, ws)
+        assert torch.equal(now[0], want), f"replay {rep}, sparse"
+
+
+def test_pieces_merged_in_launches_of_two_streams():
+    """Each stream has a workspace of its own; the launches overlap as they like."""
+    layers = [_layer(1, 32, 8, 4096, 1024, seed) for seed in (1, 2)]
+    want = []
+    for q, kv, idx, cnt, params in layers:
+        out = torch.empty_like(q)
+        cb.sparse_attn(params, q, kv, idx, cnt, out, cb.alloc_workspace(params, 4096, DEV))
+        want.append(out)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in layers]
+    wss = [cb.alloc_workspace(lay[4], 4096, DEV) for lay in layers]
+    outs = [[torch.empty_like(lay[0]) for _ in range(50)] for lay in layers]
+    torch.cuda.synchronize()
+    for i in range(50):
+        for s, lay, ws, out in zip(streams, layers, wss, outs):
+            with torch.cuda.stream(s):
+                cb.sparse_attn(lay[4], *lay[:4], out[i], ws)
+    torch.cuda.synchronize()
+    for w, out in zip(want, outs):
+        assert all(torch.equal(o, w) for o in out)
