@@ -1956,9 +1956,9 @@ __global__ __launch_bounds__(SEL_THREADS) void per_head_rho_kernel(const int32_t
 // LDS to the lanes that hold that token's V row, and P.V accumulates 8 columns per lane.
 // The four waves are merged through LDS into one partial (m, l, acc[128]) per
 // head.  With one split that is the result and is written as bf16; otherwise the
-// partial goes to the workspace and attn_reduce_kernel merges the splits.  (A merge
-// inside this kernel by the last workgroup to arrive was measured and is slower: its
-// device-coherent reads of the other workgroups' partials run at a few GB/s.)
+// partial goes to the workspace and attn_reduce_kernel merges the splits, or, where runs are short,
+// further workgroups of the launch (merge_tagged).  (A merge by the last workgroup to arrive was measured and is slower:
+// the fence, the ticket and then its reads of the other workgroups' partials come one after the other.)
 
 template <int CTRL>
 __device__ __forceinline__ float dpp_move(float v) {
