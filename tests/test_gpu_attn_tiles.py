@@ -100,6 +100,32 @@ def test_few_sequences_in_pieces(g, n):
         _check(out[0], q[0], k[0], v[0], torch.arange(length, device=DEV), f"sparse, {length} tokens")
 
 
+@pytest.mark.parametrize("g", [1, 4, 8])
+@pytest.mark.parametrize("n,b", [(40, 64), (600, 64), (9000, 24)])     # a tile, several waves, several pieces
+@pytest.mark.parametrize("below", [126, 127, 130, 132])
+def test_weights_far_below_the_largest_count_beside_large_values(g, n, b, below):
+    """The first token's weight is 2^-below of the last one's (the others': nothing) and its values are 2^120, the only ones that are not
+    zero: it makes the whole output, also where the weight is subnormal in binary32 and bf16.  Exact powers of two but for the rounding of
+    scores (2^-23 of `below`, times ln 2), weight and output (2^-9 each)."""
+    H = G * g
+    k, v = (torch.zeros((b, G, n, D), dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    k[:, :, 0, 0], k[:, :, 1:-1, 0], v[:, :, 0] = -below, -400.0, 2.0 ** 120
+    q = torch.zeros((b, H, D), dtype=torch.bfloat16, device=DEV)
+    q[..., 0] = 1.0
+    kv = cb.KvCache(k, v, torch.full((b,), n, dtype=torch.int32, device=DEV), n)
+    params = cb.make_params(b, H, G, n, n // 4, sm_scale=math.log(2.0))
+    ws, out = cb.alloc_workspace(params, n, DEV), torch.empty_like(q)
+    idx = torch.arange(n, dtype=torch.int32, device=DEV).repeat(b, 1)
+    for what in ("full", "sparse"):
+        if what == "full":
+            cb.full_attn(params, q, kv, out, ws)
+        elif n <= 8192:
+            cb.sparse_attn(params, q, kv, idx, kv.seq_lens, out, ws)
+        want = 2.0 ** (120 - below)
+        err = ((out.double() - want).abs() / want).max().item()
+        assert err <= 2.0 ** -7, f"{what}: {out.flatten()[0].item()}, not {want}"
+
+
 def _layer(b, H, Gk, L, K, seed):
     gen = torch.Generator(device=DEV)
     gen.manual_seed(seed)
