@@ -143,8 +143,11 @@ inline int in_turn(int n, int BG, int limit) {
 // 2048 rows, 8.4 / 9.7 and 9.2 / 9.3.  Runs of 512 tokens: 8 sequences, lists of 4096, 26.2 and 27.1, the waiting costs more than a launch.)
 constexpr int MERGE_ROWS_MAX = 256;
 constexpr int MERGE_RUN = 128;
+constexpr int MERGE_PIECES_MAX = 1024;   // rows of partial sums
+constexpr int MERGE_PIECES_STEP = 512;
 inline bool merges_itself(const AttnPlan& pl, int64_t rows, bool in_step) {
-    return pl.n_splits > 1 && pl.chunk <= MERGE_RUN && rows <= MERGE_ROWS_MAX && rows * pl.n_splits <= (in_step ? 512 : 1024);
+    return pl.ti == 4 && pl.n_splits > 1 && pl.chunk <= MERGE_RUN && rows <= MERGE_ROWS_MAX &&
+           rows * pl.n_splits <= (in_step ? MERGE_PIECES_STEP : MERGE_PIECES_MAX);
 }
 
 // The scoring pass (score_kernel): a workgroup for every workgroup tile, of 256 tokens (128 where these would be too few to keep every

@@ -2264,7 +2264,8 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     // block spreads them evenly over the XCDs instead of loading the first ones.
     const int gy = blockIdx.y, b = blockIdx.z, H = G * GQ;
     static_assert(sizeof(smem_raw) >= MERGE_LDS_FLOATS * 4, "the merge's sums must fit the tile buffers");
-    if constexpr (!SCORE && !PER_HEAD) {
+    constexpr bool MERGES = !SCORE && !PER_HEAD && TI == 4;   // forms whose launch may merge its pieces itself: merges_itself asks for short runs
+    if constexpr (MERGES) {
         if (__builtin_expect(b >= n_seqs, 0)) {          // behind all pieces: the workgroups that merge them
             const int item = ((b - n_seqs) * G + gy) * (int)gridDim.x + (int)blockIdx.x;
             merge_tagged(part_acc, tagged_bytes, tag, item, n_seqs * H, H, SPARSE ? cnt : seq_lens, SPARSE ? budget : 0x7fffffff, n_splits, chunk,
@@ -2819,7 +2820,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
                 for (int e = 0; e < PER; ++e) dst[e] = res[e];
             }
             if (lse && col == 0) lse[head0 + h] = M + log2f(Ls);
-        } else if (!SCORE && !PER_HEAD && tag) {         // for a merging workgroup of this launch
+        } else if (MERGES && tag) {         // for a merging workgroup of this launch
             const auto words = tagged_words(part_acc, tagged_bytes);
             const uint32_t p = (uint32_t)((head0 + h) * n_splits + split), lo = (uint32_t)tag, hi = (uint32_t)(tag >> 32);
 #pragma unroll
