@@ -128,7 +128,9 @@ typedef struct {
 
 /* Bytes of device workspace any of the calls below needs for `params` and
  * sequences up to max_seq_len.  Workspace must be 256-byte aligned; its content
- * need not be preserved between calls.  Error: INVALID_ARG. */
+ * need not be preserved between calls.  (The last 1.1 MB at most are room that
+ * saves short attention passes a launch; a workspace without it is taken, with
+ * the same results.)  Error: INVALID_ARG. */
 cusa_status cusa_workspace_bytes(const cusa_params* params, int32_t max_seq_len, size_t* bytes);
 cusa_status cusa_workspace_layout(const cusa_params* params, int32_t max_seq_len, cusa_ws_layout* layout);
 

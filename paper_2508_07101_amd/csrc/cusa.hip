@@ -228,7 +228,9 @@ bool filtered_select(const cusa_params* p, int max_seq_len) {
 struct WsLayout {
     size_t scores, rho_head, part_acc, part_ml, agg, rho_rank, lse, out_tmp, topk_parts, slice_cnt, slice_lo, total;
     size_t f_thr, f_cnt, f_fail, f_nfailed, f_cand;           // the selection's filtered fast path
-    size_t part_bytes;                                        // of part_acc and part_ml, which follow each other
+    // The end of what a workspace has to hold (a call with less is refused), and behind it room for the words of a launch that merges its pieces
+    // itself, of which the caller's workspace has words_bytes: where they do not fit, a second launch merges.
+    size_t need, words, words_bytes;
     int filter_cap;                                           // 0: not laid out
     int64_t ldp;
     int k;
@@ -250,9 +252,6 @@ WsLayout make_layout(const cusa_params* p, int max_seq_len) {
     w.rho_head = off;  off += align256((size_t)(B * w.k * H) * 4);
     w.part_acc = off;  off += align256((size_t)(B * H * w.max_splits * D) * 4);
     w.part_ml = off;   off += align256((size_t)(B * H * w.max_splits * 2) * 4);
-    // room for the words of a launch that merges its pieces itself (no more where the pieces are not few)
-    if (B * H <= MERGE_ROWS_MAX) off = std::max(off, w.part_acc + align256((size_t)(B * H * MERGE_BATCH * (D / 2 + D / MERGE_COLS)) * 16));
-    w.part_bytes = off - w.part_acc;
     w.agg = w.rho_rank = off;
     if (p->rank_mode != CUSA_RANK_FIRST_OCCURRENCE) {   // per-position ranking keys and the unified ranked list
         w.agg = off;       off += align256((size_t)(B * 2 * w.ldp) * 4);
@@ -287,15 +286,20 @@ WsLayout make_layout(const cusa_params* p, int max_seq_len) {
     }
     w.lse = off;      off += align256((size_t)(B * H * 2) * 4);        // recall: denominators over the set and over all tokens
     w.out_tmp = off;  off += align256((size_t)(B * H * D) * 2);        // recall: the attention outputs nobody reads
+    w.need = w.words = off;
+    // (more rows than the launch may have get as much: a workspace sized for them serves fewer as well)
+    off += align256((size_t)std::min<int64_t>(B * H * MERGE_BATCH, MERGE_PIECES_MAX) * MERGE_PIECE_BYTES);
+    w.words_bytes = off - w.words;
     w.total = off;
     return w;
 }
 
 bool device_ready();
 
-cusa_status check_ws(const WsLayout& w, void* ws, size_t ws_bytes) {
+cusa_status check_ws(WsLayout& w, void* ws, size_t ws_bytes) {
     if (!ws || ((uintptr_t)ws & 255)) return CUSA_ERR_INVALID_ARG;
-    if (ws_bytes < w.total) return CUSA_ERR_WORKSPACE_TOO_SMALL;
+    if (ws_bytes < w.need) return CUSA_ERR_WORKSPACE_TOO_SMALL;
+    w.words_bytes = std::min(ws_bytes, w.total) - w.words;
     return device_ready() ? CUSA_OK : CUSA_ERR_LAUNCH;
 }
 
@@ -438,10 +442,11 @@ cusa_status run_attention(const cusa_params* p, const void* q, const cusa_kv* kv
     a.chunk = pl.chunk;
     a.n_seqs = p->batch;
     a.score = score;
-    const int64_t words = (int64_t)p->batch * H * pl.n_splits * (D / 2 + D / MERGE_COLS);
-    if (merges_itself(pl, (int64_t)p->batch * H, in_step) && !score.P && !later && words * 16 <= (int64_t)w.part_bytes) {
+    const int64_t words_bytes = (int64_t)p->batch * H * pl.n_splits * MERGE_PIECE_BYTES;
+    if (merges_itself(pl, (int64_t)p->batch * H, in_step) && !score.P && !later && words_bytes <= (int64_t)w.words_bytes) {
         a.tag = new_tag();
-        a.tagged_bytes = (uint32_t)(words * 16);
+        a.pa = ws_ptr<float>(ws, w.words);
+        a.tagged_bytes = (uint32_t)words_bytes;
         const int per_slice = pl.n_splits * p->n_kv_heads, items = p->batch * H * (D / MERGE_COLS);
         a.grid.z += (items + per_slice - 1) / per_slice;
     }
@@ -960,7 +965,7 @@ cusa_status cusa_select(const cusa_params* params, const void* q, const cusa_kv*
     if ((st = check_kv(params, kv)) != CUSA_OK) return st;
     if (!q || !idx || !cnt || ((uintptr_t)q & 15)) return CUSA_ERR_INVALID_ARG;
     if ((st = check_select_length(params, kv)) != CUSA_OK) return st;
-    const WsLayout w = make_layout(params, kv->max_seq_len);
+    WsLayout w = make_layout(params, kv->max_seq_len);
     if ((st = check_ws(w, ws, ws_bytes)) != CUSA_OK) return st;
     return run_select(params, q, kv, idx, cnt, ws, w, static_cast<hipStream_t>(stream));
 }
@@ -971,7 +976,7 @@ cusa_status cusa_sparse_attn(const cusa_params* params, const void* q, const cus
     if (st != CUSA_OK) return st;
     if ((st = check_kv(params, kv)) != CUSA_OK) return st;
     if (!q || !idx || !cnt || !out || ((uintptr_t)q & 15)) return CUSA_ERR_INVALID_ARG;
-    const WsLayout w = make_layout(params, kv->max_seq_len);
+    WsLayout w = make_layout(params, kv->max_seq_len);
     if ((st = check_ws(w, ws, ws_bytes)) != CUSA_OK) return st;
     const int n_max = params->budget < kv->max_seq_len ? params->budget : kv->max_seq_len;
     return run_attention<true>(params, q, kv, idx, cnt, n_max, out, ws, w, static_cast<hipStream_t>(stream));
@@ -994,8 +999,9 @@ cusa_status cusa_sparse_attn_noalloc(const cusa_params* params, const void* q, c
     w.part_acc = 0;
     w.part_ml = align256(rows * D * 4);
     w.total = w.part_ml + align256(rows * 2 * 4);
-    w.part_bytes = NOALLOC_SCRATCH_BYTES;
     if (w.total > NOALLOC_SCRATCH_BYTES) return CUSA_ERR_UNSUPPORTED;   // beyond the static scratch
+    w.words = w.total;
+    w.words_bytes = NOALLOC_SCRATCH_BYTES - w.words;
     if (!device_ready()) return CUSA_ERR_LAUNCH;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES || !g_scratch_ptr[dev]) return CUSA_ERR_LAUNCH;
@@ -1039,7 +1045,7 @@ cusa_status cusa_select_per_head(const cusa_params* params, const void* q, const
     if ((st = check_kv(params, kv)) != CUSA_OK) return st;
     if (!q || !idx_head || !cnt || ((uintptr_t)q & 15)) return CUSA_ERR_INVALID_ARG;
     if ((st = check_select_length(params, kv)) != CUSA_OK) return st;
-    const WsLayout w = make_layout(params, kv->max_seq_len);
+    WsLayout w = make_layout(params, kv->max_seq_len);
     if ((st = check_ws(w, ws, ws_bytes)) != CUSA_OK) return st;
     return run_select(params, q, kv, idx_head, cnt, ws, w, static_cast<hipStream_t>(stream), false, true);
 }
@@ -1051,7 +1057,7 @@ cusa_status cusa_sparse_attn_per_head(const cusa_params* params, const void* q, 
     if (st != CUSA_OK) return st;
     if ((st = check_kv(params, kv)) != CUSA_OK) return st;
     if (!q || !idx_head || !cnt || !out || ((uintptr_t)q & 15)) return CUSA_ERR_INVALID_ARG;
-    const WsLayout w = make_layout(params, kv->max_seq_len);
+    WsLayout w = make_layout(params, kv->max_seq_len);
     if ((st = check_ws(w, ws, ws_bytes)) != CUSA_OK) return st;
     return run_attention_per_head(params, q, kv, idx_head, cnt, out, ws, w, static_cast<hipStream_t>(stream));
 }
@@ -1063,7 +1069,7 @@ cusa_status cusa_attention_recall(const cusa_params* params, const void* q, cons
     if (st != CUSA_OK) return st;
     if ((st = check_kv(params, kv)) != CUSA_OK) return st;
     if (!q || !idx || !cnt || !recall || ((uintptr_t)q & 15)) return CUSA_ERR_INVALID_ARG;
-    const WsLayout w = make_layout(params, kv->max_seq_len);
+    WsLayout w = make_layout(params, kv->max_seq_len);
     if ((st = check_ws(w, ws, ws_bytes)) != CUSA_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int n = params->batch * params->n_q_heads;
@@ -1086,7 +1092,7 @@ cusa_status cusa_full_attn(const cusa_params* params, const void* q, const cusa_
     if (st != CUSA_OK) return st;
     if ((st = check_kv(params, kv)) != CUSA_OK) return st;
     if (!q || !out || ((uintptr_t)q & 15)) return CUSA_ERR_INVALID_ARG;
-    const WsLayout w = make_layout(params, kv->max_seq_len);
+    WsLayout w = make_layout(params, kv->max_seq_len);
     if ((st = check_ws(w, ws, ws_bytes)) != CUSA_OK) return st;
     return run_attention<false>(params, q, kv, nullptr, nullptr, kv->max_seq_len, out, ws, w,
                                 static_cast<hipStream_t>(stream));
@@ -1099,7 +1105,7 @@ cusa_status cusa_select_layer(const cusa_params* params, const void* q, const cu
     if ((st = check_kv(params, kv)) != CUSA_OK) return st;
     if (!q || !out || !idx || !cnt || ((uintptr_t)q & 15)) return CUSA_ERR_INVALID_ARG;
     if ((st = check_select_length(params, kv)) != CUSA_OK) return st;
-    const WsLayout w = make_layout(params, kv->max_seq_len);
+    WsLayout w = make_layout(params, kv->max_seq_len);
     if ((st = check_ws(w, ws, ws_bytes)) != CUSA_OK) return st;
     return run_select_layer(params, q, kv, out, idx, cnt, ws, w, static_cast<hipStream_t>(stream));
 }
@@ -1129,7 +1135,7 @@ cusa_status cusa_decode_step(const cusa_params* params, int32_t n_layers, const 
             default: return CUSA_ERR_INVALID_ARG;
         }
     }
-    const WsLayout w = make_layout(params, max_len);
+    WsLayout w = make_layout(params, max_len);
     if ((st = check_ws(w, ws, ws_bytes)) != CUSA_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
     for (int i = 0; i < n_layers; ++i) {

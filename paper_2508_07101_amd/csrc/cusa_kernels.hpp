@@ -2042,6 +2042,7 @@ __device__ __forceinline__ int wave_base_of(unsigned tid) { return (int)(tid >> 
 // a probability of 2^-64 per word.  A launch captured into a graph is replayed with the same tag; therefore the words are cleared once they are read, each by
 // its only reader.  A lane's aligned 16 bytes are written and read in one access.
 constexpr int MERGE_COLS = 64;                        // columns of a merging workgroup: two per row (one or four: 0.3, 0.1 us more)
+constexpr int MERGE_PIECE_BYTES = (D / 2 + D / MERGE_COLS) * 16;   // words of a row's piece
 constexpr int MERGE_POLLS = 1 << 23;
 constexpr int MERGE_LDS_FLOATS = 8 * MERGE_COLS + 16;
 constexpr int CACHE_AGENT = 16;                       // cache policy of a buffer access: agent scope (sc1)

@@ -41,6 +41,24 @@ def test_workspace_bytes_grows_with_the_problem():
     assert lay.scores_offset % 256 == 0 and lay.rho_head_offset % 256 == 0
 
 
+# (batch, query heads, KV heads, budget, window, longest sequence) and the bytes that the selection and the partial sums of its layers need
+WORKSPACES = [((1, 32, 8, 1024, 256, 4096), 1696000), ((8, 32, 8, 2048, 512, 4096), 6899712), ((8, 32, 8, 2048, 512, 32768), 39454720),
+              ((9, 32, 8, 2048, 512, 4096), 7762176), ((2, 16, 16, 512, 128, 3000), 708864), ((4, 64, 8, 256, 64, 300), 2721792),
+              ((64, 32, 8, 2048, 512, 32768), 382771456)]
+
+
+@pytest.mark.parametrize("size,need", WORKSPACES)
+def test_the_room_for_pieces_merged_in_the_launch_is_what_such_a_launch_may_use(size, need):
+    """At most 1024 rows of 66 words of 16 bytes, behind everything else and the same for batches that are too large for it: a
+    workspace for the larger batch serves the smaller one, on both sides of the number of rows that the launch merges."""
+    b, H, G, K, W, L = size
+    room = cb.workspace_bytes(cb.make_params(b, H, G, K, W), L) - need
+    assert 0 <= room <= 1024 * 66 * 16 and room % 256 == 0
+    batches = range(1, 13)
+    sizes = [cb.workspace_bytes(cb.make_params(n, 32, 8, 2048, 512), 4096) for n in batches]
+    assert sizes == sorted(sizes)
+
+
 @pytest.mark.parametrize("kw,status", [
     (dict(n_q_heads=30), cb.ERR_INVALID_ARG),              # H % G != 0
     (dict(head_dim=64), cb.ERR_UNSUPPORTED),

@@ -184,6 +184,24 @@ def test_pieces_merged_in_the_launch_whatever_the_workspace_held(b, H, Gk, L, K)
         assert torch.equal(now[0], want), f"replay {rep}, sparse"
 
 
+@pytest.mark.parametrize("b,H,Gk,L,K,W,need", [(1, 32, 8, 4096, 1024, 256, 1696000), (2, 16, 16, 3000, 512, 128, 708864)])
+def test_a_workspace_without_room_for_the_words_is_taken(b, H, Gk, L, K, W, need):
+    """What a launch that merges its pieces itself wants on top is no condition: with the bytes of the partial sums alone a second launch merges,
+    to the same bits; with less the call is refused, as ever."""
+    q, kv, idx, cnt, _ = _layer(b, H, Gk, L, K, 9)
+    params = cb.make_params(b, H, Gk, K, W)
+    ws = cb.alloc_workspace(params, L, DEV)
+    assert ws.numel() > need
+    outs = []
+    for room in (ws, ws[:need], ws[:need + 256], ws[:ws.numel() - 256]):
+        outs.append(torch.zeros_like(q))
+        cb.sparse_attn(params, q, kv, idx, cnt, outs[-1], room)
+    assert all(torch.equal(o, outs[0]) for o in outs)
+    with pytest.raises(cb.CusaError) as err:
+        cb.sparse_attn(params, q, kv, idx, cnt, outs[0], ws[:need - 1])
+    assert err.value.status == cb.ERR_WORKSPACE_TOO_SMALL
+
+
 def test_pieces_merged_in_launches_of_two_streams():
     """Each stream has a workspace of its own; the launches overlap as they like."""
     layers = [_layer(1, 32, 8, 4096, 1024, seed) for seed in (1, 2)]
