@@ -137,7 +137,8 @@ inline int in_turn(int n, int BG, int limit) {
 
 // Whether an attention launch merges its pieces itself (merge_tagged) instead of leaving them to a second launch: where the host, 3 us a launch,
 // takes longer than the GPU, that is where runs are short, and where the partial sums, written past the caches in twice the bytes, are few.
-// rows: batch * query heads; in_step: one layer of several that are enqueued together, so that the GPU is behind the host.
+// rows: batch * query heads; in_step: one layer of several that are enqueued together, so that the GPU is behind the host.  (Launches captured into a
+// graph, whose replay keeps no host waiting, always leave the merge to a second one: see merge_tagged.)
 // (Layer of one sequence, us, GPU alone / calls one after the other from Python, two launches and so: 32 heads, list of 1024, 512 rows of partial
 // sums, 6.3 / 9.8 and 6.0 / 6.9; of 2048, 1024 rows, 6.87 / 9.8 and 7.04 / 7.15; all of 4096 tokens, 1024, 7.9 / 9.9 and 8.0 / 8.2; 64 heads, 4096,
 // 2048 rows, 8.4 / 9.7 and 9.2 / 9.3.  Runs of 512 tokens: 8 sequences, lists of 4096, 26.2 and 27.1, the waiting costs more than a launch.)
@@ -148,6 +149,13 @@ constexpr int MERGE_PIECES_STEP = 512;
 inline bool merges_itself(const AttnPlan& pl, int64_t rows, bool in_step) {
     return pl.ti == 4 && pl.n_splits > 1 && pl.chunk <= MERGE_RUN && rows <= MERGE_ROWS_MAX &&
            rows * pl.n_splits <= (in_step ? MERGE_PIECES_STEP : MERGE_PIECES_MAX);
+}
+
+// The pieces that a row's merge in the launch waits for: those that have tokens, and never more than the launch has (a length beyond the
+// bound that the plan was made for must not make it wait for, or take, another row's).
+constexpr int merged_pieces(int n, int chunk, int n_splits) {
+    const int a = (n + chunk - 1) / chunk;
+    return a < 1 ? 1 : a < n_splits ? a : n_splits;
 }
 
 // The scoring pass (score_kernel): a workgroup for every workgroup tile, of 256 tokens (128 where these would be too few to keep every

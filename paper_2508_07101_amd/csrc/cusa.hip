@@ -365,6 +365,14 @@ uint64_t new_tag() {
     return t ? t : 1;
 }
 
+// Whether what is enqueued on the stream now is recorded into a graph (or may be: the query itself is refused where it would break a capture).
+bool being_captured(hipStream_t s) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 template <int GQ, int TI, bool SPARSE, bool SCORE, bool FILTER = false>
 void launch_attn_partial(const AttnArgs& a) {
     const int kid = SPARSE ? KID_ATTN_SPARSE : FILTER ? KID_ATTN_FILTER : SCORE ? KID_ATTN_SELECT : KID_ATTN_FULL;
@@ -443,7 +451,7 @@ cusa_status run_attention(const cusa_params* p, const void* q, const cusa_kv* kv
     a.n_seqs = p->batch;
     a.score = score;
     const int64_t words_bytes = (int64_t)p->batch * H * pl.n_splits * MERGE_PIECE_BYTES;
-    if (merges_itself(pl, (int64_t)p->batch * H, in_step) && !score.P && !later && words_bytes <= (int64_t)w.words_bytes) {
+    if (merges_itself(pl, (int64_t)p->batch * H, in_step) && !score.P && !later && words_bytes <= (int64_t)w.words_bytes && !being_captured(s)) {
         a.tag = new_tag();
         a.pa = ws_ptr<float>(ws, w.words);
         a.tagged_bytes = (uint32_t)words_bytes;

@@ -2039,15 +2039,17 @@ __device__ __forceinline__ int wave_base_of(unsigned tid) { return (int)(tid >> 
 // ever exceed MERGE_POLLS looks (some seconds), the output is made NaN.
 //
 // The tag is 64 random-looking bits that the host draws anew for every call, so whatever the workspace held before is taken for a word of this launch with
-// a probability of 2^-64 per word.  A launch captured into a graph is replayed with the same tag; therefore the words are cleared once they are read, each by
-// its only reader.  A lane's aligned 16 bytes are written and read in one access.
+// a probability of 2^-64 per word.  A launch captured into a graph would be replayed with the same tag, over words that the replay before left: captured launches
+// leave the merge to a second one.  A merging workgroup writes nothing but its own columns of the output.  A lane's aligned 16 bytes are written and read in
+// one access.
 constexpr int MERGE_COLS = 64;                        // columns of a merging workgroup: two per row (one or four: 0.3, 0.1 us more)
-constexpr int MERGE_PIECE_BYTES = (D / 2 + D / MERGE_COLS) * 16;   // words of a row's piece
+constexpr int MERGE_PIECE_BYTES = (D / 2 + 1) * 16;   // words of a row's piece: its columns, its maximum and sum
 constexpr int MERGE_POLLS = 1 << 23;
 constexpr int MERGE_LDS_FLOATS = 8 * MERGE_COLS + 16;
 constexpr int CACHE_AGENT = 16;                       // cache policy of a buffer access: agent scope (sc1)
 
 __device__ __forceinline__ auto tagged_words(float* base, uint32_t bytes) {
+    asm volatile("" : "+s"(base));                       // other workgroups write there too: no longer the __restrict__ argument
     return __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00020000);   // accesses past `bytes` are dropped
 }
 template <typename Rsrc>
@@ -2101,7 +2103,7 @@ __device__ __forceinline__ void merge_tagged(float* base, uint32_t bytes, uint64
     const int row = item / PARTS, part = item % PARTS;
     if (row >= rows) return;
     const int n = min(n_tok[row / H], n_clip);
-    const int pieces = attn_active_splits(n, chunk);
+    const int pieces = merged_pieces(n, chunk, n_splits);
     if (pieces <= 1) return;                             // the only piece wrote the result itself
     const int tid = threadIdx.x, c = tid % WORDS, sr = tid / WORDS;
     const uint32_t lo = (uint32_t)tag, hi = (uint32_t)(tag >> 32);
@@ -2128,7 +2130,7 @@ __device__ __forceinline__ void merge_tagged(float* base, uint32_t bytes, uint64
                 got[u] = dry || s >= pieces;
                 const uint32_t p = (uint32_t)row * n_splits + s;
                 at_a[u] = (p * (D / 2) + part * WORDS + c) * 16u;
-                at_m[u] = (ml0 + p * PARTS + part) * 16u;
+                at_m[u] = (ml0 + p) * 16u;
                 wa[u] = wm[u] = u32x4{0u, 0u, 0u, 0u};
             }
             bool ready = false;
@@ -2163,13 +2165,6 @@ __device__ __forceinline__ void merge_tagged(float* base, uint32_t bytes, uint64
                 lu[u] = __uint_as_float(wm[u].z);
             }
             fold_pieces<U>(au, mu, lu, there, m, l, a);
-            // cleared by its only reader (every column's word; the maximum's and sum's by the first of the 32 lanes, which read it together)
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (there[u] && !dry) {
-                    store_tagged(words, at_a[u], u32x4{0u, 0u, 0u, 0u});
-                    if (c == 0) store_tagged(words, at_m[u], u32x4{0u, 0u, 0u, 0u});
-                }
         }
         *reinterpret_cast<f32x2*>(&la[sr][2 * c]) = a;
         if (c == 0) {
@@ -2827,9 +2822,8 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
 #pragma unroll
             for (int e = 0; e < PER; e += 2)
                 store_tagged(words, (p * (D / 2) + (col + e) / 2) * 16u, u32x4{__float_as_uint(A[e]), lo, __float_as_uint(A[e + 1]), hi});
-            if (col % MERGE_COLS == 0)                   // every merging workgroup of the row has maximum and sum to itself
-                store_tagged(words, (uint32_t)((int64_t)n_seqs * H * n_splits * (D / 2) + p * (D / MERGE_COLS) + col / MERGE_COLS) * 16u,
-                             u32x4{__float_as_uint(M), lo, __float_as_uint(Ls), hi});
+            if (col == 0)
+                store_tagged(words, ((uint32_t)(n_seqs * H) * n_splits * (D / 2) + p) * 16u, u32x4{__float_as_uint(M), lo, __float_as_uint(Ls), hi});
         } else {
             const int64_t p = (head0 + h) * n_splits + split;
             *reinterpret_cast<f32_per*>(&part_acc[p * D + col]) = A;

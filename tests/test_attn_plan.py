@@ -232,3 +232,18 @@ def test_launches_that_merge_their_pieces_themselves_have_few_short_ones(tmp_pat
     if (taken < 1000) FAIL("only %ld taken", taken);
 ''')
     assert out == "", out
+
+
+def test_a_row_waits_for_no_more_pieces_than_the_launch_has(tmp_path):
+    """Pieces with tokens, at least one; a length beyond the plan's bound (a caller's slip) stays within the row's own pieces."""
+    out = run_checks(tmp_path, r'''
+    (void)plan;
+    for (int chunk : {64, 128})
+        for (int n_splits : {2, 5, 32})
+            for (int n = 0; n <= 3 * chunk * n_splits; ++n) {
+                int with_tokens = 0;
+                for (int s = 0; s < n_splits; ++s) with_tokens += s * chunk < n;
+                if (merged_pieces(n, chunk, n_splits) != std::max(1, with_tokens)) FAIL("%d tokens in %d pieces of %d: %d", n, n_splits, chunk, merged_pieces(n, chunk, n_splits));
+            }
+''')
+    assert out == "", out

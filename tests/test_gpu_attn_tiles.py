@@ -184,6 +184,52 @@ def test_pieces_merged_in_the_launch_whatever_the_workspace_held(b, H, Gk, L, K)
         assert torch.equal(now[0], want), f"replay {rep}, sparse"
 
 
+@pytest.mark.parametrize("g", [1, 4, 8])
+def test_a_graph_replayed_with_other_lengths_and_counts(g):
+    """What a replay finds in the workspace is the replay before's: lists and sequences that grow, shrink and become empty between replays,
+    each against an eager call of the moment."""
+    b, Gk, L, K = 2, 4, 1000, 400
+    q, kv, idx, cnt, params = _layer(b, Gk * g, Gk, L, K, 21)
+    ws, ws2 = cb.alloc_workspace(params, L, DEV), cb.alloc_workspace(params, L, DEV)
+    out, full = torch.zeros_like(q), torch.zeros_like(q)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        cb.sparse_attn(params, q, kv, idx, cnt, out, ws)
+        cb.full_attn(params, q, kv, full, ws)
+    for lens, counts in (((1000, 1000), (400, 400)), ((70, 999), (65, 400)), ((1000, 64), (400, 1)), ((513, 1000), (0, 400)), ((1000, 1000), (400, 129))):
+        kv.seq_lens.copy_(torch.tensor(lens, dtype=torch.int32))
+        cnt.copy_(torch.tensor(counts, dtype=torch.int32))
+        q.copy_(torch.randn(q.shape, device=DEV).bfloat16())
+        for i, n in enumerate(lens):
+            idx[i] = torch.randint(0, n, (K,), device=DEV).to(torch.int32)
+        out.fill_(3.0), full.fill_(3.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        now, now_full = torch.empty_like(q), torch.empty_like(q)
+        cb.sparse_attn(params, q, kv, idx, cnt, now, ws2)
+        cb.full_attn(params, q, kv, now_full, ws2)
+        assert torch.equal(out, now) and torch.equal(full, now_full), f"lengths {lens}, counts {counts}"
+
+
+def test_captured_launches_leave_the_merge_to_a_second_one():
+    """A replay has the tag of the capture, so no launch in a graph may go by it: the room for the words stays as it was.  (A call writes there.)"""
+    need = 1696000                                         # bytes of the workspace before that room
+    q, kv, idx, cnt, _ = _layer(1, 32, 8, 4096, 1024, 4)
+    params = cb.make_params(1, 32, 8, 1024, 256)
+    ws, out = cb.alloc_workspace(params, 4096, DEV), torch.zeros_like(q)
+    ws.fill_(77)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        cb.sparse_attn(params, q, kv, idx, cnt, out, ws)
+    graph.replay()
+    torch.cuda.synchronize()
+    assert (ws[need:] == 77).all() and (out != 0).any()
+    cb.sparse_attn(params, q, kv, idx, cnt, out, ws)
+    assert (ws[need:] != 77).any()
+
+
 @pytest.mark.parametrize("b,H,Gk,L,K,W,need", [(1, 32, 8, 4096, 1024, 256, 1696000), (2, 16, 16, 3000, 512, 128, 708864)])
 def test_a_workspace_without_room_for_the_words_is_taken(b, H, Gk, L, K, W, need):
     """What a launch that merges its pieces itself wants on top is no condition: with the bytes of the partial sums alone a second launch merges,
