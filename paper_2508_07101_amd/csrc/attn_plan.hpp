@@ -135,19 +135,24 @@ inline int in_turn(int n, int BG, int limit) {
     return (int)std::max<int64_t>(1, (n + rounds - 1) / rounds);
 }
 
-// Whether an attention launch merges its pieces itself (merge_tagged) instead of leaving them to a second launch: where the host, 3 us a launch,
+// Whether an attention launch merges its pieces itself (wait_and_merge) instead of leaving them to a second launch: where the host, 3 us a launch,
 // takes longer than the GPU, that is where runs are short, and where the partial sums, written past the caches in twice the bytes, are few.
 // rows: batch * query heads; in_step: one layer of several that are enqueued together, so that the GPU is behind the host.  (Launches captured into a
-// graph, whose replay keeps no host waiting, always leave the merge to a second one: see merge_tagged.)
+// graph, whose replay keeps no host waiting, always leave the merge to a second one: see MergeWords.)
 // (Layer of one sequence, us, GPU alone / calls one after the other from Python, two launches and so: 32 heads, list of 1024, 512 rows of partial
-// sums, 6.3 / 9.8 and 6.0 / 6.9; of 2048, 1024 rows, 6.87 / 9.8 and 7.04 / 7.15; all of 4096 tokens, 1024, 7.9 / 9.9 and 8.0 / 8.2; 64 heads, 4096,
-// 2048 rows, 8.4 / 9.7 and 9.2 / 9.3.  Runs of 512 tokens: 8 sequences, lists of 4096, 26.2 and 27.1, the waiting costs more than a launch.)
-constexpr int MERGE_ROWS_MAX = 256;
+// sums, 6.3 / 9.8 and 6.4 / 6.7; of 2048, 1024 rows, 6.9 / 9.8 and 6.9 / 6.7; all of 4096 tokens, 1024, 7.7 / 9.9 and 7.9 / 7.7; 64 heads, 1024, 1024
+// rows, 6.9 and 7.85 / 7.5, 4096, 2048 rows, 8.4 / 9.7 and 9.2 / 9.3; 4 sequences, 512, 6.9 and 7.0 / 6.7.  Runs of 512 tokens: 8 sequences, lists of 4096, 26.2 and
+// 27.1, the waiting costs more than a launch.)
+// A merging workgroup holds a place while it waits, two of them to a row.  A CU has room for two workgroups of the kernels for groups of 8 and for four of the
+// others, an XCD of 32 CUs for 64 and 128: the waiting ones of three launches of 64 and of 128 rows, 16 and 32 of each launch on an XCD, leave a fourth launch's pieces
+// places there.  (Where they do not -- launches of both kinds, more queues, a stream bound to few CUs, other programs --, rows are handed over: wait_and_merge.)
+constexpr int MERGE_ROWS_MAX = 128;
+constexpr int MERGE_ROWS_MAX_G8 = 64;
 constexpr int MERGE_RUN = 128;
 constexpr int MERGE_PIECES_MAX = 1024;   // rows of partial sums
 constexpr int MERGE_PIECES_STEP = 512;
-inline bool merges_itself(const AttnPlan& pl, int64_t rows, bool in_step) {
-    return pl.ti == 4 && pl.n_splits > 1 && pl.chunk <= MERGE_RUN && rows <= MERGE_ROWS_MAX &&
+inline bool merges_itself(const AttnPlan& pl, int64_t rows, int g, bool in_step) {
+    return pl.ti == 4 && pl.n_splits > 1 && pl.chunk <= MERGE_RUN && rows <= (g >= 8 ? MERGE_ROWS_MAX_G8 : MERGE_ROWS_MAX) &&
            rows * pl.n_splits <= (in_step ? MERGE_PIECES_STEP : MERGE_PIECES_MAX);
 }
 

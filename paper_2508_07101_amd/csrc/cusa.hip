@@ -288,7 +288,8 @@ WsLayout make_layout(const cusa_params* p, int max_seq_len) {
     w.out_tmp = off;  off += align256((size_t)(B * H * D) * 2);        // recall: the attention outputs nobody reads
     w.need = w.words = off;
     // (more rows than the launch may have get as much: a workspace sized for them serves fewer as well)
-    off += align256((size_t)std::min<int64_t>(B * H * MERGE_BATCH, MERGE_PIECES_MAX) * MERGE_PIECE_BYTES);
+    off += align256((size_t)std::min<int64_t>(B * H * MERGE_BATCH, MERGE_PIECES_MAX) * MERGE_PIECE_BYTES +
+                    (size_t)std::min<int64_t>(B * H, MERGE_ROWS_MAX) * MERGE_ROW_BYTES);
     w.words_bytes = off - w.words;
     w.total = off;
     return w;
@@ -350,7 +351,7 @@ struct AttnArgs {
     float* lse = nullptr;   // optional: log2 of the softmax denominators, [B][H]
     int n_splits, chunk, n_seqs;
     uint64_t tag = 0;       // of the launch's partial sums, where it merges them itself
-    uint32_t tagged_bytes = 0;
+    int looks = 0;          // of its merging workgroups before they hand their rows over
     ScoreOut score;
 };
 
@@ -378,10 +379,10 @@ void launch_attn_partial(const AttnArgs& a) {
     const int kid = SPARSE ? KID_ATTN_SPARSE : FILTER ? KID_ATTN_FILTER : SCORE ? KID_ATTN_SELECT : KID_ATTN_FULL;
     if (a.paged)
         launch(kid, attn_kernel<GQ, TI, SPARSE, true, SCORE, false, FILTER>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt, a.view.seq_lens, a.q,
-               a.budget, a.n_splits, a.chunk, a.view.G, 0xffffffffu / (uint32_t)a.n_splits, a.n_seqs, a.scale, a.pa, a.pm, a.out, a.lse, a.tag, a.tagged_bytes, a.score.window, 0, a.score.dest(), a.view);
+               a.budget, a.n_splits, a.chunk, a.view.G, 0xffffffffu / (uint32_t)a.n_splits, a.n_seqs, a.scale, a.pa, a.pm, a.out, a.lse, a.tag, a.looks, a.score.window, 0, a.score.dest(), a.view);
     else
         launch(kid, attn_kernel<GQ, TI, SPARSE, false, SCORE, false, FILTER>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt, a.view.seq_lens, a.q,
-               a.budget, a.n_splits, a.chunk, a.view.G, 0xffffffffu / (uint32_t)a.n_splits, a.n_seqs, a.scale, a.pa, a.pm, a.out, a.lse, a.tag, a.tagged_bytes, a.score.window, 0, a.score.dest(), a.view);
+               a.budget, a.n_splits, a.chunk, a.view.G, 0xffffffffu / (uint32_t)a.n_splits, a.n_seqs, a.scale, a.pa, a.pm, a.out, a.lse, a.tag, a.looks, a.score.window, 0, a.score.dest(), a.view);
 }
 
 // Sparse attention with one token list per query head: grid.y counts query heads.
@@ -389,10 +390,10 @@ template <int TI>
 void launch_attn_per_head(const AttnArgs& a, int H, int hshift) {
     if (a.paged)
         launch(KID_ATTN_PER_HEAD, attn_kernel<1, TI, true, true, false, true>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt,
-               a.view.seq_lens, a.q, a.budget, a.n_splits, a.chunk, H, 0xffffffffu / (uint32_t)a.n_splits, a.n_seqs, a.scale, a.pa, a.pm, a.out, a.lse, a.tag, a.tagged_bytes, 0, hshift, FilterState{}, a.view);
+               a.view.seq_lens, a.q, a.budget, a.n_splits, a.chunk, H, 0xffffffffu / (uint32_t)a.n_splits, a.n_seqs, a.scale, a.pa, a.pm, a.out, a.lse, a.tag, a.looks, 0, hshift, FilterState{}, a.view);
     else
         launch(KID_ATTN_PER_HEAD, attn_kernel<1, TI, true, false, false, true>, a.grid, ATTN_THREADS, 0, a.s, a.idx, a.cnt,
-               a.view.seq_lens, a.q, a.budget, a.n_splits, a.chunk, H, 0xffffffffu / (uint32_t)a.n_splits, a.n_seqs, a.scale, a.pa, a.pm, a.out, a.lse, a.tag, a.tagged_bytes, 0, hshift, FilterState{}, a.view);
+               a.view.seq_lens, a.q, a.budget, a.n_splits, a.chunk, H, 0xffffffffu / (uint32_t)a.n_splits, a.n_seqs, a.scale, a.pa, a.pm, a.out, a.lse, a.tag, a.looks, 0, hshift, FilterState{}, a.view);
 }
 
 template <int GQ, bool SPARSE>
@@ -427,7 +428,8 @@ void launch_reduce(const ReduceArgs& r, int H, int B, hipStream_t s) {
 template <bool SPARSE>
 cusa_status run_attention(const cusa_params* p, const void* q, const cusa_kv* kv, const int32_t* idx,
                           const int32_t* cnt, int n_max, void* out, void* ws, const WsLayout& w, hipStream_t s,
-                          ScoreOut score = ScoreOut(), float* lse = nullptr, ReduceArgs* later = nullptr, bool in_step = false) {
+                          ScoreOut score = ScoreOut(), float* lse = nullptr, ReduceArgs* later = nullptr, bool in_step = false,
+                          int looks = MERGE_LOOKS) {
     const int g = p->n_q_heads / p->n_kv_heads, BG = p->batch * p->n_kv_heads, H = p->n_q_heads;
     const AttnPlan pl = plan_attn(n_max, BG, g, SPARSE ? ATTN_SPARSE : score.P != nullptr ? ATTN_SCORE : ATTN_FULL,
                                   kv->layout == CUSA_KV_PAGED);
@@ -450,12 +452,12 @@ cusa_status run_attention(const cusa_params* p, const void* q, const cusa_kv* kv
     a.chunk = pl.chunk;
     a.n_seqs = p->batch;
     a.score = score;
-    const int64_t words_bytes = (int64_t)p->batch * H * pl.n_splits * MERGE_PIECE_BYTES;
-    if (merges_itself(pl, (int64_t)p->batch * H, in_step) && !score.P && !later && words_bytes <= (int64_t)w.words_bytes && !being_captured(s)) {
+    const int64_t words_bytes = (int64_t)p->batch * H * (pl.n_splits * MERGE_PIECE_BYTES + MERGE_ROW_BYTES);
+    if (merges_itself(pl, (int64_t)p->batch * H, g, in_step) && !score.P && !later && words_bytes <= (int64_t)w.words_bytes && !being_captured(s)) {
         a.tag = new_tag();
         a.pa = ws_ptr<float>(ws, w.words);
-        a.tagged_bytes = (uint32_t)words_bytes;
-        const int per_slice = pl.n_splits * p->n_kv_heads, items = p->batch * H * (D / MERGE_COLS);
+        a.looks = looks;
+        const int per_slice = pl.n_splits * p->n_kv_heads, items = p->batch * H * MERGE_PARTS;
         a.grid.z += (items + per_slice - 1) / per_slice;
     }
     switch (g) {
@@ -988,6 +990,20 @@ cusa_status cusa_sparse_attn(const cusa_params* params, const void* q, const cus
     if ((st = check_ws(w, ws, ws_bytes)) != CUSA_OK) return st;
     const int n_max = params->budget < kv->max_seq_len ? params->budget : kv->max_seq_len;
     return run_attention<true>(params, q, kv, idx, cnt, n_max, out, ws, w, static_cast<hipStream_t>(stream));
+}
+
+// For tests of the library, not part of its interface: cusa_sparse_attn whose merging workgroups, where the launch has any, hand their rows over
+// after `looks` looks.  The result does not depend on it.
+cusa_status cusa_test_sparse_attn_looks(const cusa_params* params, const void* q, const cusa_kv* kv, const int32_t* idx, const int32_t* cnt, void* out,
+                                        void* ws, size_t ws_bytes, void* stream, int32_t looks) {
+    cusa_status st = check_params(params, true);
+    if (st != CUSA_OK) return st;
+    if ((st = check_kv(params, kv)) != CUSA_OK) return st;
+    if (!q || !idx || !cnt || !out || ((uintptr_t)q & 15) || looks < 0 || looks > MERGE_LOOKS) return CUSA_ERR_INVALID_ARG;
+    WsLayout w = make_layout(params, kv->max_seq_len);
+    if ((st = check_ws(w, ws, ws_bytes)) != CUSA_OK) return st;
+    const int n_max = params->budget < kv->max_seq_len ? params->budget : kv->max_seq_len;
+    return run_attention<true>(params, q, kv, idx, cnt, n_max, out, ws, w, static_cast<hipStream_t>(stream), ScoreOut(), nullptr, nullptr, false, looks);
 }
 
 size_t cusa_noalloc_max_scratch_bytes(void) { return NOALLOC_SCRATCH_BYTES; }

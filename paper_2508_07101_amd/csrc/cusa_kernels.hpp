@@ -1957,7 +1957,7 @@ __global__ __launch_bounds__(SEL_THREADS) void per_head_rho_kernel(const int32_t
 // The four waves are merged through LDS into one partial (m, l, acc[128]) per
 // head.  With one split that is the result and is written as bf16; otherwise the
 // partial goes to the workspace and attn_reduce_kernel merges the splits, or, where runs are short,
-// further workgroups of the launch (merge_tagged).  (A merge by the last workgroup to arrive was measured and is slower:
+// further workgroups of the launch (wait_and_merge).  (A merge by the last workgroup to arrive was measured and is slower:
 // the fence, the ticket and then its reads of the other workgroups' partials come one after the other.)
 
 template <int CTRL>
@@ -2028,33 +2028,37 @@ __device__ __forceinline__ int wave_base_of(unsigned tid) { return (int)(tid >> 
 // Where a layer's pieces are short, the second launch that merges them costs the host as much as the first (3 us each) and the GPU the
 // time between two kernels.  There the merge is done by further workgroups of the same launch, dispatched behind all pieces: a
 // piece leaves its partial sums as words of 16 bytes, two values with the two halves of the launch's tag between them, written past the
-// caches (agent scope), and a merging workgroup reads the words of its row until all carry the tag.  No flag, counter or fence is
-// needed, a word says itself whether it is there (flags behind the data cost a further way to memory and back: for
+// caches (agent scope), and a merging workgroup reads the words of its row until all carry the tag.  No counter, fence or flag behind
+// the data is needed, a word says itself whether it is there (flags behind the data cost a further way to memory and back: for
 // 256 pieces that read 8 MB, us, two launches 4.9, by flags 5.3, by tagged words 4.7).  What bounds it is that way, once there and once
 // back.  Words that have come are not asked for again (0.3 us), and the merge is run once over nothing beforehand: its
 // instructions come from memory the first time (0.3 us).  Where it is used: merges_itself, with both sides' times.
 //
-// Every wait ends: a merging workgroup waits only for pieces of its own launch, which wait for nobody and are dispatched before it, and
-// even out of order it could not keep them out (at most MERGE_ROWS_MAX * 2 waiting workgroups, two to a CU).  Should a wait
-// ever exceed MERGE_POLLS looks (some seconds), the output is made NaN.
+// No result hangs on the order in which workgroups are dispatched or on room for all of them: a merging workgroup looks MERGE_LOOKS times at most
+// (0.2 ms).  Then it hands its row over: it writes a flag, a tagged word as well, waits until the flag has arrived, looks once more and, if a piece
+// is still missing, leaves.  A piece whose words have arrived looks at the flags of its rows and, where one is set, at all words of the row; if all are there,
+// it merges.  Whichever arrives last at memory, a missing piece's last word or the flag, its writer reads the other's afterwards, so one of the two
+// merges (both may; they write the same bits).  No piece waits for anything but its own stores, and no other wait is longer than MERGE_LOOKS.
+// A piece's way to the flags and back runs beside the merging workgroup's to the piece's words: lists of 1024 and 2048, 32 heads, us, without the flags and with
+// them, GPU alone 6.4 and 6.4, 6.9 and 6.9, calls one after the other 6.57 and 6.70, 6.65 and 6.74.
+// Before it comes to that, merges_itself keeps the waiting workgroups few: of four launches at a time (the hardware queues of a process), those of three
+// leave room on every XCD for the pieces of the fourth.
 //
 // The tag is 64 random-looking bits that the host draws anew for every call, so whatever the workspace held before is taken for a word of this launch with
 // a probability of 2^-64 per word.  A launch captured into a graph would be replayed with the same tag, over words that the replay before left: captured launches
 // leave the merge to a second one.  A merging workgroup writes nothing but its own columns of the output.  A lane's aligned 16 bytes are written and read in
 // one access.
 constexpr int MERGE_COLS = 64;                        // columns of a merging workgroup: two per row (one or four: 0.3, 0.1 us more)
+constexpr int MERGE_PARTS = D / MERGE_COLS;
 constexpr int MERGE_PIECE_BYTES = (D / 2 + 1) * 16;   // words of a row's piece: its columns, its maximum and sum
-constexpr int MERGE_POLLS = 1 << 23;
-constexpr int MERGE_LDS_FLOATS = 8 * MERGE_COLS + 16;
+constexpr int MERGE_ROW_BYTES = MERGE_PARTS * 16;     // words of a row: its merging workgroups' flags
+constexpr int MERGE_LOOKS = 256;
+constexpr int MERGE_LDS_FLOATS = 8 * MERGE_COLS + 16 + 1;
 constexpr int CACHE_AGENT = 16;                       // cache policy of a buffer access: agent scope (sc1)
 
 __device__ __forceinline__ auto tagged_words(float* base, uint32_t bytes) {
     asm volatile("" : "+s"(base));                       // other workgroups write there too: no longer the __restrict__ argument
     return __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00020000);   // accesses past `bytes` are dropped
-}
-template <typename Rsrc>
-__device__ __forceinline__ void store_tagged(Rsrc words, uint32_t at, u32x4 w) {
-    __builtin_amdgcn_raw_buffer_store_b128(w, words, at, 0, CACHE_AGENT);
 }
 
 // One step of the merge: the pieces a thread asked for together join its running (maximum, sum, columns).
@@ -2096,97 +2100,157 @@ __device__ __forceinline__ float meet_in_lds(const float* m, const float* l, Col
     return M;
 }
 
-// 256 threads: thread (c, sr) has columns 2c, 2c + 1 of the workgroup's and the pieces sr, sr + 8, ...; the eight meet in LDS.
-__device__ __forceinline__ void merge_tagged(float* base, uint32_t bytes, uint64_t tag, int item, int rows, int H, const int32_t* __restrict__ n_tok,
-                                             int n_clip, int n_splits, int chunk, uint16_t* __restrict__ out, float* __restrict__ lse, float* lds) {
-    constexpr int PARTS = D / MERGE_COLS, WORDS = MERGE_COLS / 2, U = 4;
-    const int row = item / PARTS, part = item % PARTS;
-    if (row >= rows) return;
-    const int n = min(n_tok[row / H], n_clip);
-    const int pieces = merged_pieces(n, chunk, n_splits);
-    if (pieces <= 1) return;                             // the only piece wrote the result itself
+// A launch's words: rows x n_splits pieces of D / 2 words of columns, as many words of maximum and sum, rows x MERGE_PARTS flags.
+struct MergeWords {
+    decltype(tagged_words(nullptr, 0)) words;
+    uint32_t lo, hi, ml0, flag0;
+    int n_splits;
+
+    __device__ __forceinline__ MergeWords(float* base, uint64_t tag, uint32_t rows, int n_splits_)
+        : words(tagged_words(base, rows * (n_splits_ * MERGE_PIECE_BYTES + MERGE_ROW_BYTES))), lo((uint32_t)tag), hi((uint32_t)(tag >> 32)),
+          ml0(rows * n_splits_ * (D / 2)), flag0(ml0 + rows * n_splits_), n_splits(n_splits_) {}
+    __device__ __forceinline__ uint32_t col_at(uint32_t row, uint32_t piece, uint32_t pair) const { return ((row * n_splits + piece) * (D / 2) + pair) * 16u; }
+    __device__ __forceinline__ uint32_t ml_at(uint32_t row, uint32_t piece) const { return (ml0 + row * n_splits + piece) * 16u; }
+    __device__ __forceinline__ uint32_t flag_at(uint32_t item) const { return (flag0 + item) * 16u; }
+    __device__ __forceinline__ u32x4 load(uint32_t at) const { return __builtin_amdgcn_raw_buffer_load_b128(words, at, 0, CACHE_AGENT); }
+    __device__ __forceinline__ void store(uint32_t at, float a, float b) const {
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4{__float_as_uint(a), lo, __float_as_uint(b), hi}, words, at, 0, CACHE_AGENT);
+    }
+    __device__ __forceinline__ bool mine(u32x4 w) const { return w.y == lo && w.w == hi; }
+};
+
+// 256 threads look at a row's words, `looks` times at most, and merge its pieces if all are there: the columns of `part`.  Thread (c, sr) has columns
+// 2c, 2c + 1 of these and the pieces sr, sr + 8, ...; the eight meet in LDS.  dry: over nothing.  False: words are missing (for the whole workgroup).  ONCE: one look, which
+// needs no second set of registers.
+template <bool ONCE>
+__device__ __forceinline__ bool merge_row(const MergeWords& w, int row, int part, int pieces, int looks, bool dry, uint16_t* __restrict__ out,
+                                          float* __restrict__ lse, float* lds) {
+    constexpr int WORDS = MERGE_COLS / 2, U = 4;
     const int tid = threadIdx.x, c = tid % WORDS, sr = tid / WORDS;
-    const uint32_t lo = (uint32_t)tag, hi = (uint32_t)(tag >> 32);
-    const auto words = tagged_words(base, bytes);
-    const uint32_t ml0 = (uint32_t)rows * n_splits * (D / 2);
     float(*const la)[MERGE_COLS] = reinterpret_cast<float(*)[MERGE_COLS]>(lds);
     float* const lm = lds + 8 * MERGE_COLS;
-    // Once over nothing, while the pieces are being made, so that the instructions are in the cache when the words are there.
+    const int todo = dry ? 1 : pieces;
+    float m = -INFINITY, l = 0.0f;
+    f32x2 a = {0.0f, 0.0f};
+    bool lost = false;
+    for (int s0 = sr; s0 - sr < todo; s0 += 8 * U) {
+        // What is there (or does not exist) is not asked for again: an address past the buffer's end is no access.
+        constexpr uint32_t NOWHERE = 0xfffffff0u;
+        u32x4 wa[U], wm[U];
+        uint32_t at_a[U], at_m[U];
+        bool there[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int s = s0 + 8 * u;
+            there[u] = dry || s < pieces;
+            at_a[u] = dry || s >= pieces ? NOWHERE : w.col_at(row, s, part * WORDS + c);
+            at_m[u] = dry || s >= pieces ? NOWHERE : w.ml_at(row, s);
+            wa[u] = wm[u] = u32x4{0u, 0u, 0u, 0u};
+        }
+        bool ready = false;
+        if constexpr (ONCE) {
+            bool mine = true;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                wa[u] = w.load(at_a[u]);
+                wm[u] = w.load(at_m[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) mine = mine && (at_a[u] == NOWHERE || (w.mine(wa[u]) && w.mine(wm[u])));
+            ready = __all(mine);
+        }
+        for (int look = 0; !ONCE && look < looks && !ready; ++look) {
+            asm volatile("" ::: "memory");               // read again
+            u32x4 na[U], nm[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                na[u] = w.load(at_a[u]);
+                nm[u] = w.load(at_m[u]);
+            }
+            bool mine = true;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const bool came = w.mine(na[u]) && w.mine(nm[u]);   // (what was not asked for reads zeros, which no tag is)
+                if (came) {
+                    wa[u] = na[u];
+                    wm[u] = nm[u];
+                    at_a[u] = at_m[u] = NOWHERE;
+                }
+                mine = mine && at_a[u] == NOWHERE;
+            }
+            ready = __all(mine);
+        }
+        lost = lost || !ready;
+        float mu[U], lu[U];
+        f32x2 au[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            au[u] = f32x2{__uint_as_float(wa[u].x), __uint_as_float(wa[u].z)};
+            mu[u] = __uint_as_float(wm[u].x);
+            lu[u] = __uint_as_float(wm[u].z);
+        }
+        fold_pieces<U>(au, mu, lu, there, m, l, a);
+    }
+    *reinterpret_cast<f32x2*>(&la[sr][2 * c]) = a;
+    if (c == 0) {
+        lm[sr] = lost ? NAN : m;                         // (no piece's maximum is NaN)
+        lm[8 + sr] = l;
+    }
+    lds_barrier();
+    bool missing = false;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) missing = missing || lm[j] != lm[j];
+    if (tid < MERGE_COLS) {
+        float A, Ls;
+        const float M = meet_in_lds(lm, lm + 8, [&](int j) { return la[j][tid]; }, A, Ls);
+        const uint16_t res = f32_to_bf16_rne(Ls > 0.0f ? A / Ls : 0.0f);
+        if (!dry && !missing) {
+            out[(int64_t)row * D + part * MERGE_COLS + tid] = res;
+            if (lse && part == 0 && tid == 0) lse[row] = M + log2f(Ls);
+        } else {
+            asm volatile("" ::"v"((uint32_t)res));
+        }
+    }
+    lds_barrier();                                       // read, before the next round writes
+    return !__builtin_amdgcn_readfirstlane(missing);
+}
+
+// A merging workgroup: once over nothing, while the pieces are being made, so that the instructions are in the cache when the words are there; then up to
+// `looks` looks; then, the row handed over, one more.
+__device__ __forceinline__ void wait_and_merge(const MergeWords& w, int item, int pieces, int looks, uint16_t* __restrict__ out, float* __restrict__ lse,
+                                               float* lds) {
 #pragma nounroll
-    for (int dry = 1; dry >= 0; --dry) {
-        asm volatile("" : "+s"(dry));
-        const int todo = dry ? 1 : pieces;
-        float m = -INFINITY, l = 0.0f;
-        f32x2 a = {0.0f, 0.0f};
-        bool lost = false;
-        for (int s0 = sr; s0 - sr < todo; s0 += 8 * U) {
-            u32x4 wa[U], wm[U];
-            uint32_t at_a[U], at_m[U];
-            bool there[U], got[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int s = s0 + 8 * u;
-                there[u] = dry || s < pieces;
-                got[u] = dry || s >= pieces;
-                const uint32_t p = (uint32_t)row * n_splits + s;
-                at_a[u] = (p * (D / 2) + part * WORDS + c) * 16u;
-                at_m[u] = (ml0 + p) * 16u;
-                wa[u] = wm[u] = u32x4{0u, 0u, 0u, 0u};
-            }
-            bool ready = false;
-            for (int look = 0; look < MERGE_POLLS && !ready; ++look) {
-                asm volatile("" ::: "memory");           // read again
-                u32x4 na[U], nm[U];
-                // what is there (or does not exist) is not asked for again: an address past the buffer's end is no access
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    na[u] = __builtin_amdgcn_raw_buffer_load_b128(words, got[u] ? 0xfffffff0u : at_a[u], 0, CACHE_AGENT);
-                    nm[u] = __builtin_amdgcn_raw_buffer_load_b128(words, got[u] ? 0xfffffff0u : at_m[u], 0, CACHE_AGENT);
-                }
-                bool mine = true;
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if (!got[u]) {
-                        wa[u] = na[u];
-                        wm[u] = nm[u];
-                        got[u] = wa[u].y == lo && wa[u].w == hi && wm[u].y == lo && wm[u].w == hi;
-                    }
-                    mine = mine && got[u];
-                }
-                ready = __all(mine);
-            }
-            lost = lost || !ready;
-            float mu[U], lu[U];
-            f32x2 au[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                au[u] = f32x2{__uint_as_float(wa[u].x), __uint_as_float(wa[u].z)};
-                mu[u] = __uint_as_float(wm[u].x);
-                lu[u] = __uint_as_float(wm[u].z);
-            }
-            fold_pieces<U>(au, mu, lu, there, m, l, a);
+    for (int round = 0; round < 3; ++round) {
+        asm volatile("" : "+s"(round), "+s"(item));      // (each round makes its addresses anew: kept, they cost a wave per SIMD)
+        const bool done = merge_row<false>(w, item / MERGE_PARTS, item % MERGE_PARTS, pieces, round == 1 ? looks : 1, round == 0, out, lse, lds);
+        if (round == 0) continue;
+        if (done) return;
+        if (round == 1) {
+            float none = 0.0f;
+            asm volatile("" : "+v"(none));
+            if (threadIdx.x == 0) w.store(w.flag_at(item), none, none);
+            asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");   // arrived, before anyone looks again
         }
-        *reinterpret_cast<f32x2*>(&la[sr][2 * c]) = a;
-        if (c == 0) {
-            lm[sr] = lost ? NAN : m;
-            lm[8 + sr] = l;
-        }
-        lds_barrier();
-        if (tid < MERGE_COLS) {
-            float A, Ls;
-            const float M = meet_in_lds(lm, lm + 8, [&](int j) { return la[j][tid]; }, A, Ls);
-            bool bad = false;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) bad = bad || lm[j] != lm[j];
-            const uint16_t res = bad ? 0x7fc0 : f32_to_bf16_rne(Ls > 0.0f ? A / Ls : 0.0f);
-            if (!dry) {
-                out[(int64_t)row * D + part * MERGE_COLS + tid] = res;
-                if (lse && part == 0 && tid == 0) lse[row] = bad ? NAN : M + log2f(Ls);
-            } else {
-                asm volatile("" ::"v"((uint32_t)res));
-            }
-        }
-        lds_barrier();                                   // read, before the second time round writes
+    }
+}
+
+// A piece, behind the stores of its words: the rows row0 .. row0 + n_rows - 1 that were handed over meanwhile, for which this may have been the last piece.
+__device__ __forceinline__ void merge_if_handed_over(const MergeWords& w, int row0, int n_rows, int pieces, uint16_t* __restrict__ out,
+                                                     float* __restrict__ lse, float* lds) {
+    uint32_t* const asked = reinterpret_cast<uint32_t*>(lds + MERGE_LDS_FLOATS - 1);
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");   // all of the workgroup's words have arrived
+    if (threadIdx.x < 64) {
+        const int n_items = n_rows * MERGE_PARTS, lane = threadIdx.x;
+        const u32x4 flag = w.load(lane < n_items ? w.flag_at(row0 * MERGE_PARTS + lane) : 0xfffffff0u);
+        const uint64_t set = __ballot(lane < n_items && w.mine(flag));
+        if (lane == 0) *asked = (uint32_t)set;           // (at most 16 items)
+    }
+    lds_barrier();
+    uint32_t todo = __builtin_amdgcn_readfirstlane(*asked);
+    while (__builtin_expect(todo != 0, 0)) {
+        const int item = row0 * MERGE_PARTS + __builtin_ctz(todo);
+        todo &= todo - 1;
+        merge_row<true>(w, item / MERGE_PARTS, item % MERGE_PARTS, pieces, 1, false, out, lse, lds);
     }
 }
 
@@ -2208,7 +2272,7 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt, const int32_t* __restrict__ seq_lens,
     const uint16_t* __restrict__ q, int budget, int n_splits, int chunk, int G, uint32_t inv_splits, int n_seqs, float scale_log2e,
     float* __restrict__ part_acc, float* __restrict__ part_ml, uint16_t* __restrict__ out, float* __restrict__ lse,
-    uint64_t tag, uint32_t tagged_bytes, int window, int hshift, FilterState flt, KvView kv) {
+    uint64_t tag, int looks, int window, int hshift, FilterState flt, KvView kv) {
     static_assert(!(SCORE && SPARSE), "scores are emitted by the pass over all tokens");
     static_assert(!FILTER || SCORE, "the filter is a form of the scoring variant");
     static_assert(!PER_HEAD || (SPARSE && GQ == 1), "per-head token lists: one query head per workgroup");
@@ -2264,8 +2328,10 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
     if constexpr (MERGES) {
         if (__builtin_expect(b >= n_seqs, 0)) {          // behind all pieces: the workgroups that merge them
             const int item = ((b - n_seqs) * G + gy) * (int)gridDim.x + (int)blockIdx.x;
-            merge_tagged(part_acc, tagged_bytes, tag, item, n_seqs * H, H, SPARSE ? cnt : seq_lens, SPARSE ? budget : 0x7fffffff, n_splits, chunk,
-                         out, lse, reinterpret_cast<float*>(smem_raw));
+            if (item >= n_seqs * H * MERGE_PARTS) return;
+            const int of = item / (H * MERGE_PARTS), pieces = merged_pieces(SPARSE ? min(cnt[of], budget) : seq_lens[of], chunk, n_splits);
+            if (pieces > 1)                              // otherwise the only piece writes the result itself
+                wait_and_merge(MergeWords(part_acc, tag, n_seqs * H, n_splits), item, pieces, looks, out, lse, reinterpret_cast<float*>(smem_raw));
             return;
         }
     }
@@ -2817,18 +2883,20 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
             }
             if (lse && col == 0) lse[head0 + h] = M + log2f(Ls);
         } else if (MERGES && tag) {         // for a merging workgroup of this launch
-            const auto words = tagged_words(part_acc, tagged_bytes);
-            const uint32_t p = (uint32_t)((head0 + h) * n_splits + split), lo = (uint32_t)tag, hi = (uint32_t)(tag >> 32);
+            const MergeWords w(part_acc, tag, n_seqs * H, n_splits);
 #pragma unroll
-            for (int e = 0; e < PER; e += 2)
-                store_tagged(words, (p * (D / 2) + (col + e) / 2) * 16u, u32x4{__float_as_uint(A[e]), lo, __float_as_uint(A[e + 1]), hi});
-            if (col == 0)
-                store_tagged(words, ((uint32_t)(n_seqs * H) * n_splits * (D / 2) + p) * 16u, u32x4{__float_as_uint(M), lo, __float_as_uint(Ls), hi});
+            for (int e = 0; e < PER; e += 2) w.store(w.col_at(head0 + h, split, (col + e) / 2), A[e], A[e + 1]);
+            if (col == 0) w.store(w.ml_at(head0 + h, split), M, Ls);
         } else {
             const int64_t p = (head0 + h) * n_splits + split;
             *reinterpret_cast<f32_per*>(&part_acc[p * D + col]) = A;
             if (col == 0) *reinterpret_cast<f32x2*>(&part_ml[p * 2]) = f32x2{M, Ls};
         }
+    }
+    if constexpr (MERGES) {
+        if (tag && n > chunk)
+            merge_if_handed_over(MergeWords(part_acc, tag, n_seqs * H, n_splits), (int)head0, GQ, merged_pieces(n, chunk, n_splits), out, lse,
+                                 reinterpret_cast<float*>(smem_raw));
     }
     if constexpr (FILTER) copy_candidates(cand_reserved);
 }

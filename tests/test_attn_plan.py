@@ -214,7 +214,7 @@ def test_launches_that_merge_their_pieces_themselves_have_few_short_ones(tmp_pat
     """Only tiles of 16 tokens hold the code for it, so the rule asks for them; runs of at most 128 tokens, at most 1024 rows of partial sums,
     512 in a step of several layers."""
     out = run_checks(tmp_path, r'''
-    if (merges_itself({8, 128, 4}, 32, false) || !merges_itself({4, 128, 4}, 32, false)) FAIL("tiles of 32 tokens");
+    if (merges_itself({8, 128, 4}, 32, 4, false) || !merges_itself({4, 128, 4}, 32, 4, false)) FAIL("tiles of 32 tokens");
     long taken = 0;
     for (int pairs = 1; pairs <= 1100; ++pairs)
         for (int n = 1; n <= 9000; n += step(n))
@@ -223,9 +223,9 @@ def test_launches_that_merge_their_pieces_themselves_have_few_short_ones(tmp_pat
                     for (bool paged : {false, true}) {
                         const AttnPlan p = plan(n, pairs, g, kind, paged);
                         const int64_t rows = (int64_t)pairs * g;
-                        const bool call = merges_itself(p, rows, false), step_ = merges_itself(p, rows, true);
+                        const bool call = merges_itself(p, rows, g, false), step_ = merges_itself(p, rows, g, true);
                         taken += call;
-                        if (call && (p.ti != 4 || p.chunk > 128 || p.n_splits < 2 || rows > MERGE_ROWS_MAX || rows * p.n_splits > MERGE_PIECES_MAX))
+                        if (call && (p.ti != 4 || p.chunk > 128 || p.n_splits < 2 || rows > (g == 8 ? 64 : 128) || rows * p.n_splits > MERGE_PIECES_MAX))
                             FAIL("%d pairs of %d, groups of %d: %d pieces of %d", pairs, n, g, p.n_splits, p.chunk);
                         if (step_ && (!call || rows * p.n_splits > MERGE_PIECES_STEP)) FAIL("%d pairs of %d, groups of %d in a step", pairs, n, g);
                     }

@@ -4,6 +4,7 @@ piece, empty lists, outputs at addresses that take no wide store -- against soft
 The tolerance is derived: a weight is rounded to bf16 (2^-9 of it), in the numerator as in the denominator, which makes at most 2^-8 of the
 weighted mean of |v|; the output is rounded to bf16 (2^-9 of it); sums are binary32.
 """
+import ctypes
 import math
 
 import pytest
@@ -137,35 +138,67 @@ def _layer(b, H, Gk, L, K, seed):
     return q, kv, idx, torch.full((b,), K, dtype=torch.int32, device=DEV), cb.make_params(b, H, Gk, K, K // 4)
 
 
-@pytest.mark.parametrize("b,H,Gk,L,K", [(1, 32, 8, 4096, 1024), (1, 32, 8, 4096, 2048), (1, 8, 8, 3000, 300), (2, 8, 1, 900, 700), (4, 16, 2, 2100, 512)])
+def _two_launches(call):
+    """Runs `call` from a graph: what is captured leaves the merge of its pieces to a second launch."""
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    graph.replay()
+    torch.cuda.synchronize()
+
+
+def _words(ws, rows):
+    """The part of a workspace that only launches which merge their pieces themselves write (its last bytes)."""
+    return ws[-min(rows * 32, 1024) * 1040:]
+
+
+def _merges_itself(call, ws, rows):
+    ws.fill_(85)
+    call()
+    return bool((_words(ws, rows) != 85).any())
+
+
+# groups of 1, 2, 4 and 8, one and several sequences; rows of partial sums: 512, 1024, 176, 512, 1024, 1024, 1024
+IN_LAUNCH = [(1, 32, 8, 4096, 1024), (1, 32, 8, 4096, 2048), (1, 8, 8, 3000, 300), (4, 8, 8, 1040, 1024), (2, 16, 8, 2100, 2048), (4, 32, 8, 520, 512),
+             (2, 32, 4, 1030, 1024)]
+
+
+@pytest.mark.parametrize("b,H,Gk,L,K", IN_LAUNCH)
 def test_pieces_merged_in_the_launch_whatever_the_workspace_held(b, H, Gk, L, K):
-    """The same bits from a workspace of random words, of ones, of an earlier call's words or a selection's, in a decode step (which
-    may merge with a second launch), without a workspace, and in a graph replayed beside other work."""
+    """The bits of the two launches, from a workspace of random words, of ones, of an earlier call's words or a selection's, in a decode step,
+    without a workspace, and beside a graph that is replayed on the same workspace; lists of several lengths where there are several sequences."""
     q, kv, idx, cnt, params = _layer(b, H, Gk, L, K, 5)
+    cnt -= torch.tensor([0, 65, K, K - 65][:b], dtype=torch.int32, device=DEV)
     ws = cb.alloc_workspace(params, L, DEV)
-    want = torch.empty_like(q)
-    # an order of its own for the first bits: two launches
-    kinds = [cb.LAYER_SELECT, cb.LAYER_SPARSE, cb.LAYER_FULL]
-    outs = [torch.empty_like(q) for _ in kinds]
+    want, want_full, full, got = (torch.empty_like(q) for _ in range(4))
+    _two_launches(lambda: cb.sparse_attn(params, q, kv, idx, cnt, want, ws))
+    _two_launches(lambda: cb.full_attn(params, q, kv, want_full, ws))
+    assert _merges_itself(lambda: cb.sparse_attn(params, q, kv, idx, cnt, got, ws), ws, b * H)
+    assert _merges_itself(lambda: cb.full_attn(params, q, kv, full, ws), ws, b * H) or L in (520, 1030)   # (more than 1024 rows)
     rho, n_rho = torch.zeros_like(idx), torch.zeros_like(cnt)
-    step = cb.DecodeStep(params, kinds, [q] * 3, [kv] * 3, outs, rho, n_rho, ws)
-    step.run()
-    full = torch.empty_like(q)
     for fill in ("random", "ones", "earlier", "earlier", "selection"):
         if fill == "random":
             ws.random_(0, 256)
         elif fill == "ones":
             ws.fill_(255)
-        elif fill == "selection":
+        elif fill == "selection" and L > K:
             cb.select(params, q, kv, rho, n_rho, ws)
-        got = torch.zeros_like(q)
-        cb.sparse_attn(params, q, kv, rho, n_rho, got, ws)
-        assert torch.equal(got, outs[1]), f"sparse, workspace: {fill}"
+        got.zero_(), full.zero_()
+        cb.sparse_attn(params, q, kv, idx, cnt, got, ws)
+        assert torch.equal(got, want), f"sparse, workspace: {fill}"
         cb.full_attn(params, q, kv, full, ws)
-        assert torch.equal(full, outs[2]), f"full, workspace: {fill}"
-    cb.sparse_attn_noalloc(params, q, kv, rho, n_rho, want)
-    assert torch.equal(want, outs[1])
-    q2, got = q.clone(), torch.zeros_like(q)
+        assert torch.equal(full, want_full), f"full, workspace: {fill}"
+    got.zero_()
+    cb.sparse_attn_noalloc(params, q, kv, idx, cnt, got)
+    assert torch.equal(got, want)
+    # a step of several layers, against its selection's own list
+    outs = [torch.empty_like(q) for _ in range(3)]
+    step = cb.DecodeStep(params, [cb.LAYER_SELECT, cb.LAYER_SPARSE, cb.LAYER_FULL], [q] * 3, [kv] * 3, outs, rho, n_rho, ws)
+    step.run()
+    cb.sparse_attn(params, q, kv, rho, n_rho, got, ws)
+    assert torch.equal(outs[1], got) and torch.equal(outs[2], want_full)
+    q2 = q.clone()
     torch.cuda.synchronize()
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g):
@@ -182,6 +215,32 @@ def test_pieces_merged_in_the_launch_whatever_the_workspace_held(b, H, Gk, L, K)
         assert torch.equal(now[1], full), f"replay {rep}, full"
         cb.sparse_attn(params, q2, kv, idx, cnt, want, ws)
         assert torch.equal(now[0], want), f"replay {rep}, sparse"
+
+
+@pytest.mark.parametrize("b,H,Gk,L,K", IN_LAUNCH)
+def test_rows_handed_over_to_the_pieces(b, H, Gk, L, K):
+    """Merging workgroups that look never, once or a few times before they hand their rows over: whoever merges then, the bits are those of the
+    two launches, and no row is left out."""
+    q, kv, idx, cnt, params = _layer(b, H, Gk, L, K, 6)
+    cnt -= torch.tensor([0, 65, K, K - 65][:b], dtype=torch.int32, device=DEV)
+    ws, want = cb.alloc_workspace(params, L, DEV), torch.empty_like(q)
+    _two_launches(lambda: cb.sparse_attn(params, q, kv, idx, cnt, want, ws))
+    lib, desc = cb.load(), kv.desc()
+    vp = ctypes.c_void_p
+
+    def call(out, looks):
+        status = lib.cusa_test_sparse_attn_looks(ctypes.byref(params), vp(q.data_ptr()), ctypes.byref(desc), vp(idx.data_ptr()), vp(cnt.data_ptr()),
+                                                 vp(out.data_ptr()), vp(ws.data_ptr()), ctypes.c_size_t(ws.numel()), vp(cb._stream()), looks)
+        assert status == cb.OK
+    first = torch.empty_like(q)
+    assert _merges_itself(lambda: call(first, 0), ws, b * H)
+    for looks in (0, 1, 2, 4, 8, 256):
+        outs = [torch.full_like(q, 9.0) for _ in range(20)]
+        for out in outs:                                   # one after the other, as fast as they come
+            call(out, looks)
+        assert all(torch.equal(o, want) for o in outs), f"{looks} looks"
+    assert lib.cusa_test_sparse_attn_looks(ctypes.byref(params), vp(q.data_ptr()), ctypes.byref(desc), vp(idx.data_ptr()), vp(cnt.data_ptr()),
+                                           vp(first.data_ptr()), vp(ws.data_ptr()), ctypes.c_size_t(ws.numel()), vp(cb._stream()), -1) == cb.ERR_INVALID_ARG
 
 
 @pytest.mark.parametrize("g", [1, 4, 8])
