@@ -10,7 +10,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "libcusa.so")
 SOURCES = [os.path.join(CSRC, "cusa.hip")]
-HEADERS = [os.path.join(CSRC, "attn_plan.hpp"), os.path.join(CSRC, "cusa_kernels.hpp"),
+HEADERS = [os.path.join(CSRC, "attn_plan.hpp"), os.path.join(CSRC, "call_tag.hpp"), os.path.join(CSRC, "cusa_kernels.hpp"),
            os.path.join(os.path.dirname(_HERE), "include", "cusa.h")]
 
 HIPCC_FLAGS = [

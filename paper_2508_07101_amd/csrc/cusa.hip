@@ -8,13 +8,12 @@
 
 #include <algorithm>
 #include <atomic>
-#include <chrono>
 #include <mutex>
-#include <random>
 #include <utility>
 #include <vector>
 
 #include "attn_plan.hpp"
+#include "call_tag.hpp"
 #include "cusa_kernels.hpp"
 
 using namespace cusa;
@@ -354,17 +353,6 @@ struct AttnArgs {
     int looks = 0;          // of its merging workgroups before they hand their rows over
     ScoreOut score;
 };
-
-// A tag that no other call of this or an earlier process is likely to have had: a random start, then steps by an odd constant,
-// which come back to a value after 2^64 of them.  (0 means no tag.)
-uint64_t new_tag() {
-    static std::atomic<uint64_t> state{[] {
-        std::random_device rd;
-        return ((uint64_t)rd() << 32 | rd()) ^ (uint64_t)std::chrono::steady_clock::now().time_since_epoch().count();
-    }()};
-    const uint64_t t = state.fetch_add(0x9E3779B97F4A7C15ull, std::memory_order_relaxed);
-    return t ? t : 1;
-}
 
 // Whether what is enqueued on the stream now is recorded into a graph (or may be: the query itself is refused where it would break a capture).
 bool being_captured(hipStream_t s) {

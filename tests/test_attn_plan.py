@@ -17,6 +17,7 @@ def run_checks(tmp_path, body):
     src.write_text(r'''
 #include <cstdio>
 #include "attn_plan.hpp"
+#include "call_tag.hpp"
 using namespace cusa;
 static int fails = 0;
 #define FAIL(...) do { if (++fails <= 20) { std::printf(__VA_ARGS__); std::printf("\n"); } } while (0)
@@ -245,5 +246,22 @@ def test_a_row_waits_for_no_more_pieces_than_the_launch_has(tmp_path):
                 for (int s = 0; s < n_splits; ++s) with_tokens += s * chunk < n;
                 if (merged_pieces(n, chunk, n_splits) != std::max(1, with_tokens)) FAIL("%d tokens in %d pieces of %d: %d", n, n_splits, chunk, merged_pieces(n, chunk, n_splits));
             }
+''')
+    assert out == "", out
+
+
+def test_tags_differ_and_a_machine_without_random_numbers_is_no_exception(tmp_path):
+    """A tag stands for one call; what makes the first must not throw through the C interface."""
+    out = run_checks(tmp_path, r'''
+    (void)plan;
+    struct None { None() { throw 1; } uint32_t operator()() { return 0; } };
+    struct Empty { uint32_t operator()() { throw 2; } };
+    if (tag_start<None>() == 0 || tag_start<Empty>() == 0) FAIL("no start");
+    uint64_t last = 0;
+    for (int i = 0; i < 1000; ++i) {
+        const uint64_t t = new_tag();
+        if (t == 0 || t == last || (uint32_t)t == (uint32_t)last || t >> 32 == last >> 32) FAIL("tags %llx, %llx", (unsigned long long)last, (unsigned long long)t);
+        last = t;
+    }
 ''')
     assert out == "", out
