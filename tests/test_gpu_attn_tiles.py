@@ -102,7 +102,7 @@ def test_few_sequences_in_pieces(g, n):
 
 
 @pytest.mark.parametrize("g", [1, 4, 8])
-@pytest.mark.parametrize("n,b", [(40, 64), (600, 64), (9000, 24)])     # a tile, several waves, several pieces
+@pytest.mark.parametrize("n,b", [(40, 64), (600, 64), (9000, 24), (600, 1)])     # a tile, several waves, several pieces, pieces merged in the launch
 @pytest.mark.parametrize("below", [126, 127, 130, 132])
 def test_weights_far_below_the_largest_count_beside_large_values(g, n, b, below):
     """The first token's weight is 2^-below of the last one's (the others': nothing) and its values are 2^120, the only ones that are not
