@@ -2712,25 +2712,31 @@ __global__ __launch_bounds__(ATTN_THREADS, 2) void attn_kernel(
                 for (int h = 0; h < GQ; ++h) pstage[h * STAGE_TOK + (it - it_staged) * WG_TILE + wave * TILE + tl] = sc[h >> 2][h & 3];
             }
         } else {
-            // this lane's part of the columns; the two halves of a chunk into sums of their own (shorter chains)
-            constexpr int CHUNKS = 16 / PARTS;
-            const int part0 = (lane / TILE) * CHUNKS, slot0 = part0 ^ (tl & 15);
-            f32x4 sc2[SETS];
+            // This lane's part of the columns, in quarters of a row; the two halves of a chunk into sums of their own (shorter chains).  A score is
+            // (q0 + q1) + (q2 + q3) of its quarters whatever the tile's width -- two of them in a lane (tiles of 32 tokens), or one, the folds' first
+            // step pairing lanes 32 apart --, so that a token weighs the same in passes over many tokens and over few: the recall of a set
+            // is a ratio of two such passes (at scores of 2^20 it came out as infinity with sums of the lanes' own order).
+            constexpr int QUARTERS = 4 / PARTS;
+            const int of = lane / TILE, part0 = (PARTS == 4 ? (of & 1) * 2 + (of >> 1) : of * 2) * 4, slot0 = part0 ^ (tl & 15);
 #pragma unroll
-            for (int s = 0; s < SETS; ++s) sc2[s] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            for (int qd = 0; qd < QUARTERS; ++qd) {
+                f32x4 lo[SETS], hi[SETS];
 #pragma unroll
-            for (int j = 0; j < CHUNKS; ++j) {
-                const u32x4 kw = ktile[tl * 16 + (slot0 ^ j)];
-                const s16x4 klo = __builtin_bit_cast(s16x4, make_uint2(kw.x, kw.y)), khi = __builtin_bit_cast(s16x4, make_uint2(kw.z, kw.w));
+                for (int s = 0; s < SETS; ++s) lo[s] = hi[s] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-                for (int s = 0; s < SETS; ++s) {
-                    const u32x4 qw = *reinterpret_cast<const u32x4*>(&qlds[(s * 4 + (lane & 3)) * QSB + (part0 + j) * 8]);
-                    sc[s] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(s16x4, make_uint2(qw.x, qw.y)), klo, sc[s], 0, 0, 0);
-                    sc2[s] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(s16x4, make_uint2(qw.z, qw.w)), khi, sc2[s], 0, 0, 0);
+                for (int j = qd * 4; j < qd * 4 + 4; ++j) {
+                    const u32x4 kw = ktile[tl * 16 + (slot0 ^ j)];
+                    const s16x4 klo = __builtin_bit_cast(s16x4, make_uint2(kw.x, kw.y)), khi = __builtin_bit_cast(s16x4, make_uint2(kw.z, kw.w));
+#pragma unroll
+                    for (int s = 0; s < SETS; ++s) {
+                        const u32x4 qw = *reinterpret_cast<const u32x4*>(&qlds[(s * 4 + (lane & 3)) * QSB + (part0 + j) * 8]);
+                        lo[s] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(s16x4, make_uint2(qw.x, qw.y)), klo, lo[s], 0, 0, 0);
+                        hi[s] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(s16x4, make_uint2(qw.z, qw.w)), khi, hi[s], 0, 0, 0);
+                    }
                 }
-            }
 #pragma unroll
-            for (int s = 0; s < SETS; ++s) sc[s] += sc2[s];
+                for (int s = 0; s < SETS; ++s) sc[s] = qd == 0 ? lo[s] + hi[s] : sc[s] + (lo[s] + hi[s]);
+            }
         }
         float z[NZ];                                  // the lane's scores: token tl, heads head0_z ...
         if constexpr (PARTS == 1) {

@@ -327,3 +327,34 @@ def test_pieces_merged_in_launches_of_two_streams():
     torch.cuda.synchronize()
     for w, out in zip(want, outs):
         assert all(torch.equal(o, w) for o in out)
+
+
+@pytest.mark.parametrize("g", [1, 2, 4, 8])
+@pytest.mark.parametrize("b,Gk,L,K", [(8, 8, 5000, 2048), (16, 8, 3000, 700), (8, 2, 5000, 2048), (1, 2, 300, 65)])
+@pytest.mark.parametrize("per_head", [False, True])
+def test_a_token_scores_the_same_in_passes_of_any_tile(g, b, Gk, L, K, per_head):
+    """The recall of a set is a ratio of two passes, over the set and over all tokens, which take tiles of different widths.  Here scores reach
+    2^20, where the last bit of a sum makes a factor of 2^0.1, and each head's largest lies by more than 2^8 above its others: its weight is 1, the
+    others' are nothing.  If the sets hold the largest the recall is 1, and 2^0 exactly; otherwise it is 0."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(g + L)
+    H = Gk * g
+    k = torch.randn((b, Gk, L, D), generator=gen, device=DEV).bfloat16() * 1024
+    q = torch.randn((b, H, D), generator=gen, device=DEV).bfloat16() * 1024
+    kv = cb.KvCache(k, k, torch.full((b,), L, dtype=torch.int32, device=DEV), L)
+    params = cb.make_params(b, H, Gk, K, K // 4)
+    ws, recall = cb.alloc_workspace(params, L, DEV), torch.empty((b, H), dtype=torch.float32, device=DEV)
+    scores = torch.stack([k[:, h // g].double() @ q[:, h].double()[..., None] for h in range(H)], 1)[..., 0] / math.sqrt(D)
+    top = scores.topk(2)
+    clear = top.values[..., 0] - top.values[..., 1] > 2.0 ** 8
+    assert clear.float().mean() > 0.9
+    lists = torch.rand((b, H if per_head else 1, L), generator=gen, device=DEV)
+    held = torch.arange(H, device=DEV) % 3 > 0                 # heads whose sets hold their largest
+    for h in range(H):
+        lists[:, h if per_head else 0].scatter_(1, top.indices[:, h, :1], 2.0 if held[h] else -1.0)
+    idx = lists.topk(K).indices.sort().values.to(torch.int32)
+    want = (idx.view(b, -1, 1, K) == top.indices[:, :, :1, None].to(torch.int32)).any(-1).view(b, H).float()
+    assert (want == 1).any() and (want == 0).any()
+    cnt = torch.full((b,), K, dtype=torch.int32, device=DEV)
+    cb.attention_recall(params, q, kv, idx if per_head else idx[:, 0].contiguous(), cnt, recall, ws, per_head=per_head)
+    assert torch.equal(recall[clear], want[clear]), f"{(recall != want)[clear].sum().item()} of {clear.sum().item()}: {recall[clear & (recall != want)][:4].tolist()}"
